@@ -140,7 +140,6 @@ struct sp_stage {
   struct FwdGraph {
     int M, qt, items, any_split, units;
     int seen;
-    int S_last;                // split count of the last layer's down projection (the write-out folds it)
     bool failed;
     hipGraphExec_t exec;
   };
@@ -594,6 +593,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   AttnPlan plan;
   std::memset(&plan, 0, sizeof(plan));
   plan.n_seg = b.n_req;
+  plan.x_out = x_out;
   for (int i = 0; i < b.n_req; ++i) {              // which request and node each row belongs to
     const HostReq& r = s->reqs[b.req[i]];
     plan.seg_row0[i] = b.row0[i]; plan.seg_rows[i] = b.n[i]; plan.seg_req[i] = b.req[i];
@@ -658,9 +658,36 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   // Everything between the kernel that opens the call (rows enter, first RMSNorm, plan to device
   // memory) and the one that writes the result out.  No argument of these launches depends on the
   // caller's pointers or on the plan's contents, only on M and on the grid sizes the plan implies.
-  int S_last = 0;
 #define SP_STEP(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) return e_; } while (0)
+  // one row tile: complete projections with RoPE, residual, norm and write-out as their epilogues
+  const bool few = s->fast && M <= 16;
+  auto run_layers_few = [&]() -> hipError_t {
+    float* ssq = w.part;                            // [M][d / 16]
+    for (int l = 0; l < c.n_layers; ++l) {
+      const sp_layer_weights& L = s->W[l];
+      { ProfScope p(s, SP_K_GEMM_QKV, st);
+        SP_STEP(sp_launch_few_qkv((const bf16_t*)w.xn, (const bf16_t*)L.wqkv, s->packed, l > 0 ? ssq : nullptr, c.rms_eps,
+                                  w.rows, w.cs, (bf16_t*)w.qbuf, s->geom, l, M, d, nq, nkv, st)); }
+      { ProfScope p(s, SP_K_ATTENTION, st);
+        SP_STEP(sp_launch_attn_bf16((const bf16_t*)w.qbuf, s->d_tables, s->geom, l, plan, w.plan, w.attn_part,
+                                    (bf16_t*)w.attn, M, nq, nkv, dh, st)); }
+      { ProfScope p(s, SP_K_GEMM_O, st);
+        SP_STEP(sp_launch_few_residual((const bf16_t*)w.attn, (const bf16_t*)L.wo, s->packed, s->o_resident, w.h,
+                                       (const bf16_t*)L.norm2, (bf16_t*)w.xn, ssq, M, d, dq, st)); }
+      { ProfScope p(s, SP_K_GEMM_GATEUP, st);
+        SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d,
+                                           s->n_cu, ssq, c.rms_eps, st)); }
+      { ProfScope p(s, SP_K_GEMM_DOWN, st);
+        if (l + 1 < c.n_layers)
+          SP_STEP(sp_launch_few_residual((const bf16_t*)w.act, (const bf16_t*)L.wd, s->packed, false, w.h,
+                                         (const bf16_t*)s->W[l + 1].norm1, (bf16_t*)w.xn, ssq, M, d, F, st));
+        else
+          SP_STEP(sp_launch_few_out((const bf16_t*)w.act, (const bf16_t*)L.wd, s->packed, w.h, w.plan, M, d, F, st)); }
+    }
+    return hipSuccess;
+  };
   auto run_layers = [&]() -> hipError_t {
+    if (few) return run_layers_few();
     int S_prev = 0;                                 // split count of the previous layer's down projection
     for (int l = 0; l < c.n_layers; ++l) {
       const sp_layer_weights& L = s->W[l];
@@ -691,7 +718,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       { ProfScope p(s, SP_K_GEMM_GATEUP, st);
         if (s->fast) {
           if (wide) SP_STEP(sp_launch_gemm_wide_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, st));
-          else SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, st));
+          else SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, nullptr, 0.f, st));
         } else {
           SP_STEP(sp_launch_gemm_simple(dt, w.xn, L.wgu, w.part, M, 2 * F, d, st));
           SP_STEP(sp_launch_silu_mul(dt, w.part, w.act, M, F, st));
@@ -702,8 +729,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
         else SP_STEP(sp_launch_gemm_simple(dt, w.act, L.wd, w.part, M, d, F, st)); }
       S_prev = S;
     }
-    S_last = S_prev;
-    return hipSuccess;
+    return sp_launch_finish(dt, w.h, w.part, S_prev, strideD, x_out, s->fast ? w.plan : nullptr, M, d, st);
   };
 #undef SP_STEP
 
@@ -719,8 +745,8 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   if (s->prof_kind != 0) {
     const int k = s->prof_kind;
     if (k == SP_K_GEMM_QKV || k == SP_K_GEMM_O || k == SP_K_GEMM_GATEUP || k == SP_K_GEMM_DOWN ||
-        k == SP_K_ATTENTION || k == SP_K_ROPE_KV) n_kind = c.n_layers;
-    else if (k == SP_K_NORM) n_kind = 2 * c.n_layers - 1;
+        k == SP_K_ATTENTION || (k == SP_K_ROPE_KV && !few)) n_kind = c.n_layers;
+    else if (k == SP_K_NORM && !few) n_kind = 2 * c.n_layers - 1;
     if (n_kind > 0) {
       // whole calls are sampled: align the count to this call's group of launches
       s->prof_group = n_kind;
@@ -735,7 +761,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
         if (g.M == M && g.qt == plan.qt && g.items == plan.total_items && g.any_split == plan.any_split &&
             g.units == plan.units_total) { fg = &g; break; }
       if (!fg && s->graphs.size() < 256) {
-        s->graphs.push_back({M, plan.qt, plan.total_items, plan.any_split, plan.units_total, 0, 0, false, nullptr});
+        s->graphs.push_back({M, plan.qt, plan.total_items, plan.any_split, plan.units_total, 0, false, nullptr});
         fg = &s->graphs.back();
       }
     }
@@ -749,10 +775,8 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) == hipSuccess) {
         const hipError_t e_run = run_layers();
         const hipError_t e_end = hipStreamEndCapture(st, &graph);
-        if (e_run == hipSuccess && e_end == hipSuccess && graph &&
-            hipGraphInstantiate(&fg->exec, graph, nullptr, nullptr, 0) == hipSuccess) {
-          fg->S_last = S_last;
-        } else {
+        if (e_run != hipSuccess || e_end != hipSuccess || !graph ||
+            hipGraphInstantiate(&fg->exec, graph, nullptr, nullptr, 0) != hipSuccess) {
           fg->exec = nullptr;
           fg->failed = true;
           (void)hipGetLastError();
@@ -765,7 +789,6 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     }
     if (fg->exec) {
       SP_TRY(hipGraphLaunch(fg->exec, st));
-      S_last = fg->S_last;
       // the sampling cadence counts the replayed launches too (once: the capturing call has already
       // counted them while it recorded the launches)
       s->prof_seen = seen_before + n_kind;
@@ -773,7 +796,6 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     }
   }
   if (!done) SP_TRY(run_layers());
-  SP_TRY(sp_launch_finish(dt, w.h, w.part, S_last, strideD, x_out, M, d, st));
 #undef SP_TRY
   for (int i = 0; i < b.n_req; ++i) {
     HostReq& r = s->reqs[b.req[i]];

@@ -153,3 +153,36 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
 }
+
+// Sums of squares of up to 16 rows that the kernel producing the rows left as ssq[row][part]: a workgroup of NT threads
+// asks for them early (load), adds them up when its products are done (post) and finds the totals in LDS behind the
+// barrier that follows.  A wave takes every (NT / 64)-th row; the order of the additions is fixed.
+template <int NT>
+struct RowSquares {
+  static constexpr int NWV = NT / 64, RPW = 16 / NWV;
+  f32x4_t v[RPW][2];                               // 512 parts in registers (d_model = 8192); further ones when posting
+  __device__ __forceinline__ void load(const float* ssq, int n_part, int M) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < RPW; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int row = wave + i * NWV, p = (j * 64 + lane) * 4;
+        v[i][j] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        if (row < M && p < n_part) v[i][j] = *reinterpret_cast<const f32x4_t*>(ssq + (size_t)row * n_part + p);
+      }
+  }
+  __device__ __forceinline__ void post(const float* ssq, int n_part, int M, float* s_tot /* LDS, [16] */) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      const int row = wave + i * NWV;
+      if (row >= M) continue;
+      f32x4_t t = v[i][0] + v[i][1];
+      for (int p = (128 + lane) * 4; p < n_part; p += 256)
+        t += *reinterpret_cast<const f32x4_t*>(ssq + (size_t)row * n_part + p);
+      const float tot = wave_sum((t[0] + t[1]) + (t[2] + t[3]));
+      if (lane == 0) s_tot[row] = tot;
+    }
+  }
+};

@@ -1,5 +1,5 @@
 // bf16 projections for few rows (M = tree nodes in flight, typically <= 64) on the
-// CDNA4 matrix cores.  With so few rows every weight is used once, so the kernel is a
+// CDNA4 matrix cores (QKV, O and down of up to 16 rows have a kernel of their own, sp_gemm_few.hip).  With so few rows every weight is used once, so the kernel is a
 // weight streamer (decode is bound by loading parameters, Sec. 2.2): each wave pulls
 // its 16 weight rows straight from HBM into registers in MFMA operand layout (one
 // 16-byte load per lane per k-step, PF chunks ahead of the math), while the M x K
@@ -67,17 +67,12 @@
 #endif
 #ifndef SP_GEMM_ROT
 // Plain products split over k, K up to 8192 (the QKV and O shapes): workgroups walk their k slice from
-// different starting chunks.  At 1-16 rows: 6144 x 4096 12.3 -> 10.3 us, 8192 x 8192 25.2 -> 23.2 us,
-// 10240 x 8192 33.2 -> 32.2 us, 4096 x 4096 unchanged; at 32 and 64 rows 8192 x 8192 29.2 -> 24.8 and
-// 31.0 -> 27.9 us, the other shapes within 1 %; with K = 14336 or 28672 (down) 2-3 % slower at 1-16 rows,
-// and nothing gained in gate/up: those keep the plain order.
+// different starting chunks.  At 32 and 64 rows 8192 x 8192 29.2 -> 24.8 and 31.0 -> 27.9 us, the other shapes
+// within 1 %; nothing gained with K = 14336 or 28672 (down) and in gate/up: those keep the plain order.
 #define SP_GEMM_ROT 1
 #endif
-#ifndef SP_GEMM_TARGET_WGS
-#define SP_GEMM_TARGET_WGS 768    // one row tile: split K until the grid has about this many workgroups
-#endif
 #ifndef SP_GEMM_TARGET_WGS_ROWS
-#define SP_GEMM_TARGET_WGS_ROWS 512   // more row tiles: at most this many (two per CU)
+#define SP_GEMM_TARGET_WGS_ROWS 512   // split K until the grid has at most this many workgroups (two per CU)
 #endif
 
 // PACKED: the weights were re-laid at load time (sp_pack_weights) into MFMA fragment order --
@@ -100,7 +95,8 @@ template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX
           int NWAVES = 4, bool EVEN = false, bool WNT = true>
 __global__ void __launch_bounds__(64 * NWAVES)
 k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
-            bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int cpw = 0, int rot = 0) {
+            bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int cpw = 0, int rot = 0,
+            const float* ssq = nullptr, float eps = 0.f) {
   static_assert(!(TWO && (GATEUP || ARGMAX)), "two strips per wave: plain products only");
   static_assert(!EVEN || GATEUP, "even split: gate/up only");
   constexpr int NTH = 64 * NWAVES;
@@ -203,6 +199,10 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
     __syncthreads();                                                                                    \
   }
 
+  // one row tile of gate/up: the rows may come without their RMSNorm, whose scale is then a factor of the products
+  constexpr bool SCALED = GATEUP && MT == 1;
+  RowSquares<NTH> sq;
+  if (SCALED && ssq) sq.load(ssq, K / 16, M);
   if (c_begin < c_end) {
     SP_LOAD_X(c_begin)
     SP_LOAD_W(0, c_begin)
@@ -226,7 +226,10 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 #undef SP_PC
 #undef SP_WOFF
 
+  float* s_tot = reinterpret_cast<float*>(&lds[0][0]) + (sizeof(lds) / 4 - 16);      // behind the fold's floats
+  if (SCALED && ssq) sq.post(ssq, K / 16, M, s_tot);
   if (NKH == 2) {       // fold the two k-halves of a column group together through LDS
+    static_assert(!SCALED || (NCG * NW * MT * 64 * 4 + 16) * 4 <= (int)sizeof(lds), "fold and row sums side by side");
     float* red = reinterpret_cast<float*>(&lds[0][0]);
     if (kh == 1) {
 #pragma unroll
@@ -280,6 +283,11 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
     }
     return;
   }
+  float row_scale = 1.f;
+  if (SCALED && ssq) {
+    if (NKH != 2) __syncthreads();      // (the fold of the k-halves has passed a barrier)
+    row_scale = rsqrtf(s_tot[min(r, M - 1)] / (float)K + eps);
+  }
   if (SP_GEMM_ROWSTORE && !GATEUP && MT >= SP_GEMM_ROWSTORE_MIN_MT) {
     // Partial sums leave in whole rows of the workgroup's columns: the waves' 16-column pieces are put together in
     // LDS (the panels are no longer read: every wave has passed the barrier that ends its last chunk), and a store
@@ -314,7 +322,8 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
       float o[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float gte = acc[0][mt][i], up = acc[NW - 1][mt][i];
+        const float gte = SCALED ? acc[0][mt][i] * row_scale : acc[0][mt][i];
+        const float up = SCALED ? acc[NW - 1][mt][i] * row_scale : acc[NW - 1][mt][i];
         o[i] = gte / (1.f + __expf(-gte)) * up;
       }
       uint2 pk;
@@ -339,10 +348,10 @@ static inline int rot_for(int S, int K) { return (SP_GEMM_ROT && S > 1 && K <= 8
 
 template <int NCG, bool GATEUP, int KCV, bool PACKED, bool ARGMAX = false>
 static hipError_t launch_mt(int MT, dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out,
-                            bf16_t* act, int M, int N, int K, int S, bool two = false) {
+                            bf16_t* act, int M, int N, int K, int S, bool two = false, const float* ssq = nullptr, float eps = 0.f) {
 #define SP_GO(MTV, KCX)                                                                                        \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, NCG, GATEUP, KCX, SP_GEMM_PF, PACKED, ARGMAX>), grid, dim3(256), 0, st, X, \
-                     W, out, act, M, N, K, K / KCX, S, 0, (!GATEUP && !ARGMAX) ? rot_for(S, K) : 0)
+                     W, out, act, M, N, K, K / KCX, S, 0, (!GATEUP && !ARGMAX) ? rot_for(S, K) : 0, ssq, eps)
   if (!ARGMAX && MT == 4 && GATEUP && NCG == 4) {      // the 64 + 64 column gate/up workgroup at 49-64 rows
     hipLaunchKernelGGL((k_gemm_bf16<4, 4, true, 128, SP_GEMM_PF, PACKED, false>), grid, dim3(256), 0, st, X, W, out, act, M, N, K, K / 128, S);
     return hipGetLastError();
@@ -395,14 +404,12 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   if (M < 1 || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
   const int chunks = K / (MT == 8 ? 128 : SP_GEMM_KC_PLAIN);
   const int tiles = N / TILE;
-  // Enough workgroups to keep every CU streaming, within the partial-sum buffer.
-  // With one row tile the partial sums are small and three workgroups per CU stream best.  With more
-  // rows every slice costs M*N*4 bytes written here and read again by the kernel that folds them, which
-  // outweighs the finer split: at most two workgroups per CU (measured on the whole 64-row step:
-  // 0.608 ms against 0.617 ms; a count between two and three per CU, which leaves the CUs unevenly
-  // loaded, 0.638 ms; two waves per column group with half the slices again: 0.612 ms).
-  int S = MT == 1 ? (SP_GEMM_TARGET_WGS + tiles * mblocks - 1) / (tiles * mblocks)
-                  : (eight ? SP_GEMM_TARGET_WGS_ROWS / 2 : SP_GEMM_TARGET_WGS_ROWS) / (tiles * mblocks);
+  // Enough workgroups to keep every CU streaming, within the partial-sum buffer.  Every slice costs M*N*4 bytes
+  // written here and read again by the kernel that folds them, which outweighs a finer split: at most two
+  // workgroups per CU (measured on the whole 64-row step: 0.608 ms against 0.617 ms with three; a count between
+  // two and three per CU, which leaves the CUs unevenly loaded, 0.638 ms; two waves per column group with half
+  // the slices again: 0.612 ms).
+  int S = (eight ? SP_GEMM_TARGET_WGS_ROWS / 2 : SP_GEMM_TARGET_WGS_ROWS) / (tiles * mblocks);
   if (S > max_split) S = max_split;
   if (S > chunks) S = chunks;
   while (S > 1 && (size_t)S * M * N > part_capacity_floats) --S;
@@ -430,15 +437,6 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
     if (packed) { if (MT == 2) SP_GO8(2, true); else if (MT == 3) SP_GO8(3, true); else if (MT == 4) SP_GO8(4, true); else SP_GO8(8, true); }
     else { if (MT == 2) SP_GO8(2, false); else if (MT == 3) SP_GO8(3, false); else if (MT == 4) SP_GO8(4, false); else SP_GO8(8, false); }
 #undef SP_GO8
-    return hipGetLastError();
-  }
-  if (resident && MT == 1) {     // one row tile of a matrix that is to stay in the Infinity Cache: ordinary weight loads
-    if (packed)
-      hipLaunchKernelGGL((k_gemm_bf16<1, SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, true, false, false, 4, false, false>),
-                         grid, dim3(256), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K));
-    else
-      hipLaunchKernelGGL((k_gemm_bf16<1, SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, false, false, false, 4, false, false>),
-                         grid, dim3(256), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K));
     return hipGetLastError();
   }
   if (packed) return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, true>(MT, grid, st, X, W, out, nullptr, M, N, K, S, two);
@@ -482,9 +480,10 @@ static hipError_t launch_even7(int MT, int n_wg, hipStream_t st, const bf16_t* X
 }
 
 hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F,
-                                      int K, int n_cu, hipStream_t st) {
+                                      int K, int n_cu, const float* ssq, float eps, hipStream_t st) {
   int MT, mblocks;
   row_blocks(M, &MT, &mblocks);
+  if (ssq && MT != 1) return hipErrorInvalidValue;
   if (M < 1 || F % 64 || K % SP_GEMM_KC_GATEUP || K % 128) return hipErrorInvalidValue;
   // 17-64 rows and a d_ff that gives every CU the same 56 or 64 columns: one eight-wave workgroup per CU
   if (MT >= SP_GEMM_EVEN_MIN_MT && (MT <= 4 || (SP_GEMM_EVEN_MT8 && mblocks == 1)) && n_cu > 0 && F % n_cu == 0 && (F / n_cu) % 8 == 0 && F / n_cu > 48 &&
@@ -508,8 +507,8 @@ hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool pac
   }
   const int TILE = tile_cols(MT, true);
   const dim3 grid(F / TILE, 1, mblocks);
-  if (packed) return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, true>(MT, grid, st, X, W, nullptr, act, M, F, K, 1);
-  return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, false>(MT, grid, st, X, W, nullptr, act, M, F, K, 1);
+  if (packed) return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, true>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, false, ssq, eps);
+  return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, false>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, false, ssq, eps);
 }
 
 // Output head: per row the top column of every 64-column tile, as (value, index) pairs

@@ -1,0 +1,199 @@
+// Plain projections for one row tile (M <= 16: streaming steps of a few nodes, the single node after a stall), whole
+// in one launch each.  A workgroup owns 16 output columns and its waves cut the k range between them, so that the sums
+// over k are complete inside the workgroup: there are no partial sums in memory, and what used to be a kernel of its own
+// behind every split product -- RoPE and the cache append behind QKV, residual and RMSNorm behind O and down, the
+// write-out behind the last layer -- is the epilogue here.
+//
+//   QKV:      q | k | v = scale[m] * sum_k X[m][k] W[n][k], rotated, to qbuf and to the node's cache rows
+//   O, down:  h[m][n] += sum_k X[m][k] W[n][k];  X' = bf16(h * gain);  ssq[m][n / 16] = sum of the workgroup's h^2
+//
+// The RMSNorm of a row needs the whole row, which no workgroup sees: the producing kernel leaves h * gain and, per
+// workgroup, the sum of its 16 squares, and the consuming kernel adds those up while its weights are on their way and
+// multiplies the row's products by 1 / rms at the end (the norm is a factor per row, the projection is linear).
+//
+// With so few rows each weight is used once and the launch is bound by the weight stream and by its own start and end.
+// A wave has D fragments of weights and of activations in flight: registers only, no LDS panel, no barrier before the
+// waves are folded.  Measured at 6 rows, 8B shape, weights from HBM: QKV + RoPE 15.2 -> 13.0 us, O + residual + norm
+// 12.1 -> 7.3 us, down + residual + norm 25.1 -> 20.0 us (before: split product and the kernel behind it); the step
+// of four layers at a context of 32768 507 -> 465 us.  Four or sixteen waves, 4 to 16 fragments in flight and staggered starting
+// steps are all within 2 % of this.
+#include "sp_launch.h"
+
+#define FEW_WAVES 8        // waves per workgroup, each with an eighth of the k range
+#define FEW_QKV 0
+#define FEW_RESIDUAL 1
+#define FEW_OUT 2          // residual of the last layer: the rows leave the stage
+
+struct FewArgs {
+  const bf16_t* X;         // [M][K]
+  const bf16_t* W;         // [N][K], row-major or in fragment order
+  int M, N, K;
+  const float* ssq_in;     // [M][K / 16] sums of squares of the rows behind X (nullptr: X is normalised already)
+  float eps;
+  // QKV
+  const RowInfo* rows;
+  const float* cs;
+  bf16_t* qbuf;
+  KvGeom g;
+  int layer, n_q, n_kv;
+  // O, down
+  float* h;                // [M][N]
+  const bf16_t* gain;      // [N] gain of the norm that follows
+  bf16_t* xn;              // [M][N]
+  float* ssq_out;          // [M][N / 16]
+  const AttnPlan* plan;    // FEW_OUT: x_out
+};
+
+template <int D, int MODE, bool PACKED, bool WNT>
+__global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
+  __shared__ __attribute__((aligned(16))) f32x4_t s_acc[FEW_WAVES][64];
+  __shared__ __attribute__((aligned(16))) float s_tot[16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, kg = lane >> 4;
+  const int b = blockIdx.x;
+  const int K = a.K, M = a.M;
+  const int n = (K >> 5) / FEW_WAVES;              // k steps of this wave, a multiple of D
+  // QKV: columns t0 .. t0+7 of a head and their rotation partners t0+64 .. t0+71
+  const int head = b >> 3, t0 = (b & 7) * 8;
+  const int wrow = MODE == FEW_QKV ? head * 128 + t0 + (r & 7) + ((r & 8) << 3) : b * 16 + r;
+  const bf16_t* w = PACKED ? a.W + ((size_t)(wrow >> 4) * (K >> 5) + (size_t)wave * n) * 512 + (kg * 16 + (wrow & 15)) * 8
+                           : a.W + (size_t)wrow * K + (size_t)wave * n * 32 + kg * 8;
+  constexpr int WSTEP = PACKED ? 512 : 32;
+  // rows past M repeat the last row and multiply into output rows that are never stored
+  const bf16_t* x = a.X + (size_t)min(r, M - 1) * K + (size_t)wave * n * 32 + kg * 8;
+  u32x4_t wf[D], xf[D];
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#define SP_LD(j, S)                                                                             \
+  {                                                                                             \
+    const u32x4_t* wp_ = reinterpret_cast<const u32x4_t*>(w + (size_t)(S) * WSTEP);             \
+    wf[j] = WNT ? __builtin_nontemporal_load(wp_) : *wp_;                                       \
+    xf[j] = *reinterpret_cast<const u32x4_t*>(x + (S) * 32);                                    \
+  }
+#define SP_MM(j)                                                                                \
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&wf[j]),     \
+                                                *reinterpret_cast<const bf16x8_t*>(&xf[j]), acc, 0, 0, 0);
+  // what the epilogue needs is asked for first: loads return in order, so nothing waits for it later
+  RowSquares<64 * FEW_WAVES> sq;
+  if (MODE == FEW_QKV && a.ssq_in) sq.load(a.ssq_in, K / 16, M);
+  f32x4_t e0 = {0.f, 0.f, 0.f, 0.f}, e1 = {0.f, 0.f, 0.f, 0.f};   // h, or cos and sin
+  uint2 gn = {0u, 0u};
+  RowInfo ri;
+  const int rc = min(r, M - 1);
+  const int col = b * 16 + kg * 4;                 // O, down: this lane's four columns
+  if (wave == 0) {
+    if (MODE == FEW_QKV) {
+      ri = a.rows[rc];
+      const float* c = a.cs + (size_t)rc * 128 + t0 + (kg & 1) * 4;
+      e0 = *reinterpret_cast<const f32x4_t*>(c);
+      e1 = *reinterpret_cast<const f32x4_t*>(c + 64);
+    } else {
+      e0 = *reinterpret_cast<const f32x4_t*>(a.h + (size_t)rc * a.N + col);
+      if (MODE == FEW_RESIDUAL) gn = *reinterpret_cast<const uint2*>(a.gain + col);
+    }
+  }
+
+#pragma unroll
+  for (int j = 0; j < D; ++j) SP_LD(j, j)
+  for (int s = D; s < n; s += D) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      SP_MM(j)
+      SP_LD(j, s + j)
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < D; ++j) SP_MM(j)
+#undef SP_LD
+#undef SP_MM
+
+  s_acc[wave][lane] = acc;
+  if (MODE == FEW_QKV && a.ssq_in) sq.post(a.ssq_in, K / 16, M, s_tot);
+  __syncthreads();
+  if (wave != 0) return;
+  // lane holds, for row r, columns 4 * kg .. + 3 of the workgroup's sixteen
+  f32x4_t y = s_acc[0][lane];
+#pragma unroll
+  for (int v = 1; v < FEW_WAVES; ++v) y += s_acc[v][lane];
+  if (MODE == FEW_QKV) {
+    if (a.ssq_in) y *= rsqrtf(s_tot[rc] / (float)K + a.eps);
+    f32x4_t o = y;
+    if (head < a.n_q + a.n_kv) {                   // rotate: the partner columns are 32 lanes away
+      f32x4_t p;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = __shfl_xor(y[i], 32, 64);
+      o = kg < 2 ? y * e0 - p * e1 : y * e0 + p * e1;
+    }
+    if (r >= M) return;
+    const int t = t0 + (kg & 1) * 4 + (kg >> 1) * 64;
+    bf16_t* dst;
+    if (head < a.n_q) {
+      dst = a.qbuf + ((size_t)r * a.n_q + head) * 128;
+    } else {
+      const bool is_k = head < a.n_q + a.n_kv;
+      const int kvh = head - a.n_q - (is_k ? 0 : a.n_kv);
+      const size_t slot = sp_phys_slot(a.g, ri.req, ri.base, ri.P + ri.node);
+      dst = reinterpret_cast<bf16_t*>(a.g.kv + ((size_t)(a.layer * 2 + (is_k ? 0 : 1)) * a.n_kv + kvh) * a.g.plane_bytes +
+                                      slot * a.g.row_bytes);
+    }
+    uint2 pk;
+    pk.x = pack_bf16x2(o[0], o[1]);
+    pk.y = pack_bf16x2(o[2], o[3]);
+    *reinterpret_cast<uint2*>(dst + t) = pk;
+  } else {
+    y += e0;
+    uint2 pk;
+    if (MODE == FEW_OUT) {
+      pk.x = pack_bf16x2(y[0], y[1]);
+      pk.y = pack_bf16x2(y[2], y[3]);
+      if (r < M) *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(a.plan->x_out) + (size_t)r * a.N + col) = pk;
+      return;
+    }
+    const float s2 = quad_rows_sum((y[0] * y[0] + y[1] * y[1]) + (y[2] * y[2] + y[3] * y[3]));
+    if (r >= M) return;
+    if (kg == 0) a.ssq_out[r * (a.N / 16) + b] = s2;
+    *reinterpret_cast<f32x4_t*>(a.h + (size_t)r * a.N + col) = y;
+    pk.x = pack_bf16x2(y[0] * bf16_lo(gn.x), y[1] * bf16_hi(gn.x));
+    pk.y = pack_bf16x2(y[2] * bf16_lo(gn.y), y[3] * bf16_hi(gn.y));
+    *reinterpret_cast<uint2*>(a.xn + (size_t)r * a.N + col) = pk;
+  }
+}
+
+// Eight fragments in flight per wave; shapes whose k slices are shorter, or no multiple of that, take fewer.
+template <int MODE, bool PACKED, bool WNT>
+static hipError_t launch_few(const FewArgs& a, hipStream_t st) {
+  const int n = a.K / (32 * FEW_WAVES);
+#define SP_GO(DV) hipLaunchKernelGGL((k_gemm_few<DV, MODE, PACKED, WNT>), dim3(a.N / 16), dim3(64 * FEW_WAVES), 0, st, a)
+  if (n % 8 == 0) SP_GO(8);
+  else if (n % 2 == 0) SP_GO(2);
+  else SP_GO(1);
+#undef SP_GO
+  return hipGetLastError();
+}
+
+hipError_t sp_launch_few_qkv(const bf16_t* X, const bf16_t* W, bool packed, const float* ssq, float eps, const RowInfo* rows,
+                             const float* cs, bf16_t* qbuf, KvGeom g, int layer, int M, int K, int n_q, int n_kv,
+                             hipStream_t st) {
+  if (M < 1 || M > 16 || K % 256 || g.row_bytes != 256) return hipErrorInvalidValue;
+  FewArgs a = {};
+  a.X = X; a.W = W; a.M = M; a.N = (n_q + 2 * n_kv) * 128; a.K = K; a.ssq_in = ssq; a.eps = eps;
+  a.rows = rows; a.cs = cs; a.qbuf = qbuf; a.g = g; a.layer = layer; a.n_q = n_q; a.n_kv = n_kv;
+  return packed ? launch_few<FEW_QKV, true, true>(a, st) : launch_few<FEW_QKV, false, true>(a, st);
+}
+
+hipError_t sp_launch_few_residual(const bf16_t* X, const bf16_t* W, bool packed, bool resident, float* h, const bf16_t* gain,
+                                  bf16_t* xn, float* ssq_out, int M, int N, int K, hipStream_t st) {
+  if (M < 1 || M > 16 || K % 256 || N % 16) return hipErrorInvalidValue;
+  FewArgs a = {};
+  a.X = X; a.W = W; a.M = M; a.N = N; a.K = K; a.h = h; a.gain = gain; a.xn = xn; a.ssq_out = ssq_out;
+  if (resident) return packed ? launch_few<FEW_RESIDUAL, true, false>(a, st) : launch_few<FEW_RESIDUAL, false, false>(a, st);
+  return packed ? launch_few<FEW_RESIDUAL, true, true>(a, st) : launch_few<FEW_RESIDUAL, false, true>(a, st);
+}
+
+hipError_t sp_launch_few_out(const bf16_t* X, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
+                             int N, int K, hipStream_t st) {
+  if (M < 1 || M > 16 || K % 256 || N % 16) return hipErrorInvalidValue;
+  FewArgs a = {};
+  a.X = X; a.W = W; a.M = M; a.N = N; a.K = K; a.h = const_cast<float*>(h); a.plan = plan_dev;
+  return packed ? launch_few<FEW_OUT, true, true>(a, st) : launch_few<FEW_OUT, false, true>(a, st);
+}

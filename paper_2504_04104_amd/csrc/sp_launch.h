@@ -80,6 +80,7 @@ struct AttnPlan {          // host-made split of a forward call's attention work
   int seg_P[SP_BATCH];     // host mirror of prefix length and live nodes
   int seg_T[SP_BATCH];
   long long seg_base[SP_BATCH];
+  void* x_out;             // where the call's result rows go
 };
 
 // ---- elementwise / row kernels --------------------------------------------------
@@ -103,8 +104,9 @@ hipError_t sp_launch_rope_kv(int dtype, const float* part, int S, size_t part_st
 hipError_t sp_launch_argmax_rows(bool pairs, const float* part, int n_items, const FwdBatch& b, ReqTables* tables,
                                  int* pred_out /*nullable*/, float* max_out /*nullable*/, hipStream_t st);
 hipError_t sp_launch_silu_mul(int dtype, const float* gu, void* act, int M, int F, hipStream_t st);
+// plan_dev (nullable): the call's plan on the device; its x_out then takes the place of `out`
 hipError_t sp_launch_finish(int dtype, const float* h, const float* part, int S, size_t part_stride, void* out,
-                            int M, int d, hipStream_t st);
+                            const AttnPlan* plan_dev, int M, int d, hipStream_t st);
 
 // ---- GEMM: out[s][m][n] (f32) = sum over the s-th K slice of X[m][k] * W[n][k] -----
 hipError_t sp_launch_gemm_simple(int dtype, const void* X, const void* W, float* out, int M, int N, int K,
@@ -117,8 +119,20 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
 // act[m][f] = silu(X Wg^T) * (X Wu^T), W = [gate rows ; up rows]
 hipError_t sp_launch_gemm_argmax_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* pairs, int M, int V, int K,
                                       size_t pair_capacity_floats, int* tiles_out, hipStream_t st);
+// ssq (nullable, M <= 16 only): [M][K / 16] sums of squares of the rows, X is then not normalised yet
 hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F,
-                                      int K, int n_cu, hipStream_t st);
+                                      int K, int n_cu, const float* ssq, float eps, hipStream_t st);
+// One row tile (M <= 16), fast path: complete projections with what follows them as their epilogue (sp_gemm_few.hip).
+// ssq (nullable): [M][d / 16] sums of squares of the rows, X is then not normalised yet.
+hipError_t sp_launch_few_qkv(const bf16_t* X, const bf16_t* W, bool packed, const float* ssq, float eps, const RowInfo* rows,
+                             const float* cs, bf16_t* qbuf, KvGeom g, int layer, int M, int K, int n_q, int n_kv,
+                             hipStream_t st);
+// h += X W^T; xn = bf16(h * gain); ssq_out[M][N / 16]
+hipError_t sp_launch_few_residual(const bf16_t* X, const bf16_t* W, bool packed, bool resident, float* h, const bf16_t* gain,
+                                  bf16_t* xn, float* ssq_out, int M, int N, int K, hipStream_t st);
+// rows of the plan's x_out = bf16(h + X W^T)
+hipError_t sp_launch_few_out(const bf16_t* X, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
+                             int N, int K, hipStream_t st);
 // Many rows (M > 128): workgroups of 128 rows x 256 columns, weights kept in registers per wave.
 // Needs N % 256 == 0 (gate/up: F % 128 == 0) and K % 64 == 0.
 hipError_t sp_launch_gemm_wide(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,

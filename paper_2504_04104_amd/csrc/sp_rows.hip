@@ -174,7 +174,9 @@ __global__ void k_silu_mul(const float* gu, T* act, int M, int F) {
 }
 
 template <typename T>
-__global__ void k_finish(const float* h, const float* part, int S, size_t part_stride, T* out, size_t n) {
+__global__ void k_finish(const float* h, const float* part, int S, size_t part_stride, T* out, const AttnPlan* plan,
+                         size_t n) {
+  if (plan) out = reinterpret_cast<T*>(plan->x_out);
   for (size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < n; i += (size_t)gridDim.x * blockDim.x * 4)
     Vec4<T>::st(out + i, *reinterpret_cast<const f32x4_t*>(h + i) + fold4(part + i, S, part_stride));
 }
@@ -290,13 +292,13 @@ hipError_t sp_launch_silu_mul(int dtype, const float* gu, void* act, int M, int 
 }
 
 hipError_t sp_launch_finish(int dtype, const float* h, const float* part, int S, size_t part_stride, void* out,
-                            int M, int d, hipStream_t st) {
+                            const AttnPlan* plan_dev, int M, int d, hipStream_t st) {
   const size_t n = (size_t)M * d;
   if (dtype == 0)
     hipLaunchKernelGGL(k_finish<float>, dim3(grid_for(n / 4, 256)), dim3(256), 0, st, h, part, S, part_stride,
-                       (float*)out, n);
+                       (float*)out, plan_dev, n);
   else
     hipLaunchKernelGGL(k_finish<bf16_t>, dim3(grid_for(n / 4, 256)), dim3(256), 0, st, h, part, S, part_stride,
-                       (bf16_t*)out, n);
+                       (bf16_t*)out, plan_dev, n);
   return hipGetLastError();
 }
