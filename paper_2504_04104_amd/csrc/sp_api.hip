@@ -649,6 +649,9 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   // projections: few rows stream the weights (HBM-bound); many rows use the register-blocked kernel
   const bool wide = s->fast && M > 128 && nqkv % 256 == 0 && d % 256 == 0 && F % 128 == 0 && dq % 128 == 0;
   auto gemm = [&](const void* X, const void* Wm, int N_, int K_, int* S_, bool resident = false) -> hipError_t {
+    if (sp_gemm_mid_takes(M, N_, K_))
+      return sp_launch_gemm_mid((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, s->n_cu, 16,
+                                w.part_floats, S_, st, resident);
     if (wide)
       return sp_launch_gemm_wide((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, s->n_cu,
                                  w.part_floats, S_, st);
@@ -717,7 +720,8 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
         SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S, strideD, L.norm2, w.xn, M, d, c.rms_eps, st)); }
       { ProfScope p(s, SP_K_GEMM_GATEUP, st);
         if (s->fast) {
-          if (wide) SP_STEP(sp_launch_gemm_wide_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, st));
+          if (sp_gemm_mid_takes_gateup(M, F, d, s->n_cu)) SP_STEP(sp_launch_gemm_mid_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, st));
+          else if (wide) SP_STEP(sp_launch_gemm_wide_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, st));
           else SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, nullptr, 0.f, st));
         } else {
           SP_STEP(sp_launch_gemm_simple(dt, w.xn, L.wgu, w.part, M, 2 * F, d, st));

@@ -1,5 +1,6 @@
 // bf16 projections for few rows (M = tree nodes in flight, typically <= 64) on the
-// CDNA4 matrix cores (QKV, O and down of up to 16 rows have a kernel of their own, sp_gemm_few.hip).  With so few rows every weight is used once, so the kernel is a
+// CDNA4 matrix cores (QKV, O and down of up to 16 rows have a kernel of their own, sp_gemm_few.hip, and most products
+// from 49 rows on, sp_gemm_mid.hip).  With so few rows every weight is used once, so the kernel is a
 // weight streamer (decode is bound by loading parameters, Sec. 2.2): each wave pulls
 // its 16 weight rows straight from HBM into registers in MFMA operand layout (one
 // 16-byte load per lane per k-step, PF chunks ahead of the math), while the M x K
@@ -29,9 +30,6 @@
 #ifndef SP_GEMM_PLAIN8
 #define SP_GEMM_PLAIN8 1          // plain products, 17-64 rows: eight waves over 128 columns, one workgroup per CU
 #endif
-#ifndef SP_GEMM_PLAIN8_MT8
-#define SP_GEMM_PLAIN8_MT8 1      // ... and at 65-128 rows (small matrices; the large ones take two strips per wave)
-#endif
 #ifndef SP_GEMM_PLAIN6
 #define SP_GEMM_PLAIN6 1          // ... six waves over 96 columns where that divides the CUs evenly and 128 do not
 #endif
@@ -40,9 +38,6 @@
 #endif
 #ifndef SP_GEMM_EVEN7
 #define SP_GEMM_EVEN7 1           // gate/up, one workgroup per CU over 96 < d_ff / CUs <= 112 columns (seven waves)
-#endif
-#ifndef SP_GEMM_EVEN_MT8
-#define SP_GEMM_EVEN_MT8 1        // gate/up, one workgroup per CU, also at 65-128 rows
 #endif
 #ifndef SP_GEMM_PF_EVEN
 #define SP_GEMM_PF_EVEN 3         // the eight-wave gate/up kernel has the registers for a third chunk (45.5 -> 44.9 us)
@@ -58,12 +53,6 @@
 #endif
 #ifndef SP_GEMM_NCG_GATEUP
 #define SP_GEMM_NCG_GATEUP 2
-#endif
-#ifndef SP_GEMM_ROWSTORE
-#define SP_GEMM_ROWSTORE 1        // split-K partial sums written in whole rows through LDS ...
-#endif
-#ifndef SP_GEMM_ROWSTORE_MIN_MT
-#define SP_GEMM_ROWSTORE_MIN_MT 8 // ... from this many row tiles
 #endif
 #ifndef SP_GEMM_ROT
 // Plain products split over k, K up to 8192 (the QKV and O shapes): workgroups walk their k slice from
@@ -81,9 +70,6 @@
 // ARGMAX (output head of the last stage, Algorithm 1 "verify new token"): instead of the
 // products, a workgroup leaves per row the largest of its 16*NCG columns and that column's
 // index (the lowest one among equal maxima) as a (float, int) pair at out[(m * tiles + tile) * 2].
-// TWO (plain products only): a wave holds two strips of 16 weight rows, 64 rows apart, so that a workgroup
-// covers 32*NCG columns: with 128 activation rows the staged panel would otherwise be twice the size of the
-// weights it meets, and the reads of the panel out of L2, not HBM, would set the pace.
 // EVEN (gate/up): one workgroup per CU covers cpw = d_ff / CUs activation columns, a multiple of 8, in NCG column
 // groups of 16 columns and a last one of cpw - 16 * (NCG - 1) -- eight waves as four groups times two k-halves for
 // 48 < cpw <= 64, seven waves as seven groups for 96 < cpw <= 112 (the upper lanes of a short last group re-read
@@ -91,18 +77,16 @@
 // fetched twice).  Every CU then streams the same bytes, which 16-row
 // strips in fixed 32-column workgroups cannot do when d_ff / 32 is not a multiple of the CU count (d_ff = 14336:
 // 1.75 workgroups per CU), and the panel is staged once per CU instead of once per four waves.
-template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, bool TWO = false,
-          int NWAVES = 4, bool EVEN = false, bool WNT = true>
+template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, int NWAVES = 4, bool EVEN = false, bool WNT = true>
 __global__ void __launch_bounds__(64 * NWAVES)
 k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
             bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int cpw = 0, int rot = 0,
             const float* ssq = nullptr, float eps = 0.f) {
-  static_assert(!(TWO && (GATEUP || ARGMAX)), "two strips per wave: plain products only");
   static_assert(!EVEN || GATEUP, "even split: gate/up only");
   constexpr int NTH = 64 * NWAVES;
   constexpr int NKH = NWAVES / NCG;       // waves sharing a column group split each chunk's k-steps
   constexpr int KSTEPS = (KC / 32) / NKH;
-  constexpr int NW = (GATEUP || TWO) ? 2 : 1;
+  constexpr int NW = GATEUP ? 2 : 1;
   constexpr int ROWS = MT * 16;
   constexpr int XS = KC * 2 + 16;         // LDS row stride in bytes (conflict-free 16-byte reads)
   constexpr int UPR = KC / 8;             // 16-byte units per X row chunk
@@ -115,9 +99,9 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int cg = wave % NCG, kh = wave / NCG;
   const int r = lane & 15, kg = lane >> 4;
-  const int n0 = EVEN ? blockIdx.x * cpw + cg * 16 : blockIdx.x * (16 * NCG * (TWO ? 2 : 1)) + cg * 16;
+  const int n0 = EVEN ? blockIdx.x * cpw + cg * 16 : blockIdx.x * (16 * NCG) + cg * 16;
   const int vr = EVEN ? min(16, cpw - cg * 16) : 16;     // valid columns of this wave's group (8 or 16)
-  const int pair_off = TWO ? 16 * NCG : N;   // rows between a wave's two strips (gate/up: the up rows follow the N gate rows)
+  const int pair_off = N;                    // gate/up: the up rows follow the N gate rows
   const int m_base = blockIdx.z * ROWS;
   const int c_begin = (int)(((long long)blockIdx.y * chunks_total) / S);
   const int c_end = (int)(((long long)(blockIdx.y + 1) * chunks_total) / S);
@@ -288,32 +272,6 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
     if (NKH != 2) __syncthreads();      // (the fold of the k-halves has passed a barrier)
     row_scale = rsqrtf(s_tot[min(r, M - 1)] / (float)K + eps);
   }
-  if (SP_GEMM_ROWSTORE && !GATEUP && MT >= SP_GEMM_ROWSTORE_MIN_MT) {
-    // Partial sums leave in whole rows of the workgroup's columns: the waves' 16-column pieces are put together in
-    // LDS (the panels are no longer read: every wave has passed the barrier that ends its last chunk), and a store
-    // instruction then writes 1 KB of consecutive addresses instead of 64 bytes in each of 16 rows.
-    static_assert(NKH == 1 || GATEUP, "plain products: one wave per column group");
-    constexpr int WCOLS = 16 * NCG * (TWO ? 2 : 1);
-    constexpr int LSF = WCOLS + 4;                        // floats per LDS row
-    static_assert(ROWS * LSF * 4 <= (int)sizeof(lds), "the row tile fits the panels' LDS");
-    float* tile = reinterpret_cast<float*>(&lds[0][0]);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int a = 0; a < NW; ++a)
-        *reinterpret_cast<f32x4_t*>(tile + (mt * 16 + r) * LSF + a * (16 * NCG) + cg * 16 + 4 * kg) = acc[a][mt];
-    __syncthreads();
-    constexpr int UPRW = WCOLS / 4;                       // 16-byte units per row
-    const int col0 = blockIdx.x * WCOLS;
-    for (int idx = tid; idx < ROWS * UPRW; idx += NTH) {
-      const int row = idx / UPRW, u = idx - row * UPRW;
-      const int m = m_base + row;
-      if (m < M)
-        *reinterpret_cast<f32x4_t*>(out + ((size_t)blockIdx.y * M + m) * N + col0 + u * 4) =
-            *reinterpret_cast<const f32x4_t*>(tile + row * LSF + u * 4);
-    }
-    return;
-  }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     const int m = m_base + mt * 16 + r;
@@ -333,22 +291,20 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
     } else {
       float* o = out + ((size_t)blockIdx.y * M + m) * N + ncol;
       *reinterpret_cast<f32x4_t*>(o) = acc[0][mt];
-      if (TWO) *reinterpret_cast<f32x4_t*>(o + pair_off) = acc[NW - 1][mt];
     }
   }
 }
 
 // ---- launchers -------------------------------------------------------------------
-// Up to 64 rows run as one block of MT = ceil(M/16) tiles; more rows run in blocks of 128 (MT = 8,
-// always with the 128-wide chunk so that the two LDS panels fit), each block streaming the weights once.
-// More than 64 rows (MT = 8): workgroups of twice the columns -- two strips per wave for the plain products,
-// four column groups instead of two for gate/up -- so that panel and weights stay one to one.
+// Up to 64 rows run as one block of MT = ceil(M/16) tiles; more rows (gate/up shapes that sp_gemm_mid.hip does not
+// cover, the output head) run in blocks of 128 (MT = 8, always with the 128-wide chunk so that the two LDS panels
+// fit), each block streaming the weights once.
 // staggered starting chunks: plain products that are split over k, K up to 8192 (see SP_GEMM_ROT)
 static inline int rot_for(int S, int K) { return (SP_GEMM_ROT && S > 1 && K <= 8192) ? 1 : 0; }
 
 template <int NCG, bool GATEUP, int KCV, bool PACKED, bool ARGMAX = false>
 static hipError_t launch_mt(int MT, dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out,
-                            bf16_t* act, int M, int N, int K, int S, bool two = false, const float* ssq = nullptr, float eps = 0.f) {
+                            bf16_t* act, int M, int N, int K, int S, const float* ssq = nullptr, float eps = 0.f) {
 #define SP_GO(MTV, KCX)                                                                                        \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, NCG, GATEUP, KCX, SP_GEMM_PF, PACKED, ARGMAX>), grid, dim3(256), 0, st, X, \
                      W, out, act, M, N, K, K / KCX, S, 0, (!GATEUP && !ARGMAX) ? rot_for(S, K) : 0, ssq, eps)
@@ -366,10 +322,8 @@ static hipError_t launch_mt(int MT, dim3 grid, hipStream_t st, const bf16_t* X, 
       else if (GATEUP && NCG == 4)
         hipLaunchKernelGGL((k_gemm_bf16<8, 4, true, 128, SP_GEMM_PF, PACKED, false>), grid, dim3(256), 0, st, X, W, out, act,
                            M, N, K, K / 128, S);
-      else if (GATEUP || !two) SP_GO(8, 128);
-      else
-        hipLaunchKernelGGL((k_gemm_bf16<8, 4, false, 128, SP_GEMM_PF, PACKED, false, true>), grid, dim3(256), 0, st, X, W,
-                           out, act, M, N, K, K / 128, S, 0, rot_for(S, K));
+      else if (GATEUP) SP_GO(8, 128);
+      else return hipErrorInvalidValue;               // plain products: 64 rows at most
       break;
   }
 #undef SP_GO
@@ -387,22 +341,16 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
                                int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident) {
   int MT, mblocks;
   row_blocks(M, &MT, &mblocks);
-  // 128-row blocks: two strips per wave (128 columns per workgroup) halve the panel traffic out of L2 (the
-  // 128 x K panel is read once per column tile: N/128 instead of N/64 times) but double the split count that
-  // fills the chip, i.e. the partial sums that go to memory and back.  The panel saving is N/128 * M*K*2 bytes
-  // of L2 reads, the price 65536/N * M*N*4 bytes of memory traffic: worth it for the large matrices (70B
-  // shape: 5.38 -> 4.78 ms per 128-node step), not for the 8B shape (65-128 rows: +3 to +6 %).
-  const bool two = MT == 8 && N % 128 == 0 && (double)N * (double)K >= 64.0 * 1048576.0;
   // 17-64 rows: workgroups of eight waves over 128 columns, one per CU -- the same waves per CU as two
   // four-wave workgroups of 64 columns, but the panel slice is staged once for all eight
-  const bool eight = SP_GEMM_PLAIN8 && N % 128 == 0 && ((MT >= 2 && MT <= 4) || (SP_GEMM_PLAIN8_MT8 && MT == 8 && !two && mblocks == 1));
+  const bool eight = SP_GEMM_PLAIN8 && N % 128 == 0 && MT >= 2;
   // ... or six waves over 96 columns where that divides the CUs evenly and 128 columns do not (N = 6144 on 256 CUs:
   // 64 tiles x 4 slices of equal length instead of 48 x 5 of 6 or 7 chunks)
-  const bool six = SP_GEMM_PLAIN6 && eight && MT <= 4 && N % 96 == 0 && (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 128) != 0 &&
+  const bool six = SP_GEMM_PLAIN6 && eight && N % 96 == 0 && (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 128) != 0 &&
                    (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 96) == 0;
-  const int TILE = six ? 96 : (two || eight) ? 128 : 16 * SP_GEMM_NCG_PLAIN;
-  if (M < 1 || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
-  const int chunks = K / (MT == 8 ? 128 : SP_GEMM_KC_PLAIN);
+  const int TILE = six ? 96 : eight ? 128 : 16 * SP_GEMM_NCG_PLAIN;
+  if (M < 1 || M > 64 || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
+  const int chunks = K / SP_GEMM_KC_PLAIN;
   const int tiles = N / TILE;
   // Enough workgroups to keep every CU streaming, within the partial-sum buffer.  Every slice costs M*N*4 bytes
   // written here and read again by the kernel that folds them, which outweighs a finer split: at most two
@@ -419,7 +367,7 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   const dim3 grid(tiles, S, mblocks);
   if (six) {
 #define SP_GO6(MTV, PK)                                                                                          \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 6, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, false, 6>), grid, dim3(384), 0, \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, 6, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, 6>), grid, dim3(384), 0, \
                      st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K))
     if (packed) { if (MT == 2) SP_GO6(2, true); else if (MT == 3) SP_GO6(3, true); else SP_GO6(4, true); }
     else { if (MT == 2) SP_GO6(2, false); else if (MT == 3) SP_GO6(3, false); else SP_GO6(4, false); }
@@ -429,34 +377,29 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   if (eight) {
 #define SP_GO8(MTV, PK)                                                                                          \
   if (resident)                                                                                                  \
-    hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, PK, false, false, 8, false, false>), \
+    hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, PK, false, 8, false, false>), \
                        grid, dim3(512), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K)); \
   else                                                                                                           \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, PK, false, false, 8>), grid, dim3(512), 0, \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, PK, false, 8>), grid, dim3(512), 0, \
                      st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K))
-    if (packed) { if (MT == 2) SP_GO8(2, true); else if (MT == 3) SP_GO8(3, true); else if (MT == 4) SP_GO8(4, true); else SP_GO8(8, true); }
-    else { if (MT == 2) SP_GO8(2, false); else if (MT == 3) SP_GO8(3, false); else if (MT == 4) SP_GO8(4, false); else SP_GO8(8, false); }
+    if (packed) { if (MT == 2) SP_GO8(2, true); else if (MT == 3) SP_GO8(3, true); else SP_GO8(4, true); }
+    else { if (MT == 2) SP_GO8(2, false); else if (MT == 3) SP_GO8(3, false); else SP_GO8(4, false); }
 #undef SP_GO8
     return hipGetLastError();
   }
-  if (packed) return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, true>(MT, grid, st, X, W, out, nullptr, M, N, K, S, two);
-  return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, false>(MT, grid, st, X, W, out, nullptr, M, N, K, S, two);
+  if (packed) return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, true>(MT, grid, st, X, W, out, nullptr, M, N, K, S);
+  return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, false>(MT, grid, st, X, W, out, nullptr, M, N, K, S);
 }
 
 template <bool PACKED>
 static hipError_t launch_even(int MT, int n_wg, hipStream_t st, const bf16_t* X, const bf16_t* W, bf16_t* act, int M,
                               int F, int K, int cpw) {
 #define SP_GO(MTV)                                                                                              \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 4, true, SP_GEMM_KC_GATEUP, SP_GEMM_PF_EVEN, PACKED, false, false, 8, true>),   \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, 4, true, SP_GEMM_KC_GATEUP, SP_GEMM_PF_EVEN, PACKED, false, 8, true>),   \
                      dim3(n_wg), dim3(512), 0, st, X, W, nullptr, act, M, F, K, K / SP_GEMM_KC_GATEUP, 1, cpw)
   switch (MT) {
     case 2: SP_GO(2); break;
-    case 3: SP_GO(3); break;
-    case 4: SP_GO(4); break;
-    default:      // 65-128 rows: the 128-k chunk, so that the two 128-row panels fit
-      hipLaunchKernelGGL((k_gemm_bf16<8, 4, true, 128, SP_GEMM_PF_EVEN, PACKED, false, false, 8, true>), dim3(n_wg), dim3(512), 0,
-                         st, X, W, nullptr, act, M, F, K, K / 128, 1, cpw);
-      break;
+    default: SP_GO(3); break;
   }
 #undef SP_GO
   return hipGetLastError();
@@ -467,7 +410,7 @@ static hipError_t launch_even7(int MT, int n_wg, hipStream_t st, const bf16_t* X
                                int F, int K, int cpw) {
   // three weight chunks in flight up to 64 rows (148 -> 145 us per launch), two with 128 (three: 171 -> 179 us)
 #define SP_GO(MTV, PFV)                                                                                         \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 7, true, 128, PFV, PACKED, false, false, 7, true>), dim3(n_wg), dim3(448), 0, st, X, \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, 7, true, 128, PFV, PACKED, false, 7, true>), dim3(n_wg), dim3(448), 0, st, X, \
                      W, nullptr, act, M, F, K, K / 128, 1, cpw)
   switch (MT) {
     case 2: SP_GO(2, 3); break;
@@ -485,8 +428,9 @@ hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool pac
   row_blocks(M, &MT, &mblocks);
   if (ssq && MT != 1) return hipErrorInvalidValue;
   if (M < 1 || F % 64 || K % SP_GEMM_KC_GATEUP || K % 128) return hipErrorInvalidValue;
-  // 17-64 rows and a d_ff that gives every CU the same 56 or 64 columns: one eight-wave workgroup per CU
-  if (MT >= SP_GEMM_EVEN_MIN_MT && (MT <= 4 || (SP_GEMM_EVEN_MT8 && mblocks == 1)) && n_cu > 0 && F % n_cu == 0 && (F / n_cu) % 8 == 0 && F / n_cu > 48 &&
+  // 17-48 rows and a d_ff that gives every CU the same 56 or 64 columns: one eight-wave workgroup per CU (more rows:
+  // sp_gemm_mid.hip)
+  if (MT >= SP_GEMM_EVEN_MIN_MT && MT <= 3 && n_cu > 0 && F % n_cu == 0 && (F / n_cu) % 8 == 0 && F / n_cu > 48 &&
       F / n_cu <= 64 && SP_GEMM_KC_GATEUP == 256) {
     return packed ? launch_even<true>(MT, n_cu, st, X, W, act, M, F, K, F / n_cu)
                   : launch_even<false>(MT, n_cu, st, X, W, act, M, F, K, F / n_cu);
@@ -496,7 +440,7 @@ hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool pac
     return packed ? launch_even7<true>(MT, n_cu, st, X, W, act, M, F, K, F / n_cu)
                   : launch_even7<false>(MT, n_cu, st, X, W, act, M, F, K, F / n_cu);
   }
-  // From 49 rows on: 64 gate + 64 up columns per workgroup (four column groups, 128-k chunks) where that
+  // Other widths from 49 rows on: 64 gate + 64 up columns per workgroup (four column groups, 128-k chunks) where that
   // still gives every CU a workgroup, so that the staged panel is at most as large as the weights it meets
   // (70B shape: gate/up 193.6 -> 179.3 us at 64 rows, 252 -> 212 us at 128 rows); else 32 + 32 columns.  With
   // d_ff = 14336 the wider workgroups number 224 and run level with the 448 narrow ones (53.2 against 53.9 us).
@@ -507,8 +451,8 @@ hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool pac
   }
   const int TILE = tile_cols(MT, true);
   const dim3 grid(F / TILE, 1, mblocks);
-  if (packed) return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, true>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, false, ssq, eps);
-  return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, false>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, false, ssq, eps);
+  if (packed) return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, true>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, ssq, eps);
+  return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, false>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, ssq, eps);
 }
 
 // Output head: per row the top column of every 64-column tile, as (value, index) pairs
@@ -528,7 +472,7 @@ hipError_t sp_launch_gemm_argmax_bf16(const bf16_t* X, const bf16_t* W, bool pac
   const dim3 grid(tiles, 1, mblocks);
   if (eight) {
 #define SP_GOA(MTV, PK)                                                                                        \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, 128, SP_GEMM_PF, PK, true, false, 8>), grid, dim3(512), 0, st, X, W, \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, 128, SP_GEMM_PF, PK, true, 8>), grid, dim3(512), 0, st, X, W, \
                      pairs, nullptr, M, V, K, K / 128, 1, 0)
     if (packed) { if (MT == 2) SP_GOA(2, true); else if (MT == 3) SP_GOA(3, true); else SP_GOA(4, true); }
     else { if (MT == 2) SP_GOA(2, false); else if (MT == 3) SP_GOA(3, false); else SP_GOA(4, false); }

@@ -133,6 +133,14 @@ hipError_t sp_launch_few_residual(const bf16_t* X, const bf16_t* W, bool packed,
 // rows of the plan's x_out = bf16(h + X W^T)
 hipError_t sp_launch_few_out(const bf16_t* X, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
                              int N, int K, hipStream_t st);
+// 49-160 rows (sp_gemm_mid.hip): one workgroup per CU, two strips of weight rows per wave; `takes` says for which
+// sizes these are to be called (gate/up: where every CU gets the same 56 or 64 columns)
+bool sp_gemm_mid_takes(int M, int N, int K);
+bool sp_gemm_mid_takes_gateup(int M, int F, int K, int n_cu);
+hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,
+                              int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident);
+hipError_t sp_launch_gemm_mid_gateup(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F, int K, int n_cu,
+                                     hipStream_t st);
 // Many rows (M > 128): workgroups of 128 rows x 256 columns, weights kept in registers per wave.
 // Needs N % 256 == 0 (gate/up: F % 128 == 0) and K % 64 == 0.
 hipError_t sp_launch_gemm_wide(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
