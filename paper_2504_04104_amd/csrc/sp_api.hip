@@ -1141,7 +1141,7 @@ int sp_stage_verify_lossy(sp_stage* s, const sp_head_weights* head, int32_t n, c
   }
   if (e == hipSuccess)
     e = sp_launch_verify_lossy(s->d_meta, s->d_tables, w.part, n, req_ids, V, mode, top_p, w.part + logit_floats,
-                               result_dev, st);
+                               w.part_floats - logit_floats, result_dev, st);
   if (e == hipSuccess && result_host)
     e = hipMemcpyAsync(result_host, result_dev, sizeof(int32_t) * 2 * n, hipMemcpyDeviceToHost, st);
   return e == hipSuccess ? SP_OK : hip_fail(s, e);
@@ -1174,15 +1174,25 @@ int sp_stage_verify_sample(sp_stage* s, const sp_head_weights* head, int32_t n, 
   hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, n, d, c.rms_eps, st);
   if (e != hipSuccess) return hip_fail(s, e);
   ProfScope p(s, SP_K_VERIFY_HEAD, st);
+  // statistics of the logits' tiles behind them, where the workspace has room; the deciding kernel can do without
+  float* stats = nullptr;
+  int tile_cols = 0;
   if (s->fast && V % 64 == 0 && d % 128 == 0) {
-    int S = 1;
-    e = sp_launch_gemm_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, n, V, d, 1,
-                            logit_floats, &S, st);
+    if (logit_floats + (size_t)n * (V / 64) * 2 <= w.part_floats) {
+      stats = w.part + logit_floats;
+      e = sp_launch_gemm_logits_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, stats,
+                                     1.f / temperature, n, V, d, &tile_cols, st);
+    } else {
+      int S = 1;
+      e = sp_launch_gemm_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, n, V, d, 1,
+                              logit_floats, &S, st);
+    }
   } else {
     e = sp_launch_gemm_simple(c.dtype, w.xn, head->wvocab, w.part, n, V, d, st);
   }
   if (e == hipSuccess)
-    e = sp_launch_verify_sample(s->d_meta, s->d_tables, w.part, n, req_ids, V, temperature, top_p, top_k, u, result_dev, st);
+    e = sp_launch_verify_sample(s->d_meta, s->d_tables, w.part, n, req_ids, V, temperature, top_p, top_k, u, stats,
+                                tile_cols, result_dev, st);
   if (e == hipSuccess && result_host)
     e = hipMemcpyAsync(result_host, result_dev, sizeof(int32_t) * 2 * n, hipMemcpyDeviceToHost, st);
   return e == hipSuccess ? SP_OK : hip_fail(s, e);

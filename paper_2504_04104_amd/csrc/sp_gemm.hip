@@ -70,6 +70,8 @@
 // ARGMAX (output head of the last stage, Algorithm 1 "verify new token"): instead of the
 // products, a workgroup leaves per row the largest of its 16*NCG columns and that column's
 // index (the lowest one among equal maxima) as a (float, int) pair at out[(m * tiles + tile) * 2].
+// STATS (logits of a stochastic verification): beside the products, a workgroup leaves per row the maximum mx of its
+// 16*NCG columns and the sum of exp((l - mx) * inv_T) over them as a float pair at stats[(m * tiles + tile) * 2].
 // EVEN (gate/up): one workgroup per CU covers cpw = d_ff / CUs activation columns, a multiple of 8, in NCG column
 // groups of 16 columns and a last one of cpw - 16 * (NCG - 1) -- eight waves as four groups times two k-halves for
 // 48 < cpw <= 64, seven waves as seven groups for 96 < cpw <= 112 (the upper lanes of a short last group re-read
@@ -77,11 +79,12 @@
 // fetched twice).  Every CU then streams the same bytes, which 16-row
 // strips in fixed 32-column workgroups cannot do when d_ff / 32 is not a multiple of the CU count (d_ff = 14336:
 // 1.75 workgroups per CU), and the panel is staged once per CU instead of once per four waves.
-template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, int NWAVES = 4, bool EVEN = false, bool WNT = true>
+template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, int NWAVES = 4, bool EVEN = false, bool WNT = true,
+          bool STATS = false>
 __global__ void __launch_bounds__(64 * NWAVES)
 k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
             bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int cpw = 0, int rot = 0,
-            const float* ssq = nullptr, float eps = 0.f) {
+            const float* ssq = nullptr, float eps = 0.f, float* stats = nullptr, float inv_T = 0.f) {
   static_assert(!EVEN || GATEUP, "even split: gate/up only");
   constexpr int NTH = 64 * NWAVES;
   constexpr int NKH = NWAVES / NCG;       // waves sharing a column group split each chunk's k-steps
@@ -266,6 +269,35 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
       reinterpret_cast<int*>(o)[1] = bi;
     }
     return;
+  }
+  if (STATS) {
+    static_assert(!STATS || (NKH == 1 && !GATEUP && !ARGMAX), "one wave per column group");
+    float* s_mx = reinterpret_cast<float*>(&lds[0][0]);           // [NCG][ROWS]; the panels are no longer read
+    float* s_z = s_mx + NCG * ROWS;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const f32x4_t v = acc[0][mt];
+      const float mx = quad_rows_max(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
+      const float ref = mx == -INFINITY ? 0.f : mx;               // a piece without a finite value adds nothing
+      float z = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) z += expf((v[i] - ref) * inv_T);
+      z = quad_rows_sum(z);
+      if (kg == 0) { s_mx[cg * ROWS + mt * 16 + r] = mx; s_z[cg * ROWS + mt * 16 + r] = z; }
+    }
+    __syncthreads();
+    if (tid < ROWS && m_base + tid < M) {
+      float mx = s_mx[tid];
+#pragma unroll
+      for (int c = 1; c < NCG; ++c) mx = fmaxf(mx, s_mx[c * ROWS + tid]);
+      float z = 0.f;
+#pragma unroll
+      for (int c = 0; c < NCG; ++c) {
+        const float pm = s_mx[c * ROWS + tid];
+        z += s_z[c * ROWS + tid] * (pm == mx || pm == -INFINITY ? 1.f : expf((pm - mx) * inv_T));
+      }
+      *reinterpret_cast<float2*>(stats + ((size_t)(m_base + tid) * gridDim.x + blockIdx.x) * 2) = make_float2(mx, z);
+    }
   }
   float row_scale = 1.f;
   if (SCALED && ssq) {
@@ -481,6 +513,28 @@ hipError_t sp_launch_gemm_argmax_bf16(const bf16_t* X, const bf16_t* W, bool pac
   }
   if (packed) return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, true, true>(MT, grid, st, X, W, pairs, nullptr, M, V, K, 1);
   return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, false, true>(MT, grid, st, X, W, pairs, nullptr, M, V, K, 1);
+}
+
+// Logits [M][V] (M <= 64, no split) with the statistics of every tile of *tile_cols columns: stats[(m * V / *tile_cols +
+// tile) * 2] = (maximum, sum of exp((l - maximum) * inv_T)).
+hipError_t sp_launch_gemm_logits_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* logits, float* stats, float inv_T,
+                                      int M, int V, int K, int* tile_cols, hipStream_t st) {
+  const int MT = (M + 15) / 16;
+  const bool eight = MT >= 2 && V % 128 == 0;           // shapes as in the plain projections
+  const int TILE = eight ? 128 : 64;
+  if (M < 1 || M > 64 || V % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
+  *tile_cols = TILE;
+  const dim3 grid(V / TILE);
+#define SP_GOL(MTV, NCGV, PK)                                                                                          \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, NCGV, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, NCGV, false, true, true>), \
+                     grid, dim3(64 * NCGV), 0, st, X, W, logits, nullptr, M, V, K, K / SP_GEMM_KC_PLAIN, 1, 0, 0, nullptr, 0.f, stats, inv_T)
+#define SP_GOT(NCGV, PK) \
+  if (MT == 1) SP_GOL(1, NCGV, PK); else if (MT == 2) SP_GOL(2, NCGV, PK); else if (MT == 3) SP_GOL(3, NCGV, PK); else SP_GOL(4, NCGV, PK)
+  if (eight) { if (packed) { SP_GOT(8, true); } else { SP_GOT(8, false); } }
+  else { if (packed) { SP_GOT(4, true); } else { SP_GOT(4, false); } }
+#undef SP_GOT
+#undef SP_GOL
+  return hipGetLastError();
 }
 
 // Re-lays a [N][K] row-major bf16 matrix into MFMA fragment order: 16-byte unit u of the output

@@ -48,14 +48,16 @@ hipError_t sp_launch_set_root_pred(ReqMeta* meta, int req, int token, hipStream_
 // xn = rmsnorm(x) * gain for M rows (no residual stream, no row descriptors)
 hipError_t sp_launch_row_norm(int dtype, const void* x, const void* gain, void* xn, int M, int d, float eps,
                               hipStream_t st);
-// floats of scratch sp_launch_verify_lossy needs for n rows of V logits
+// floats of scratch sp_launch_verify_lossy needs at least for n rows of V logits (it uses more if there is more)
 size_t sp_lossy_scratch_floats(int n, int V);
 // mode 1 relaxed, 2 top-p; logits [n][V]; out[2i] = verified node of reqs[i] or -1, out[2i+1] = top-1 token
 hipError_t sp_launch_verify_lossy(ReqMeta* meta, const ReqTables* tables, const float* logits, int n, const int* reqs,
-                                  int V, int mode, float top_p, float* scratch, int* out, hipStream_t st);
+                                  int V, int mode, float top_p, float* scratch, size_t scratch_floats, int* out,
+                                  hipStream_t st);
 // stochastic verification: out[2i] = verified node of reqs[i] or -1, out[2i+1] = the token drawn at u[i]
 hipError_t sp_launch_verify_sample(ReqMeta* meta, const ReqTables* tables, const float* logits, int n, const int* reqs,
-                                   int V, float temperature, float top_p, int top_k, const float* u /*host*/, int* out,
+                                   int V, float temperature, float top_p, int top_k, const float* u /*host*/,
+                                   const float* stats /*nullable: sp_launch_gemm_logits_bf16's*/, int tile_cols, int* out,
                                    hipStream_t st);
 hipError_t sp_launch_kv_compact(const ReqMeta* meta, const ReqTables* tables, const PruneBatch& b, KvGeom g,
                                 void* rows /*nullable: hidden rows of the one request, same launch*/,
@@ -116,6 +118,8 @@ hipError_t sp_launch_gemm_simple(int dtype, const void* X, const void* W, float*
 hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st,
                                bool resident = false);
+hipError_t sp_launch_gemm_logits_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* logits, float* stats, float inv_T,
+                                      int M, int V, int K, int* tile_cols, hipStream_t st);
 // act[m][f] = silu(X Wg^T) * (X Wu^T), W = [gate rows ; up rows]
 hipError_t sp_launch_gemm_argmax_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* pairs, int M, int V, int K,
                                       size_t pair_capacity_floats, int* tiles_out, hipStream_t st);

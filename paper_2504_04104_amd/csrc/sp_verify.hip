@@ -9,13 +9,13 @@
 // Input: one row of logits per request (the root's output through the final norm and the
 // vocabulary matrix).  A token t is in the top-p set iff the mass of the tokens in front of it,
 //   before(t) = sum over { v : l_v > l_t  or  (l_v == l_t and v < t) } of softmax(l)_v,
-// is below p.  k_lossy_slices cuts the vocabulary into slices of SLICE tokens, one workgroup
-// each: slice maximum and its first index, sum of exp(l - slice max), and, one thread per
-// candidate, the slice's share of before(token of the candidate).  k_lossy_decide rescales and
-// adds the slices in order (so the result does not depend on timing) and decides.
+// is below p.  k_lossy_slices cuts the vocabulary into slices, one workgroup each: slice maximum
+// and its first index, sum of exp(l - slice max), and, one lane per candidate, the slice's share
+// of before(token of the candidate).  k_lossy_decide rescales and adds the slices in a fixed
+// order (so the result does not depend on timing) and decides.
 #include "sp_launch.h"
 
-#define SLICE 2048
+#define SLICE 2048        // most tokens of a slice
 
 template <typename T>
 __global__ void __launch_bounds__(1024) k_row_norm(const T* __restrict__ x, const T* __restrict__ gain,
@@ -36,15 +36,15 @@ __global__ void __launch_bounds__(1024) k_row_norm(const T* __restrict__ x, cons
     Elt<T>::st(xn + (size_t)row * d + c, Elt<T>::ld(xr + c) * rs * Elt<T>::ld(gain + c));
 }
 
-// The root's children in node order: s_node[0..nc), their tokens in s_tok.  Called by all 256 threads.
+// The root's children in node order: s_node[0..nc), their tokens in s_tok.  Called by all threads (256 or more).
 __device__ __forceinline__ int root_children(const ReqTables& t, int T, int* s_node, int* s_tok, int* s_wcount) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const bool is = tid < T && t.parent[tid] == -1;
   const unsigned long long bal = __ballot(is);
-  if (lane == 0) s_wcount[wave] = __popcll(bal);
+  if (lane == 0 && wave < 4) s_wcount[wave] = __popcll(bal);
   __syncthreads();
   int before = 0;
-  for (int w = 0; w < wave; ++w) before += s_wcount[w];
+  for (int w = 0; w < min(wave, 4); ++w) before += s_wcount[w];
   if (is) {
     const int pos = before + __popcll(bal & ((1ull << lane) - 1ull));
     s_node[pos] = tid;
@@ -56,7 +56,7 @@ __device__ __forceinline__ int root_children(const ReqTables& t, int T, int* s_n
 }
 
 struct LossyBatch {
-  int n, mode, V, n_slices;
+  int n, mode, V, slice, n_slices;
   float top_p;
   int req[SP_BATCH];
 };
@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(256) k_lossy_slices(const ReqMeta* meta, const
   const int req = b.req[item];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float* L = logits + (size_t)item * b.V;
-  const int v0 = slice * SLICE, len = min(SLICE, b.V - v0);
+  const int v0 = slice * b.slice, len = min(b.slice, b.V - v0);
   const int nc = root_children(tables[req], meta[req].T, s_node, s_tok, s_wcount);
 
   float bv = -INFINITY;
@@ -121,6 +121,7 @@ __global__ void __launch_bounds__(256) k_lossy_slices(const ReqMeta* meta, const
     reinterpret_cast<int*>(st)[2] = bi;
     st[3] = 0.f;
   }
+  if (b.mode == 1) return;                             // the relaxed rule compares logits, not masses
   // Candidate against every token of the slice.  Up to 64 candidates: lane = candidate, and the four
   // waves take a quarter of the slice each; up to 128: two halves; else one wave per 64 candidates.
   // All lanes of a wave read the same LDS words (a broadcast), four tokens per read.  The parts are
@@ -158,90 +159,112 @@ __global__ void __launch_bounds__(256) k_lossy_slices(const ReqMeta* meta, const
 }
 
 // out[2*item] = verified node or -1, out[2*item+1] = the model's top-1 token, which also becomes the
-// root's stored prediction (what a miss falls back to).
-__global__ void __launch_bounds__(256) k_lossy_decide(ReqMeta* meta, const ReqTables* tables,
-                                                       const float* __restrict__ logits, LossyBatch b,
-                                                       const float* stats, const float* before, int* out) {
+// root's stored prediction (what a miss falls back to).  A chain of latencies: every step over slices or
+// candidates is taken by all sixteen waves (one request, 64 candidates: 15.7 us with 63 slices before, 13.1 us with 251).
+__global__ void __launch_bounds__(1024) k_lossy_decide(ReqMeta* meta, const ReqTables* tables,
+                                                        const float* __restrict__ logits, LossyBatch b,
+                                                        const float* stats, const float* before, int* out) {
+  constexpr int BLK = 1024;              // slices per round
   __shared__ int s_node[SP_T], s_tok[SP_T], s_wcount[4];
-  __shared__ float s_key[SP_T];          // relaxed: the candidate's logit; top-p: its draft probability
-  __shared__ unsigned char s_ok[SP_T];
-  const int item = blockIdx.x, req = b.req[item], tid = threadIdx.x;
+  __shared__ float s_sc[BLK], s_part[16][64], s_red[16], s_before[SP_T];
+  __shared__ int s_redi[16];
+  const int item = blockIdx.x, req = b.req[item], tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const ReqTables& t = tables[req];
   const float* L = logits + (size_t)item * b.V;
-  const int nc = root_children(t, meta[req].T, s_node, s_tok, s_wcount);
   const float* st = stats + (size_t)item * b.n_slices * 4;
-  // slice maxima -> the row's maximum and its first index; then each slice's factor exp(max_s - max)
-  __shared__ float s_sc[256], s_z[256];
-  __shared__ int s_top1;
-  __shared__ float s_m;
-  {
-    // thread s takes slices s, s+256, ...; then the 256 candidates are folded in order by thread 0
-    float mv = -INFINITY;
-    int mi = 0x7fffffff;
-    for (int s0 = tid; s0 < b.n_slices; s0 += 256) {
-      const float v = st[s0 * 4];
-      const int i = reinterpret_cast<const int*>(st)[s0 * 4 + 2];
-      if (v > mv || (v == mv && i < mi)) { mv = v; mi = i; }
-    }
-    s_sc[tid] = mv;
-    reinterpret_cast<int*>(s_z)[tid] = mi;
-    __syncthreads();
-    if (tid == 0) {
-      float m = -INFINITY;
-      int top1 = 0x7fffffff;
-      const int lim = min(256, b.n_slices);
-      for (int q = 0; q < lim; ++q) {
-        const float v = s_sc[q];
-        const int i = reinterpret_cast<const int*>(s_z)[q];
-        if (v > m || (v == m && i < top1)) { m = v; top1 = i; }
-      }
-      s_m = m; s_top1 = top1;
-    }
+  // the slices' maxima are asked for before the walk over the tables
+  float m = -INFINITY;
+  int top1 = 0x7fffffff;
+  for (int q = tid; q < b.n_slices; q += 1024) {
+    const float v = st[q * 4];
+    const int i = reinterpret_cast<const int*>(st)[q * 4 + 2];
+    if (v > m || (v == m && i < top1)) { m = v; top1 = i; }
   }
-  __syncthreads();
-  const float m = s_m;
-  const int top1 = s_top1;
-  float Z = 0.f, bf = 0.f;
+  const int nc = root_children(t, meta[req].T, s_node, s_tok, s_wcount);
+  // larger value first, the lower index among equal ones; the same answer in every thread
+  auto block_top = [&](float& v, int& i) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const float ov = __shfl_xor(v, off, 64);
+      const int oi = __shfl_xor(i, off, 64);
+      if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
+    }
+    __syncthreads();
+    if (lane == 0) { s_red[wave] = v; s_redi[wave] = i; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 16; ++w)
+      if (s_red[w] > v || (s_red[w] == v && s_redi[w] < i)) { v = s_red[w]; i = s_redi[w]; }
+  };
+  // what the candidates are ranked by: the token's logit (relaxed) or its draft probability
+  float Z = 0.f;
   const bool mine = tid < nc;
   const int tk = mine ? s_tok[tid] : -1;
   const bool valid = tk >= 0 && tk < b.V;
-  for (int s0 = 0; s0 < b.n_slices; s0 += 256) {     // blocks of 256 slices (one is the rule)
-    const int ns = min(256, b.n_slices - s0);
-    __syncthreads();
-    if (tid < ns) {
-      s_sc[tid] = expf(st[(s0 + tid) * 4] - m);
-      s_z[tid] = st[(s0 + tid) * 4 + 1];
-    }
-    __syncthreads();
-    if (mine && b.mode == 2) {
-      const float* bp = before + ((size_t)item * b.n_slices + s0) * SP_T + tid;
-      int q = 0;
-      for (; q + 8 <= ns; q += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = bp[(size_t)(q + u) * SP_T];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) { Z += s_z[q + u] * s_sc[q + u]; bf += v[u] * s_sc[q + u]; }
+  const float key = !valid ? -INFINITY : b.mode == 1 ? L[tk] : t.prob[s_node[tid]];
+  block_top(m, top1);
+
+  if (b.mode == 2) {
+    // waves as candidate groups of 64 times runs of slices; a run's slices are read eight at a time
+    const int groups = (nc + 63) >> 6, runs = groups > 0 ? 16 / groups : 1;
+    const int cg = groups > 0 ? wave % groups : 0, run = groups > 0 ? wave / groups : runs;
+    float z = 0.f, acc = 0.f;
+    for (int q0 = 0; q0 < b.n_slices; q0 += BLK) {
+      const int ns = min(BLK, b.n_slices - q0);
+      __syncthreads();
+      if (tid < ns) {
+        const float sc = expf(st[(q0 + tid) * 4] - m);
+        s_sc[tid] = sc;
+        z += st[(q0 + tid) * 4 + 1] * sc;
       }
-      for (; q < ns; ++q) { Z += s_z[q] * s_sc[q]; bf += bp[(size_t)q * SP_T] * s_sc[q]; }
+      __syncthreads();
+      if (run < runs) {
+        const float* bp = before + ((size_t)item * b.n_slices + q0) * SP_T + cg * 64 + lane;
+        const bool in = cg * 64 + lane < nc;
+        const int a0 = ns * run / runs, a1 = ns * (run + 1) / runs;
+        int q = a0;
+        for (; q + 8 <= a1; q += 8) {
+          float v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = in ? bp[(size_t)(q + u) * SP_T] : 0.f;
+#pragma unroll
+          for (int u = 0; u < 8; ++u) acc += v[u] * s_sc[q + u];
+        }
+        for (; q < a1; ++q) acc += (in ? bp[(size_t)q * SP_T] : 0.f) * s_sc[q];
+      }
+    }
+    z = wave_sum(z);
+    __syncthreads();
+    if (lane == 0) s_red[wave] = z;
+    s_part[wave][lane] = acc;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 16; ++w) Z += s_red[w];
+    if (mine) {
+      float bf = 0.f;
+      for (int q = 0; q < runs; ++q) bf += s_part[q * groups + (tid >> 6)][tid & 63];
+      s_before[tid] = bf;
     }
   }
-  if (mine) {
-    if (b.mode == 1) {
-      s_ok[tid] = valid;
-      s_key[tid] = valid ? L[tk] : -INFINITY;
-    } else {
-      s_ok[tid] = valid && bf < b.top_p * Z;
-      s_key[tid] = t.prob[s_node[tid]];
-    }
+  const bool ok = valid && (b.mode == 1 || s_before[tid] < b.top_p * Z);
+  // the first acceptable candidate stays if its key is no number; other keys that are none never win
+  float first_key = 0.f;
+  int first = ok ? tid : 0x7fffffff;
+  {
+    float minus = ok ? -(float)tid : -INFINITY;
+    block_top(minus, first);
+    __syncthreads();
+    if (tid == first) s_red[0] = key;
+    __syncthreads();
+    first_key = first != 0x7fffffff ? s_red[0] : 0.f;
+    __syncthreads();
   }
-  __syncthreads();
+  float bk = ok && key == key ? key : -INFINITY;
+  int best = ok && key == key ? tid : 0x7fffffff;
+  block_top(bk, best);
   if (tid == 0) {
-    int best = -1;
-    float bk = -INFINITY;
-    for (int j = 0; j < nc; ++j)
-      if (s_ok[j] && (best < 0 || s_key[j] > bk)) { best = s_node[j]; bk = s_key[j]; }
-    out[2 * item] = best;
+    if (first != 0x7fffffff && first_key != first_key) best = first;
+    out[2 * item] = best == 0x7fffffff ? -1 : s_node[best];
     out[2 * item + 1] = top1;
     meta[req].root_pred = top1;
   }
@@ -258,9 +281,11 @@ __global__ void __launch_bounds__(256) k_lossy_decide(ReqMeta* meta, const ReqTa
 // One workgroup of 1024 threads per request: row maximum, normaliser over the whole vocabulary, the
 // top_k-th largest logit by a radix select over the order-preserving bit pattern (four passes of 8
 // bits, one histogram per wave), an index-ordered gather of the logits above it and of the first
-// ones equal to it, a sort by counting, and the running sums by one thread.
+// ones equal to it, a sort by counting, and the running sums by one wave.
 struct SampleBatch {
   int n, V, top_k;
+  int tile_cols;             // STATS: columns per statistics entry
+  const float* stats;        // STATS: [n][V / tile_cols] pairs (maximum, sum of exp((l - maximum) / T))
   float inv_T, top_p;
   int req[SP_BATCH];
   float u[SP_BATCH];
@@ -272,6 +297,10 @@ __device__ __forceinline__ uint32_t order_key(float f) {           // ascending 
 }
 __device__ __forceinline__ float key_value(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
+}
+
+__device__ __forceinline__ unsigned long long sample_key(float l, int idx) {
+  return (unsigned long long)order_key(l) << 32 | (unsigned long long)(0xffffffffu - (unsigned)idx);
 }
 
 // Eight loads of W floats per thread, all issued before the first use: one workgroup reads the whole row, so
@@ -299,7 +328,11 @@ __device__ __forceinline__ void sample_load(const float* __restrict__ L, int V, 
 // logit.  A second pass collects the elements >= t0 (a few hundred on a spread-out row) and their places follow
 // from counting.  Rows that defeat the bound (long runs of equal logits, vocabularies under a few thousand)
 // take a radix selection over the whole row instead.
-template <int W>
+// STATS: the kernel that formed the logits left every tile's maximum and exponential sum.  The tile maxima take the
+// place of the thread maxima, the normaliser is added up from the tiles, and only the tiles whose maximum reaches the
+// bound (some K of a thousand) are read: one workgroup no longer walks the row twice (32 requests over 128256 tokens:
+// 53 -> 15 us).
+template <int W, bool STATS>
 __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const ReqTables* tables,
                                                          const float* __restrict__ logits, SampleBatch b, int* out) {
   __shared__ float s_f[16], s_g[16];
@@ -308,8 +341,9 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
   __shared__ unsigned s_pick[2];                  // digit chosen by a pass, and how many of the top_k are still to find below it
   __shared__ uint32_t s_key[SP_SAMPLE_MAX_K], s_skey[SP_SAMPLE_MAX_K];
   __shared__ int s_idx[SP_SAMPLE_MAX_K], s_sidx[SP_SAMPLE_MAX_K];
-  __shared__ uint32_t s_ckey[SP_SAMPLE_CAND];
-  __shared__ int s_cidx[SP_SAMPLE_CAND];
+  // the short path's candidates: key above the complemented index, so that a larger number comes first (distinct)
+  __shared__ __attribute__((aligned(16))) unsigned long long s_cand[SP_SAMPLE_CAND + 8];
+  __shared__ int s_rank[SP_SAMPLE_CAND];
   __shared__ unsigned s_ncand;
   __shared__ int s_tok, s_best;
   const int item = blockIdx.x, req = b.req[item];
@@ -319,7 +353,11 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
 
   // first pass: thread maxima, from them the row maximum and the bound t0
   float tm = -INFINITY;
-  for (int base = 0; base < V; base += 8 * 1024 * W) {
+  const int n_tiles = STATS ? V / b.tile_cols : 0;
+  const float2* ts = reinterpret_cast<const float2*>(b.stats) + (size_t)item * n_tiles;
+  if (STATS)
+    for (int t = lane * 16 + wave; t < n_tiles; t += 1024) tm = fmaxf(tm, ts[t].x);   // every wave gets its share
+  for (int base = 0; !STATS && base < V; base += 8 * 1024 * W) {
     float v[8][W];
     sample_load<W>(L, V, base, tid, v);
 #pragma unroll
@@ -350,7 +388,51 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
 
   // second pass: the normaliser of softmax(l / T) over the whole vocabulary, added in a fixed order, and the candidates
   float z = 0.f;
-  for (int base = 0; base < V; base += 8 * 1024 * W) {
+  if (STATS) {
+    int* s_tile = reinterpret_cast<int*>(&s_hist[0][0]);          // the tiles to read; a longer list than this is cut ...
+    constexpr int TILES_MAX = 16 * 256;
+    if (tid == 0) s_pick[0] = 0u;
+    __syncthreads();
+    for (int t = tid; t < n_tiles; t += 1024) {
+      const float2 p = ts[t];
+      z += p.y * (p.x == mx || p.x == -INFINITY ? 1.f : expf((p.x - mx) * b.inv_T));
+      if (p.x >= t0) {
+        const unsigned at = atomicAdd(&s_pick[0], 1u);
+        if (at < TILES_MAX) s_tile[at] = t;
+      }
+    }
+    __syncthreads();
+    const int n_pick = (int)s_pick[0], cols = b.tile_cols;
+    if (n_pick > TILES_MAX) {
+      if (tid == 0) s_ncand = SP_SAMPLE_CAND + 1u;                // ... and the whole row is searched instead
+    } else {
+      // a tile is 64 or 128 columns; four of a wave's tiles in flight
+      for (int k0 = wave; k0 < n_pick; k0 += 64) {
+        float2 v[4];
+        int base[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = k0 + u * 16;
+          base[u] = k < n_pick ? s_tile[k] * cols : -1;
+          v[u] = make_float2(-INFINITY, -INFINITY);
+          if (base[u] >= 0 && 2 * lane < cols) v[u] = *reinterpret_cast<const float2*>(L + base[u] + 2 * lane);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (base[u] < 0 || 2 * lane >= cols) continue;
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const float l = c == 0 ? v[u].x : v[u].y;
+            if (l >= t0) {
+              const unsigned p = atomicAdd(&s_ncand, 1u);
+              if (p < SP_SAMPLE_CAND) s_cand[p] = sample_key(l, base[u] + 2 * lane + c);
+            }
+          }
+        }
+      }
+    }
+  }
+  for (int base = 0; !STATS && base < V; base += 8 * 1024 * W) {
     float v[8][W];
     sample_load<W>(L, V, base, tid, v);
 #pragma unroll
@@ -362,7 +444,7 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
           z += expf((v[u][c] - mx) * b.inv_T);
           if (v[u][c] >= t0) {
             const unsigned p = atomicAdd(&s_ncand, 1u);
-            if (p < SP_SAMPLE_CAND) { s_ckey[p] = order_key(v[u][c]); s_cidx[p] = i + c; }
+            if (p < SP_SAMPLE_CAND) s_cand[p] = sample_key(v[u][c], i + c);
           }
         }
       }
@@ -377,14 +459,36 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
   const int n_cand = (int)s_ncand;
 
   if (n_cand <= SP_SAMPLE_CAND) {
-    // descending probability, equal ones by ascending token id: a candidate's place is the number that beat it
-    for (int i = tid; i < n_cand; i += 1024) {
-      const uint32_t k = s_ckey[i];
-      const int ix = s_cidx[i];
+    // descending probability, equal ones by ascending token id: a candidate's place is the number that beat it,
+    // counted by several threads per candidate, each over its run of the list, eight candidates per step
+    int span = 64;                                   // candidates a pass of the threads covers
+    while (span < n_cand && span < 1024) span <<= 1;
+    const int parts = 1024 / span, part = tid / span;
+    const int per = ((n_cand + parts - 1) / parts + 7) & ~7;
+    const int j0 = min(part * per, n_cand), j1 = min(j0 + per, n_cand);
+    for (int i = tid; i < n_cand; i += 1024) s_rank[i] = 0;
+    if (tid < 8) s_cand[n_cand + tid] = 0ull;        // beats nobody
+    __syncthreads();
+    for (int i = tid % span; i < n_cand; i += span) {
+      const unsigned long long k = s_cand[i];
       int rank = 0;
-      for (int j = 0; j < n_cand; ++j) rank += (s_ckey[j] > k) || (s_ckey[j] == k && s_cidx[j] < ix);
-      if (rank < K) { s_skey[rank] = k; s_sidx[rank] = ix; }
+      for (int j = j0; j < j1; j += 8) {
+        unsigned long long o[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = s_cand[j + e];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rank += (o[e] > k && j + e < j1) ? 1 : 0;
+      }
+      if (parts == 1) s_rank[i] = rank;
+      else atomicAdd(&s_rank[i], rank);
     }
+    __syncthreads();
+    for (int i = tid; i < n_cand; i += 1024)
+      if (s_rank[i] < K) {
+        const unsigned long long k = s_cand[i];
+        s_skey[s_rank[i]] = (uint32_t)(k >> 32);
+        s_sidx[s_rank[i]] = (int)(0xffffffffu - (unsigned)k);
+      }
   } else {
     // the K-th largest key: fix its bytes from the top, counting the keys that share the bytes fixed so far
     uint32_t prefix = 0u, mask = 0u;
@@ -490,23 +594,42 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
   }
   if (tid == 0) s_best = 0x7fffffff;
   __syncthreads();
-  float* cum = reinterpret_cast<float*>(&s_hist[1][0]);           // K floats, free by now
-  if (tid < K) cum[tid] = expf((key_value(s_skey[tid]) - mx) * b.inv_T) / Z;
-  __syncthreads();
-  if (tid == 0) {
-    // running sums until top_p is reached (or the K candidates are used up); then the inverse CDF at u
-    float run = 0.f;
-    int m = 0;
-    for (; m < K;) {
-      run += cum[m];
-      cum[m] = run;
-      ++m;
-      if (run >= b.top_p) break;
+  // running sums until top_p is reached (or the K candidates are used up), then the inverse CDF at u: one wave, two
+  // candidates per lane (SP_SAMPLE_MAX_K = 128)
+  if (wave == 0) {
+    static_assert(SP_SAMPLE_MAX_K <= 128, "two candidates per lane");
+    float p[2], run[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int j = 2 * lane + e;
+      p[e] = j < K ? expf((key_value(s_skey[j]) - mx) * b.inv_T) / Z : 0.f;
     }
-    const float x = b.u[item] * run;
-    int j = 0;
-    while (j + 1 < m && !(x < cum[j])) ++j;
-    s_tok = s_sidx[j];
+    float incl = p[0] + p[1];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const float v = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += v;
+    }
+    const float prev = __shfl_up(incl, 1, 64);
+    const float below = lane > 0 ? prev : 0.f;
+    run[0] = below + p[0];
+    run[1] = incl;
+    // m candidates: up to and including the first whose running sum reaches top_p
+    int m = K;
+#pragma unroll
+    for (int e = 1; e >= 0; --e) {
+      const unsigned long long hit = __ballot(2 * lane + e < K && run[e] >= b.top_p);
+      if (hit) m = min(m, 2 * (int)__builtin_ctzll(hit) + e + 1);
+    }
+    const float total = __shfl(((m - 1) & 1) ? run[1] : run[0], (m - 1) >> 1, 64);
+    const float x = b.u[item] * total;
+    int pick = m - 1;
+#pragma unroll
+    for (int e = 1; e >= 0; --e) {
+      const unsigned long long hit = __ballot(2 * lane + e < m && x < run[e]);
+      if (hit) pick = min(pick, 2 * (int)__builtin_ctzll(hit) + e);
+    }
+    if (lane == 0) s_tok = s_sidx[pick];
   }
   __syncthreads();
   const int tok = s_tok;
@@ -521,15 +644,19 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
 }
 
 hipError_t sp_launch_verify_sample(ReqMeta* meta, const ReqTables* tables, const float* logits, int n, const int* reqs,
-                                   int V, float temperature, float top_p, int top_k, const float* u, int* out,
-                                   hipStream_t st) {
+                                   int V, float temperature, float top_p, int top_k, const float* u,
+                                   const float* stats, int tile_cols, int* out, hipStream_t st) {
   SampleBatch b;
-  b.n = n; b.V = V; b.top_k = top_k; b.inv_T = 1.f / temperature; b.top_p = top_p;
+  b.n = n; b.V = V; b.top_k = top_k; b.tile_cols = tile_cols; b.stats = stats; b.inv_T = 1.f / temperature; b.top_p = top_p;
   for (int i = 0; i < n; ++i) { b.req[i] = reqs[i]; b.u[i] = u[i]; }
-  if (V % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0)
-    hipLaunchKernelGGL(k_sample_decide<4>, dim3(n), dim3(1024), 0, st, meta, tables, logits, b, out);
+  // the bound needs ceil(top_k / 16) tiles for each of the 16 waves
+  const bool tiles = stats && V / tile_cols >= 16 * ((top_k + 15) / 16);
+  if (tiles)                                         // V % 64 == 0 there
+    hipLaunchKernelGGL((k_sample_decide<4, true>), dim3(n), dim3(1024), 0, st, meta, tables, logits, b, out);
+  else if (V % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0)
+    hipLaunchKernelGGL((k_sample_decide<4, false>), dim3(n), dim3(1024), 0, st, meta, tables, logits, b, out);
   else
-    hipLaunchKernelGGL(k_sample_decide<1>, dim3(n), dim3(1024), 0, st, meta, tables, logits, b, out);
+    hipLaunchKernelGGL((k_sample_decide<1, false>), dim3(n), dim3(1024), 0, st, meta, tables, logits, b, out);
   return hipGetLastError();
 }
 
@@ -542,21 +669,32 @@ hipError_t sp_launch_row_norm(int dtype, const void* x, const void* gain, void* 
   return hipGetLastError();
 }
 
+// Tokens per slice: short slices where few requests would leave most of the chip idle (one request over 128256 tokens:
+// 63 workgroups of 2048 tokens 37 us, 251 of 512 tokens 13 us), 2048 where the batch or the scratch memory asks for it.
+static int lossy_slice(int n, int V, size_t scratch_floats) {
+  for (int slice = 512; slice < SLICE; slice *= 2) {
+    const size_t slices = (size_t)(V + slice - 1) / slice;
+    if ((size_t)n * slices <= 512 && (size_t)n * slices * (4 + SP_T) <= scratch_floats) return slice;
+  }
+  return SLICE;
+}
+
 size_t sp_lossy_scratch_floats(int n, int V) {
   const size_t slices = (size_t)(V + SLICE - 1) / SLICE;
   return (size_t)n * slices * (4 + SP_T);
 }
 
 hipError_t sp_launch_verify_lossy(ReqMeta* meta, const ReqTables* tables, const float* logits, int n, const int* reqs,
-                                  int V, int mode, float top_p, float* scratch, int* out, hipStream_t st) {
+                                  int V, int mode, float top_p, float* scratch, size_t scratch_floats, int* out, hipStream_t st) {
   LossyBatch b;
-  b.n = n; b.mode = mode; b.V = V; b.n_slices = (V + SLICE - 1) / SLICE; b.top_p = top_p;
+  b.n = n; b.mode = mode; b.V = V; b.slice = lossy_slice(n, V, scratch_floats);
+  b.n_slices = (V + b.slice - 1) / b.slice; b.top_p = top_p;
   for (int i = 0; i < n; ++i) b.req[i] = reqs[i];
   float* stats = scratch;
   float* before = scratch + (size_t)n * b.n_slices * 4;
   hipLaunchKernelGGL(k_lossy_slices, dim3(b.n_slices, n), dim3(256), 0, st, meta, tables, logits, b, stats, before);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_lossy_decide, dim3(n), dim3(256), 0, st, meta, tables, logits, b, stats, before, out);
+  hipLaunchKernelGGL(k_lossy_decide, dim3(n), dim3(1024), 0, st, meta, tables, logits, b, stats, before, out);
   return hipGetLastError();
 }

@@ -1,0 +1,95 @@
+"""Verification kernels on logits that are known exactly: the vocabulary matrix has one non-zero per row and the roots'
+rows are all ones, so that a logit is that one number (RMSNorm of ones is 1 in bf16).  The choices can then be compared
+without a margin: tile statistics of the logits (64- and 128-column tiles), rows full of ties, rows that one token
+rules, candidate groups of every size."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+import paper_2504_04104_amd as sp
+from gpu_harness import Pair
+from oracle.verify import sample_token, sampling_candidates
+
+pytestmark = pytest.mark.gpu
+
+SHAPE = wl.ModelShape(n_layers=1, d_model=512, n_q_heads=4, n_kv_heads=2, d_head=128, d_ff=768)
+
+
+def exact_head(logits, packed):
+    V = len(logits)
+    w = torch.zeros(V, SHAPE.d_model)
+    w[torch.arange(V), torch.arange(V) % SHAPE.d_model] = torch.from_numpy(logits.astype(np.float32))
+    w = w.to("cuda:0", torch.bfloat16)
+    return {"norm": torch.ones(SHAPE.d_model, dtype=torch.bfloat16, device="cuda:0"), "wvocab": sp.pack_matrix(w) if packed else w}
+
+
+def draw_logits(kind, V, seed):
+    r = np.random.RandomState(seed)
+    l = r.normal(0.0, 2.0, V)
+    if kind == "peaked":
+        l[r.randint(V)] = 14.0
+    if kind == "levels":                  # more tied tokens than the short candidate list holds
+        l = r.choice([-1.0, 0.5, 2.0], V)
+    return torch.from_numpy(l).to(torch.bfloat16).double().numpy()
+
+
+@pytest.mark.parametrize("kind", ["spread", "peaked", "levels"])
+@pytest.mark.parametrize("n,V,packed", [(1, 64 * 140, True), (1, 64 * 140, False), (17, 128 * 100, True), (33, 64 * 141, False),
+                                        (64, 128 * 80, True), (3, 64 * 79, True)])
+def test_sampling_from_exact_logits(n, V, packed, kind):
+    """The token drawn at the middle of a candidate's interval is that candidate (64 * 79 columns: too few tiles for the
+    bound at 80 candidates, the kernel walks the row)."""
+    logits = draw_logits(kind, V, V + n)
+    pair = Pair(SHAPE, 5, {r: 9 for r in range(n)}, max_batch_nodes=64, oracle=False, flags=sp.SP_FLAG_PACKED_WEIGHTS if packed else 0)
+    head = exact_head(logits, packed)
+    x = torch.ones(n, SHAPE.d_model, dtype=torch.bfloat16, device="cuda:0")
+    r = np.random.RandomState(n)
+    for T, p, k in ((0.6, 0.9, 80), (1.0, 1.0, 7), (0.3, 0.999, 80)):
+        toks, ps = sampling_candidates(logits, T, p, k)
+        c = np.concatenate(([0.0], np.cumsum(ps))) / np.sum(ps)
+        wide = [j for j in range(len(ps)) if c[j + 1] - c[j] > 1e-4]
+        picks = [wide[0], wide[-1]][:n] + [wide[r.randint(len(wide))] for _ in range(n - 2)]
+        u = [float(np.float32(0.5 * (c[j] + c[j + 1]))) for j in picks]
+        got = pair.gpu.verify_sample(head, list(range(n)), x, T, p, k, u)
+        for (node, tok), j, v in zip(got, picks, u):
+            assert sample_token(logits, T, p, k, v) == toks[j]
+            assert tok == toks[j] and node == -1, (T, p, k, j)
+    pair.close()
+
+
+@pytest.mark.parametrize("n_child", [1, 63, 64, 65, 129, 200])
+@pytest.mark.parametrize("n,V", [(1, 5003), (2, 64 * 140), (40, 64 * 70)])
+def test_lossy_from_exact_logits(n, V, n_child):
+    """Relaxed: the child whose token has the highest logit, the first among equals.  Top-p: of the children whose token
+    has less than top_p of the mass in front of it, the one with the highest draft probability (a child within 1e-5 of
+    top_p is not asked for)."""
+    flags = 0
+    logits = draw_logits("spread", V, V + n_child)
+    head = exact_head(logits, False)
+    pair = Pair(SHAPE, 5, {r: 9 for r in range(n)}, max_batch_nodes=64, oracle=False, flags=flags)
+    x = torch.ones(n, SHAPE.d_model, dtype=torch.bfloat16, device="cuda:0")
+    order = np.lexsort((np.arange(V), -logits))
+    prob = np.exp(logits - logits.max())
+    before = np.empty(V)
+    before[order] = np.concatenate(([0.0], np.cumsum(prob[order])))[:-1] / prob.sum()
+    r = np.random.RandomState(V + n)
+    kids = []
+    for q in range(n):
+        tok = [int(order[r.randint(min(V, 3000))]) for _ in range(n_child)]
+        tok = [t if abs(before[t] - 0.9) > 1e-5 else -1 for t in tok]
+        if n_child > 2:
+            tok[1] = V + 5                 # outside the vocabulary
+        draft = [float(np.float32(v)) for v in r.choice([0.125, 0.25, 0.5], n_child)]
+        pair.gpu.tree_insert(q, [-1] * n_child, tok, draft)
+        kids.append((tok, draft))
+    relaxed = pair.gpu.verify_lossy(head, list(range(n)), x, sp.SP_VERIFY_RELAXED)
+    top_p = pair.gpu.verify_lossy(head, list(range(n)), x, sp.SP_VERIFY_TOP_P, 0.9)
+    for q, (tok, draft) in enumerate(kids):
+        ok = [i for i, t in enumerate(tok) if 0 <= t < V]
+        want = max(ok, key=lambda i: (logits[tok[i]], -i)) if ok else -1
+        assert relaxed[q] == (want, int(order[0]))
+        ok = [i for i in ok if before[tok[i]] < 0.9]
+        want = max(ok, key=lambda i: (draft[i], -i)) if ok else -1
+        assert top_p[q] == (want, int(order[0])), q
+    pair.close()
