@@ -146,6 +146,7 @@ struct sp_stage {
   std::vector<FwdGraph> graphs;
   bool use_graphs = true;
   bool fast = false;           // bf16 MFMA kernels in use
+  bool f32 = false;            // float32 MFMA kernels in use
   bool packed = false;         // weights are in MFMA fragment order
   int* pin_nodes = nullptr;    // pinned host copy of the device-side verification results (sp_tree_prune_verified)
   hipEvent_t rec_ev = nullptr; // done when that copy has arrived
@@ -168,6 +169,14 @@ namespace {
 inline int hip_fail(sp_stage* s, hipError_t e) {
   s->last_hip = (int)e;
   return SP_E_HIP;
+}
+
+// out[m][n] = sum_k X[m][k] W[n][k] for a stage without the bf16 matrix-core path
+inline hipError_t other_gemm(const sp_stage* s, const void* X, const void* W, float* out, int M, int N, int K, hipStream_t st) {
+  // 16-byte loads: every row starts at a multiple of K * 4 bytes behind its matrix
+  if (s->f32 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0)
+    return sp_launch_gemm_f32((const float*)X, (const float*)W, out, M, N, K, st);
+  return sp_launch_gemm_simple(s->cfg.dtype, X, W, out, M, N, K, st);
 }
 
 // Brackets a launch with events when its kind is being profiled.
@@ -346,6 +355,7 @@ int sp_stage_create(const sp_config* cfg, const sp_layer_weights* layers, const 
   s->fast = cfg->dtype == SP_BF16 && !(cfg->flags & SP_FLAG_SIMPLE_KERNELS) && cfg->d_head == 128 &&
             cfg->d_model % 256 == 0 && cfg->d_ff % 256 == 0 &&
             (cfg->n_q_heads * cfg->d_head) % 256 == 0;
+  s->f32 = cfg->dtype == SP_F32 && !(cfg->flags & SP_FLAG_SIMPLE_KERNELS);
   {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= SP_NOALLOC_MAX_DEVICES) { delete s; return SP_E_HIP; }
@@ -701,7 +711,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       int S = 1;
       { ProfScope p(s, SP_K_GEMM_QKV, st);
         if (s->fast) SP_STEP(gemm(w.xn, L.wqkv, nqkv, d, &S));
-        else SP_STEP(sp_launch_gemm_simple(dt, w.xn, L.wqkv, w.part, M, nqkv, d, st)); }
+        else SP_STEP(other_gemm(s, w.xn, L.wqkv, w.part, M, nqkv, d, st)); }
       { ProfScope p(s, SP_K_ROPE_KV, st);
         SP_STEP(sp_launch_rope_kv(dt, w.part, S, strideQ, w.rows, w.cs, w.qbuf, s->geom, l, M, nq, nkv, dh, st)); }
       if (s->fast) {
@@ -710,12 +720,13 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
                                     (bf16_t*)w.attn, M, nq, nkv, dh, st));
       } else {
         ProfScope p(s, SP_K_ATTENTION, st);
-        SP_STEP(sp_launch_attn_simple(dt, w.qbuf, w.rows, s->d_tables, s->geom, l, w.attn, M, nq, nkv, dh, st));
+        if (s->f32) SP_STEP(sp_launch_attn_f32((const float*)w.qbuf, w.rows, s->d_tables, s->geom, l, (float*)w.attn, M, nq, nkv, dh, st));
+        else SP_STEP(sp_launch_attn_simple(dt, w.qbuf, w.rows, s->d_tables, s->geom, l, w.attn, M, nq, nkv, dh, st));
       }
       { ProfScope p(s, SP_K_GEMM_O, st);
         S = 1;
         if (s->fast) SP_STEP(gemm(w.attn, L.wo, d, dq, &S, s->o_resident));
-        else SP_STEP(sp_launch_gemm_simple(dt, w.attn, L.wo, w.part, M, d, dq, st)); }
+        else SP_STEP(other_gemm(s, w.attn, L.wo, w.part, M, d, dq, st)); }
       { ProfScope p(s, SP_K_NORM, st);
         SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S, strideD, L.norm2, w.xn, M, d, c.rms_eps, st)); }
       { ProfScope p(s, SP_K_GEMM_GATEUP, st);
@@ -723,6 +734,8 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
           if (sp_gemm_mid_takes_gateup(M, F, d, s->n_cu)) SP_STEP(sp_launch_gemm_mid_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, st));
           else if (wide) SP_STEP(sp_launch_gemm_wide_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, st));
           else SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, nullptr, 0.f, st));
+        } else if (s->f32) {
+          SP_STEP(sp_launch_gateup_f32((const float*)w.xn, (const float*)L.wgu, (float*)w.act, M, F, d, st));
         } else {
           SP_STEP(sp_launch_gemm_simple(dt, w.xn, L.wgu, w.part, M, 2 * F, d, st));
           SP_STEP(sp_launch_silu_mul(dt, w.part, w.act, M, F, st));
@@ -730,15 +743,15 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       { ProfScope p(s, SP_K_GEMM_DOWN, st);
         S = 1;
         if (s->fast) SP_STEP(gemm(w.act, L.wd, d, F, &S));
-        else SP_STEP(sp_launch_gemm_simple(dt, w.act, L.wd, w.part, M, d, F, st)); }
+        else SP_STEP(other_gemm(s, w.act, L.wd, w.part, M, d, F, st)); }
       S_prev = S;
     }
-    return sp_launch_finish(dt, w.h, w.part, S_prev, strideD, x_out, s->fast ? w.plan : nullptr, M, d, st);
+    return sp_launch_finish(dt, w.h, w.part, S_prev, strideD, x_out, w.plan, M, d, st);
   };
 #undef SP_STEP
 
   { ProfScope p(s, SP_K_NORM, st);
-    SP_TRY(sp_launch_enter_norm(dt, x_in, plan, s->fast ? w.plan : nullptr, s->d_meta, s->d_tables, w.rows, w.cs, dh,
+    SP_TRY(sp_launch_enter_norm(dt, x_in, plan, w.plan, s->d_meta, s->d_tables, w.rows, w.cs, dh,
                                 c.rope_theta, w.h, s->W[0].norm1, w.xn, M, d, c.rms_eps, st)); }
 
   // A shape that comes back replays its graph; one seen for the second time is captured.  Not while a
@@ -758,7 +771,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       timed = s->prof_n < s->prof_max && ((s->prof_seen / n_kind) % s->prof_every) == 0;
     }
   }
-  if (s->use_graphs && s->fast && !timed) {
+  if (s->use_graphs && (s->fast || s->f32) && !timed) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
       for (auto& g : s->graphs)
@@ -1069,7 +1082,7 @@ static int verify_head_on(sp_stage* s, const HeadScratch& w, const sp_head_weigh
     if (e == hipSuccess) e = sp_launch_argmax_rows(true, w.part, tiles, b, s->d_tables, pred_out, max_out, st);
   } else {
     if ((size_t)M * V > w.part_floats) return SP_E_CAPACITY;
-    e = sp_launch_gemm_simple(c.dtype, w.xn, head->wvocab, w.part, M, V, d, st);
+    e = other_gemm(s, w.xn, head->wvocab, w.part, M, V, d, st);
     if (e == hipSuccess) e = sp_launch_argmax_rows(false, w.part, V, b, s->d_tables, pred_out, max_out, st);
   }
   return e == hipSuccess ? SP_OK : hip_fail(s, e);
@@ -1137,7 +1150,7 @@ int sp_stage_verify_lossy(sp_stage* s, const sp_head_weights* head, int32_t n, c
     e = sp_launch_gemm_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, n, V, d, 1,
                             logit_floats, &S, st);
   } else {
-    e = sp_launch_gemm_simple(c.dtype, w.xn, head->wvocab, w.part, n, V, d, st);
+    e = other_gemm(s, w.xn, head->wvocab, w.part, n, V, d, st);
   }
   if (e == hipSuccess)
     e = sp_launch_verify_lossy(s->d_meta, s->d_tables, w.part, n, req_ids, V, mode, top_p, w.part + logit_floats,
@@ -1188,7 +1201,7 @@ int sp_stage_verify_sample(sp_stage* s, const sp_head_weights* head, int32_t n, 
                               logit_floats, &S, st);
     }
   } else {
-    e = sp_launch_gemm_simple(c.dtype, w.xn, head->wvocab, w.part, n, V, d, st);
+    e = other_gemm(s, w.xn, head->wvocab, w.part, n, V, d, st);
   }
   if (e == hipSuccess)
     e = sp_launch_verify_sample(s->d_meta, s->d_tables, w.part, n, req_ids, V, temperature, top_p, top_k, u, stats,

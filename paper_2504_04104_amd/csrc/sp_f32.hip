@@ -1,0 +1,241 @@
+// float32 kernels: products on the matrix cores (v_mfma_f32_16x16x4_f32: float32 operands and accumulation) and tree
+// attention by four waves per (row, query head).  At the sizes a float32 stage is run with (d = 256, some 16 nodes) a
+// launch is a chain of memory latencies, so what counts is how few of them stand in a row: the waves of a workgroup cut
+// the k range (or the cache slots) between them and have several loads each in flight, and are folded through LDS.
+// Measured on the two-layer d = 256 stage, 16 nodes, context 128 (one thread column per output and one wave per row
+// and head before): products of 256 and 688 k 12.0 and 18.3 -> 4.6 and 4.7 us, attention 27.8 -> 5.5 us.
+#include "sp_launch.h"
+
+#define F_WAVES 8
+#define F_D 4              // 16-byte pieces of every operand in flight per lane
+
+// out[m][n] = sum_k X[m][k] W[n][k]; GATEUP: act[m][f] = silu(X Wg^T) * (X Wu^T), W = [N gate rows ; N up rows].
+// A workgroup covers 16 columns and 16 * MT rows.  A lane's 16-byte piece holds four consecutive k of its row; MFMA i of
+// the four takes element i of every lane's piece, so lane group kg contributes k = 16 * step + 4 * kg + i on both sides.
+template <int MT, bool GATEUP>
+__global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restrict__ X, const float* __restrict__ W,
+                                                           float* __restrict__ out, int M, int N, int K) {
+  constexpr int NS = GATEUP ? 2 : 1;
+  __shared__ __attribute__((aligned(16))) f32x4_t s_acc[F_WAVES][NS * MT][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int r = lane & 15, kg = lane >> 4;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * MT);
+  const int pieces = K / 4, steps = (pieces + 3) / 4;
+  const int s_begin = steps * wave / F_WAVES, s_end = steps * (wave + 1) / F_WAVES;
+  // rows past the end repeat the last one; their products are not stored
+  const float* w[NS];
+  const float* x[MT];
+#pragma unroll
+  for (int a = 0; a < NS; ++a) w[a] = W + (size_t)(a * N + min(n0 + r, N - 1)) * K;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) x[mt] = X + (size_t)min(m0 + mt * 16 + r, M - 1) * K;
+  // Several short chains of additions per result instead of one long one, and their sums taken in 64 bits: the error
+  // against 64-bit arithmetic stays below that of the plain kernel (64 lanes with a few terms each, added pairwise),
+  // which float32 sums of the chains miss by 2 % (the matrix unit rounds inside its four-term step).
+  constexpr int CH = MT == 1 ? 8 : 4;
+  f32x4_t acc[CH][NS][MT];
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+#pragma unroll
+    for (int a = 0; a < NS; ++a)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[c][a][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  for (int s0 = s_begin; s0 < s_end; s0 += F_D) {
+    f32x4_t wf[F_D][NS], xf[F_D][MT];
+#pragma unroll
+    for (int j = 0; j < F_D; ++j) {
+      const int p = (s0 + j) * 4 + kg;
+      const bool in = s0 + j < s_end && p < pieces;          // k past the end multiplies as zero
+      const int pc = in ? p : 0;
+#pragma unroll
+      for (int a = 0; a < NS; ++a) {
+        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(w[a] + pc * 4);
+        wf[j][a] = in ? v : (f32x4_t){0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(x[mt] + pc * 4);
+        xf[j][mt] = in ? v : (f32x4_t){0.f, 0.f, 0.f, 0.f};
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < F_D; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int a = 0; a < NS; ++a)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+            acc[(j * 4 + i) % CH][a][mt] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(wf[j][a][i], xf[j][mt][i], acc[(j * 4 + i) % CH][a][mt], 0, 0, 0);
+  }
+#pragma unroll
+  for (int a = 0; a < NS; ++a)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      f32x4_t t;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        double d = 0.0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) d += (double)acc[c][a][mt][i];
+        t[i] = (float)d;
+      }
+      s_acc[wave][a * MT + mt][lane] = t;
+    }
+  __syncthreads();
+  if (wave >= MT) return;
+  // wave mt finishes row tile mt: row r, columns n0 + 4 * kg .. + 3
+  f32x4_t y[NS];
+#pragma unroll
+  for (int a = 0; a < NS; ++a) {
+    f32x4_t p[F_WAVES];
+#pragma unroll
+    for (int v = 0; v < F_WAVES; ++v) p[v] = s_acc[v][a * MT + wave][lane];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      double d = 0.0;
+#pragma unroll
+      for (int v = 0; v < F_WAVES; ++v) d += (double)p[v][i];
+      y[a][i] = (float)d;
+    }
+  }
+  const int m = m0 + wave * 16 + r, n = n0 + 4 * kg;
+  if (m >= M) return;
+  f32x4_t o = y[0];
+  if (GATEUP) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = y[0][i] / (1.f + __expf(-y[0][i])) * y[NS - 1][i];
+  }
+  float* dst = out + (size_t)m * N + n;
+  if (n + 4 <= N && (N & 3) == 0) {
+    *reinterpret_cast<f32x4_t*>(dst) = o;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) if (n + i < N) dst[i] = o[i];
+  }
+}
+
+// Tree attention, one workgroup per (row, query head): every wave takes a quarter of the visible range, 64 slots at a
+// time -- scores with a slot per lane, then the weighted sum of the V rows with the head's columns across the lanes --
+// and keeps an online softmax; the four states are folded at the end.
+template <int DH>
+__global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, const RowInfo* rows, const ReqTables* tables,
+                                                  KvGeom g, int layer, float* __restrict__ out, int n_q, int n_kv) {
+  constexpr int C = DH / 64;               // columns per lane
+  __shared__ __attribute__((aligned(16))) float s_q[DH];
+  __shared__ __attribute__((aligned(16))) float s_p[4][64];
+  __shared__ int s_slot[4][64];
+  __shared__ float s_o[4][DH], s_m[4], s_l[4];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int row = blockIdx.x / n_q, head = blockIdx.x - row * n_q;
+  const int kvh = head / (n_q / n_kv);
+  if ((int)threadIdx.x < DH) s_q[threadIdx.x] = q[((size_t)row * n_q + head) * DH + threadIdx.x];
+  const RowInfo ri = rows[row];
+  unsigned long long anc[SP_W];
+#pragma unroll
+  for (int w = 0; w < SP_W; ++w) anc[w] = tables[ri.req].anc[ri.node][w];
+  const float* kplane = reinterpret_cast<const float*>(g.kv + ((size_t)(layer * 2 + 0) * n_kv + kvh) * g.plane_bytes);
+  const float* vplane = reinterpret_cast<const float*>(g.kv + ((size_t)(layer * 2 + 1) * n_kv + kvh) * g.plane_bytes);
+  const float scale = rsqrtf((float)DH);
+  const int total = ri.P + ri.T;
+  const int c0 = (int)((long long)total * wave / 4), c1 = (int)((long long)total * (wave + 1) / 4);
+  float mx = -INFINITY, l = 0.f, o[8][C];      // eight chains of additions per column
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int c = 0; c < C; ++c) o[e][c] = 0.f;
+  __syncthreads();
+  for (int s0 = c0; s0 < c1; s0 += 64) {
+    const int s = s0 + lane;
+    const bool in = s < c1;
+    bool vis = in;
+    if (in && s >= ri.P) {
+      const int j = s - ri.P;
+      unsigned long long word = 0ull;
+#pragma unroll
+      for (int w = 0; w < SP_W; ++w) word = (j >> 6) == w ? anc[w] : word;
+      vis = (word >> (j & 63)) & 1ull;
+    }
+    // slots that are not visible read the range's first slot and get weight zero
+    const int slot = (int)sp_phys_slot(g, ri.req, ri.base, vis ? s : 0);
+    const f32x4_t* k = reinterpret_cast<const f32x4_t*>(kplane + (size_t)slot * DH);
+    f32x4_t d4 = {0.f, 0.f, 0.f, 0.f}, d4b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < DH / 4; t += 2) {
+      d4 += k[t] * *reinterpret_cast<const f32x4_t*>(&s_q[t * 4]);
+      d4b += k[t + 1] * *reinterpret_cast<const f32x4_t*>(&s_q[t * 4 + 4]);
+    }
+    d4 += d4b;
+    const float sc = vis ? ((d4[0] + d4[1]) + (d4[2] + d4[3])) * scale : -INFINITY;
+    const float mn = fmaxf(mx, wave_max(sc));
+    const float corr = mn == -INFINITY ? 1.f : __expf(mx - mn);          // 0 from -inf
+    const float p = vis ? __expf(sc - mn) : 0.f;
+    l = l * corr + wave_sum(p);
+    mx = mn;
+    s_p[wave][lane] = p;
+    s_slot[wave][lane] = slot;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int c = 0; c < C; ++c) o[e][c] *= corr;
+    __builtin_amdgcn_wave_barrier();
+    const int ns = min(64, c1 - s0);
+    for (int j = 0; j < ns; j += 16) {
+      float pv[16], vv[16][C];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        pv[u] = s_p[wave][j + u];
+        const float* vp = vplane + (size_t)s_slot[wave][j + u] * DH + lane;
+#pragma unroll
+        for (int c = 0; c < C; ++c) vv[u][c] = vp[c * 64];
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+#pragma unroll
+        for (int c = 0; c < C; ++c) o[u & 7][c] += pv[u] * vv[u][c];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    s_o[wave][c * 64 + lane] = ((o[0][c] + o[1][c]) + (o[2][c] + o[3][c])) + ((o[4][c] + o[5][c]) + (o[6][c] + o[7][c]));
+  if (lane == 0) { s_m[wave] = mx; s_l[wave] = l; }
+  __syncthreads();
+  if ((int)threadIdx.x >= DH) return;
+  const float gm = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+  float num = 0.f, den = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float f = s_m[w] == -INFINITY ? 0.f : __expf(s_m[w] - gm);
+    num += s_o[w][threadIdx.x] * f;
+    den += s_l[w] * f;
+  }
+  out[((size_t)row * n_q + head) * DH + threadIdx.x] = num / den;
+}
+
+template <bool GATEUP>
+static hipError_t launch_gemm_f32(const float* X, const float* W, float* out, int M, int N, int K, hipStream_t st) {
+  if (M < 1 || N < 1 || K < 4 || K % 4) return hipErrorInvalidValue;
+  const int tiles = (M + 15) / 16, mt = tiles >= 4 ? 4 : tiles >= 2 ? 2 : 1;     // row tiles that share a read of the weights
+  const dim3 grid((N + 15) / 16, (tiles + mt - 1) / mt);
+#define SP_GO(MTV) hipLaunchKernelGGL((k_gemm_f32<MTV, GATEUP>), grid, dim3(64 * F_WAVES), 0, st, X, W, out, M, N, K)
+  if (mt == 1) SP_GO(1); else if (mt == 2) SP_GO(2); else SP_GO(4);
+#undef SP_GO
+  return hipGetLastError();
+}
+hipError_t sp_launch_gemm_f32(const float* X, const float* W, float* out, int M, int N, int K, hipStream_t st) {
+  return launch_gemm_f32<false>(X, W, out, M, N, K, st);
+}
+hipError_t sp_launch_gateup_f32(const float* X, const float* W, float* act, int M, int F, int K, hipStream_t st) {
+  return launch_gemm_f32<true>(X, W, act, M, F, K, st);
+}
+
+hipError_t sp_launch_attn_f32(const float* q, const RowInfo* rows, const ReqTables* tables, KvGeom g, int layer, float* out,
+                              int M, int n_q, int n_kv, int d_head, hipStream_t st) {
+  const dim3 grid(M * n_q);
+  if (d_head == 64) hipLaunchKernelGGL(k_attn_f32<64>, grid, dim3(256), 0, st, q, rows, tables, g, layer, out, n_q, n_kv);
+  else if (d_head == 128) hipLaunchKernelGGL(k_attn_f32<128>, grid, dim3(256), 0, st, q, rows, tables, g, layer, out, n_q, n_kv);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}

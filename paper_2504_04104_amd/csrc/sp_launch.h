@@ -113,6 +113,11 @@ hipError_t sp_launch_finish(int dtype, const float* h, const float* part, int S,
 // ---- GEMM: out[s][m][n] (f32) = sum over the s-th K slice of X[m][k] * W[n][k] -----
 hipError_t sp_launch_gemm_simple(int dtype, const void* X, const void* W, float* out, int M, int N, int K,
                                  hipStream_t st);
+// float32 on the matrix cores (K % 4 == 0, rows 16-byte aligned)
+hipError_t sp_launch_gemm_f32(const float* X, const float* W, float* out, int M, int N, int K, hipStream_t st);
+hipError_t sp_launch_gateup_f32(const float* X, const float* W, float* act, int M, int F, int K, hipStream_t st);
+hipError_t sp_launch_attn_f32(const float* q, const RowInfo* rows, const ReqTables* tables, KvGeom g, int layer, float* out,
+                              int M, int n_q, int n_kv, int d_head, hipStream_t st);
 // bf16 MFMA kernels.  Returns the split count used in *S_out (partials [S][M][N]).  packed: the
 // weights are in MFMA fragment order (sp_launch_pack_weights).
 hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,

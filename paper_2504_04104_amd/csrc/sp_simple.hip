@@ -1,7 +1,7 @@
 // Plain kernels for any dtype: a dot-product GEMM and a one-wave-per-(row, head)
-// tree attention.  They carry the float32 configuration and serve as the slow
-// path selected by SP_FLAG_SIMPLE_KERNELS; the bf16 MFMA kernels replace them on
-// the hot path.
+// tree attention.  They are the slow path selected by SP_FLAG_SIMPLE_KERNELS and
+// carry the bf16 shapes that the MFMA kernels do not cover; the MFMA kernels (bf16,
+// float32) replace them on the hot path.
 #include "sp_launch.h"
 
 // out[m][n] = sum_k X[m][k] W[n][k].  A wave owns one n and eight rows m at a time;
