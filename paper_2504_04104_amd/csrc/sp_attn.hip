@@ -35,6 +35,118 @@ struct AttnArgs {
   const AttnPlan* plan;     // device copy of the call's plan (written by the kernel that opens the forward)
 };
 
+// Online softmax of a wave over QT tiles of 16 query rows.  mrun is the running maximum of the raw scores q.k; negm =
+// -mrun*sc (0 while mrun is -inf), so that exp2(fma(s, sc, negm)) is the softmax weight.
+template <int QT>
+struct AttnState {
+  f32x4_t o[QT][8];
+  float mrun[QT], lrun[QT], negm[QT];
+  __device__ __forceinline__ void init() {
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      mrun[t] = -INFINITY; lrun[t] = 0.f; negm[t] = 0.f;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) o[t][d] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    }
+  }
+};
+#define ATTN_SC (0.08838834764831845f * 1.4426950408889634f)   // 1/sqrt(128) * log2(e)
+
+// One 32-slot tile, first slot s0, of a run that ends at w1, from its LDS copies kt and vt.
+template <int QT>
+__device__ __forceinline__ void attn_tile(AttnState<QT>& st, const u32x4_t (&qf)[QT][4], const unsigned long long (&anc)[QT][SP_W],
+                                          const char* kt, const char* vt, int s0, int w1, int P, int span, int l15, int kg) {
+  const float sc = ATTN_SC;
+  f32x4_t sacc[QT][2];
+#pragma unroll
+  for (int t = 0; t < QT; ++t)
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2) sacc[t][t2] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const u32x4_t kf = *reinterpret_cast<const u32x4_t*>(kt + (t2 * 16 + l15) * VS + s * 64 + kg * 16);
+#pragma unroll
+      for (int t = 0; t < QT; ++t)
+        sacc[t][t2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&kf),
+                                                              *reinterpret_cast<const bf16x8_t*>(&qf[t][s]),
+                                                              sacc[t][t2], 0, 0, 0);
+    }
+
+  const bool tail = s0 + 32 > P || s0 + 32 > w1;   // tile touches the tree region or the run's end
+  uint32_t pb[QT][4];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    float sv[8];
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sv[t2 * 4 + i] = sacc[t][t2][i];
+    if (tail) {
+      // bits [n0, n0+64) of the row's 256-bit ancestor mask, n0 = first tree index of the tile
+      const int n0 = s0 - P;
+      unsigned long long win = 0ull;
+#pragma unroll
+      for (int w = 0; w < SP_W; ++w) {
+        const int sh = w * 64 - n0;
+        if (sh > -64 && sh < 64) win |= sh >= 0 ? (anc[t][w] << sh) : (anc[t][w] >> (-sh));
+      }
+      const int lim = w1 - s0, pfx = P - s0, tl = span - s0;   // offsets below: in run / committed / live
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int off = (j >> 2) * 16 + kg * 4 + (j & 3);
+        const bool vis = (off < lim) & ((off < pfx) | ((off < tl) & (bool)((win >> off) & 1ull)));
+        sv[j] = vis ? sv[j] : -INFINITY;
+      }
+    }
+    float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+    // The running maximum only has to bound the scores, so it is raised (and the
+    // accumulators rescaled) only when some lane of the wave sees a larger score.
+    if (__builtin_amdgcn_ballot_w64(mx > st.mrun[t])) {
+      mx = quad_rows_max(mx);
+      const float mnew = fmaxf(st.mrun[t], mx);
+      const float alpha = (mnew == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((st.mrun[t] - mnew) * sc);  // 0 from -inf
+      st.lrun[t] *= alpha;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) st.o[t][d] *= alpha;
+      st.mrun[t] = mnew;
+      st.negm[t] = (mnew == -INFINITY) ? 0.f : -mnew * sc;
+    }
+    float pv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[j], sc, st.negm[t]));
+    st.lrun[t] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) pb[t][j] = pack_bf16x2(pv[2 * j], pv[2 * j + 1]);
+  }
+
+  // O^T += V^T P^T.  Lane (l15, kg) of the d-group G pair reads V[slot(kg,j)][G*32 + 2*l15 .. +1].
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int G = 0; G < 4; ++G) {
+    uint32_t w[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int srow = (j >> 2) * 16 + kg * 4 + (j & 3);
+      w[j] = *reinterpret_cast<const uint32_t*>(vt + srow * VS + (G * 32 + 2 * l15) * 2);
+    }
+    u32x4_t alo, ahi;     // low halves: column 2*l15; high halves: column 2*l15+1
+    alo.x = __builtin_amdgcn_perm(w[1], w[0], 0x05040100); ahi.x = __builtin_amdgcn_perm(w[1], w[0], 0x07060302);
+    alo.y = __builtin_amdgcn_perm(w[3], w[2], 0x05040100); ahi.y = __builtin_amdgcn_perm(w[3], w[2], 0x07060302);
+    alo.z = __builtin_amdgcn_perm(w[5], w[4], 0x05040100); ahi.z = __builtin_amdgcn_perm(w[5], w[4], 0x07060302);
+    alo.w = __builtin_amdgcn_perm(w[7], w[6], 0x05040100); ahi.w = __builtin_amdgcn_perm(w[7], w[6], 0x07060302);
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      const bf16x8_t pfrag = *reinterpret_cast<const bf16x8_t*>(&pb[t][0]);
+      st.o[t][2 * G] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&alo), pfrag,
+                                                            st.o[t][2 * G], 0, 0, 0);
+      st.o[t][2 * G + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&ahi), pfrag,
+                                                                st.o[t][2 * G + 1], 0, 0, 0);
+    }
+  }
+}
+
 // STREAM: every request of the call has a single block of query rows, so each K/V row is read by one workgroup
 // only; the loads then carry the non-temporal hint and the rows pass through the caches without staying.
 // The K rows take the same way as the V rows: loaded as whole 256-byte rows (a load instruction covers four rows)
@@ -53,11 +165,13 @@ __global__ void __launch_bounds__(64 * AW) k_attn_bf16(AttnArgs a) {
   __shared__ float s_m[AW][QT * 16];
   __shared__ float s_l[AW][QT * 16];
 
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   // KV head fastest: consecutive workgroup ids go round-robin over the 8 XCDs, so all query
   // blocks and chunks of one KV head share one XCD's L2 and its K/V rows are fetched from HBM once
-  const int kvh = blockIdx.x % a.n_kv;
-  const int item = blockIdx.x / a.n_kv;
+  // (uni: quotients come out of vector registers; what the tiles' buffers are built from has to be scalar)
+  auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+  const int item = uni(blockIdx.x / a.n_kv);
+  const int kvh = blockIdx.x - item * a.n_kv;
   // Segment 0's fields are asked for together with the segment count: a call with one request (the rule) then
   // waits for one round trip to the plan, not for two in a row.
   int sg_item0 = plan.seg_item0[0], sg_chunks = plan.seg_chunks[0], sg_rows = plan.seg_rows[0], sg_row0 = plan.seg_row0[0];
@@ -75,7 +189,7 @@ __global__ void __launch_bounds__(64 * AW) k_attn_bf16(AttnArgs a) {
   }
   const int local = item - sg_item0;
   const int chunks = sg_chunks;
-  const int qb = local / chunks, ch = local - qb * chunks;
+  const int qb = uni(local / chunks), ch = local - qb * chunks;
   const int g = a.n_q / a.n_kv;
   const float inv_g = 1.f / (float)g;              // (qi + 0.5) * inv_g truncates to qi / g for these small integers
   const int seg_rows = sg_rows, row0 = sg_row0;
@@ -97,30 +211,27 @@ __global__ void __launch_bounds__(64 * AW) k_attn_bf16(AttnArgs a) {
   const char* vplane = a.g.kv + ((size_t)(a.layer * 2 + 1) * a.n_kv + kvh) * a.g.plane_bytes + base_b;
   const int* pt = PAGED ? a.g.page_table + (size_t)sg_req * a.g.pt_stride : nullptr;
   const int pg_sh = PAGED ? a.g.pg_shift : 0, pg_mask = (1 << pg_sh) - 1;
-  const int page0 = PAGED ? pt[0] : 0;
-#define SP_PHYS(slot, pg) (PAGED ? (((slot) < span ? (pg) : page0) << pg_sh | ((slot) < span ? ((slot) & pg_mask) : 0)) \
-                                 : ((slot) < span ? (slot) : 0))
-
-  // Loads of one 32-slot tile: K and V as plain 16-byte pieces (row i*4+kg, piece l15).  Slots past
-  // the request's data are read from slot 0 (always valid) and masked later.
-#define SP_LOAD_TILE(S0)                                                                           \
+  // Loads of one 32-slot tile: K and V as plain 16-byte pieces (row i*4+kg, piece l15).  The tile is a buffer of its own,
+  // as long as its rows inside the request's data: rows behind them come back as zeros without a memory access (and are
+  // masked later), and a load's address is one of two constant lane offsets plus an immediate.  With a clamp and a
+  // 64-bit address per load the address arithmetic alone took a sixth of a tile's instructions.
+  const unsigned lofs = kg * 256 + l15 * 16;
+#define SP_LOAD_ROWS(DST, PLANE, S0)                                                               \
   {                                                                                                \
-    const int pg_ = PAGED ? pt[((S0) < span ? (S0) : 0) >> pg_sh] : 0;                             \
-    _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                \
-      int slot = (S0) + i * 4 + kg;                                                                \
-      slot = SP_PHYS(slot, pg_);                                                                   \
-      const u32x4_t* vp_ = reinterpret_cast<const u32x4_t*>(vplane + (size_t)slot * 256 + l15 * 16); \
-      vreg[i] = STREAM ? __builtin_nontemporal_load(vp_) : *vp_;                                   \
-      const u32x4_t* kp_ = reinterpret_cast<const u32x4_t*>(kplane + (size_t)slot * 256 + l15 * 16); \
-      kreg[i >> 2][i & 3] = STREAM ? __builtin_nontemporal_load(kp_) : *kp_;                       \
-    }                                                                                              \
+    const int t0_ = (S0) < span ? (S0) : 0;        /* a tile past the data: no rows of slot 0's */  \
+    const size_t slot_ = PAGED ? ((size_t)pt[t0_ >> pg_sh] << pg_sh) + (t0_ & pg_mask) : (size_t)t0_; \
+    const auto buf_ = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(PLANE) + slot_ * 256, (short)0, \
+                                                        uni(max(0, min(32, span - (S0)))) * 256, 0x00020000); \
+    _Pragma("unroll") for (int i = 0; i < 8; ++i)                                                  \
+        DST[i] = __builtin_amdgcn_raw_buffer_load_b128(buf_, lofs + i * 1024, 0, STREAM ? 2 : 0);  \
   }
 
   // the first tile's loads go out before anything else that has to wait
-  u32x4_t kreg[2][4], vreg[8];
+  u32x4_t kreg[8], vreg[8];
   char* vt = s_v + wave * VT_BYTES;
   char* kt = s_v + (AW + wave) * VT_BYTES;         // this wave's K tile, rows as in the V tile
-  SP_LOAD_TILE(w0 < w1 ? w0 : span)
+  SP_LOAD_ROWS(kreg, kplane, w0 < w1 ? w0 : span)
+  SP_LOAD_ROWS(vreg, vplane, w0 < w1 ? w0 : span)
 
   // ---- query fragments and ancestor masks of this lane's query row per tile ------
   u32x4_t qf[QT][4];
@@ -145,20 +256,8 @@ __global__ void __launch_bounds__(64 * AW) k_attn_bf16(AttnArgs a) {
     }
   }
 
-  f32x4_t o[QT][8];
-  float mrun[QT], lrun[QT];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    mrun[t] = -INFINITY; lrun[t] = 0.f;
-#pragma unroll
-    for (int d = 0; d < 8; ++d) o[t][d] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-  }
-  const float sc = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(128) * log2(e)
-  // mrun is the running maximum of the raw scores q.k; negm = -mrun*sc (0 while mrun is -inf),
-  // so that exp2(fma(s, sc, negm)) is the softmax weight
-  float negm[QT];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) negm[t] = 0.f;
+  AttnState<QT> st;
+  st.init();
 
   for (int s0 = w0; s0 < w1; s0 += 32) {
     // K and V tiles -> LDS; then the next tile's loads are issued, so that they fly during
@@ -169,104 +268,17 @@ __global__ void __launch_bounds__(64 * AW) k_attn_bf16(AttnArgs a) {
     for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4_t*>(vt + (i * 4 + kg) * VS + l15 * 16) = vreg[i];
     // K rows to the wave's K tile and back as A fragments: row l15 of each 16-slot half, 16 B at d = s*32 + kg*8
 #pragma unroll
-    for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4_t*>(kt + (i * 4 + kg) * VS + l15 * 16) = kreg[i >> 2][i & 3];
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4_t*>(kt + (i * 4 + kg) * VS + l15 * 16) = kreg[i];
     __builtin_amdgcn_wave_barrier();
     // the tile is in LDS: the next tile's loads go out now and fly during everything below
     {
-      const int nxt = (s0 + 32 < w1) ? s0 + 32 : span;     // span: every slot clamps to 0
-      SP_LOAD_TILE(nxt)
+      const int nxt = (s0 + 32 < w1) ? s0 + 32 : span;     // span: no rows
+      SP_LOAD_ROWS(kreg, kplane, nxt)
+      SP_LOAD_ROWS(vreg, vplane, nxt)
     }
-    f32x4_t sacc[QT][2];
-#pragma unroll
-    for (int t = 0; t < QT; ++t)
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2) sacc[t][t2] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const u32x4_t kf = *reinterpret_cast<const u32x4_t*>(kt + (t2 * 16 + l15) * VS + s * 64 + kg * 16);
-#pragma unroll
-        for (int t = 0; t < QT; ++t)
-          sacc[t][t2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&kf),
-                                                                *reinterpret_cast<const bf16x8_t*>(&qf[t][s]),
-                                                                sacc[t][t2], 0, 0, 0);
-      }
-
-    const bool tail = s0 + 32 > P || s0 + 32 > w1;   // tile touches the tree region or the run's end
-    uint32_t pb[QT][4];
-#pragma unroll
-    for (int t = 0; t < QT; ++t) {
-      float sv[8];
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sv[t2 * 4 + i] = sacc[t][t2][i];
-      if (tail) {
-        // bits [n0, n0+64) of the row's 256-bit ancestor mask, n0 = first tree index of the tile
-        const int n0 = s0 - P;
-        unsigned long long win = 0ull;
-#pragma unroll
-        for (int w = 0; w < SP_W; ++w) {
-          const int sh = w * 64 - n0;
-          if (sh > -64 && sh < 64) win |= sh >= 0 ? (anc[t][w] << sh) : (anc[t][w] >> (-sh));
-        }
-        const int lim = w1 - s0, pfx = P - s0, tl = span - s0;   // offsets below: in run / committed / live
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int off = (j >> 2) * 16 + kg * 4 + (j & 3);
-          const bool vis = (off < lim) & ((off < pfx) | ((off < tl) & (bool)((win >> off) & 1ull)));
-          sv[j] = vis ? sv[j] : -INFINITY;
-        }
-      }
-      float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-      // The running maximum only has to bound the scores, so it is raised (and the
-      // accumulators rescaled) only when some lane of the wave sees a larger score.
-      if (__builtin_amdgcn_ballot_w64(mx > mrun[t])) {
-        mx = quad_rows_max(mx);
-        const float mnew = fmaxf(mrun[t], mx);
-        const float alpha = (mnew == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((mrun[t] - mnew) * sc);  // 0 from -inf
-        lrun[t] *= alpha;
-#pragma unroll
-        for (int d = 0; d < 8; ++d) o[t][d] *= alpha;
-        mrun[t] = mnew;
-        negm[t] = (mnew == -INFINITY) ? 0.f : -mnew * sc;
-      }
-      float pv[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[j], sc, negm[t]));
-      lrun[t] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
-#pragma unroll
-      for (int j = 0; j < 4; ++j) pb[t][j] = pack_bf16x2(pv[2 * j], pv[2 * j + 1]);
-    }
-
-    // O^T += V^T P^T.  Lane (l15, kg) of the d-group G pair reads V[slot(kg,j)][G*32 + 2*l15 .. +1].
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int G = 0; G < 4; ++G) {
-      uint32_t w[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int srow = (j >> 2) * 16 + kg * 4 + (j & 3);
-        w[j] = *reinterpret_cast<const uint32_t*>(vt + srow * VS + (G * 32 + 2 * l15) * 2);
-      }
-      u32x4_t alo, ahi;     // low halves: column 2*l15; high halves: column 2*l15+1
-      alo.x = __builtin_amdgcn_perm(w[1], w[0], 0x05040100); ahi.x = __builtin_amdgcn_perm(w[1], w[0], 0x07060302);
-      alo.y = __builtin_amdgcn_perm(w[3], w[2], 0x05040100); ahi.y = __builtin_amdgcn_perm(w[3], w[2], 0x07060302);
-      alo.z = __builtin_amdgcn_perm(w[5], w[4], 0x05040100); ahi.z = __builtin_amdgcn_perm(w[5], w[4], 0x07060302);
-      alo.w = __builtin_amdgcn_perm(w[7], w[6], 0x05040100); ahi.w = __builtin_amdgcn_perm(w[7], w[6], 0x07060302);
-#pragma unroll
-      for (int t = 0; t < QT; ++t) {
-        const bf16x8_t pfrag = *reinterpret_cast<const bf16x8_t*>(&pb[t][0]);
-        o[t][2 * G] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&alo), pfrag,
-                                                              o[t][2 * G], 0, 0, 0);
-        o[t][2 * G + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&ahi), pfrag,
-                                                                  o[t][2 * G + 1], 0, 0, 0);
-      }
-    }
+    attn_tile<QT>(st, qf, anc, kt, vt, s0, w1, P, span, l15, kg);
   }
-#undef SP_LOAD_TILE
-#undef SP_PHYS
+#undef SP_LOAD_ROWS
 
   // ---- fold the eight wave states (fixed order, so results do not depend on timing) ----
   // Every wave rescales its state to the common maximum and leaves it in LDS; after one barrier the block's
@@ -274,9 +286,9 @@ __global__ void __launch_bounds__(64 * AW) k_attn_bf16(AttnArgs a) {
   // wave of their own.
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
-    lrun[t] = quad_rows_sum(lrun[t]);
-    mrun[t] = mrun[t] * sc;              // to the log2 domain (-inf stays -inf)
-    if (kg == 0) s_m[wave][t * 16 + l15] = mrun[t];
+    st.lrun[t] = quad_rows_sum(st.lrun[t]);
+    st.mrun[t] = st.mrun[t] * ATTN_SC;              // to the log2 domain (-inf stays -inf)
+    if (kg == 0) s_m[wave][t * 16 + l15] = st.mrun[t];
   }
   __syncthreads();                       // every wave is done with its V tile; maxima are posted
   f32x4_t* fold = reinterpret_cast<f32x4_t*>(s_v);
@@ -287,10 +299,10 @@ __global__ void __launch_bounds__(64 * AW) k_attn_bf16(AttnArgs a) {
 #pragma unroll
     for (int w = 0; w < AW; ++w) m = fmaxf(m, s_m[w][t * 16 + l15]);
     mall[t] = m;
-    const float f = (mrun[t] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mrun[t] - m);
+    const float f = (st.mrun[t] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(st.mrun[t] - m);
 #pragma unroll
-    for (int d = 0; d < 8; ++d) fold[((wave * QT + t) * 8 + d) * 64 + lane] = o[t][d] * f;
-    if (kg == 0) s_l[wave][t * 16 + l15] = lrun[t] * f;
+    for (int d = 0; d < 8; ++d) fold[((wave * QT + t) * 8 + d) * 64 + lane] = st.o[t][d] * f;
+    if (kg == 0) s_l[wave][t * 16 + l15] = st.lrun[t] * f;
   }
   __syncthreads();
   if (wave >= 4 * QT) return;
