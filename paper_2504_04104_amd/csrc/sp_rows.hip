@@ -50,50 +50,55 @@ __device__ __forceinline__ f32x4_t fold4(const float* p, int S, size_t stride) {
   return a;
 }
 
-// One workgroup (1024 threads) per row, four columns per thread and pass.
-//   FIRST: the row enters the stage: h[row] = x[row]; the row's descriptor and its rotary
-//          table are written as well.  Position of a node = prefix length + depth: each tree
-//          level is one future position (Sec. 3.2).  The angle is formed in double so that
-//          positions of tens of thousands keep full float accuracy in cos and sin.
+// One workgroup per row (1024 threads; the entering rows of large calls 512), four columns per thread and pass.
+//   FIRST: the row enters the stage: h[row] = x[row].  Workgroups behind the rows' write the row descriptors and rotary
+//          tables while the rows are normalised (in the row's own workgroup, one wave formed the angles while fifteen
+//          waited: 638 rows 13.8 -> 8.4 us, 64 rows 5.4 -> 4.5 us).  Position of a node = prefix length + depth: each tree
+//          level is one future position (Sec. 3.2).  The angle is formed in double so that positions of tens of
+//          thousands keep full float accuracy in cos and sin.
 //   else:  h[row] += sum_s part[s][row].
 // Then xn[row] = h * rsqrt(mean(h^2)+eps) * gain.  The first two passes stay in registers.
+#define ENTER_ROWS 4       // rows a workgroup of descriptors and rotary tables takes (few: double precision is slow)
 struct NoPlan { int unused; };
 template <bool FIRST> struct PlanArg { typedef NoPlan type; };
 template <> struct PlanArg<true> { typedef AttnPlan type; };
 
 template <typename T, bool FIRST>
 __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, int S, size_t part_stride,
-                                                    const T* gain, T* xn, int d, float eps, const T* x,
+                                                    const T* gain, T* xn, int M, int d, float eps, const T* x,
                                                     typename PlanArg<FIRST>::type b, AttnPlan* plan_dev,
                                                     const ReqMeta* meta, const ReqTables* tables, RowInfo* rows,
                                                     float* cs, int d_head, float theta) {
   __shared__ float s_red[16];
   const int row = blockIdx.x;
   if constexpr (FIRST) {
-    // the call's plan goes to device memory for the kernels that follow
-    if (plan_dev && row == 0) {
-      const uint32_t* src = reinterpret_cast<const uint32_t*>(&b);
-      uint32_t* dst = reinterpret_cast<uint32_t*>(plan_dev);
-      for (int i = threadIdx.x; i < (int)(sizeof(AttnPlan) / 4); i += blockDim.x) dst[i] = src[i];
-    }
     const int half = d_head >> 1;
-    if ((int)threadIdx.x < half) {
-      const int tt = threadIdx.x;
-      int seg = 0;
-      while (seg + 1 < b.n_seg && row >= b.seg_row0[seg + 1]) ++seg;
-      const int req = b.seg_req[seg];
-      const int node = b.seg_first[seg] + (row - b.seg_row0[seg]);
-      const ReqMeta m = meta[req];
-      const int pos = m.P + tables[req].depth[node];
-      if (tt == 0) {
-        RowInfo ri;
-        ri.base = m.base; ri.req = req; ri.node = node; ri.pos = pos; ri.P = m.P; ri.T = m.T; ri.seg = seg;
-        rows[row] = ri;
+    if (row >= M) {
+      const int r = (row - M) * ENTER_ROWS + (int)threadIdx.x / half, tt = (int)threadIdx.x % half;
+      if (r < M && (int)threadIdx.x < ENTER_ROWS * half) {
+        int seg = 0;
+        while (seg + 1 < b.n_seg && r >= b.seg_row0[seg + 1]) ++seg;
+        const int req = b.seg_req[seg];
+        const int node = b.seg_first[seg] + (r - b.seg_row0[seg]);
+        const ReqMeta m = meta[req];
+        const int pos = m.P + tables[req].depth[node];
+        if (tt == 0) {
+          RowInfo ri;
+          ri.base = m.base; ri.req = req; ri.node = node; ri.pos = pos; ri.P = m.P; ri.T = m.T; ri.seg = seg;
+          rows[r] = ri;
+        }
+        const double inv_freq = exp2(-(2.0 * (double)tt / (double)d_head) * log2((double)theta));
+        const double ang = (double)pos * inv_freq;
+        cs[(size_t)r * d_head + tt] = (float)cos(ang);
+        cs[(size_t)r * d_head + half + tt] = (float)sin(ang);
       }
-      const double inv_freq = exp2(-(2.0 * (double)tt / (double)d_head) * log2((double)theta));
-      const double ang = (double)pos * inv_freq;
-      cs[(size_t)row * d_head + tt] = (float)cos(ang);
-      cs[(size_t)row * d_head + half + tt] = (float)sin(ang);
+      // the call's plan goes to device memory for the kernels that follow
+      if (plan_dev && row == M) {
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(&b);
+        uint32_t* dst = reinterpret_cast<uint32_t*>(plan_dev);
+        for (int i = threadIdx.x; i < (int)(sizeof(AttnPlan) / 4); i += blockDim.x) dst[i] = src[i];
+      }
+      return;
     }
   }
   float* hr = h + (size_t)row * d;
@@ -238,13 +243,18 @@ hipError_t sp_launch_enter_norm(int dtype, const void* x, const AttnPlan& plan, 
                                 const ReqMeta* meta, const ReqTables* tables, RowInfo* rows, float* cs, int d_head,
                                 float theta, float* h, const void* gain, void* xn, int M, int d, float eps,
                                 hipStream_t st) {
+  // 1024 threads per row up to two rows per CU; with more rows 512, so that four rows per CU are in flight (638 rows of
+  // 4096, with the tables apart: 13.9 -> 8.4 us) -- as long as a row takes no more than the two passes that stay in
+  // registers
+  const int nth = M > 512 && d <= 4096 ? 512 : 1024;
+  const int extra = (M + ENTER_ROWS - 1) / ENTER_ROWS;         // workgroups of descriptors and rotary tables
   static_assert(sizeof(AttnPlan) % 4 == 0 && sizeof(AttnPlan) < 3900, "the plan travels as a kernel argument");
   if (dtype == 0)
-    hipLaunchKernelGGL((k_add_norm<float, true>), dim3(M), dim3(1024), 0, st, h, nullptr, 0, 0, (const float*)gain,
-                       (float*)xn, d, eps, (const float*)x, plan, plan_dev, meta, tables, rows, cs, d_head, theta);
+    hipLaunchKernelGGL((k_add_norm<float, true>), dim3(M + extra), dim3(nth), 0, st, h, nullptr, 0, 0, (const float*)gain,
+                       (float*)xn, M, d, eps, (const float*)x, plan, plan_dev, meta, tables, rows, cs, d_head, theta);
   else
-    hipLaunchKernelGGL((k_add_norm<bf16_t, true>), dim3(M), dim3(1024), 0, st, h, nullptr, 0, 0,
-                       (const bf16_t*)gain, (bf16_t*)xn, d, eps, (const bf16_t*)x, plan, plan_dev, meta, tables, rows,
+    hipLaunchKernelGGL((k_add_norm<bf16_t, true>), dim3(M + extra), dim3(nth), 0, st, h, nullptr, 0, 0,
+                       (const bf16_t*)gain, (bf16_t*)xn, M, d, eps, (const bf16_t*)x, plan, plan_dev, meta, tables, rows,
                        cs, d_head, theta);
   return hipGetLastError();
 }
@@ -254,11 +264,11 @@ hipError_t sp_launch_add_norm(int dtype, float* h, const float* part, int S, siz
   const NoPlan none{0};
   if (dtype == 0)
     hipLaunchKernelGGL((k_add_norm<float, false>), dim3(M), dim3(1024), 0, st, h, part, S, part_stride,
-                       (const float*)gain, (float*)xn, d, eps, nullptr, none, nullptr, nullptr, nullptr, nullptr,
+                       (const float*)gain, (float*)xn, M, d, eps, nullptr, none, nullptr, nullptr, nullptr, nullptr,
                        nullptr, 0, 0.f);
   else
     hipLaunchKernelGGL((k_add_norm<bf16_t, false>), dim3(M), dim3(1024), 0, st, h, part, S, part_stride,
-                       (const bf16_t*)gain, (bf16_t*)xn, d, eps, nullptr, none, nullptr, nullptr, nullptr, nullptr,
+                       (const bf16_t*)gain, (bf16_t*)xn, M, d, eps, nullptr, none, nullptr, nullptr, nullptr, nullptr,
                        nullptr, 0, 0.f);
   return hipGetLastError();
 }
