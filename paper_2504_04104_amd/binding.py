@@ -6,6 +6,7 @@ raises on a non-zero status.  torch is used for device memory and streams only.
 """
 from __future__ import annotations
 
+import array
 import ctypes as C
 import os
 from typing import Dict, List, Optional, Sequence
@@ -141,6 +142,14 @@ def load_library(path: Optional[str] = None) -> C.CDLL:
 def _i32(a: Optional[Sequence[int]]):
     if a is None:
         return None, None
+    if type(a) is list and a:
+        # lists of integers, the rule: a third of the time of the way through numpy (64 entries: 6.5 -> 1.9 us), with the
+        # same refusal of values that do not fit; lists of anything else take that way
+        try:
+            buf = array.array("i", a)
+            return buf, (C.c_int32 * len(buf)).from_buffer(buf)
+        except TypeError:
+            pass
     arr = np.ascontiguousarray(np.asarray(a, dtype=np.int32))
     return arr, arr.ctypes.data_as(C.POINTER(C.c_int32))
 
@@ -276,7 +285,7 @@ class Stage:
             x_out = self.torch.empty_like(x_in)
         assert x_in.is_cuda and x_in.is_contiguous() and x_in.dtype == self.tdtype
         assert x_out.is_cuda and x_out.is_contiguous() and x_out.dtype == self.tdtype and x_out.shape == x_in.shape
-        assert x_in.shape[0] == int(na.sum()) and x_in.shape[1] == self.shape.d_model
+        assert x_in.shape[0] == int(sum(na)) and x_in.shape[1] == self.shape.d_model
         _check(self.lib.sp_stage_forward(self.handle, len(ra), rp, fp, np_, C.c_void_p(x_in.data_ptr()),
                                          C.c_void_p(x_out.data_ptr()), self._stream()), "sp_stage_forward")
         return x_out
@@ -408,7 +417,8 @@ class Stage:
                                               C.cast(host.data_ptr(), C.POINTER(C.c_int32)), self._stream()),
                "sp_stage_verify_lossy")
         torch.cuda.current_stream(self.device).synchronize()
-        return [(int(host[2 * i]), int(host[2 * i + 1])) for i in range(n)]
+        got = host.tolist()                      # one conversion, not an element of the tensor at a time
+        return [(got[2 * i], got[2 * i + 1]) for i in range(n)]
 
     def verify_sample(self, head: Dict[str, "object"], req_ids: Sequence[int], x_root, temperature: float, top_p: float,
                       top_k: int, u: Sequence[float]) -> List[tuple]:
@@ -425,7 +435,8 @@ class Stage:
                                                dev.data_ptr(), C.cast(host.data_ptr(), C.POINTER(C.c_int32)),
                                                self._stream()), "sp_stage_verify_sample")
         torch.cuda.current_stream(self.device).synchronize()
-        return [(int(host[2 * i]), int(host[2 * i + 1])) for i in range(n)]
+        got = host.tolist()                      # one conversion, not an element of the tensor at a time
+        return [(got[2 * i], got[2 * i + 1]) for i in range(n)]
 
     def tree_match_dev(self, req_ids: Sequence[int]):
         """sp_tree_match without the host copy: the device tensor of verified nodes (int32 per request),
@@ -456,7 +467,7 @@ class Stage:
         _check(self.lib.sp_tree_match(self.handle, len(ra), rp, dev.data_ptr(),
                                       C.cast(host.data_ptr(), C.POINTER(C.c_int32)), self._stream()), "sp_tree_match")
         torch.cuda.current_stream(self.device).synchronize()
-        return [int(v) for v in host[:len(ra)]]
+        return host.tolist()[:len(ra)]
 
     def request_info(self, req: int):
         p, t, f = C.c_int32(), C.c_int32(), C.c_int32()
