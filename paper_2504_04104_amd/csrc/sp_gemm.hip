@@ -57,7 +57,9 @@
 #ifndef SP_GEMM_ROT
 // Plain products split over k, K up to 8192 (the QKV and O shapes): workgroups walk their k slice from
 // different starting chunks.  At 32 and 64 rows 8192 x 8192 29.2 -> 24.8 and 31.0 -> 27.9 us, the other shapes
-// within 1 %; nothing gained with K = 14336 or 28672 (down) and in gate/up: those keep the plain order.
+// within 1 %; nothing gained with K = 14336 or 28672 (down) and in gate/up over weights in fragment order: those keep
+// the plain order.  Gate/up over row-major weights, one workgroup per CU, takes staggered starts too (its rows are 8 or
+// 16 KB apart): 8B shape at 37 rows 58.8 -> 52.7 us, 70B shape at 20 rows 183 -> 176 us (16 rows and fewer: level).
 #define SP_GEMM_ROT 1
 #endif
 #ifndef SP_GEMM_TARGET_WGS_ROWS
@@ -428,7 +430,7 @@ static hipError_t launch_even(int MT, int n_wg, hipStream_t st, const bf16_t* X,
                               int F, int K, int cpw) {
 #define SP_GO(MTV)                                                                                              \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, 4, true, SP_GEMM_KC_GATEUP, SP_GEMM_PF_EVEN, PACKED, false, 8, true>),   \
-                     dim3(n_wg), dim3(512), 0, st, X, W, nullptr, act, M, F, K, K / SP_GEMM_KC_GATEUP, 1, cpw)
+                     dim3(n_wg), dim3(512), 0, st, X, W, nullptr, act, M, F, K, K / SP_GEMM_KC_GATEUP, 1, cpw, PACKED ? 0 : 1)
   switch (MT) {
     case 2: SP_GO(2); break;
     default: SP_GO(3); break;
@@ -443,7 +445,7 @@ static hipError_t launch_even7(int MT, int n_wg, hipStream_t st, const bf16_t* X
   // three weight chunks in flight up to 64 rows (148 -> 145 us per launch), two with 128 (three: 171 -> 179 us)
 #define SP_GO(MTV, PFV)                                                                                         \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, 7, true, 128, PFV, PACKED, false, 7, true>), dim3(n_wg), dim3(448), 0, st, X, \
-                     W, nullptr, act, M, F, K, K / 128, 1, cpw)
+                     W, nullptr, act, M, F, K, K / 128, 1, cpw, PACKED ? 0 : 1)
   switch (MT) {
     case 2: SP_GO(2, 3); break;
     case 3: SP_GO(3, 3); break;
