@@ -672,8 +672,12 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   // memory) and the one that writes the result out.  No argument of these launches depends on the
   // caller's pointers or on the plan's contents, only on M and on the grid sizes the plan implies.
 #define SP_STEP(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) return e_; } while (0)
-  // one row tile: complete projections with RoPE, residual, norm and write-out as their epilogues
-  const bool few = s->fast && M <= 16;
+  // One row tile: complete projections with RoPE, residual, norm and write-out as their epilogues.  Every workgroup there
+  // reads all M rows of X, which with long rows outgrows what the small kernels cost, sooner over row-major weights (16
+  // half lines a request, as X's own).  One layer with split products / complete ones, row-major: 8B shape 8 rows 136.1 /
+  // 131.9 us, 10 rows 136.2 / 135.0, 16 rows 138.4 / 145.3; 70B shape 4 rows 383 / 385, 6 rows 384 / 394, 16 rows 397 /
+  // 440.  Fragment order: 8B shape 16 rows 114.3 / 112.9; 70B shape, two layers, 13 rows 608 / 609, 16 rows 608 / 635.
+  const bool few = s->fast && M <= 16 && M * d <= (s->packed ? 12 : 4) * 8192;
   auto run_layers_few = [&]() -> hipError_t {
     float* ssq = w.part;                            // [M][d / 16]
     for (int l = 0; l < c.n_layers; ++l) {

@@ -1,5 +1,5 @@
 // Plain projections for one row tile (M <= 16: streaming steps of a few nodes, the single node after a stall), whole
-// in one launch each.  A workgroup owns 16 output columns and its waves cut the k range between them, so that the sums
+// in one launch each.  A workgroup owns 16 output columns, or two strips of 16, and its waves cut the k range between them, so that the sums
 // over k are complete inside the workgroup: there are no partial sums in memory, and what used to be a kernel of its own
 // behind every split product -- RoPE and the cache append behind QKV, residual and RMSNorm behind O and down, the
 // write-out behind the last layer -- is the epilogue here.
@@ -17,6 +17,12 @@
 // 12.1 -> 7.3 us, down + residual + norm 25.1 -> 20.0 us (before: split product and the kernel behind it); the step
 // of four layers at a context of 32768 507 -> 465 us.  Four or sixteen waves, 4 to 16 fragments in flight and staggered starting
 // steps are all within 2 % of this.
+//
+// Every workgroup reads all of X from L2, as much as it reads of the weights when all 16 rows are there, and that is
+// what more rows cost (8192 x 28672: 71.5 us with one row, 95.4 with 16).  Where N has 32 columns for each of the CUs a
+// workgroup takes two strips of 16 and so half of that: 8192 x 28672 at 8 / 16 rows 75.6 -> 71.8 / 95.4 -> 80.8 us,
+// 8192 x 8192 29.6 -> 27.2 / 35.4 -> 28.1, level up to 4 rows.  The two strips of all workgroups start 16 KB or a
+// multiple apart in X, so these walk k from staggered starts (8192 x 8192: 31.1 -> 28.1 us; with one strip no gain).
 #include "sp_launch.h"
 
 #define FEW_WAVES 8        // waves per workgroup, each with an eighth of the k range
@@ -44,35 +50,46 @@ struct FewArgs {
   const AttnPlan* plan;    // FEW_OUT: x_out
 };
 
-template <int D, int MODE, bool PACKED, bool WNT>
+template <int D, int NS, int MODE, bool PACKED, bool WNT>
 __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
-  __shared__ __attribute__((aligned(16))) f32x4_t s_acc[FEW_WAVES][64];
+  __shared__ __attribute__((aligned(16))) f32x4_t s_acc[NS][FEW_WAVES][64];
   __shared__ __attribute__((aligned(16))) float s_tot[16];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kg = lane >> 4;
-  const int b = blockIdx.x;
   const int K = a.K, M = a.M;
   const int n = (K >> 5) / FEW_WAVES;              // k steps of this wave, a multiple of D
-  // QKV: columns t0 .. t0+7 of a head and their rotation partners t0+64 .. t0+71
-  const int head = b >> 3, t0 = (b & 7) * 8;
-  const int wrow = MODE == FEW_QKV ? head * 128 + t0 + (r & 7) + ((r & 8) << 3) : b * 16 + r;
-  const bf16_t* w = PACKED ? a.W + ((size_t)(wrow >> 4) * (K >> 5) + (size_t)wave * n) * 512 + (kg * 16 + (wrow & 15)) * 8
+  // QKV: a strip is columns t0 .. t0+7 of a head and their rotation partners t0+64 .. t0+71
+  const bf16_t* w[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const int bi = blockIdx.x * NS + i;
+    const int wrow = MODE == FEW_QKV ? (bi >> 3) * 128 + (bi & 7) * 8 + (r & 7) + ((r & 8) << 3) : bi * 16 + r;
+    w[i] = PACKED ? a.W + ((size_t)(wrow >> 4) * (K >> 5) + (size_t)wave * n) * 512 + (kg * 16 + (wrow & 15)) * 8
                            : a.W + (size_t)wrow * K + (size_t)wave * n * 32 + kg * 8;
+  }
+  const int b = blockIdx.x * NS + (wave < NS ? wave : 0), head = b >> 3, t0 = (b & 7) * 8;
   constexpr int WSTEP = PACKED ? 512 : 32;
   // rows past M repeat the last row and multiply into output rows that are never stored
   const bf16_t* x = a.X + (size_t)min(r, M - 1) * K + (size_t)wave * n * 32 + kg * 8;
-  u32x4_t wf[D], xf[D];
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  u32x4_t wf[NS][D], xf[D];
+  f32x4_t acc[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int rot = NS > 1 ? (int)(((blockIdx.x >> 3) * 2) % (unsigned)n) : 0;
 #define SP_LD(j, S)                                                                             \
   {                                                                                             \
-    const u32x4_t* wp_ = reinterpret_cast<const u32x4_t*>(w + (size_t)(S) * WSTEP);             \
-    wf[j] = WNT ? __builtin_nontemporal_load(wp_) : *wp_;                                       \
-    xf[j] = *reinterpret_cast<const u32x4_t*>(x + (S) * 32);                                    \
+    const int p_ = NS > 1 && (S) + rot >= n ? (S) + rot - n : (S) + rot;                        \
+    _Pragma("unroll") for (int i = 0; i < NS; ++i) {                                            \
+      const u32x4_t* wp_ = reinterpret_cast<const u32x4_t*>(w[i] + (size_t)p_ * WSTEP);                 \
+      wf[i][j] = WNT ? __builtin_nontemporal_load(wp_) : *wp_;                                  \
+    }                                                                                           \
+    xf[j] = *reinterpret_cast<const u32x4_t*>(x + p_ * 32);                                    \
   }
 #define SP_MM(j)                                                                                \
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&wf[j]),     \
-                                                *reinterpret_cast<const bf16x8_t*>(&xf[j]), acc, 0, 0, 0);
+  _Pragma("unroll") for (int i = 0; i < NS; ++i)                                                \
+  acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&wf[i][j]),\
+                                                *reinterpret_cast<const bf16x8_t*>(&xf[j]), acc[i], 0, 0, 0);
   // what the epilogue needs is asked for first: loads return in order, so nothing waits for it later
   RowSquares<64 * FEW_WAVES> sq;
   if (MODE == FEW_QKV && a.ssq_in) sq.load(a.ssq_in, K / 16, M);
@@ -81,7 +98,7 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
   RowInfo ri;
   const int rc = min(r, M - 1);
   const int col = b * 16 + kg * 4;                 // O, down: this lane's four columns
-  if (wave == 0) {
+  if (wave < NS) {
     if (MODE == FEW_QKV) {
       ri = a.rows[rc];
       const float* c = a.cs + (size_t)rc * 128 + t0 + (kg & 1) * 4;
@@ -107,14 +124,15 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
 #undef SP_LD
 #undef SP_MM
 
-  s_acc[wave][lane] = acc;
+#pragma unroll
+  for (int i = 0; i < NS; ++i) s_acc[i][wave][lane] = acc[i];
   if (MODE == FEW_QKV && a.ssq_in) sq.post(a.ssq_in, K / 16, M, s_tot);
   __syncthreads();
-  if (wave != 0) return;
+  if (wave >= NS) return;
   // lane holds, for row r, columns 4 * kg .. + 3 of the workgroup's sixteen
-  f32x4_t y = s_acc[0][lane];
+  f32x4_t y = s_acc[wave][0][lane];
 #pragma unroll
-  for (int v = 1; v < FEW_WAVES; ++v) y += s_acc[v][lane];
+  for (int v = 1; v < FEW_WAVES; ++v) y += s_acc[wave][v][lane];
   if (MODE == FEW_QKV) {
     if (a.ssq_in) y *= rsqrtf(s_tot[rc] / (float)K + a.eps);
     f32x4_t o = y;
@@ -163,10 +181,13 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
 template <int MODE, bool PACKED, bool WNT>
 static hipError_t launch_few(const FewArgs& a, hipStream_t st) {
   const int n = a.K / (32 * FEW_WAVES);
-#define SP_GO(DV) hipLaunchKernelGGL((k_gemm_few<DV, MODE, PACKED, WNT>), dim3(a.N / 16), dim3(64 * FEW_WAVES), 0, st, a)
-  if (n % 8 == 0) SP_GO(8);
-  else if (n % 2 == 0) SP_GO(2);
-  else SP_GO(1);
+#define SP_GO(DV, NSV) hipLaunchKernelGGL((k_gemm_few<DV, NSV, MODE, PACKED, WNT>), dim3(a.N / 16 / NSV), dim3(64 * FEW_WAVES), 0, st, a)
+  // Two strips where that leaves a workgroup for each of the 256 CUs.  Not in QKV: 10240 columns make 320 workgroups, and
+  // an uneven last round (8192 deep, 1 / 16 rows: 31.0 -> 38.2 / 44.0 -> 46.7 us).
+  if (MODE != FEW_QKV && a.N % 32 == 0 && a.N >= 32 * 256 && n % 8 == 0) SP_GO(8, 2);
+  else if (n % 8 == 0) SP_GO(8, 1);
+  else if (n % 2 == 0) SP_GO(2, 1);
+  else SP_GO(1, 1);
 #undef SP_GO
   return hipGetLastError();
 }

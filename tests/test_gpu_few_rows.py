@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
 # k steps per wave: 8 / 8 / 16 (eight fragments in flight), 2 / 4 / 6 (two), 3 / 4 / 5 (one and two)
 SHAPES = {"k2048": wl.ModelShape(n_layers=2, d_model=2048, n_q_heads=16, n_kv_heads=4, d_head=128, d_ff=4096),
           "k512": wl.ModelShape(n_layers=2, d_model=512, n_q_heads=8, n_kv_heads=8, d_head=128, d_ff=1536),
+          # 8192 columns in O and down: two strips per workgroup; 16 rows, and 6 row-major: split products
+          "n8192": wl.ModelShape(n_layers=2, d_model=8192, n_q_heads=16, n_kv_heads=2, d_head=128, d_ff=2048),
           "k768": wl.ModelShape(n_layers=2, d_model=768, n_q_heads=8, n_kv_heads=1, d_head=128, d_ff=1280)}
 
 
