@@ -179,7 +179,7 @@ def main() -> int:
     # factors from a 1 GiB copy), read from the committed summary of those runs; it holds the profiled shape
     # only (C2 at 64 rows), and without the file or its line the field stays null.
     traffic = profiled_traffic() if (args.workload == "C2" and n == 64) else None
-    roofline = {"bound": "hbm", "kernel": "gemm_gateup (k_gemm_bf16 GATEUP)", "achieved": round(achieved, 1),
+    roofline = {"bound": "hbm", "kernel": "gemm_gateup (%s GATEUP)" % ("k_gemm_mid" if 49 <= n <= 160 else "k_gemm_bf16"), "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "avg_launch_us": round(gu_us, 2), "launches": n_launch,
                 "bytes_per_launch": gu_bytes}

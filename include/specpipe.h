@@ -22,7 +22,7 @@
  * valid until sp_stage_destroy().  The library allocates no device memory of
  * its own and creates no streams (the HIP graphs sp_stage_forward may build hold
  * whatever the runtime needs for them: up to 256 instantiated graphs per stage, one per distinct call
- * shape, each of 9-10 kernel nodes per layer, i.e. some tens of kilobytes of host and device memory
+ * shape, each of 5-10 kernel nodes per layer, i.e. some tens of kilobytes of host and device memory
  * per graph that the HIP runtime allocates at the capturing call).  All device work of a call is enqueued
  * on the stream passed to it, in call order; calls return without waiting for
  * the GPU unless stated.  Host arrays passed in are read before the call returns.
@@ -239,7 +239,7 @@ int sp_tree_insert_batch(sp_stage* stage, int32_t n_req, const int32_t* req_ids 
  * The nodes' K and V rows are written to the slab.  A node's parent must have been
  * forwarded before or be part of this call (SP_E_ORDER).  A request may appear once.
  * Launch overhead: when a call has the same shape (rows, attention work items) as an
- * earlier one, its launches except the first and the last are replayed from a HIP graph
+ * earlier one, its launches except the first are replayed from a HIP graph
  * captured the second time that shape was seen; results are identical.  The call stays
  * eager on a stream that cannot be captured (the default stream: pass a stream of your
  * own), while the stream is being captured by the caller, while sp_profile_begin

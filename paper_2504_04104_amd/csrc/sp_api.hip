@@ -136,7 +136,7 @@ struct sp_stage {
   int* d_page_table = nullptr;
   std::vector<int> free_pages;
   // Forward calls of a shape seen before replay a HIP graph of their launches (all but the first
-  // and the last kernel, which carry the caller's pointers and the call's plan).
+  // kernel, which carries the caller's input pointer and the call's plan with the pointer of the result).
   struct FwdGraph {
     int M, qt, items, any_split, units;
     int seen;
@@ -668,8 +668,8 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     return sp_launch_gemm_bf16((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, 16, w.part_floats,
                                S_, st, resident);
   };
-  // Everything between the kernel that opens the call (rows enter, first RMSNorm, plan to device
-  // memory) and the one that writes the result out.  No argument of these launches depends on the
+  // Everything behind the kernel that opens the call (rows enter, first RMSNorm, plan to device
+  // memory), the write-out included: it takes the result's pointer from the plan.  No argument of these launches depends on the
   // caller's pointers or on the plan's contents, only on M and on the grid sizes the plan implies.
 #define SP_STEP(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) return e_; } while (0)
   // One row tile: complete projections with RoPE, residual, norm and write-out as their epilogues.  Every workgroup there
