@@ -105,9 +105,10 @@ __global__ void __launch_bounds__(256) k_lossy_slices(const ReqMeta* meta, const
   for (int w = 0; w < 4; ++w)
     if (s_rv[w] > bv || (s_rv[w] == bv && s_ri[w] < bi)) { bv = s_rv[w]; bi = s_ri[w]; }
   __syncthreads();
+  const float ref = bv == -INFINITY ? 0.f : bv;        // a slice without a finite logit (masked padding rows) has no mass
   float z = 0.f;
   for (int i = tid; i < len; i += 256) {
-    const float e = expf(s_l[i] - bv);
+    const float e = expf(s_l[i] - ref);
     s_e[i] = e;
     z += e;
   }
@@ -213,7 +214,8 @@ __global__ void __launch_bounds__(1024) k_lossy_decide(ReqMeta* meta, const ReqT
       const int ns = min(BLK, b.n_slices - q0);
       __syncthreads();
       if (tid < ns) {
-        const float sc = expf(st[(q0 + tid) * 4] - m);
+        const float top = st[(q0 + tid) * 4];
+        const float sc = top == -INFINITY ? 0.f : expf(top - m);   // (m may be minus infinity itself)
         s_sc[tid] = sc;
         z += st[(q0 + tid) * 4 + 1] * sc;
       }

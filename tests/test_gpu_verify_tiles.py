@@ -93,3 +93,23 @@ def test_lossy_from_exact_logits(n, V, n_child):
         want = max(ok, key=lambda i: (draft[i], -i)) if ok else -1
         assert top_p[q] == (want, int(order[0])), q
     pair.close()
+
+
+@pytest.mark.parametrize("V,first_masked", [(64 * 140, 8448), (5003, 4608)])
+def test_lossy_with_masked_tail(V, first_masked):
+    """The end of the vocabulary masked with minus infinity, as padding rows are: a slice of tokens that holds nothing
+    else has no mass, and neither rule may notice it."""
+    logits = draw_logits("spread", V, V)
+    logits[first_masked:] = -np.inf
+    head = exact_head(logits, False)
+    pair = Pair(SHAPE, 5, {0: 9}, max_batch_nodes=64, oracle=False)
+    x = torch.ones(1, SHAPE.d_model, dtype=torch.bfloat16, device="cuda:0")
+    order = np.lexsort((np.arange(V), -logits))
+    tok = [int(order[2000]), int(order[40]), V - 1, int(order[0])]
+    draft = [0.5, 0.25, 0.75, 0.125]
+    pair.gpu.tree_insert(0, [-1] * 4, tok, draft)
+    assert pair.gpu.verify_lossy(head, [0], x, sp.SP_VERIFY_RELAXED) == [(3, tok[3])]
+    mass = np.cumsum(np.exp(logits[order] - logits.max()))
+    assert mass[39] / mass[-1] < 0.9 < mass[1999] / mass[-1]
+    assert pair.gpu.verify_lossy(head, [0], x, sp.SP_VERIFY_TOP_P, 0.9) == [(1, tok[3])]
+    pair.close()
