@@ -606,16 +606,16 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
       const int j = 2 * lane + e;
       p[e] = j < K ? expf((key_value(s_skey[j]) - mx) * b.inv_T) / Z : 0.f;
     }
-    float incl = p[0] + p[1];
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const float v = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += v;
+    // added one by one in candidate order: sums that never fall, and no candidate of probability zero with an interval
+    // of its own (a scan in tree order differs by a rounding from lane to lane, and u near one drew such candidates)
+    float sum = 0.f;
+    run[0] = run[1] = 0.f;
+    for (int j = 0; 2 * j < K; ++j) {
+      const float r0 = sum + __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p[0]), j));
+      const float r1 = r0 + __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p[1]), j));
+      if (lane == j) { run[0] = r0; run[1] = r1; }
+      sum = r1;
     }
-    const float prev = __shfl_up(incl, 1, 64);
-    const float below = lane > 0 ? prev : 0.f;
-    run[0] = below + p[0];
-    run[1] = incl;
     // m candidates: up to and including the first whose running sum reaches top_p
     int m = K;
 #pragma unroll

@@ -113,3 +113,24 @@ def test_lossy_with_masked_tail(V, first_masked):
     assert mass[39] / mass[-1] < 0.9 < mass[1999] / mass[-1]
     assert pair.gpu.verify_lossy(head, [0], x, sp.SP_VERIFY_TOP_P, 0.9) == [(1, tok[3])]
     pair.close()
+
+
+def test_sampling_never_draws_a_token_without_probability():
+    """A few tokens hold all the mass (the others' exponentials are zero in float32) and u is the largest number below
+    one: the draw is the last token with a probability, whatever the rounding of the running sums."""
+    V, u = 64 * 140, float(np.float32(1.0) - np.float32(2.0 ** -24))
+    pair = Pair(SHAPE, 5, {0: 9}, max_batch_nodes=64, oracle=False)
+    x = torch.ones(1, SHAPE.d_model, dtype=torch.bfloat16, device="cuda:0")
+    r = np.random.RandomState(3)
+    wrong = []
+    for case in range(60):
+        k = 3 + case % 12
+        logits = np.full(V, -120.0)
+        top = r.choice(V, k, replace=False)
+        logits[top] = 1.0 + r.randint(0, 16, k) / 8.0
+        last = int(np.lexsort((np.arange(V), -logits))[k - 1])
+        (_, tok), = pair.gpu.verify_sample(exact_head(logits, False), [0], x, 1.0, 1.0, 80, [u])
+        if tok != last:
+            wrong.append((case, k, float(logits[tok])))
+    pair.close()
+    assert not wrong, wrong
