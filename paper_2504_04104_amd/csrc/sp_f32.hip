@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, c
       for (int w = 0; w < SP_W; ++w) word = (j >> 6) == w ? anc[w] : word;
       vis = (word >> (j & 63)) & 1ull;
     }
-    // slots that are not visible read the range's first slot and get weight zero
+    // slots that are not visible read K of the request's first slot, which then does not count, and add nothing below
     const int slot = (int)sp_phys_slot(g, ri.req, ri.base, vis ? s : 0);
     const f32x4_t* k = reinterpret_cast<const f32x4_t*>(kplane + (size_t)slot * DH);
     f32x4_t d4 = {0.f, 0.f, 0.f, 0.f}, d4b = {0.f, 0.f, 0.f, 0.f};
@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, c
     l = l * corr + wave_sum(p);
     mx = mn;
     s_p[wave][lane] = p;
-    s_slot[wave][lane] = slot;
+    s_slot[wave][lane] = vis ? slot : -1;
 #pragma unroll
     for (int e = 0; e < 8; ++e)
 #pragma unroll
@@ -186,9 +186,13 @@ __global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, c
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         pv[u] = s_p[wave][j + u];
-        const float* vp = vplane + (size_t)s_slot[wave][j + u] * DH + lane;
+        const int sl = s_slot[wave][j + u];
+        const float* vp = vplane + (size_t)max(sl, 0) * DH + lane;
 #pragma unroll
-        for (int c = 0; c < C; ++c) vv[u][c] = vp[c * 64];
+        for (int c = 0; c < C; ++c) {
+          const float v = vp[c * 64];
+          vv[u][c] = sl >= 0 ? v : 0.f;              // a weight of zero would make NaN of an infinity
+        }
       }
 #pragma unroll
       for (int u = 0; u < 16; ++u)

@@ -3,6 +3,7 @@ that end inside a tile, one to four row tiles per workgroup, both head sizes, co
 shares."""
 import numpy as np
 import pytest
+import torch
 
 import workloads as wl
 import paper_2504_04104_amd as sp
@@ -31,3 +32,29 @@ def test_f32_tiles(shape, n, prefix, page_slots):
         assert e <= 2e-5
     pair.check_kv(0, 2e-5)
     pair.close()
+
+
+@pytest.mark.parametrize("page_slots", [0, 32], ids=["contiguous", "pages32"])
+@pytest.mark.parametrize("shape", SHAPES.values(), ids=SHAPES.keys())
+def test_f32_infinite_value_row(shape, page_slots):
+    """An infinity in the committed context's first V row makes that column of the head's attention rows infinite and
+    leaves the other columns finite: slots that a row does not see (siblings, the padding of a step) add nothing.  Read
+    where the kernel leaves the rows, in the workspace (behind the row descriptors, the rotary tables, the residual rows,
+    the normalised rows and the queries, each part aligned to 256 bytes); past the norm that follows all would be NaN."""
+    n, MB, col = 5, 16, 3
+    pair = Pair(shape, 29, {0: 41}, max_batch_nodes=MB, page_slots=page_slots, oracle=False)
+    g = pair.gpu
+    first = int(g.logical_slots(0, 0, 1)[0]) if page_slots else pair.base[0]
+    g.kv_view()[shape.n_layers - 1, 1, 0, first, col] = float("inf")
+    g.tree_insert(0, [-1] * n)
+    x = torch.from_numpy(wl.hidden_rows(shape, 29, ("inf",), n)).to("cuda:0")
+    g.stage_forward([0], [0], [n], x)
+    dq = shape.n_q_heads * shape.d_head
+    parts = (MB * 32, MB * shape.d_head * 4, MB * shape.d_model * 4, MB * shape.d_model * 4, MB * dq * 4)
+    at = sum((b + 255) // 256 * 256 for b in parts)
+    rows = g.workspace[at:at + n * dq * 4].view(torch.float32).view(n, shape.n_q_heads, shape.d_head).cpu()
+    pair.close()
+    want_inf = torch.zeros_like(rows, dtype=torch.bool)
+    want_inf[:, :shape.n_q_heads // shape.n_kv_heads, col] = True
+    assert int((~torch.isposinf(rows[want_inf])).sum()) == 0
+    assert int((~torch.isfinite(rows[~want_inf])).sum()) == 0
