@@ -610,11 +610,19 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
     // of its own (a scan in tree order differs by a rounding from lane to lane, and u near one drew such candidates)
     float sum = 0.f;
     run[0] = run[1] = 0.f;
-    for (int j = 0; 2 * j < K; ++j) {
-      const float r0 = sum + __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p[0]), j));
-      const float r1 = r0 + __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p[1]), j));
-      if (lane == j) { run[0] = r0; run[1] = r1; }
-      sum = r1;
+    for (int j0 = 0; 2 * j0 < K; j0 += 8) {           // (probabilities past the K-th are zero)
+      float a[8], c[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        a[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p[0]), j0 + j));
+        c[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p[1]), j0 + j));
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float r0 = sum + a[j];
+        sum = r0 + c[j];
+        if (lane == j0 + j) { run[0] = r0; run[1] = sum; }
+      }
     }
     // m candidates: up to and including the first whose running sum reaches top_p
     int m = K;
