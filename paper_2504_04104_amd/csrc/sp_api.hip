@@ -672,34 +672,30 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   // memory), the write-out included: it takes the result's pointer from the plan.  No argument of these launches depends on the
   // caller's pointers or on the plan's contents, only on M and on the grid sizes the plan implies.
 #define SP_STEP(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) return e_; } while (0)
-  // One row tile: complete projections with RoPE, residual, norm and write-out as their epilogues.  Every workgroup there
-  // reads all M rows of X, which with long rows outgrows what the small kernels cost, sooner over row-major weights (16
-  // half lines a request, as X's own).  One layer with split products / complete ones, row-major: 8B shape 8 rows 136.1 /
-  // 131.9 us, 10 rows 136.2 / 135.0, 16 rows 138.4 / 145.3; 70B shape 4 rows 383 / 385, 6 rows 384 / 394, 16 rows 397 /
-  // 440.  Fragment order: 8B shape 16 rows 114.3 / 112.9; 70B shape, two layers, 13 rows 608 / 609, 16 rows 608 / 635.
-  const bool few = s->fast && M <= 16 && M * d <= (s->packed ? 12 : 4) * 8192;
+  // One row tile: complete projections with RoPE, residual, norm and write-out as their epilogues.
+  const bool few = s->fast && sp_few_takes(M, d, dq, F, s->packed, s->n_cu);
   auto run_layers_few = [&]() -> hipError_t {
     float* ssq = w.part;                            // [M][d / 16]
     for (int l = 0; l < c.n_layers; ++l) {
       const sp_layer_weights& L = s->W[l];
       { ProfScope p(s, SP_K_GEMM_QKV, st);
         SP_STEP(sp_launch_few_qkv((const bf16_t*)w.xn, (const bf16_t*)L.wqkv, s->packed, l > 0 ? ssq : nullptr, c.rms_eps,
-                                  w.rows, w.cs, (bf16_t*)w.qbuf, s->geom, l, M, d, nq, nkv, st)); }
+                                  w.rows, w.cs, (bf16_t*)w.qbuf, s->geom, l, M, d, nq, nkv, s->n_cu, st)); }
       { ProfScope p(s, SP_K_ATTENTION, st);
         SP_STEP(sp_launch_attn_bf16((const bf16_t*)w.qbuf, s->d_tables, s->geom, l, plan, w.plan, w.attn_part,
                                     (bf16_t*)w.attn, M, nq, nkv, dh, st)); }
       { ProfScope p(s, SP_K_GEMM_O, st);
         SP_STEP(sp_launch_few_residual((const bf16_t*)w.attn, (const bf16_t*)L.wo, s->packed, s->o_resident, w.h,
-                                       (const bf16_t*)L.norm2, (bf16_t*)w.xn, ssq, M, d, dq, st)); }
+                                       (const bf16_t*)L.norm2, (bf16_t*)w.xn, ssq, M, d, dq, s->n_cu, st)); }
       { ProfScope p(s, SP_K_GEMM_GATEUP, st);
         SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d,
                                            s->n_cu, ssq, c.rms_eps, st)); }
       { ProfScope p(s, SP_K_GEMM_DOWN, st);
         if (l + 1 < c.n_layers)
           SP_STEP(sp_launch_few_residual((const bf16_t*)w.act, (const bf16_t*)L.wd, s->packed, false, w.h,
-                                         (const bf16_t*)s->W[l + 1].norm1, (bf16_t*)w.xn, ssq, M, d, F, st));
+                                         (const bf16_t*)s->W[l + 1].norm1, (bf16_t*)w.xn, ssq, M, d, F, s->n_cu, st));
         else
-          SP_STEP(sp_launch_few_out((const bf16_t*)w.act, (const bf16_t*)L.wd, s->packed, w.h, w.plan, M, d, F, st)); }
+          SP_STEP(sp_launch_few_out((const bf16_t*)w.act, (const bf16_t*)L.wd, s->packed, w.h, w.plan, M, d, F, s->n_cu, st)); }
     }
     return hipSuccess;
   };

@@ -177,14 +177,39 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
   }
 }
 
+// Two strips per workgroup where that leaves a workgroup for each CU.  Not in QKV: 10240 columns make 320 workgroups, and
+// an uneven last round (8192 deep, 1 / 16 rows: 31.0 -> 38.2 / 44.0 -> 46.7 us).
+static bool two_strips(int N, int K, int n_cu) { return N % 32 == 0 && N >= 32 * n_cu && K % (256 * FEW_WAVES) == 0; }
+
+// Where complete projections are faster than split products and the small kernels behind them.  Measured with both over
+// the widths 1024 to 8192, one layer, us complete / split:
+// - Workgroups of O and down in whole rounds over the CUs (up to 4096 columns in strips of 16, 8192 in two strips):
+//   packed 1024 16 rows 40 / 46, 3072 16 rows 72 / 77, 4096 16 rows 106.7 / 107.1, 8192 12 rows 302 / 305, 13 rows 306 /
+//   305.  An uneven last round leaves most of the chip idle and more X to read: 4608 (288 workgroups) 1 / 4 / 16 rows 143 /
+//   146 / 177 against 142 / 143 / 147, 5120 (320) 116 / 122 / 151 against 123 / 127 / 128, 6144 (384) 156 / 163 / 178
+//   against 160 / 164 / 162, 7168 (448) 217 / 212 / 250 against 221 / 216 / 222: up to four rows there.
+// - Row-major weights (16 half lines a request, as X's own): 3072 10 / 14 rows 83 / 87 against 86 / 87, 4096 8 / 12 rows
+//   127 / 133 against 129 / 133, 3584 8 rows 146 / 145; from 4608 on slower or level with any number of rows (4608 one row
+//   195 / 177, 8192 four rows 378 / 372).
+// - One load in flight per wave does not stream: d_ff = 8960 and 11008 (35 and 43 k steps a wave) 54.5 / 51.1 and 106.6 /
+//   106.0 with one row, 61.3 / 58.6 and 113.4 / 109.9 with 16.  Up to 1792 deep a wave has seven steps and it does not matter.
+bool sp_few_takes(int M, int d, int dq, int F, bool packed, int n_cu) {
+  auto streams = [](int K) { return K % (64 * FEW_WAVES) == 0 || K < 256 * FEW_WAVES; };
+  auto whole_rounds = [&](int K) {
+    const int wgs = d / (two_strips(d, K, n_cu) ? 32 : 16);
+    return wgs <= n_cu || wgs % n_cu == 0;
+  };
+  if (M < 1 || M > 16 || !streams(d) || !streams(dq) || !streams(F)) return false;
+  if (!packed) return d <= 16 * n_cu && M * d <= 4 * 8192;
+  return whole_rounds(dq) && whole_rounds(F) ? M * d <= 12 * 8192 : M <= 4;
+}
+
 // Eight fragments in flight per wave; shapes whose k slices are shorter, or no multiple of that, take fewer.
 template <int MODE, bool PACKED, bool WNT>
-static hipError_t launch_few(const FewArgs& a, hipStream_t st) {
+static hipError_t launch_few(const FewArgs& a, int n_cu, hipStream_t st) {
   const int n = a.K / (32 * FEW_WAVES);
 #define SP_GO(DV, NSV) hipLaunchKernelGGL((k_gemm_few<DV, NSV, MODE, PACKED, WNT>), dim3(a.N / 16 / NSV), dim3(64 * FEW_WAVES), 0, st, a)
-  // Two strips where that leaves a workgroup for each of the 256 CUs.  Not in QKV: 10240 columns make 320 workgroups, and
-  // an uneven last round (8192 deep, 1 / 16 rows: 31.0 -> 38.2 / 44.0 -> 46.7 us).
-  if (MODE != FEW_QKV && a.N % 32 == 0 && a.N >= 32 * 256 && n % 8 == 0) SP_GO(8, 2);
+  if (MODE != FEW_QKV && two_strips(a.N, a.K, n_cu)) SP_GO(8, 2);
   else if (n % 8 == 0) SP_GO(8, 1);
   else if (n % 2 == 0) SP_GO(2, 1);
   else SP_GO(1, 1);
@@ -194,27 +219,28 @@ static hipError_t launch_few(const FewArgs& a, hipStream_t st) {
 
 hipError_t sp_launch_few_qkv(const bf16_t* X, const bf16_t* W, bool packed, const float* ssq, float eps, const RowInfo* rows,
                              const float* cs, bf16_t* qbuf, KvGeom g, int layer, int M, int K, int n_q, int n_kv,
-                             hipStream_t st) {
+                             int n_cu, hipStream_t st) {
   if (M < 1 || M > 16 || K % 256 || g.row_bytes != 256) return hipErrorInvalidValue;
   FewArgs a = {};
   a.X = X; a.W = W; a.M = M; a.N = (n_q + 2 * n_kv) * 128; a.K = K; a.ssq_in = ssq; a.eps = eps;
   a.rows = rows; a.cs = cs; a.qbuf = qbuf; a.g = g; a.layer = layer; a.n_q = n_q; a.n_kv = n_kv;
-  return packed ? launch_few<FEW_QKV, true, true>(a, st) : launch_few<FEW_QKV, false, true>(a, st);
+  return packed ? launch_few<FEW_QKV, true, true>(a, n_cu, st) : launch_few<FEW_QKV, false, true>(a, n_cu, st);
 }
 
 hipError_t sp_launch_few_residual(const bf16_t* X, const bf16_t* W, bool packed, bool resident, float* h, const bf16_t* gain,
-                                  bf16_t* xn, float* ssq_out, int M, int N, int K, hipStream_t st) {
+                                  bf16_t* xn, float* ssq_out, int M, int N, int K, int n_cu,
+                                  hipStream_t st) {
   if (M < 1 || M > 16 || K % 256 || N % 16) return hipErrorInvalidValue;
   FewArgs a = {};
   a.X = X; a.W = W; a.M = M; a.N = N; a.K = K; a.h = h; a.gain = gain; a.xn = xn; a.ssq_out = ssq_out;
-  if (resident) return packed ? launch_few<FEW_RESIDUAL, true, false>(a, st) : launch_few<FEW_RESIDUAL, false, false>(a, st);
-  return packed ? launch_few<FEW_RESIDUAL, true, true>(a, st) : launch_few<FEW_RESIDUAL, false, true>(a, st);
+  if (resident) return packed ? launch_few<FEW_RESIDUAL, true, false>(a, n_cu, st) : launch_few<FEW_RESIDUAL, false, false>(a, n_cu, st);
+  return packed ? launch_few<FEW_RESIDUAL, true, true>(a, n_cu, st) : launch_few<FEW_RESIDUAL, false, true>(a, n_cu, st);
 }
 
 hipError_t sp_launch_few_out(const bf16_t* X, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
-                             int N, int K, hipStream_t st) {
+                             int N, int K, int n_cu, hipStream_t st) {
   if (M < 1 || M > 16 || K % 256 || N % 16) return hipErrorInvalidValue;
   FewArgs a = {};
   a.X = X; a.W = W; a.M = M; a.N = N; a.K = K; a.h = const_cast<float*>(h); a.plan = plan_dev;
-  return packed ? launch_few<FEW_OUT, true, true>(a, st) : launch_few<FEW_OUT, false, true>(a, st);
+  return packed ? launch_few<FEW_OUT, true, true>(a, n_cu, st) : launch_few<FEW_OUT, false, true>(a, n_cu, st);
 }

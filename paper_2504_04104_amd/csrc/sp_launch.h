@@ -131,17 +131,20 @@ hipError_t sp_launch_gemm_argmax_bf16(const bf16_t* X, const bf16_t* W, bool pac
 // ssq (nullable, M <= 16 only): [M][K / 16] sums of squares of the rows, X is then not normalised yet
 hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F,
                                       int K, int n_cu, const float* ssq, float eps, hipStream_t st);
-// One row tile (M <= 16), fast path: complete projections with what follows them as their epilogue (sp_gemm_few.hip).
+// One row tile (M <= 16), fast path: complete projections with what follows them as their epilogue (sp_gemm_few.hip);
+// `takes` says for which sizes these are to be called (d = d_model, dq = n_q * d_head).
+bool sp_few_takes(int M, int d, int dq, int F, bool packed, int n_cu);
 // ssq (nullable): [M][d / 16] sums of squares of the rows, X is then not normalised yet.
 hipError_t sp_launch_few_qkv(const bf16_t* X, const bf16_t* W, bool packed, const float* ssq, float eps, const RowInfo* rows,
                              const float* cs, bf16_t* qbuf, KvGeom g, int layer, int M, int K, int n_q, int n_kv,
-                             hipStream_t st);
+                             int n_cu, hipStream_t st);
 // h += X W^T; xn = bf16(h * gain); ssq_out[M][N / 16]
 hipError_t sp_launch_few_residual(const bf16_t* X, const bf16_t* W, bool packed, bool resident, float* h, const bf16_t* gain,
-                                  bf16_t* xn, float* ssq_out, int M, int N, int K, hipStream_t st);
+                                  bf16_t* xn, float* ssq_out, int M, int N, int K, int n_cu,
+                                  hipStream_t st);
 // rows of the plan's x_out = bf16(h + X W^T)
 hipError_t sp_launch_few_out(const bf16_t* X, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
-                             int N, int K, hipStream_t st);
+                             int N, int K, int n_cu, hipStream_t st);
 // 49-160 rows (sp_gemm_mid.hip): one workgroup per CU, two strips of weight rows per wave; `takes` says for which
 // sizes these are to be called (gate/up: where every CU gets the same 56 or 64 columns)
 bool sp_gemm_mid_takes(int M, int N, int K);

@@ -10,10 +10,12 @@ from gpu_harness import Pair, rel_err, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
+SP_K_ROPE_KV = 11          # sp_kernel_kind
+
 # k steps per wave: 8 / 8 / 16 (eight fragments in flight), 2 / 4 / 6 (two), 3 / 4 / 5 (one and two)
 SHAPES = {"k2048": wl.ModelShape(n_layers=2, d_model=2048, n_q_heads=16, n_kv_heads=4, d_head=128, d_ff=4096),
           "k512": wl.ModelShape(n_layers=2, d_model=512, n_q_heads=8, n_kv_heads=8, d_head=128, d_ff=1536),
-          # 8192 columns in O and down: two strips per workgroup; 16 rows, and 6 row-major: split products
+          # 8192 columns in O and down: two strips per workgroup; 16 rows, and all of row-major: split products
           "n8192": wl.ModelShape(n_layers=2, d_model=8192, n_q_heads=16, n_kv_heads=2, d_head=128, d_ff=2048),
           "k768": wl.ModelShape(n_layers=2, d_model=768, n_q_heads=8, n_kv_heads=1, d_head=128, d_ff=1280)}
 
@@ -40,4 +42,38 @@ def test_one_row_tile(shape, n, packed, page_slots):
         pair.check_kv(0, 2e-2)
     for y, seen in outs:
         assert np.array_equal(to_np(y), seen)
+    pair.close()
+
+
+# shape, weights, [(rows, complete projections?)]
+ROUTES = [
+    # up to one workgroup per CU in O and down, whole rounds (8192: two strips each), else up to four rows
+    ("d4096", (4096, 32, 8, 512), True, [(16, True)]),
+    ("d8192", (8192, 16, 2, 512), True, [(12, True), (13, False)]),
+    ("d4608", (4608, 36, 4, 512), True, [(4, True), (5, False), (16, False)]),
+    # row-major weights: up to 4096 columns, and rows by their length
+    ("d4096", (4096, 32, 8, 512), False, [(8, True), (9, False)]),
+    ("d4608", (4608, 36, 4, 512), False, [(1, False)]),
+    # an odd number of k steps per wave leaves one load in flight: only short k ranges
+    ("ff8960", (512, 4, 2, 8960), True, [(1, False)]),
+    ("ff1792", (512, 4, 2, 1792), True, [(16, True)]),
+]
+
+
+@pytest.mark.parametrize("name,dims,packed,calls", ROUTES, ids=[f"{r[0]}_{'packed' if r[2] else 'rowmajor'}" for r in ROUTES])
+def test_which_rows_take_complete_projections(name, dims, packed, calls):
+    """Where the line between complete and split projections lies (a call with complete ones has no RoPE launch of its
+    own), and results on both of its sides against the oracle."""
+    d, nq, nkv, ff = dims
+    shape = wl.ModelShape(n_layers=1, d_model=d, n_q_heads=nq, n_kv_heads=nkv, d_head=128, d_ff=ff)
+    pair = Pair(shape, 37, {r: 30 for r in range(len(calls))}, flags=sp.SP_FLAG_PACKED_WEIGHTS if packed else 0)
+    for r, (n, complete) in enumerate(calls):
+        pair.insert(r, wl.tree_deep(37 + n, n, 7))
+        x = wl.hidden_rows(shape, 37, ("route", n), n)
+        pair.gpu.profile_begin(SP_K_ROPE_KV, 4)
+        y, ref = pair.forward([r], [0], [n], x)
+        launches, _ = pair.gpu.profile_end()
+        assert (launches == 0) == complete, (n, launches)
+        assert rel_err(y - x, ref - x) <= 2e-2, n
+        pair.check_kv(r, 2e-2)
     pair.close()
