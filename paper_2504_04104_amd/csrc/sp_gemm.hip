@@ -65,6 +65,9 @@
 #ifndef SP_GEMM_TARGET_WGS_ROWS
 #define SP_GEMM_TARGET_WGS_ROWS 512   // split K until the grid has at most this many workgroups (two per CU)
 #endif
+#ifndef SP_GEMM_TARGET_WGS_ONE
+#define SP_GEMM_TARGET_WGS_ONE 768    // ... or this many, for one row tile that those would load unevenly
+#endif
 
 // PACKED: the weights were re-laid at load time (sp_pack_weights) into MFMA fragment order --
 // per strip of 16 rows, one contiguous 1 KB block per k-step of 32, lane-major -- so that every
@@ -392,6 +395,11 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   // two and three per CU, which leaves the CUs unevenly loaded, 0.638 ms; two waves per column group with half
   // the slices again: 0.612 ms).
   int S = (eight ? SP_GEMM_TARGET_WGS_ROWS / 2 : SP_GEMM_TARGET_WGS_ROWS) / (tiles * mblocks);
+  // One row tile, whose partial sums are small: three workgroups per CU where two per CU would be an uneven round (12288
+  // columns: 192 tiles x 4 instead of x 2; one layer, row-major, with those in QKV 128.8 -> 124.7 us at one row and 140.3
+  // -> 136.7 at 16, with those in O and down 430 -> 398 and 461 -> 428).  Not throughout: 7168 and 5120 columns in 112 x 7
+  // and 80 x 10 workgroups, a few more than three per CU, 156 -> 165 us at one row.
+  if (MT == 1 && S >= 1 && 4 * S * tiles <= 3 * SP_GEMM_TARGET_WGS_ROWS) S = (SP_GEMM_TARGET_WGS_ONE + tiles - 1) / tiles;
   if (S > max_split) S = max_split;
   if (S > chunks) S = chunks;
   while (S > 1 && (size_t)S * M * N > part_capacity_floats) --S;

@@ -56,6 +56,9 @@ ROUTES = [
     ("d4608", (4608, 36, 4, 512), False, [(1, False)]),
     # an odd number of k steps per wave leaves one load in flight: only short k ranges
     ("ff8960", (512, 4, 2, 8960), True, [(1, False)]),
+    # ... with QKV's 192 tiles in four slices (three workgroups per CU), O and down in sixteen
+    ("mha", (1024, 32, 32, 8960), True, [(1, False), (16, False)]),
+    ("mha", (1024, 32, 32, 8960), False, [(9, False)]),
     ("ff1792", (512, 4, 2, 1792), True, [(16, True)]),
 ]
 
