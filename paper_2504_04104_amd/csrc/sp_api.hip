@@ -659,7 +659,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   // projections: few rows stream the weights (HBM-bound); many rows use the register-blocked kernel
   const bool wide = s->fast && M > 128 && nqkv % 256 == 0 && d % 256 == 0 && F % 128 == 0 && dq % 128 == 0;
   auto gemm = [&](const void* X, const void* Wm, int N_, int K_, int* S_, bool resident = false) -> hipError_t {
-    if (sp_gemm_mid_takes(M, N_, K_))
+    if (sp_gemm_mid_takes(M, N_, K_, s->n_cu))
       return sp_launch_gemm_mid((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, s->n_cu, 16,
                                 w.part_floats, S_, st, resident);
     if (wide)

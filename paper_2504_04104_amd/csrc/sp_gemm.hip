@@ -75,6 +75,8 @@
 // ARGMAX (output head of the last stage, Algorithm 1 "verify new token"): instead of the
 // products, a workgroup leaves per row the largest of its 16*NCG columns and that column's
 // index (the lowest one among equal maxima) as a (float, int) pair at out[(m * tiles + tile) * 2].
+// TWO (plain products of eight row tiles): a wave holds two strips of 16 weight rows, 64 rows apart, so that a workgroup
+// of four waves covers 128 columns.
 // STATS (logits of a stochastic verification): beside the products, a workgroup leaves per row the maximum mx of its
 // 16*NCG columns and the sum of exp((l - mx) * inv_T) over them as a float pair at stats[(m * tiles + tile) * 2].
 // EVEN (gate/up): one workgroup per CU covers cpw = d_ff / CUs activation columns, a multiple of 8, in NCG column
@@ -85,16 +87,17 @@
 // strips in fixed 32-column workgroups cannot do when d_ff / 32 is not a multiple of the CU count (d_ff = 14336:
 // 1.75 workgroups per CU), and the panel is staged once per CU instead of once per four waves.
 template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, int NWAVES = 4, bool EVEN = false, bool WNT = true,
-          bool STATS = false>
+          bool STATS = false, bool TWO = false>
 __global__ void __launch_bounds__(64 * NWAVES)
 k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
             bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int cpw = 0, int rot = 0,
             const float* ssq = nullptr, float eps = 0.f, float* stats = nullptr, float inv_T = 0.f) {
+  static_assert(!(TWO && (GATEUP || ARGMAX || STATS)), "two strips per wave: plain products only");
   static_assert(!EVEN || GATEUP, "even split: gate/up only");
   constexpr int NTH = 64 * NWAVES;
   constexpr int NKH = NWAVES / NCG;       // waves sharing a column group split each chunk's k-steps
   constexpr int KSTEPS = (KC / 32) / NKH;
-  constexpr int NW = GATEUP ? 2 : 1;
+  constexpr int NW = (GATEUP || TWO) ? 2 : 1;
   constexpr int ROWS = MT * 16;
   constexpr int XS = KC * 2 + 16;         // LDS row stride in bytes (conflict-free 16-byte reads)
   constexpr int UPR = KC / 8;             // 16-byte units per X row chunk
@@ -107,9 +110,9 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int cg = wave % NCG, kh = wave / NCG;
   const int r = lane & 15, kg = lane >> 4;
-  const int n0 = EVEN ? blockIdx.x * cpw + cg * 16 : blockIdx.x * (16 * NCG) + cg * 16;
+  const int n0 = EVEN ? blockIdx.x * cpw + cg * 16 : blockIdx.x * (16 * NCG * (TWO ? 2 : 1)) + cg * 16;
   const int vr = EVEN ? min(16, cpw - cg * 16) : 16;     // valid columns of this wave's group (8 or 16)
-  const int pair_off = N;                    // gate/up: the up rows follow the N gate rows
+  const int pair_off = TWO ? 16 * NCG : N;   // rows between a wave's two strips (gate/up: the up rows follow the N gate rows)
   const int m_base = blockIdx.z * ROWS;
   const int c_begin = (int)(((long long)blockIdx.y * chunks_total) / S);
   const int c_end = (int)(((long long)(blockIdx.y + 1) * chunks_total) / S);
@@ -304,6 +307,32 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
       *reinterpret_cast<float2*>(stats + ((size_t)(m_base + tid) * gridDim.x + blockIdx.x) * 2) = make_float2(mx, z);
     }
   }
+  if (!GATEUP && !STATS && MT == 8) {
+    // Eight row tiles: partial sums leave in whole rows of the workgroup's columns.  The waves' 16-column pieces are put
+    // together in LDS (the panels are no longer read: every wave has passed the barrier that ends its last chunk), and a
+    // store instruction then writes 1 KB of consecutive addresses instead of 64 bytes in each of 16 rows.
+    static_assert(NKH == 1 || GATEUP, "plain products: one wave per column group");
+    constexpr int WCOLS = 16 * NCG * (TWO ? 2 : 1);
+    constexpr int LSF = WCOLS + 4;                        // floats per LDS row
+    static_assert(MT != 8 || ROWS * LSF * 4 <= (int)sizeof(lds), "the row tile fits the panels' LDS");
+    float* tile = reinterpret_cast<float*>(&lds[0][0]);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int a = 0; a < NW; ++a)
+        *reinterpret_cast<f32x4_t*>(tile + (mt * 16 + r) * LSF + a * (16 * NCG) + cg * 16 + 4 * kg) = acc[a][mt];
+    __syncthreads();
+    constexpr int UPRW = WCOLS / 4;                       // 16-byte units per row
+    const int col0 = blockIdx.x * WCOLS;
+    for (int idx = tid; idx < ROWS * UPRW; idx += NTH) {
+      const int row = idx / UPRW, u = idx - row * UPRW;
+      const int m = m_base + row;
+      if (m < M)
+        *reinterpret_cast<f32x4_t*>(out + ((size_t)blockIdx.y * M + m) * N + col0 + u * 4) =
+            *reinterpret_cast<const f32x4_t*>(tile + row * LSF + u * 4);
+    }
+    return;
+  }
   float row_scale = 1.f;
   if (SCALED && ssq) {
     if (NKH != 2) __syncthreads();      // (the fold of the k-halves has passed a barrier)
@@ -333,8 +362,8 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 }
 
 // ---- launchers -------------------------------------------------------------------
-// Up to 64 rows run as one block of MT = ceil(M/16) tiles; more rows (gate/up shapes that sp_gemm_mid.hip does not
-// cover, the output head) run in blocks of 128 (MT = 8, always with the 128-wide chunk so that the two LDS panels
+// Up to 64 rows run as one block of MT = ceil(M/16) tiles; more rows (shapes that sp_gemm_mid.hip does not take, the
+// output head) run in blocks of 128 (MT = 8, always with the 128-wide chunk so that the two LDS panels
 // fit), each block streaming the weights once.
 // staggered starting chunks: plain products that are split over k, K up to 8192 (see SP_GEMM_ROT)
 static inline int rot_for(int S, int K) { return (SP_GEMM_ROT && S > 1 && K <= 8192) ? 1 : 0; }
@@ -360,7 +389,7 @@ static hipError_t launch_mt(int MT, dim3 grid, hipStream_t st, const bf16_t* X, 
         hipLaunchKernelGGL((k_gemm_bf16<8, 4, true, 128, SP_GEMM_PF, PACKED, false>), grid, dim3(256), 0, st, X, W, out, act,
                            M, N, K, K / 128, S);
       else if (GATEUP) SP_GO(8, 128);
-      else return hipErrorInvalidValue;               // plain products: 64 rows at most
+      else return hipErrorInvalidValue;               // plain products of eight row tiles: not in these workgroups
       break;
   }
 #undef SP_GO
@@ -381,12 +410,16 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   // 17-64 rows: workgroups of eight waves over 128 columns, one per CU -- the same waves per CU as two
   // four-wave workgroups of 64 columns, but the panel slice is staged once for all eight
   const bool eight = SP_GEMM_PLAIN8 && N % 128 == 0 && MT >= 2;
+  // 97-128 rows where sp_gemm_mid.hip does not take the product (slices of one chunk, two slices of a wide matrix): the
+  // same, and for large matrices four waves with two strips each, two workgroups per CU: the panel is then read once per
+  // 128 columns, which is worth the partial sums of twice the slices (12288 wide, 97 rows: QKV 79 -> 76 us per launch)
+  const bool two = MT == 8 && (double)N * (double)K >= 64.0 * 1048576.0;
   // ... or six waves over 96 columns where that divides the CUs evenly and 128 columns do not (N = 6144 on 256 CUs:
   // 64 tiles x 4 slices of equal length instead of 48 x 5 of 6 or 7 chunks)
-  const bool six = SP_GEMM_PLAIN6 && eight && N % 96 == 0 && (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 128) != 0 &&
+  const bool six = SP_GEMM_PLAIN6 && eight && MT <= 4 && N % 96 == 0 && (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 128) != 0 &&
                    (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 96) == 0;
   const int TILE = six ? 96 : eight ? 128 : 16 * SP_GEMM_NCG_PLAIN;
-  if (M < 1 || M > 64 || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
+  if (M < 1 || M > 128 || (MT == 8 && !eight) || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
   const int chunks = K / SP_GEMM_KC_PLAIN;
   const int tiles = N / TILE;
   // Enough workgroups to keep every CU streaming, within the partial-sum buffer.  Every slice costs M*N*4 bytes
@@ -394,7 +427,7 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   // workgroups per CU (measured on the whole 64-row step: 0.608 ms against 0.617 ms with three; a count between
   // two and three per CU, which leaves the CUs unevenly loaded, 0.638 ms; two waves per column group with half
   // the slices again: 0.612 ms).
-  int S = (eight ? SP_GEMM_TARGET_WGS_ROWS / 2 : SP_GEMM_TARGET_WGS_ROWS) / (tiles * mblocks);
+  int S = (eight && !two ? SP_GEMM_TARGET_WGS_ROWS / 2 : SP_GEMM_TARGET_WGS_ROWS) / (tiles * mblocks);
   // One row tile, whose partial sums are small: three workgroups per CU where two per CU would be an uneven round (12288
   // columns: 192 tiles x 4 instead of x 2; one layer, row-major, with those in QKV 128.8 -> 124.7 us at one row and 140.3
   // -> 136.7 at 16, with those in O and down 430 -> 398 and 461 -> 428).  Not throughout: 7168 and 5120 columns in 112 x 7
@@ -407,6 +440,14 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   if ((size_t)S * M * N > part_capacity_floats) return hipErrorInvalidValue;
   *S_out = S;
   const dim3 grid(tiles, S, mblocks);
+  if (two) {
+#define SP_GO2(PK)                                                                                               \
+  hipLaunchKernelGGL((k_gemm_bf16<8, 4, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, 4, false, true, false, true>), grid, \
+                     dim3(256), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K))
+    if (packed) SP_GO2(true); else SP_GO2(false);
+#undef SP_GO2
+    return hipGetLastError();
+  }
   if (six) {
 #define SP_GO6(MTV, PK)                                                                                          \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, 6, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, 6>), grid, dim3(384), 0, \
@@ -424,8 +465,8 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   else                                                                                                           \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, PK, false, 8>), grid, dim3(512), 0, \
                      st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K))
-    if (packed) { if (MT == 2) SP_GO8(2, true); else if (MT == 3) SP_GO8(3, true); else SP_GO8(4, true); }
-    else { if (MT == 2) SP_GO8(2, false); else if (MT == 3) SP_GO8(3, false); else SP_GO8(4, false); }
+    if (packed) { if (MT == 2) SP_GO8(2, true); else if (MT == 3) SP_GO8(3, true); else if (MT == 4) SP_GO8(4, true); else SP_GO8(8, true); }
+    else { if (MT == 2) SP_GO8(2, false); else if (MT == 3) SP_GO8(3, false); else if (MT == 4) SP_GO8(4, false); else SP_GO8(8, false); }
 #undef SP_GO8
     return hipGetLastError();
   }

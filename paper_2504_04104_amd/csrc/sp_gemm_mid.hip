@@ -238,13 +238,38 @@ static hipError_t launch_gateup(int n_cu, hipStream_t st, const bf16_t* X, const
   return hipGetLastError();
 }
 
-// Where this kernel is the faster one (8B and 70B shapes, us per launch, k_gemm_bf16 or k_gemm_wide against this one):
+// How a plain product is cut: columns per workgroup and k slices, one workgroup per CU (every further slice costs M*N*4
+// bytes written here and read again by the folding kernel).  96 columns where those tiles divide the CUs evenly and tiles
+// of 128 do not (N = 6144 on 256 CUs: 64 tiles x 4 slices of equal length instead of 48 x 5 of 6 or 7 chunks).  Six waves
+// on four SIMDs leave half of the matrix cores idle for half of the time, which counts as soon as these, not the
+// weights, set the pace: from 97 rows on, only for short slices (one layer, us with 96 / 128 columns: 6144 wide, slices of
+// 12 to 32 chunks, 65 rows 198 / 196, 97 rows 228 / 209, 160 rows 259 / 243; 3072 wide, slices of 3 and 8 chunks, 65 rows
+// 104 / 106, 97 rows 117 / 117, 160 rows 142 / 146).
+struct MidCut { int cols, S; };
+static MidCut mid_cut(int M, int N, int K, int n_cu) {
+  const int chunks = K / MID_KC;
+  const bool even96 = N % 96 == 0 && n_cu % (N / 128) != 0 && n_cu % (N / 96) == 0;
+  const bool six = even96 && (M <= 96 || chunks <= 8 * (n_cu / (N / 96)));
+  return {six ? 96 : 128, n_cu / (N / (six ? 96 : 128))};
+}
+
+// Where this kernel is the faster one (us per launch, k_gemm_bf16 or k_gemm_wide against this one, 8B and 70B shapes):
 // gate/up 64 rows 45.5 / 43.7, 128 rows 60.4 / 54.6, 145 rows 70.2 / 59.3, at 48 rows 43.5 / 49.8; down, 14336 or 28672
 // deep, 64 rows 28.1 / 26.8 and 83 / 77, 145 rows 42.1 / 35.9; QKV and O of both shapes lose up to 8 % at 64 rows (their
 // k slices are four to eight chunks long) and gain from 65 on (145 rows 25.5 / 24.4 and 22.2 / 18.6).  From 161 rows on
 // the register-blocked kernel is level, and with twelve row tiles slower here.
-bool sp_gemm_mid_takes(int M, int N, int K) {
-  return M > 48 && M <= 160 && (M > 64 || K > 8192) && N % 128 == 0 && K % MID_KC == 0;
+// Over other widths (one layer, us, k_gemm_bf16 against this one): up to 64 rows it loses in tiles of 96 columns (6144
+// wide, 64 rows 199 / 205) and where the columns leave two slices or one (12288 wide, row-major 534 / 550).  With seven
+// and eight row tiles a launch costs 0.8 us more here, the fold of the waves that share their strips, which slices of one
+// chunk do not earn back (97 rows: 768 wide 60.5 / 62.9, 1024 wide 69.5 / 71.8; with two chunks in QKV alone, 2048 wide,
+// 94.5 / 92.5), nor do two slices of a wide matrix (12288 wide 451 / 470, row-major 605 / 638).  65-96 and 129-160 rows:
+// level (768 wide) to 8 % faster throughout.
+bool sp_gemm_mid_takes(int M, int N, int K, int n_cu) {
+  if (M <= 48 || M > 160 || N % 128 || K % MID_KC) return false;
+  const MidCut cut = mid_cut(M, N, K, n_cu);
+  if (M <= 64) return K > 8192 && cut.cols == 128 && cut.S >= 3;
+  if (M > 96 && M <= 128) return cut.S >= 3 && K / MID_KC >= 2 * (cut.S < 16 ? cut.S : 16);
+  return true;
 }
 bool sp_gemm_mid_takes_gateup(int M, int F, int K, int n_cu) {
   return M > 48 && M <= 160 && K % MID_KC == 0 && n_cu > 0 && F % n_cu == 0 && (F / n_cu) % 8 == 0 && F / n_cu > 48 &&
@@ -253,13 +278,11 @@ bool sp_gemm_mid_takes_gateup(int M, int F, int K, int n_cu) {
 
 hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,
                               int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident) {
-  if (!sp_gemm_mid_takes(M, N, K)) return hipErrorInvalidValue;
-  // 96 columns where those tiles divide the CUs evenly and tiles of 128 do not (N = 6144 on 256 CUs: 64 tiles x 4
-  // slices of equal length instead of 48 x 5 of 6 or 7 chunks)
-  const bool six = N % 96 == 0 && n_cu % (N / 128) != 0 && n_cu % (N / 96) == 0;
-  const int tiles = N / (six ? 96 : 128), chunks = K / MID_KC;
-  // one workgroup per CU: every further slice costs M*N*4 bytes written here and read again by the folding kernel
-  int S = n_cu / tiles;
+  if (!sp_gemm_mid_takes(M, N, K, n_cu)) return hipErrorInvalidValue;
+  const MidCut cut = mid_cut(M, N, K, n_cu);
+  const bool six = cut.cols == 96;
+  const int tiles = N / cut.cols, chunks = K / MID_KC;
+  int S = cut.S;
   if (S > max_split) S = max_split;
   if (S > chunks) S = chunks;
   while (S > 1 && (size_t)S * M * N > part_capacity_floats) --S;
@@ -267,6 +290,7 @@ hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, flo
   if ((size_t)S * M * N > part_capacity_floats) return hipErrorInvalidValue;
   *S_out = S;
   const dim3 grid(tiles, S);
+  if (six && resident) return packed ? launch_plain<6, true, false>(grid, st, X, W, out, M, N, K, S) : launch_plain<6, false, false>(grid, st, X, W, out, M, N, K, S);
   if (six) return packed ? launch_plain<6, true, true>(grid, st, X, W, out, M, N, K, S) : launch_plain<6, false, true>(grid, st, X, W, out, M, N, K, S);
   if (resident) return packed ? launch_plain<8, true, false>(grid, st, X, W, out, M, N, K, S) : launch_plain<8, false, false>(grid, st, X, W, out, M, N, K, S);
   return packed ? launch_plain<8, true, true>(grid, st, X, W, out, M, N, K, S) : launch_plain<8, false, true>(grid, st, X, W, out, M, N, K, S);

@@ -147,7 +147,7 @@ hipError_t sp_launch_few_out(const bf16_t* X, const bf16_t* W, bool packed, cons
                              int N, int K, int n_cu, hipStream_t st);
 // 49-160 rows (sp_gemm_mid.hip): one workgroup per CU, two strips of weight rows per wave; `takes` says for which
 // sizes these are to be called (gate/up: where every CU gets the same 56 or 64 columns)
-bool sp_gemm_mid_takes(int M, int N, int K);
+bool sp_gemm_mid_takes(int M, int N, int K, int n_cu);
 bool sp_gemm_mid_takes_gateup(int M, int F, int K, int n_cu);
 hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,
                               int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident);
