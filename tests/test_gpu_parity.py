@@ -434,7 +434,9 @@ WIDE_BATCHES = {
     "574": {0: (200, 100), 1: (180, 257), 2: (130, 31), 3: (64, 500)},
     # rows 200: blocks of 128, the last with 72 rows
     "200": {0: (120, 90), 1: (80, 300)},
-    # rows 130: blocks of 128, the last with 2 rows
+    # rows 258: blocks of 128, the last with 2 rows
+    "258": {0: (130, 77), 1: (128, 40)},
+    # rows 130: gate/up in blocks of 128, the last with 2 rows (the other products: kernels for 49-160 rows)
     "130": {0: (130, 77)},
 }
 
@@ -924,11 +926,12 @@ def test_c2_full_size_in_bench_configuration():
                          ids=["128_packed", "60_rowmajor", "100_rowmajor", "8_packed", "40_packed", "12_rowmajor"])
 def test_c3_dimensions_one_layer(n_nodes, flags):
     """One layer at the 70B shape (d=8192, 64/8 heads, FFN 28672) with config 3's 128-node tree and
-    prefix 4096: a 128-row block per projection (two strips of 16 weight rows per wave, 64 + 64 gate/up
-    columns per workgroup), 8 query heads per KV head; and with 60 nodes, where the gate/up projection
-    takes the same wide workgroups with four row tiles, the last one ragged; both weight layouts.
-    With 8, 12 and 40 nodes the QKV and O products (K = 8192) run as one or three row tiles whose
-    workgroups walk their k slices from staggered starting chunks (slices of 10-11 and 16 chunks).
+    prefix 4096: eight row tiles per projection (two strips of 16 weight rows per wave, seven waves over
+    the CU's share of the gate/up columns), 8 query heads per KV head; and with 60 nodes, where the gate/up projection
+    takes the same workgroups with four row tiles, the last one ragged; both weight layouts.  With 8 nodes
+    the layer runs in complete projections (two strips per workgroup in O and down); with 12 row-major and
+    40 the QKV and O products (K = 8192) are split, one or three row tiles whose workgroups walk their k
+    slices from staggered starting chunks (slices of 16 to 22 chunks).
     (All ten layers: the full-depth test.)"""
     w = wl.CONFIGS["C3"]
     shape = wl.scaled(w.shape, n_layers=1)
