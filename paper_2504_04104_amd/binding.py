@@ -142,14 +142,12 @@ def load_library(path: Optional[str] = None) -> C.CDLL:
 def _i32(a: Optional[Sequence[int]]):
     if a is None:
         return None, None
-    if type(a) is list and a:
-        # lists of integers, the rule: a third of the time of the way through numpy (64 entries: 6.5 -> 1.9 us), with the
-        # same refusal of values that do not fit; lists of anything else take that way
-        try:
-            buf = array.array("i", a)
-            return buf, (C.c_int32 * len(buf)).from_buffer(buf)
-        except TypeError:
-            pass
+    if type(a) is list and set(map(type, a)) == {int}:
+        # lists of plain integers, the rule: two thirds of the time of the way through numpy (64 entries, 7.0 -> 4.7
+        # us), with the same refusal of values that do not fit.  What else converts, or is refused, is numpy's to
+        # say: array() would take a tensor on a device, waiting for it, and refuse what numpy casts.
+        buf = array.array("i", a)
+        return buf, (C.c_int32 * len(buf)).from_buffer(buf)
     arr = np.ascontiguousarray(np.asarray(a, dtype=np.int32))
     return arr, arr.ctypes.data_as(C.POINTER(C.c_int32))
 

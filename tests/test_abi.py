@@ -3,8 +3,11 @@ and the pure-host entry points behave (no GPU needed)."""
 import ctypes as C
 import os
 import re
+import warnings
 
+import numpy as np
 import pytest
+import torch
 
 import paper_2504_04104_amd as sp
 from paper_2504_04104_amd import binding
@@ -55,3 +58,37 @@ def test_struct_layouts_match_the_header():
     assert binding.sp_tree_view.pred.offset == 8 + 4 * 4 * 256 + 8 * 4 * 256
     assert C.sizeof(binding.sp_head_weights) == 24
     assert C.sizeof(binding.sp_config) == 64
+
+
+class _Elsewhere:
+    """Stands for a tensor on a device: an index to Python (by waiting for it), nothing that numpy converts."""
+
+    def __index__(self):
+        return 3
+
+    def __array__(self, *args, **kwargs):
+        raise TypeError("not in host memory")
+
+
+@pytest.mark.parametrize("values", [[1, 2, 3], [], [True, 2], [np.int64(5), 6], [np.array(2 ** 40)], [1.0, 2], [2 ** 31], [-1],
+                                    [torch.tensor(4)], [torch.tensor([4])], [_Elsewhere()], [1, _Elsewhere()], [None], ["x"],
+                                    (1, 2), np.arange(3), range(4)], ids=repr)
+def test_integer_arguments_convert_as_numpy_does(values):
+    """Lists of plain integers take a way of their own; values, lengths and refusals are those of numpy's conversion."""
+    def outcome(f):
+        try:
+            with warnings.catch_warnings():
+                warnings.simplefilter("error")
+                return f()
+        except Exception as e:
+            return type(e)
+
+    def through_binding():
+        arr, ptr = binding._i32(values)
+        return len(arr), [ptr[k] for k in range(np.asarray(arr).size)]
+
+    def through_numpy():
+        arr = np.ascontiguousarray(np.asarray(values, dtype=np.int32))
+        return len(arr), arr.ravel().tolist()
+
+    assert outcome(through_binding) == outcome(through_numpy)
