@@ -72,7 +72,7 @@ class _Elsewhere:
 
 @pytest.mark.parametrize("values", [[1, 2, 3], [], [True, 2], [np.int64(5), 6], [np.array(2 ** 40)], [1.0, 2], [2 ** 31], [-1],
                                     [torch.tensor(4)], [torch.tensor([4])], [_Elsewhere()], [1, _Elsewhere()], [None], ["x"],
-                                    (1, 2), np.arange(3), range(4)], ids=repr)
+                                    (1, 2), np.arange(3), range(4)])
 def test_integer_arguments_convert_as_numpy_does(values):
     """Lists of plain integers take a way of their own; values, lengths and refusals are those of numpy's conversion."""
     def outcome(f):
