@@ -4,6 +4,8 @@
 // the k range (or the cache slots) between them and have several loads each in flight, and are folded through LDS.
 // Measured on the two-layer d = 256 stage, 16 nodes, context 128 (one thread column per output and one wave per row
 // and head before): products of 256 and 688 k 12.0 and 18.3 -> 4.6 and 4.7 us, attention 27.8 -> 5.5 us.
+#include <type_traits>
+
 #include "sp_launch.h"
 
 #define F_WAVES 8
@@ -181,24 +183,28 @@ __global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, c
       for (int c = 0; c < C; ++c) o[e][c] *= corr;
     __builtin_amdgcn_wave_barrier();
     const int ns = min(64, c1 - s0);
-    for (int j = 0; j < ns; j += 16) {
+    // sixteen V rows; where some are not visible these become zeros (a weight of zero would make NaN of an infinity)
+    auto add16 = [&](int j, auto all_visible) {
       float pv[16], vv[16][C];
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         pv[u] = s_p[wave][j + u];
         const int sl = s_slot[wave][j + u];
-        const float* vp = vplane + (size_t)max(sl, 0) * DH + lane;
+        const float* vp = vplane + (size_t)(all_visible.value ? sl : max(sl, 0)) * DH + lane;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
           const float v = vp[c * 64];
-          vv[u][c] = sl >= 0 ? v : 0.f;              // a weight of zero would make NaN of an infinity
+          vv[u][c] = all_visible.value || sl >= 0 ? v : 0.f;
         }
       }
 #pragma unroll
       for (int u = 0; u < 16; ++u)
 #pragma unroll
         for (int c = 0; c < C; ++c) o[u & 7][c] += pv[u] * vv[u][c];
-    }
+    };
+    int j = 0;
+    for (const int lim = min(c1, ri.P) - s0; j + 16 <= min(ns, lim); j += 16) add16(j, std::true_type{});    // committed context
+    for (; j < ns; j += 16) add16(j, std::false_type{});
     __builtin_amdgcn_wave_barrier();
   }
 #pragma unroll
