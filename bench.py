@@ -29,18 +29,31 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16, published
 
 
-def profiled_traffic():
+def gateup_kernel(n, d_ff, n_cu):
+    """Name of the kernel that runs a packed stage's gate/up projection of n rows on n_cu compute units (the rules of
+    sp_stage_forward, sp_gemm_mid_takes_gateup and sp_launch_gemm_gateup_bf16)."""
+    cols = d_ff // n_cu if d_ff % n_cu == 0 else 0          # columns per compute unit
+    if 49 <= n <= 160 and cols % 8 == 0 and 48 < cols <= 64:
+        return "k_gemm_mid"
+    return "k_gemm_wide" if n > 128 else "k_gemm_bf16"
+
+
+def profiled_traffic(kernel=None, path=os.path.join(ROOT, "profiles", "pmc_hbm_traffic_stage_step_c2.txt")):
     """Bytes per gate/up launch as the rocprofv3 counter runs measured them: the line
-    `bench.roofline.traffic_bytes = <number>` of profiles/pmc_hbm_traffic_stage_step_c2.txt, else None."""
-    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "pmc_hbm_traffic_stage_step_c2.txt")
+    `bench.roofline.traffic_bytes = <number>` of the committed summary.  None without it, and None if the line
+    `bench.roofline.traffic_kernel = <name>` does not name the kernel asked for."""
+    found = {}
     try:
         with open(path) as f:
             for line in f:
-                if line.startswith("bench.roofline.traffic_bytes"):
-                    return float(line.split("=", 1)[1])
-    except (OSError, ValueError):
-        pass
-    return None
+                for key in ("traffic_bytes", "traffic_kernel"):
+                    if line.startswith("bench.roofline.%s " % key):
+                        found[key] = line.split("=", 1)[1].strip()
+        if kernel is not None and found.get("traffic_kernel") != kernel:
+            return None
+        return float(found["traffic_bytes"])
+    except (OSError, ValueError, KeyError):
+        return None
 
 
 def main() -> int:
@@ -177,9 +190,10 @@ def main() -> int:
     achieved = gu_bytes / (gu_us * 1e-6) / 1e9
     # HBM bytes per launch from rocprofv3 PMC runs of this same command (FETCH_SIZE x 2.00 + WRITE_SIZE x 1.00,
     # factors from a 1 GiB copy), read from the committed summary of those runs; it holds the profiled shape
-    # only (C2 at 64 rows), and without the file or its line the field stays null.
-    traffic = profiled_traffic() if (args.workload == "C2" and n == 64) else None
-    roofline = {"bound": "hbm", "kernel": "gemm_gateup (%s GATEUP)" % ("k_gemm_mid" if 49 <= n <= 160 else "k_gemm_bf16"), "achieved": round(achieved, 1),
+    # only (C2 at 64 rows) and the kernel that ran then, and otherwise the field stays null.
+    gu_kernel = gateup_kernel(n, sh.d_ff, torch.cuda.get_device_properties(0).multi_processor_count)
+    traffic = profiled_traffic(gu_kernel) if (args.workload == "C2" and n == 64 and not args.unpacked) else None
+    roofline = {"bound": "hbm", "kernel": "gemm_gateup (%s GATEUP)" % gu_kernel, "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "avg_launch_us": round(gu_us, 2), "launches": n_launch,
                 "bytes_per_launch": gu_bytes}

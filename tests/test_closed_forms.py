@@ -54,3 +54,23 @@ def test_bench_traffic_comes_from_the_profile_summary():
     t = bench.profiled_traffic()
     assert t is not None
     assert algorithmic <= t <= 1.1 * algorithmic
+
+
+def test_bench_traffic_is_that_of_the_kernel_that_runs(tmp_path):
+    """The roofline record names the kernel the library launches, and reports counted bytes only if they were counted on
+    that kernel."""
+    import bench
+    c2, c3 = wl.CONFIGS["C2"].shape, wl.CONFIGS["C3"].shape
+    assert [bench.gateup_kernel(n, c2.d_ff, 256) for n in (16, 48, 49, 64, 160, 161)] == \
+        ["k_gemm_bf16", "k_gemm_bf16", "k_gemm_mid", "k_gemm_mid", "k_gemm_mid", "k_gemm_wide"]
+    # 112 columns per compute unit: not a shape of the kernel for 49-160 rows
+    assert [bench.gateup_kernel(n, c3.d_ff, 256) for n in (64, 128, 129)] == ["k_gemm_bf16", "k_gemm_bf16", "k_gemm_wide"]
+    summary = tmp_path / "summary.txt"
+    summary.write_text("bench.roofline.traffic_bytes = 1000\n")
+    assert bench.profiled_traffic("k_gemm_mid", str(summary)) is None
+    summary.write_text("bench.roofline.traffic_kernel = k_gemm_mid\nbench.roofline.traffic_bytes = 1000\n")
+    assert bench.profiled_traffic("k_gemm_mid", str(summary)) == 1000.0
+    assert bench.profiled_traffic("k_gemm_bf16", str(summary)) is None
+    assert bench.profiled_traffic("k_gemm_mid", str(tmp_path / "none")) is None
+    # the committed summary is of the kernel that runs the profiled shape
+    assert bench.profiled_traffic(bench.gateup_kernel(64, c2.d_ff, 256)) is not None
