@@ -420,7 +420,13 @@ int sp_request_info(const sp_stage* stage, int32_t req, int32_t* prefix_len, int
 /* Per-kernel timing.  After sp_profile_begin(kind), every launch of that kernel
  * kind is bracketed by HIP events on its stream (at most max_launches of them);
  * sp_profile_end waits for the last event and returns the launch count and the sum
- * of their durations. */
+ * of their durations.  A kind counts launches of its own: where work of one kind is
+ * the epilogue of another's kernel it is timed there.  bf16 calls of up to 16 rows
+ * that run complete projections (most shapes; others and longer calls split them)
+ * have no SP_K_ROPE_KV launch and of SP_K_NORM only the one that opens the call;
+ * SP_K_GEMM_QKV then includes RoPE and the cache append, SP_K_GEMM_O and
+ * SP_K_GEMM_DOWN the residual and the next norm's gain.  In float32 SP_K_GEMM_GATEUP
+ * includes SiLU*mul, as in bf16.  SP_K_ATTENTION includes the merge of split ranges. */
 typedef enum sp_kernel_kind {
   SP_K_NONE = 0, SP_K_GEMM_QKV = 1, SP_K_GEMM_O = 2, SP_K_GEMM_GATEUP = 3, SP_K_GEMM_DOWN = 4,
   SP_K_ATTENTION = 5, SP_K_ATTENTION_MERGE = 6, SP_K_KV_COMPACT = 7, SP_K_TREE_PRUNE = 8,

@@ -114,28 +114,29 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   if (c_begin < c_end) {
     SP_LOAD_X(c_begin)
     SP_LOAD_W(0, c_begin)
-    if (PF >= 2 && c_begin + 1 < c_end) { SP_LOAD_W(1 % NB, c_begin + 1) }
-    if (PF >= 3 && c_begin + 2 < c_end) { SP_LOAD_W(2 % NB, c_begin + 2) }
+    if (c_begin + 1 < c_end) { SP_LOAD_W(1, c_begin + 1) }
     SP_STORE_X(0)
     if (c_begin + 1 < c_end) { SP_LOAD_X(c_begin + 1) }
   }
   __syncthreads();
-  constexpr int PERIOD = NB % 2 == 0 ? NB : 2 * NB;      // chunk index modulo this fixes every buffer
-  constexpr int AHEAD = PF > 2 ? PF : 2;                 // furthest chunk a body asks for
+  constexpr int PERIOD = 2 * NB;          // chunk index modulo this fixes every buffer
+  static_assert(PF == 2 && PERIOD == 6, "the loops below are written for two chunks ahead");
   int c = c_begin;
-  for (; c + PERIOD - 1 + AHEAD < c_end; c += PERIOD) {
+  for (; c + PERIOD - 1 + PF < c_end; c += PERIOD) {
     SP_CHUNK(0, c, false)
     SP_CHUNK(1, c + 1, false)
-    if (PERIOD >= 4) { SP_CHUNK(2, c + 2, false) SP_CHUNK(3, c + 3, false) }
-    if (PERIOD >= 6) { SP_CHUNK(4, c + 4, false) SP_CHUNK(5, c + 5, false) }
+    SP_CHUNK(2, c + 2, false)
+    SP_CHUNK(3, c + 3, false)
+    SP_CHUNK(4, c + 4, false)
+    SP_CHUNK(5, c + 5, false)
   }
   for (; c < c_end; c += PERIOD) {
     SP_CHUNK(0, c, true)
     if (c + 1 < c_end) SP_CHUNK(1, c + 1, true)
-    if (PERIOD >= 4 && c + 2 < c_end) SP_CHUNK(2, c + 2, true)
-    if (PERIOD >= 4 && c + 3 < c_end) SP_CHUNK(3, c + 3, true)
-    if (PERIOD >= 6 && c + 4 < c_end) SP_CHUNK(4, c + 4, true)
-    if (PERIOD >= 6 && c + 5 < c_end) SP_CHUNK(5, c + 5, true)
+    if (c + 2 < c_end) SP_CHUNK(2, c + 2, true)
+    if (c + 3 < c_end) SP_CHUNK(3, c + 3, true)
+    if (c + 4 < c_end) SP_CHUNK(4, c + 4, true)
+    if (c + 5 < c_end) SP_CHUNK(5, c + 5, true)
   }
 #undef SP_CHUNK
 #undef SP_PC

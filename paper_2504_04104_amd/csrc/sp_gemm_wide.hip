@@ -1,5 +1,5 @@
-// bf16 projections for many rows (M > 128: a cold ragged batch forwards several hundred tree
-// nodes at once, Sec. 4 "Implementation" / Sec. 4.4).  Here the matrix cores, not the weight
+// bf16 projections for many rows (plain products from 161 rows on, gate/up from 129 or, where sp_gemm_mid.hip takes it,
+// 161: a cold ragged batch forwards several hundred tree nodes at once, Sec. 4 "Implementation" / Sec. 4.4).  Here the matrix cores, not the weight
 // stream, set the pace, so each wave keeps SPW strips of 16 weight rows in registers and every
 // activation fragment it reads from LDS feeds SPW MFMAs.  A workgroup covers up to 16*MT rows x
 // 64*SPW output columns.  Full row blocks come first in launch order, and those of one column

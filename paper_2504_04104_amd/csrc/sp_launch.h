@@ -153,7 +153,7 @@ hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, flo
                               int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident);
 hipError_t sp_launch_gemm_mid_gateup(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F, int K, int n_cu,
                                      hipStream_t st);
-// Many rows (M > 128): workgroups of 128 rows x 256 columns, weights kept in registers per wave.
+// Many rows (more than the kernels above take): workgroups of 128 or 256 rows x 256 columns, weights kept in registers per wave.
 // Needs N % 256 == 0 (gate/up: F % 128 == 0) and K % 64 == 0.
 hipError_t sp_launch_gemm_wide(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int n_cu, size_t part_capacity_floats, int* S_out, hipStream_t st);

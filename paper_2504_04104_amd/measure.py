@@ -2,6 +2,7 @@
 """Timing runs of the other workloads of the stage library (bench.py covers the headline one).
 
     python -m paper_2504_04104_amd.measure --run sweep        # n = 1..256 nodes on the 8B-shaped stage
+    python -m paper_2504_04104_amd.measure --run c1           # float32 two-layer stage, 16 nodes
     python -m paper_2504_04104_amd.measure --run c3           # 70B-shaped 10-layer stage, 128 nodes
     python -m paper_2504_04104_amd.measure --run c4           # streaming, prefix 32768, 1-8 nodes per step
     python -m paper_2504_04104_amd.measure --run c5           # 32 requests, ragged batch
@@ -111,6 +112,27 @@ def run_sweep(args):
             stage.stage_forward([0], [0], [n], x, y)
         out[n] = round(timed(step, 15) * 1e6, 1)
     print(json.dumps({"run": "sweep", "workload": "8B-shaped 4-layer stage, prefix 2048", "us_per_step_by_nodes": out}))
+    stage.close()
+
+
+def run_c1(args):
+    w = wl.CONFIGS["C1"]
+    sh, P, n = w.shape, w.prefix_len, w.n_nodes
+    layers = [sp.pack_layer_weights(wl.layer_weights(sh, w.seed, l), sh.dtype, DEV) for l in range(sh.n_layers)]
+    cap = P + 320
+    stage = sp.Stage(sh, layers, kv_slots=cap, max_batch_nodes=n)
+    stage.kv_view().normal_()
+    par = wl.tree_uniform_parents(w.seed, n, w.max_levels)
+    x = torch.randn(n, sh.d_model, device=DEV)
+    y = torch.empty_like(x)
+
+    def step():
+        stage.request_init(0, 0, cap, P)
+        stage.tree_insert(0, par)
+        stage.stage_forward([0], [0], [n], x, y)
+    t = timed(step, args.steps or 200)
+    print(json.dumps({"run": "c1", "workload": "float32 two-layer stage, d %d, prefix %d, %d nodes" % (sh.d_model, P, n),
+                      "us_per_step": round(t * 1e6, 1)}))
     stage.close()
 
 
@@ -455,13 +477,13 @@ def run_verify(args):
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--page-slots", type=int, default=0, help="c5: keep the cache in pages of this many slots")
-    ap.add_argument("--run", required=True, choices=["sweep", "c3", "c4", "c5", "compact", "verify", "wide", "wide_context"])
+    ap.add_argument("--run", required=True, choices=["c1", "sweep", "c3", "c4", "c5", "compact", "verify", "wide", "wide_context"])
     ap.add_argument("--steps", type=int, default=0)
     ap.add_argument("--prefix", type=int, default=0, help="c4: committed context length (default: the workload's 32768)")
     args = ap.parse_args()
     # a stream of our own: the forward call replays HIP graphs of its launches only on a stream that can be captured
     torch.cuda.set_stream(torch.cuda.Stream(device=DEV))
-    {"sweep": run_sweep, "c3": run_c3, "c4": run_c4, "c5": run_c5, "compact": run_compact, "verify": run_verify, "wide": run_wide, "wide_context": run_wide_context}[args.run](args)
+    {"c1": run_c1, "sweep": run_sweep, "c3": run_c3, "c4": run_c4, "c5": run_c5, "compact": run_compact, "verify": run_verify, "wide": run_wide, "wide_context": run_wide_context}[args.run](args)
 
 
 if __name__ == "__main__":
