@@ -1,8 +1,8 @@
 #!/usr/bin/env python3
 """Stage-step benchmark of the SpecPipe stage library on one MI355X.
 
-A step is one pass of the whole hot path on the 8B-shaped 4-layer stage (BASELINE
-config 2): reset the request to its 2048-token committed context, insert the 64-node
+A step is one pass of the whole hot path on the 8B-shaped 4-layer stage (workload
+C2): reset the request to its 2048-token committed context, insert the 64-node
 tree (sp_tree_insert), run the four decoder layers on those nodes under the tree mask
 (sp_stage_forward), accept one child of the root (sp_tree_prune) and compact the KV
 cache and the in-flight hidden rows (sp_kv_compact).  Inputs are seeded, synthetic and
