@@ -179,6 +179,9 @@ inline hipError_t other_gemm(const sp_stage* s, const void* X, const void* W, fl
   return sp_launch_gemm_simple(s->cfg.dtype, X, W, out, M, N, K, st);
 }
 
+// vocabulary products on the bf16 matrix-core kernels
+inline bool head_on_mfma(const sp_stage* s, int V) { return s->fast && V % 64 == 0 && s->cfg.d_model % 128 == 0; }
+
 // Brackets a launch with events when its kind is being profiled.
 struct ProfScope {
   sp_stage* s;
@@ -706,7 +709,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       const sp_layer_weights& L = s->W[l];
       if (l > 0) {
         ProfScope p(s, SP_K_NORM, st);
-        SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S_prev, strideD, L.norm1, w.xn, M, d, c.rms_eps, st));
+        SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S_prev, strideD, L.norm1, w.xn, s->fast, M, d, c.rms_eps, st));
       }
       int S = 1;
       { ProfScope p(s, SP_K_GEMM_QKV, st);
@@ -728,7 +731,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
         if (s->fast) SP_STEP(gemm(w.attn, L.wo, d, dq, &S, s->o_resident));
         else SP_STEP(other_gemm(s, w.attn, L.wo, w.part, M, d, dq, st)); }
       { ProfScope p(s, SP_K_NORM, st);
-        SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S, strideD, L.norm2, w.xn, M, d, c.rms_eps, st)); }
+        SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S, strideD, L.norm2, w.xn, s->fast, M, d, c.rms_eps, st)); }
       { ProfScope p(s, SP_K_GEMM_GATEUP, st);
         if (s->fast) {
           if (sp_gemm_mid_takes_gateup(M, F, d, s->n_cu)) SP_STEP(sp_launch_gemm_mid_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, st));
@@ -752,7 +755,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
 
   { ProfScope p(s, SP_K_NORM, st);
     SP_TRY(sp_launch_enter_norm(dt, x_in, plan, w.plan, s->d_meta, s->d_tables, w.rows, w.cs, dh,
-                                c.rope_theta, w.h, s->W[0].norm1, w.xn, M, d, c.rms_eps, st)); }
+                                c.rope_theta, w.h, s->W[0].norm1, w.xn, s->fast, M, d, c.rms_eps, st)); }
 
   // A shape that comes back replays its graph; one seen for the second time is captured.  Not while a
   // kernel kind is being timed (the events sit between the launches) and not inside a caller's capture.
@@ -1071,10 +1074,10 @@ static int verify_head_on(sp_stage* s, const HeadScratch& w, const sp_head_weigh
     rows_of.seg_first[i] = b.first[i];
   }
   e = sp_launch_enter_norm(c.dtype, x, rows_of, nullptr, s->d_meta, s->d_tables, w.rows, w.cs, c.d_head, c.rope_theta,
-                           w.h, head->norm, w.xn, M, d, c.rms_eps, st);
+                           w.h, head->norm, w.xn, head_on_mfma(s, V), M, d, c.rms_eps, st);
   if (e != hipSuccess) return hip_fail(s, e);
   ProfScope p(s, SP_K_VERIFY_HEAD, st);
-  if (s->fast && V % 64 == 0 && d % 128 == 0) {
+  if (head_on_mfma(s, V)) {
     int tiles = 0;
     e = sp_launch_gemm_argmax_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, M, V, d,
                                    w.part_floats, &tiles, st);
@@ -1142,10 +1145,10 @@ int sp_stage_verify_lossy(sp_stage* s, const sp_head_weights* head, int32_t n, c
   const size_t logit_floats = (size_t)n * V;
   if (logit_floats + sp_lossy_scratch_floats(n, V) > w.part_floats) return SP_E_CAPACITY;
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, n, d, c.rms_eps, st);
+  hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, head_on_mfma(s, V), n, d, c.rms_eps, st);
   if (e != hipSuccess) return hip_fail(s, e);
   ProfScope p(s, SP_K_VERIFY_HEAD, st);
-  if (s->fast && V % 64 == 0 && d % 128 == 0) {
+  if (head_on_mfma(s, V)) {
     int S = 1;
     e = sp_launch_gemm_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, n, V, d, 1,
                             logit_floats, &S, st);
@@ -1184,13 +1187,13 @@ int sp_stage_verify_sample(sp_stage* s, const sp_head_weights* head, int32_t n, 
   const size_t logit_floats = (size_t)n * V;
   if (logit_floats > w.part_floats) return SP_E_CAPACITY;
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, n, d, c.rms_eps, st);
+  hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, head_on_mfma(s, V), n, d, c.rms_eps, st);
   if (e != hipSuccess) return hip_fail(s, e);
   ProfScope p(s, SP_K_VERIFY_HEAD, st);
   // statistics of the logits' tiles behind them, where the workspace has room; the deciding kernel can do without
   float* stats = nullptr;
   int tile_cols = 0;
-  if (s->fast && V % 64 == 0 && d % 128 == 0) {
+  if (head_on_mfma(s, V)) {
     if (logit_floats + (size_t)n * (V / 64) * 2 <= w.part_floats) {
       stats = w.part + logit_floats;
       e = sp_launch_gemm_logits_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, stats,

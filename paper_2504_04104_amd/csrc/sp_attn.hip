@@ -31,7 +31,7 @@ struct AttnArgs {
   KvGeom g;
   int layer, n_q, n_kv;
   float* part_o;            // [units][DH], followed by [units][2] (running max, sum)
-  bf16_t* out;              // [M][n_q][DH]
+  bf16_t* out;              // rows of n_q * DH columns in fragment order
   const AttnPlan* plan;     // device copy of the call's plan (written by the kernel that opens the forward)
 };
 
@@ -323,13 +323,12 @@ __global__ void __launch_bounds__(64 * AW) k_attn_bf16(AttnArgs a) {
   const int head = kvh * g + gq;
   if (chunks == 1) {
     const float inv = 1.f / lsum;
-    bf16_t* po = a.out + ((size_t)(row0 + nl) * a.n_q + head) * DH;
     u32x4_t pk;
     pk.x = pack_bf16x2(e0[0] * inv, e1[0] * inv);
     pk.y = pack_bf16x2(e0[1] * inv, e1[1] * inv);
     pk.z = pack_bf16x2(e0[2] * inv, e1[2] * inv);
     pk.w = pack_bf16x2(e0[3] * inv, e1[3] * inv);
-    *reinterpret_cast<u32x4_t*>(po + G * 32 + 8 * kg) = pk;
+    *reinterpret_cast<u32x4_t*>(a.out + frag_at(row0 + nl, head * DH + G * 32 + 8 * kg, a.n_q * DH)) = pk;
   } else {
     const size_t unit = (size_t)sg_unit0 + (size_t)ch * seg_rows * a.n_q + (size_t)nl * a.n_q + head;
     float* po = a.part_o + unit * DH;
@@ -356,9 +355,11 @@ __global__ void __launch_bounds__(256) k_attn_merge(AttnArgs a, int M) {
   const int n_seg = plan.n_seg;
   const float* part_ml = a.part_o + (size_t)plan.units_total * DH;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int item = blockIdx.x * 4 + wave;
-  if (item >= M * a.n_q) return;
-  const int row = item / a.n_q, head = item - row * a.n_q;
+  // a workgroup takes four rows of a head; the two that fill the output's 128-byte lines (eight rows in fragment order)
+  // run on the same XCD, whose L2 puts the lines together
+  const int pair = (blockIdx.x >> 4) * 8 + (blockIdx.x & 7), row8 = pair / a.n_q, head = pair - row8 * a.n_q;
+  const int row = row8 * 8 + ((blockIdx.x >> 3) & 1) * 4 + wave;
+  if (row >= M) return;
   int seg = 0;
   while (seg + 1 < n_seg && row >= plan.seg_row0[seg + 1]) ++seg;
   if (seg != 0) {
@@ -392,7 +393,8 @@ __global__ void __launch_bounds__(256) k_attn_merge(AttnArgs a, int M) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const float* po = a.part_o + (u0 + (size_t)(c0 + j + i) * stride) * DH;
-        o0[i] = po[lane]; o1[i] = po[64 + lane];
+        const float2 v = *reinterpret_cast<const float2*>(po + 2 * lane);
+        o0[i] = v.x; o1[i] = v.y;
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -406,21 +408,20 @@ __global__ void __launch_bounds__(256) k_attn_merge(AttnArgs a, int M) {
       for (int i = 0; i < 4; ++i) {
         w4[i] = __shfl(wgt, j + i, 64);
         const float* po = a.part_o + (u0 + (size_t)(c0 + j + i) * stride) * DH;
-        o0[i] = po[lane]; o1[i] = po[64 + lane];
+        const float2 v = *reinterpret_cast<const float2*>(po + 2 * lane);
+        o0[i] = v.x; o1[i] = v.y;
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) { acc0 += w4[i] * o0[i]; acc1 += w4[i] * o1[i]; }
     }
     for (; j < nb; ++j) {
       const float w1 = __shfl(wgt, j, 64);
-      const float* po = a.part_o + (u0 + (size_t)(c0 + j) * stride) * DH;
-      acc0 += w1 * po[lane]; acc1 += w1 * po[64 + lane];
+      const float2 v = *reinterpret_cast<const float2*>(a.part_o + (u0 + (size_t)(c0 + j) * stride) * DH + 2 * lane);
+      acc0 += w1 * v.x; acc1 += w1 * v.y;
     }
   }
   const float inv = 1.f / lsum;
-  bf16_t* po = a.out + ((size_t)row * a.n_q + head) * DH;
-  po[lane] = f32_to_bf16(acc0 * inv);
-  po[64 + lane] = f32_to_bf16(acc1 * inv);
+  *reinterpret_cast<uint32_t*>(a.out + frag_at(row, head * DH + 2 * lane, a.n_q * DH)) = pack_bf16x2(acc0 * inv, acc1 * inv);
 }
 
 hipError_t sp_launch_attn_bf16(const bf16_t* q, const ReqTables* tables, KvGeom g, int layer, const AttnPlan& plan,
@@ -448,6 +449,6 @@ hipError_t sp_launch_attn_bf16(const bf16_t* q, const ReqTables* tables, KvGeom 
 #undef SP_ATTN_GO
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !plan.any_split) return e;
-  hipLaunchKernelGGL(k_attn_merge, dim3((M * n_q + 3) / 4), dim3(256), 0, st, a, M);
+  hipLaunchKernelGGL(k_attn_merge, dim3(((M + 7) / 8 * n_q + 7) / 8 * 16), dim3(256), 0, st, a, M);
   return hipGetLastError();
 }

@@ -119,6 +119,38 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) { return (bf16_t)(pack_bf
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
+// Activations between the bf16 matrix-core kernels lie in fragment order: per 16 rows and 32 columns one block of 1 KB,
+// lane-major as v_mfma_f32_16x16x32_bf16 takes its operands (lane l: row l % 16, columns (l / 16) * 8 .. + 7).  Every
+// workgroup of a projection reads all of its input rows out of L2, and a load instruction that covers 1 KB of consecutive
+// addresses gets 120 GB/s per CU from there (31 TB/s over the chip), one that covers 128 bytes of each of eight rows of
+// 8 KB 78, and one that covers 64 bytes of each of sixteen rows 38 (256 workgroups of eight waves that read 0.5 to 18 MB
+// in step).  Element index of (row m, column k) in rows of K columns:
+__device__ __forceinline__ size_t frag_at(int m, int k, int K) {
+  return ((size_t)(m >> 4) * (K >> 5) + (k >> 5)) * 512 + (((k >> 3) & 3) * 16 + (m & 15)) * 8 + (k & 7);
+}
+
+// A buffer over `p` for raw buffer loads: 2 GB long, or, where `on` is false, empty (its loads return zeros without a
+// memory access, so that a loop's loads need no branch around them past the end).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p, bool on) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, on ? 0x7fffffff : 0, 0x00020000);
+}
+// 16 bytes per lane straight from memory to LDS: lane l's go to l * 16 bytes behind `dst`, which is the same in all lanes.
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buf, char* dst, int lane_offset, int offset) {
+#ifdef __HIP_DEVICE_COMPILE__      // (the host pass of the compiler does not know the builtin)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)dst, 16, lane_offset, offset, 0, 0);
+#endif
+}
+// Waits until at most n of the wave's vector memory accesses are outstanding.
+#define SP_WAIT_VMEM(n) __builtin_amdgcn_s_waitcnt(0x0f70 | ((n) & 15) | (((n) >> 4) << 14))
+// A barrier that waits for no memory access: what has to have arrived is waited for explicitly.  The compiler moves no
+// memory access across it.
+__device__ __forceinline__ void bare_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // max / sum over the four lanes l, l^16, l^32, l^48 (the lanes that share an MFMA column)
 __device__ __forceinline__ float quad_rows_max(float v) {
   auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);

@@ -99,13 +99,18 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   constexpr int KSTEPS = (KC / 32) / NKH;
   constexpr int NW = (GATEUP || TWO) ? 2 : 1;
   constexpr int ROWS = MT * 16;
-  constexpr int XS = KC * 2 + 16;         // LDS row stride in bytes (conflict-free 16-byte reads)
-  constexpr int UPR = KC / 8;             // 16-byte units per X row chunk
-  constexpr int RPP = NTH / UPR;          // rows per staging pass
-  constexpr int PASSES = (ROWS + RPP - 1) / RPP;   // the last pass may cover fewer rows (48 rows, 32 per pass)
-  constexpr bool RAGGED_PASS = ROWS % RPP != 0;
+  constexpr int UPT = KC * 2;             // 16-byte units of a row tile's chunk (KC / 32 fragment blocks, consecutive in X)
+  constexpr int UNITS = MT * UPT;
+  constexpr int PASSES = (UNITS + NTH - 1) / NTH;  // the last staging pass may cover fewer units
+  constexpr bool RAGGED_PASS = UNITS % NTH != 0;
   constexpr int NB = PF + 1;              // weight register buffers
-  __shared__ __attribute__((aligned(16))) char lds[2][ROWS * XS];
+  // two panels in fragment order, as X: the fragment reads are conflict-free without padding.  Plain products of eight
+  // row tiles put their rows together here at the end.
+  constexpr int WCOLS = 16 * NCG * (TWO ? 2 : 1);
+  constexpr int LSF = WCOLS + 4;                        // floats per row of those
+  constexpr int OUT_BYTES = MT == 8 && !GATEUP && !ARGMAX ? ROWS * LSF * 4 : 0;
+  constexpr int LDS_BYTES = 2 * UNITS * 16 > OUT_BYTES ? 2 * UNITS * 16 : OUT_BYTES;
+  __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int cg = wave % NCG, kh = wave / NCG;
@@ -137,9 +142,13 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   const int c_n = c_end - c_begin;
   const int c_rot = rot && c_n > 1 ? (int)((blockIdx.x >> 3) % (unsigned)c_n) : 0;
 #define SP_PC(C) ((C) + c_rot < c_end ? (C) + c_rot : (C) + c_rot - c_n)
-  const int xu = tid % UPR, xr = tid / UPR;
-  // rows past M are read from the last valid row and multiply into output rows that are never stored
-  const int m_last = M - 1;
+  // row tiles past the last one repeat it; what they and the last tile's rows past M multiply is never stored
+  unsigned xo[PASSES];
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p) {
+    const int u = p * NTH + tid;
+    xo[p] = (unsigned)min(blockIdx.z * MT + u / UPT, (M - 1) >> 4) * (unsigned)(K * 16) + (u % UPT) * 8;
+  }
 
   u32x4_t wb[NB][NW][KSTEPS];
   u32x4_t xnxt[PASSES];
@@ -151,13 +160,12 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 
 #define SP_LOAD_X(C)                                                                                   \
   _Pragma("unroll") for (int p = 0; p < PASSES; ++p) {                                                  \
-    const int m = min(m_base + p * RPP + xr, m_last);                                                   \
-    xnxt[p] = *reinterpret_cast<const u32x4_t*>(X + (size_t)m * K + (size_t)SP_PC(C) * KC + xu * 8);     \
+    xnxt[p] = *reinterpret_cast<const u32x4_t*>(X + (size_t)SP_PC(C) * (KC * 16) + xo[p]);               \
   }
 #define SP_STORE_X(BUF)                                                                                 \
   _Pragma("unroll") for (int p = 0; p < PASSES; ++p)                                                    \
-      if (!RAGGED_PASS || p * RPP + xr < ROWS)                                                          \
-        *reinterpret_cast<u32x4_t*>(&lds[BUF][(p * RPP + xr) * XS + xu * 16]) = xnxt[p];
+      if (!RAGGED_PASS || p * NTH + tid < UNITS)                                                        \
+        *reinterpret_cast<u32x4_t*>(&lds[((BUF) * UNITS + p * NTH + tid) * 16]) = xnxt[p];
   // Every weight is read once per launch: the loads carry the non-temporal hint (WNT), so the stream does not
   // push the activation panel (which every workgroup re-reads) out of L2 nor fill the Infinity Cache
   // (gate/up at 8 rows: 43.4 -> 38.8 us, at 64 rows: 50.7 -> 49.5 us).  The exception is a matrix the caller
@@ -186,7 +194,7 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
     _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s) {                                                \
       _Pragma("unroll") for (int mt = 0; mt < MT; ++mt) {                                               \
         const bf16x8_t b = *reinterpret_cast<const bf16x8_t*>(                                          \
-            &lds[buf][(mt * 16 + r) * XS + ((kh * KSTEPS + s) * 32 + kg * 8) * 2]);                     \
+            &lds[(buf * UNITS + (mt * (KC / 32) + kh * KSTEPS + s) * 64 + lane) * 16]);                 \
         _Pragma("unroll") for (int a = 0; a < NW; ++a) acc[a][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16( \
             *reinterpret_cast<const bf16x8_t*>(&wb[B][a][s]), b, acc[a][mt], 0, 0, 0);                  \
       }                                                                                                 \
@@ -221,11 +229,11 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 #undef SP_PC
 #undef SP_WOFF
 
-  float* s_tot = reinterpret_cast<float*>(&lds[0][0]) + (sizeof(lds) / 4 - 16);      // behind the fold's floats
+  float* s_tot = reinterpret_cast<float*>(lds) + (sizeof(lds) / 4 - 16);      // behind the fold's floats
   if (SCALED && ssq) sq.post(ssq, K / 16, M, s_tot);
   if (NKH == 2) {       // fold the two k-halves of a column group together through LDS
     static_assert(!SCALED || (NCG * NW * MT * 64 * 4 + 16) * 4 <= (int)sizeof(lds), "fold and row sums side by side");
-    float* red = reinterpret_cast<float*>(&lds[0][0]);
+    float* red = reinterpret_cast<float*>(lds);
     if (kh == 1) {
 #pragma unroll
       for (int a = 0; a < NW; ++a)
@@ -247,7 +255,7 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   if (EVEN && 4 * kg >= vr) return;       // columns past a short last group
   if (ARGMAX) {
     static_assert(!ARGMAX || (NKH == 1 && !GATEUP), "one wave per column group");
-    float* s_val = reinterpret_cast<float*>(&lds[0][0]);          // [NCG][ROWS]; the panels are no longer read
+    float* s_val = reinterpret_cast<float*>(lds);          // [NCG][ROWS]; the panels are no longer read
     int* s_idx = reinterpret_cast<int*>(s_val + NCG * ROWS);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -280,7 +288,7 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   }
   if (STATS) {
     static_assert(!STATS || (NKH == 1 && !GATEUP && !ARGMAX), "one wave per column group");
-    float* s_mx = reinterpret_cast<float*>(&lds[0][0]);           // [NCG][ROWS]; the panels are no longer read
+    float* s_mx = reinterpret_cast<float*>(lds);           // [NCG][ROWS]; the panels are no longer read
     float* s_z = s_mx + NCG * ROWS;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -312,10 +320,7 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
     // together in LDS (the panels are no longer read: every wave has passed the barrier that ends its last chunk), and a
     // store instruction then writes 1 KB of consecutive addresses instead of 64 bytes in each of 16 rows.
     static_assert(NKH == 1 || GATEUP, "plain products: one wave per column group");
-    constexpr int WCOLS = 16 * NCG * (TWO ? 2 : 1);
-    constexpr int LSF = WCOLS + 4;                        // floats per LDS row
-    static_assert(MT != 8 || ROWS * LSF * 4 <= (int)sizeof(lds), "the row tile fits the panels' LDS");
-    float* tile = reinterpret_cast<float*>(&lds[0][0]);
+    float* tile = reinterpret_cast<float*>(lds);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -353,7 +358,7 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
       uint2 pk;
       pk.x = pack_bf16x2(o[0], o[1]);
       pk.y = pack_bf16x2(o[2], o[3]);
-      *reinterpret_cast<uint2*>(act + (size_t)m * N + ncol) = pk;
+      *reinterpret_cast<uint2*>(act + frag_at(m, ncol, N)) = pk;
     } else {
       float* o = out + ((size_t)blockIdx.y * M + m) * N + ncol;
       *reinterpret_cast<f32x4_t*>(o) = acc[0][mt];

@@ -31,7 +31,7 @@
 #define FEW_OUT 2          // residual of the last layer: the rows leave the stage
 
 struct FewArgs {
-  const bf16_t* X;         // [M][K]
+  const bf16_t* X;         // [M][K] in fragment order
   const bf16_t* W;         // [N][K], row-major or in fragment order
   int M, N, K;
   const float* ssq_in;     // [M][K / 16] sums of squares of the rows behind X (nullptr: X is normalised already)
@@ -45,7 +45,7 @@ struct FewArgs {
   // O, down
   float* h;                // [M][N]
   const bf16_t* gain;      // [N] gain of the norm that follows
-  bf16_t* xn;              // [M][N]
+  bf16_t* xn;              // [M][N] in fragment order
   float* ssq_out;          // [M][N / 16]
   const AttnPlan* plan;    // FEW_OUT: x_out
 };
@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
   const int b = blockIdx.x * NS + (wave < NS ? wave : 0), head = b >> 3, t0 = (b & 7) * 8;
   constexpr int WSTEP = PACKED ? 512 : 32;
   // rows past M repeat the last row and multiply into output rows that are never stored
-  const bf16_t* x = a.X + (size_t)min(r, M - 1) * K + (size_t)wave * n * 32 + kg * 8;
+  const bf16_t* x = a.X + (size_t)wave * n * 512 + (kg * 16 + min(r, M - 1)) * 8;
   u32x4_t wf[NS][D], xf[D];
   f32x4_t acc[NS];
 #pragma unroll
@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
       const u32x4_t* wp_ = reinterpret_cast<const u32x4_t*>(w[i] + (size_t)p_ * WSTEP);                 \
       wf[i][j] = WNT ? __builtin_nontemporal_load(wp_) : *wp_;                                  \
     }                                                                                           \
-    xf[j] = *reinterpret_cast<const u32x4_t*>(x + p_ * 32);                                    \
+    xf[j] = *reinterpret_cast<const u32x4_t*>(x + (size_t)p_ * 512);                           \
   }
 #define SP_MM(j)                                                                                \
   _Pragma("unroll") for (int i = 0; i < NS; ++i)                                                \
@@ -173,7 +173,7 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
     *reinterpret_cast<f32x4_t*>(a.h + (size_t)r * a.N + col) = y;
     pk.x = pack_bf16x2(y[0] * bf16_lo(gn.x), y[1] * bf16_hi(gn.x));
     pk.y = pack_bf16x2(y[2] * bf16_lo(gn.y), y[3] * bf16_hi(gn.y));
-    *reinterpret_cast<uint2*>(a.xn + (size_t)r * a.N + col) = pk;
+    *reinterpret_cast<uint2*>(a.xn + frag_at(r, col, a.N)) = pk;
   }
 }
 

@@ -15,64 +15,39 @@
 //   gate/up:      act[m][f] = silu(X Wg^T) * (X Wu^T)
 #include "sp_launch.h"
 
-#define MID_KC 128                       // k per staged chunk
-#define MID_XS (MID_KC * 2 + 16)         // LDS row stride of a panel in bytes (conflict-free 16-byte reads)
+#define MID_NS 2                         // strips of 16 weight rows per wave
+#define MID_NPR 2                        // waves that bring the panels in
+#define MID_KC 128                       // slices of plain products are cut between blocks of this many k
 
-template <int MT, int NSTRIPS, bool GATEUP, bool PACKED, bool WNT>
-__global__ void __launch_bounds__(64 * NSTRIPS)
+// MT row tiles; CW waves side by side, KQ that share their strips and cut a chunk's k steps between them; chunks of KC k;
+// activation panels D chunks ahead, weights PF chunks ahead; NPR waves that bring the panels in.
+template <int MT, int CW, int KQ, bool GATEUP, bool PACKED, bool WNT, int KC, int D, int PF, int NPR>
+__global__ void __launch_bounds__(64 * (CW * KQ + NPR))
 k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
            bf16_t* __restrict__ act, int M, int N, int K, int S, int cpw) {
-  constexpr int NS = 2;                   // strips per wave; as many waves share them and split the k steps
-  constexpr int NTH = 64 * NSTRIPS;
-  constexpr int CW = NSTRIPS / NS;        // waves side by side
-  constexpr int KSTEPS = 4 / NS;          // of the chunk's four
+  constexpr int NS = MID_NS;
+  constexpr int NMM = CW * KQ, NTH = 64 * (NMM + NPR);  // waves that multiply, threads
+  constexpr int CS = KC / 32, KSTEPS = CS / KQ;         // k steps of a chunk, and of a wave in it
   constexpr int ROWS = MT * 16;
-  constexpr int UPR = MID_KC / 8, RPP = NTH / UPR, PASSES = (ROWS + RPP - 1) / RPP;
-  constexpr bool RAGGED = ROWS % RPP != 0;              // the last staging pass covers fewer rows
-  constexpr int PF = 2;                   // weight chunks in flight ahead of the math (three: 1-3 % slower)
-  constexpr int NB = PF + 1;              // weight register buffers
-  __shared__ __attribute__((aligned(16))) char lds[2][ROWS * MID_XS];
+  constexpr int BLOCKS = MT * CS, NX = BLOCKS / NPR;    // 1 KB fragment blocks of a panel, and of a loading wave in it
+  constexpr int PANEL = BLOCKS * 1024;
+  constexpr int NP = D + 1, NB = PF + 1;                // panels, weight register buffers
+  constexpr int OT = (MT + KQ - 1) / KQ;                // row tiles a wave finishes
+  constexpr int FOLD_BYTES = KQ > 1 ? NMM * OT * 1024 : 0;
+  constexpr int WCOLS = 16 * NS * CW, LSF = WCOLS + 4;  // columns, and floats per LDS row of the plain products
+  constexpr int OUT_BYTES = GATEUP ? 0 : ROWS * LSF * 4;
+  constexpr int END_BYTES = FOLD_BYTES > OUT_BYTES ? FOLD_BYTES : OUT_BYTES;
+  static_assert(BLOCKS % NPR == 0 && CS % KQ == 0 && KQ <= 2 && (D - 1) * NX < 64 && PF >= 1 && PF <= 3, "shape of the pipeline");
+  __shared__ __attribute__((aligned(16))) char lds[NP * PANEL > END_BYTES ? NP * PANEL : END_BYTES];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int cw = wave % CW, kq = wave / CW;
+  const int cw = wave % CW, kq = wave / CW;             // (kq == KQ and beyond: loading waves)
+  const bool mm = wave < NMM;
   const int r = lane & 15, kg = lane >> 4;
-  const int chunks = K / MID_KC;
+  const int chunks = K / KC;
   const int c_begin = (int)(((long long)blockIdx.y * chunks) / S);
   const int c_end = (int)(((long long)(blockIdx.y + 1) * chunks) / S);
-
-  // strip a of this wave: plain, strip cw * NS + a; gate/up, the first half of a wave's strips are gate strips and the
-  // second half the up strips of the same columns
-  constexpr int GS = GATEUP ? NS / 2 : NS;
-  const int col0 = GATEUP ? blockIdx.x * cpw + cw * GS * 16 : blockIdx.x * (16 * NSTRIPS) + cw * NS * 16;
-  // addresses as a uniform base per strip and a 32-bit offset per lane (elements), which up and gate strip share
-  const bf16_t* w[NS];
-  unsigned wl[GS];
-#pragma unroll
-  for (int a = 0; a < NS; ++a) {
-    const int row0 = (GATEUP && a >= GS ? N : 0) + col0 + (a % GS) * 16;
-    w[a] = PACKED ? W + ((size_t)(row0 >> 4) * (K / 32) + kq * KSTEPS) * 512 : W + (size_t)row0 * K + kq * (KSTEPS * 32);
-  }
-#pragma unroll
-  for (int g = 0; g < GS; ++g) {
-    // a short last group re-reads its last row; its surplus products are dropped at the end
-    const int rr = GATEUP ? min(r, cpw - (cw * GS + g) * 16 - 1) : r;
-    const int in = (col0 & 15) + rr;      // row inside the strip's first fragment block, or in the one after it
-    wl[g] = PACKED ? (unsigned)((in >> 4) * (K / 32) * 512 + (kg * 16 + (in & 15)) * 8) : (unsigned)(rr * K + kg * 8);
-  }
-  const int xu = tid % UPR, xr = tid / UPR;
-  unsigned xo[PASSES];                    // rows past M repeat the last row and multiply into rows that are never stored
-#pragma unroll
-  for (int p = 0; p < PASSES; ++p) xo[p] = (unsigned)(min(p * RPP + xr, M - 1) * K + xu * 8);
-
-  u32x4_t wb[NB][NS][KSTEPS];
-  u32x4_t xb[PASSES];
-  f32x4_t acc[NS][MT];
-#pragma unroll
-  for (int a = 0; a < NS; ++a)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[a][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-
   const int c_n = c_end - c_begin;
   // Staggered starting chunks where the rows that the workgroups stream lie a multiple of 8 KB apart and would be at the
   // same offset of it at the same moment: gate/up over row-major weights (8B shape 64 rows 58.8 -> 54.3 us, 145 rows 75.6
@@ -82,95 +57,131 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   const bool stagger = GATEUP ? !PACKED : K > 4096 && K <= 8192;
   const int rot = stagger && c_n > 1 ? (int)((blockIdx.x >> 3) % (unsigned)c_n) : 0;
 #define SP_PC(C) ((GATEUP && PACKED) || (C) + rot < c_end ? (C) + rot : (C) + rot - c_n)
-#define SP_LOAD_X(C)                                                                                    \
-  _Pragma("unroll") for (int p = 0; p < PASSES; ++p)                                                    \
-      xb[p] = *reinterpret_cast<const u32x4_t*>(X + (size_t)SP_PC(C)*MID_KC + xo[p]);
-#define SP_STORE_X(BUF)                                                                                 \
-  _Pragma("unroll") for (int p = 0; p < PASSES; ++p)                                                    \
-      if (!RAGGED || p * RPP + xr < ROWS)                                                               \
-        *reinterpret_cast<u32x4_t*>(&lds[BUF][(p * RPP + xr) * MID_XS + xu * 16]) = xb[p];
-#define SP_LOAD_W(B, C)                                                                                 \
-  _Pragma("unroll") for (int a = 0; a < NS; ++a) _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s) {   \
-    const u32x4_t* p_ = reinterpret_cast<const u32x4_t*>(                                               \
-        w[a] + (PACKED ? ((size_t)SP_PC(C)*4 + s) * 512 : (size_t)SP_PC(C)*MID_KC + s * 32) + wl[a % GS]);        \
-    wb[B][a][s] = WNT ? __builtin_nontemporal_load(p_) : *p_;                                           \
-  }
-  // Chunk C, weights in register set I % NB, activations in panel I & 1: the next panel goes from registers to LDS,
-  // the loads of panel C+2 and of weight chunk C+PF are issued, and the chunk is multiplied.  G: guarded (last chunks).
-#define SP_CHUNK(I, C, G)                                                                               \
-  {                                                                                                     \
-    const int c_ = (C);                                                                                 \
-    if (!(G) || c_ + 1 < c_end) { SP_STORE_X(((I) & 1) ^ 1) }                                           \
-    if (!(G) || c_ + 2 < c_end) { SP_LOAD_X(c_ + 2) }                                                   \
-    if (!(G) || c_ + PF < c_end) { SP_LOAD_W(((I) + PF) % NB, c_ + PF) }                                \
-    _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s) _Pragma("unroll") for (int mt = 0; mt < MT; ++mt) { \
-      const bf16x8_t b = *reinterpret_cast<const bf16x8_t*>(                                            \
-          &lds[(I) & 1][(mt * 16 + r) * MID_XS + ((kq * KSTEPS + s) * 32 + kg * 8) * 2]);               \
-      _Pragma("unroll") for (int a = 0; a < NS; ++a) acc[a][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16( \
-          *reinterpret_cast<const bf16x8_t*>(&wb[(I) % NB][a][s]), b, acc[a][mt], 0, 0, 0);             \
-    }                                                                                                   \
-    __syncthreads();                                                                                    \
-  }
-  if (c_begin < c_end) {
-    SP_LOAD_X(c_begin)
-    SP_LOAD_W(0, c_begin)
-    if (c_begin + 1 < c_end) { SP_LOAD_W(1, c_begin + 1) }
-    SP_STORE_X(0)
-    if (c_begin + 1 < c_end) { SP_LOAD_X(c_begin + 1) }
-  }
-  __syncthreads();
-  constexpr int PERIOD = 2 * NB;          // chunk index modulo this fixes every buffer
-  static_assert(PF == 2 && PERIOD == 6, "the loops below are written for two chunks ahead");
-  int c = c_begin;
-  for (; c + PERIOD - 1 + PF < c_end; c += PERIOD) {
-    SP_CHUNK(0, c, false)
-    SP_CHUNK(1, c + 1, false)
-    SP_CHUNK(2, c + 2, false)
-    SP_CHUNK(3, c + 3, false)
-    SP_CHUNK(4, c + 4, false)
-    SP_CHUNK(5, c + 5, false)
-  }
-  for (; c < c_end; c += PERIOD) {
-    SP_CHUNK(0, c, true)
-    if (c + 1 < c_end) SP_CHUNK(1, c + 1, true)
-    if (c + 2 < c_end) SP_CHUNK(2, c + 2, true)
-    if (c + 3 < c_end) SP_CHUNK(3, c + 3, true)
-    if (c + 4 < c_end) SP_CHUNK(4, c + 4, true)
-    if (c + 5 < c_end) SP_CHUNK(5, c + 5, true)
-  }
-#undef SP_CHUNK
-#undef SP_PC
-#undef SP_LOAD_W
-#undef SP_STORE_X
-#undef SP_LOAD_X
 
-  // Fold the NS waves that share their strips: strip by strip, every wave leaves the row tiles that are not its own
-  // (tile mt belongs to wave mt % NS of the sharers) and adds the other waves' products of its own tiles, in order.
-  f32x4_t* fold = reinterpret_cast<f32x4_t*>(&lds[0][0]);           // [waves][MT][64 lanes]
-  static_assert(NSTRIPS * MT * 64 * 16 <= (int)sizeof(lds), "one strip of every wave fits the panels");
+  // strip a of a wave: plain, strip cw * NS + a; gate/up, a gate strip and the up strip of the same columns
+  constexpr int GS = GATEUP ? NS / 2 : NS;
+  const int col0 = GATEUP ? blockIdx.x * cpw + cw * GS * 16 : blockIdx.x * WCOLS + cw * NS * 16;
+  f32x4_t acc[NS][MT];
 #pragma unroll
-  for (int a = 0; a < NS; ++a) {
-    if (a > 0) __syncthreads();           // (the last chunk ended with a barrier)
+  for (int a = 0; a < NS; ++a)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-      if (mt % NS != kq) fold[(wave * MT + mt) * 64 + lane] = acc[a][mt];
-    __syncthreads();
+    for (int mt = 0; mt < MT; ++mt) acc[a][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+
+  // One barrier per chunk.  Behind that of chunk C, panel C is complete and nobody reads panel C - 1 any more, whose
+  // place panel C + D takes.  Loads past the last chunk go to an empty buffer: they cost an issue slot and keep every
+  // chunk's wait the same.
+  if (!mm) {
+    const int pr = wave - NMM;
+    const int lane16 = lane * 16;
+    int xo[NX];                           // row tiles past the last one repeat it and multiply into rows that are never stored
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      if (mt % NS != kq) continue;
-      f32x4_t t = {0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NX; ++j) {
+      const int b = pr * NX + j;
+      xo[j] = min(b / CS, (M - 1) >> 4) * (K * 32) + (b % CS) * 1024;
+    }
+    int pan = pr * NX * 1024;
+    auto load_x = [&](int c) {
+      const auto buf = buffer_at(X, c < c_end);
+      const int pc = SP_PC(c) * (KC * 32);
 #pragma unroll
-      for (int q = 0; q < NS; ++q) t += q == kq ? acc[a][mt] : fold[((q * CW + cw) * MT + mt) * 64 + lane];
-      acc[a][mt] = t;
+      for (int j = 0; j < NX; ++j) load_to_lds(buf, lds + pan + j * 1024, lane16, pc + xo[j]);
+      pan += PANEL;
+      if (pan >= NP * PANEL) pan -= NP * PANEL;
+    };
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_x(c_begin + i);
+    for (int c = c_begin; c < c_end; ++c) {
+      SP_WAIT_VMEM((D - 1) * NX);
+      bare_barrier();
+      load_x(c + D);
+    }
+    SP_WAIT_VMEM(0);
+  } else {
+    // addresses as a uniform base per strip and an offset per lane (bytes), which up and gate strip share
+    const bf16_t* w[NS];
+    int wl[GS];
+#pragma unroll
+    for (int a = 0; a < NS; ++a) {
+      const int row0 = (GATEUP && a >= GS ? N : 0) + col0 + (a % GS) * 16;
+      w[a] = PACKED ? W + ((size_t)(row0 >> 4) * (K / 32) + kq * KSTEPS) * 512 : W + (size_t)row0 * K + kq * (KSTEPS * 32);
+    }
+#pragma unroll
+    for (int g = 0; g < GS; ++g) {
+      // a short last group re-reads its last row; its surplus products are dropped at the end
+      const int rr = GATEUP ? min(r, cpw - (cw * GS + g) * 16 - 1) : r;
+      const int in = (col0 & 15) + rr;    // row inside the strip's first fragment block, or in the one after it
+      wl[g] = PACKED ? (in >> 4) * (K * 32) + (kg * 16 + (in & 15)) * 16 : (rr * K + kg * 8) * 2;
+    }
+    u32x4_t wb[NB][NS][KSTEPS];
+#define SP_LOAD_W(B, C)                                                                                 \
+  {                                                                                                     \
+    const bool on_ = (C) < c_end;                                                                       \
+    const int pc_ = SP_PC(C);                                                                           \
+    _Pragma("unroll") for (int a = 0; a < NS; ++a) {                                                    \
+      const auto buf_ = buffer_at(w[a], on_);                                                           \
+      _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s)                                                \
+        wb[B][a][s] = __builtin_amdgcn_raw_buffer_load_b128(                                            \
+            buf_, wl[a % GS], PACKED ? (pc_ * CS + s) * 1024 : (pc_ * KC + s * 32) * 2, WNT ? 2 : 0);   \
+    }                                                                                                   \
+    __builtin_amdgcn_sched_barrier(0);                                                                  \
+  }
+    int pan = lane * 16;
+#define SP_CHUNK(B, C)                                                                                  \
+  if ((C) < c_end) {                                                                                    \
+    bare_barrier();                                                                                     \
+    SP_LOAD_W(((B) + PF) % NB, (C) + PF)                                                                \
+    _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s) _Pragma("unroll") for (int mt = 0; mt < MT; ++mt) { \
+      const bf16x8_t b = *reinterpret_cast<const bf16x8_t*>(lds + pan + (mt * CS + kq * KSTEPS + s) * 1024); \
+      _Pragma("unroll") for (int a = 0; a < NS; ++a) acc[a][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16( \
+          *reinterpret_cast<const bf16x8_t*>(&wb[B][a][s]), b, acc[a][mt], 0, 0, 0);                    \
+    }                                                                                                   \
+    pan = pan + PANEL >= NP * PANEL ? pan + PANEL - NP * PANEL : pan + PANEL;                           \
+    __builtin_amdgcn_sched_barrier(0);                                                                  \
+  }
+#pragma unroll
+    for (int i = 0; i < PF; ++i) SP_LOAD_W(i, c_begin + i)
+    for (int c = c_begin; c < c_end; c += NB) {
+      SP_CHUNK(0, c)
+      SP_CHUNK(1, c + 1)
+      if (NB > 2) SP_CHUNK(2 % NB, c + 2)
+      if (NB > 3) SP_CHUNK(3 % NB, c + 3)
+    }
+#undef SP_CHUNK
+#undef SP_LOAD_W
+  }
+#undef SP_PC
+
+  if (KQ > 1) {
+    // Fold the two waves that share their strips: strip by strip, a wave leaves the row tiles that are not its own (tile
+    // mt belongs to wave mt % 2) and adds the other's products of its own tiles, in order.
+    f32x4_t* fold = reinterpret_cast<f32x4_t*>(lds);               // [waves][OT][64 lanes]
+#pragma unroll
+    for (int a = 0; a < NS; ++a) {
+      __syncthreads();                    // the panels, or the strip before, are no longer read
+      if (mm) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          if (mt % KQ != kq) fold[(wave * OT + mt / KQ) * 64 + lane] = acc[a][mt];
+      }
+      __syncthreads();
+      if (mm) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          if (mt % KQ != kq) continue;
+          const f32x4_t o = fold[(((KQ - 1 - kq) * CW + cw) * OT + mt / KQ) * 64 + lane];
+          acc[a][mt] = kq == 0 ? acc[a][mt] + o : o + acc[a][mt];
+        }
+      }
     }
   }
 
   // lane holds, for row m = mt*16 + l%16 of its own tiles, columns (strip base) + 4*(l/16) + 0..3
   if (GATEUP) {
+    if (!mm) return;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const int m = mt * 16 + r;
-      if (mt % NS != kq || m >= M) continue;
+      if (mt % KQ != kq || m >= M) continue;
 #pragma unroll
       for (int g = 0; g < GS; ++g) {
         if (4 * kg >= cpw - (cw * GS + g) * 16) continue;           // columns past a short last group
@@ -183,24 +194,24 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
         uint2 pk;
         pk.x = pack_bf16x2(o[0], o[1]);
         pk.y = pack_bf16x2(o[2], o[3]);
-        *reinterpret_cast<uint2*>(act + (size_t)m * N + col0 + g * 16 + 4 * kg) = pk;
+        *reinterpret_cast<uint2*>(act + frag_at(m, col0 + g * 16 + 4 * kg, N)) = pk;
       }
     }
     return;
   }
   // Partial sums leave in whole rows of the workgroup's columns, put together in LDS: a store instruction then writes
   // 1 KB of consecutive addresses instead of 64 bytes in each of 16 rows.
-  constexpr int WCOLS = 16 * NSTRIPS, LSF = WCOLS + 4;    // columns, and floats per LDS row
-  static_assert(ROWS * LSF * 4 <= (int)sizeof(lds), "the row tile fits the panels' LDS");
-  float* tile = reinterpret_cast<float*>(&lds[0][0]);
+  float* tile = reinterpret_cast<float*>(lds);
   __syncthreads();
+  if (mm) {
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-    if (mt % NS == kq) {
+    for (int mt = 0; mt < MT; ++mt)
+      if (mt % KQ == kq) {
 #pragma unroll
-      for (int a = 0; a < NS; ++a)
-        *reinterpret_cast<f32x4_t*>(tile + (mt * 16 + r) * LSF + (cw * NS + a) * 16 + 4 * kg) = acc[a][mt];
-    }
+        for (int a = 0; a < NS; ++a)
+          *reinterpret_cast<f32x4_t*>(tile + (mt * 16 + r) * LSF + (cw * NS + a) * 16 + 4 * kg) = acc[a][mt];
+      }
+  }
   __syncthreads();
   constexpr int UPW = WCOLS / 4;                          // 16-byte units per row
   for (int idx = tid; idx < ROWS * UPW; idx += NTH) {
@@ -213,28 +224,35 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
 
 // row tiles of a launch: the kernel is compiled for these heights
 static inline int mid_tiles(int M) { return M <= 64 ? 4 : M <= 96 ? 6 : M <= 128 ? 8 : 10; }
-#define SP_BY_TILES(GO)                  \
-  switch (mid_tiles(M)) {                \
-    case 4: GO(4); break;                \
-    case 6: GO(6); break;                \
-    case 8: GO(8); break;                \
-    default: GO(10); break;              \
-  }
 
 template <int NSTRIPS, bool PACKED, bool WNT>
 static hipError_t launch_plain(dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out, int M, int N, int K, int S) {
-#define SP_GO(MTV) \
-  hipLaunchKernelGGL((k_gemm_mid<MTV, NSTRIPS, false, PACKED, WNT>), grid, dim3(64 * NSTRIPS), 0, st, X, W, out, nullptr, M, N, K, S, 0)
-  SP_BY_TILES(SP_GO)
+#define SP_GO(MTV, KCV, DV, PFV)                                                                                          \
+  hipLaunchKernelGGL((k_gemm_mid<MTV, NSTRIPS / 2, 2, false, PACKED, WNT, KCV, DV, PFV, MID_NPR>), grid,                  \
+                     dim3(64 * (NSTRIPS + MID_NPR)), 0, st, X, W, out, nullptr, M, N, K, S, 0)
+  switch (mid_tiles(M)) {
+    case 4: SP_GO(4, 128, 2, 2); break;
+    case 6: SP_GO(6, 128, 2, 2); break;
+    case 8: SP_GO(8, 128, 2, 2); break;
+    default: SP_GO(10, 64, 3, 3); break;
+  }
 #undef SP_GO
   return hipGetLastError();
 }
 
-template <bool PACKED>
+// gate/up: CW groups of 16 columns
+template <int CW, int KQ, bool PACKED>
 static hipError_t launch_gateup(int n_cu, hipStream_t st, const bf16_t* X, const bf16_t* W, bf16_t* act, int M, int F, int K) {
-#define SP_GO(MTV) \
-  hipLaunchKernelGGL((k_gemm_mid<MTV, 8, true, PACKED, true>), dim3(n_cu), dim3(512), 0, st, X, W, nullptr, act, M, F, K, 1, F / n_cu)
-  SP_BY_TILES(SP_GO)
+  constexpr int NPR = KQ == 2 ? MID_NPR : 1, PF = KQ == 2 ? 2 : 1;
+#define SP_GO(MTV)                                                                                                   \
+  hipLaunchKernelGGL((k_gemm_mid<MTV, CW, KQ, true, PACKED, true, 128, 2, PF, NPR>), dim3(n_cu), dim3(64 * (CW * KQ + NPR)), 0, \
+                     st, X, W, nullptr, act, M, F, K, 1, F / n_cu)
+  switch (mid_tiles(M)) {
+    case 4: SP_GO(4); break;
+    case 6: SP_GO(6); break;
+    case 8: SP_GO(8); break;
+    default: SP_GO(10); break;
+  }
 #undef SP_GO
   return hipGetLastError();
 }
@@ -272,9 +290,12 @@ bool sp_gemm_mid_takes(int M, int N, int K, int n_cu) {
   if (M > 96 && M <= 128) return cut.S >= 3 && K / MID_KC >= 2 * (cut.S < 16 ? cut.S : 16);
   return true;
 }
+// columns of a CU's share of the gate/up product: 48 < cpw <= 64 (four groups, two waves each) or, from 65 rows on,
+// 96 < cpw <= 112 (seven groups, one wave each)
 bool sp_gemm_mid_takes_gateup(int M, int F, int K, int n_cu) {
-  return M > 48 && M <= 160 && K % MID_KC == 0 && n_cu > 0 && F % n_cu == 0 && (F / n_cu) % 8 == 0 && F / n_cu > 48 &&
-         F / n_cu <= 64;
+  if (M <= 48 || M > 160 || K % 128 || n_cu < 1 || F % n_cu || (F / n_cu) % 8) return false;
+  const int cpw = F / n_cu;
+  return (cpw > 48 && cpw <= 64) || (M > 64 && cpw > 96 && cpw <= 112);
 }
 
 hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,
@@ -300,5 +321,7 @@ hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, flo
 hipError_t sp_launch_gemm_mid_gateup(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F, int K, int n_cu,
                                      hipStream_t st) {
   if (!sp_gemm_mid_takes_gateup(M, F, K, n_cu)) return hipErrorInvalidValue;
-  return packed ? launch_gateup<true>(n_cu, st, X, W, act, M, F, K) : launch_gateup<false>(n_cu, st, X, W, act, M, F, K);
+  if (F / n_cu > 64)
+    return packed ? launch_gateup<7, 1, true>(n_cu, st, X, W, act, M, F, K) : launch_gateup<7, 1, false>(n_cu, st, X, W, act, M, F, K);
+  return packed ? launch_gateup<4, 2, true>(n_cu, st, X, W, act, M, F, K) : launch_gateup<4, 2, false>(n_cu, st, X, W, act, M, F, K);
 }

@@ -15,7 +15,6 @@
 #ifndef WKC
 #define WKC 64                  // k per staged chunk
 #endif
-#define WXS (WKC * 2 + 16)      // LDS row stride of the activation panel in bytes
 
 // Loads run NB-1 chunks ahead of the math in NB weight register sets, with NB LDS panels.  The
 // memory counter retires loads in issue order, so activations and weights of one chunk are
@@ -27,15 +26,15 @@ template <int SPW, int MT, bool GATEUP, bool PACKED>
 __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W,
                                           float* __restrict__ out, bf16_t* __restrict__ act, int M, int N, int K,
                                           int tile, int m_base, int c_begin, int c_end, char* lds_raw) {
-  constexpr int WROWS = MT * 16;
   constexpr int NB = MT > 8 ? 3 : 4;               // weight register sets and LDS panels
   constexpr int NBX = MT > 8 ? 2 : 4;              // activation register sets
   constexpr int KSTEPS = WKC / 32;
   constexpr int ITEMS = KSTEPS * MT;               // (k step, row tile) pairs of a chunk
   constexpr int BQ = 4;                            // activation fragments read ahead of their MFMAs
-  constexpr int UPR = WKC / 8, RPP = 256 / UPR, PASSES = WROWS / RPP;
+  constexpr int UPT = WKC * 2, UNITS = MT * UPT;   // 16-byte units of a row tile's chunk, and of a panel (fragment order)
+  constexpr int PASSES = UNITS / 256;
   constexpr int GS = GATEUP ? SPW / 2 : SPW;       // strips per wave and matrix half
-  char (*lds)[WROWS * WXS] = reinterpret_cast<char (*)[WROWS * WXS]>(lds_raw);
+  char (*lds)[UNITS * 16] = reinterpret_cast<char (*)[UNITS * 16]>(lds_raw);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // known uniform: addresses split into scalar + lane part
@@ -53,12 +52,13 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
   }
   const unsigned wl = PACKED ? lane * 8 : r * K + kg * 8;
 #define SP_WOFF(C, s) (PACKED ? ((size_t)(C) * (WKC / 32) + (s)) * 512 : (size_t)(C)*WKC + (s) * 32)
-  // activations: per-thread row offset (elements; rows past the end repeat the last row) + uniform chunk origin
-  const int xu = tid % UPR, xr = tid / UPR;
+  // activations: per-thread offset (elements; row tiles past the last one repeat it) + uniform chunk origin
   unsigned xo[PASSES];
 #pragma unroll
-  for (int p = 0; p < PASSES; ++p) xo[p] = (unsigned)min(m_base + p * RPP + xr, M - 1) * K + xu * 8;
-  const unsigned bl = r * WXS + kg * 16;            // fragment read: row (tile*16 + l%16), k group l/16
+  for (int p = 0; p < PASSES; ++p) {
+    const int u = p * 256 + tid;
+    xo[p] = (unsigned)min((m_base >> 4) + u / UPT, (M - 1) >> 4) * (unsigned)(K * 16) + (u % UPT) * 8;
+  }
 
   u32x4_t wb[NB][SPW][KSTEPS];
   u32x4_t xb[NBX][PASSES];
@@ -70,13 +70,13 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
 
 #define SP_LOAD_X(B, C)                                                                                 \
   {                                                                                                     \
-    const bf16_t* xs = X + (size_t)min((C), c_last) * WKC;                                              \
+    const bf16_t* xs = X + (size_t)min((C), c_last) * (WKC * 16);                                       \
     _Pragma("unroll") for (int p = 0; p < PASSES; ++p)                                                  \
         xb[B][p] = *reinterpret_cast<const u32x4_t*>(xs + xo[p]);                                       \
   }
 #define SP_STORE_X(B, BUF)                                                                              \
   _Pragma("unroll") for (int p = 0; p < PASSES; ++p)                                                    \
-      *reinterpret_cast<u32x4_t*>(&lds[BUF][(p * RPP + xr) * WXS + xu * 16]) = xb[B][p];
+      *reinterpret_cast<u32x4_t*>(&lds[BUF][(p * 256 + tid) * 16]) = xb[B][p];
 #define SP_LOAD_W(B, C)                                                                                 \
   {                                                                                                     \
     const int cw = min((C), c_last);                                                                    \
@@ -86,7 +86,7 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
   }
   // item j of a chunk: k step j / MT, row tile j % MT
 #define SP_LDS_B(BUF, j)                                                                                \
-  (*reinterpret_cast<const bf16x8_t*>(&lds[BUF][((j) % MT) * 16 * WXS + ((j) / MT) * 64 + bl]))
+  (*reinterpret_cast<const bf16x8_t*>(&lds[BUF][(((j) % MT) * KSTEPS + (j) / MT) * 1024 + lane * 16]))
   // Chunk C, weights in register set B, activations in LDS panel B.  The activations of chunk
   // C+2 go from their register set BX to their panel; that set then takes chunk C+2+NBX and
   // weight set B-1 the weights of chunk C+NB-1.  The last BQ fragment reads already address the
@@ -165,7 +165,7 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
         uint2 pk;
         pk.x = pack_bf16x2(o[0], o[1]);
         pk.y = pack_bf16x2(o[2], o[3]);
-        *reinterpret_cast<uint2*>(act + (size_t)m * N + n0 + a * 16 + 4 * kg) = pk;
+        *reinterpret_cast<uint2*>(act + frag_at(m, n0 + a * 16 + 4 * kg, N)) = pk;
       }
     } else {
 #pragma unroll
@@ -214,7 +214,7 @@ k_gemm_wide(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 template <int SPW, int MT, bool GATEUP, bool PACKED>
 static hipError_t launch_wide(dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out, bf16_t* act,
                               int M, int N, int K, int n_tiles, int S) {
-  constexpr int LDS_BYTES = (MT > 8 ? 3 : 4) * MT * 16 * WXS;    // NB panels of the tallest body
+  constexpr int LDS_BYTES = (MT > 8 ? 3 : 4) * MT * 16 * WKC * 2;    // NB panels of the tallest body
   static bool ready = false;
   if (!ready) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_wide<SPW, MT, GATEUP, PACKED>),

@@ -46,7 +46,7 @@ hipError_t sp_launch_set_root_pred(ReqMeta* meta, int req, int token, hipStream_
 
 // ---- lossy verification (sp_verify.hip) -------------------------------------------
 // xn = rmsnorm(x) * gain for M rows (no residual stream, no row descriptors)
-hipError_t sp_launch_row_norm(int dtype, const void* x, const void* gain, void* xn, int M, int d, float eps,
+hipError_t sp_launch_row_norm(int dtype, const void* x, const void* gain, void* xn, bool frag, int M, int d, float eps,
                               hipStream_t st);
 // floats of scratch sp_launch_verify_lossy needs at least for n rows of V logits (it uses more if there is more)
 size_t sp_lossy_scratch_floats(int n, int V);
@@ -87,17 +87,17 @@ struct AttnPlan {          // host-made split of a forward call's attention work
 
 // ---- elementwise / row kernels --------------------------------------------------
 // Rows enter the stage: row descriptors and rotary tables (cs: [rows][d_head], cos then sin),
-// h = x, xn = rmsnorm(h) * gain.
+// h = x, xn = rmsnorm(h) * gain (frag, bf16 only: in fragment order, as every bf16 matrix-core product reads its rows).
 // The segment fields of `plan` say which request and node each row belongs to; if plan_dev is given the
 // whole plan is also stored there for the attention kernels of the call.
 hipError_t sp_launch_enter_norm(int dtype, const void* x, const AttnPlan& plan, AttnPlan* plan_dev /*nullable*/,
                                 const ReqMeta* meta, const ReqTables* tables, RowInfo* rows, float* cs, int d_head,
-                                float theta, float* h, const void* gain, void* xn, int M, int d, float eps,
+                                float theta, float* h, const void* gain, void* xn, bool frag, int M, int d, float eps,
                                 hipStream_t st);
 
 // h += sum_s part[s]; xn = rmsnorm(h) * gain
 hipError_t sp_launch_add_norm(int dtype, float* h, const float* part, int S, size_t part_stride,
-                              const void* gain, void* xn, int M, int d, float eps, hipStream_t st);
+                              const void* gain, void* xn, bool frag, int M, int d, float eps, hipStream_t st);
 // q,k rotated, v copied; q -> qbuf [M][n_q*d_head]; k,v -> slab rows
 hipError_t sp_launch_rope_kv(int dtype, const float* part, int S, size_t part_stride, const RowInfo* rows,
                              const float* cs, void* qbuf, KvGeom g, int layer, int M, int n_q, int n_kv,
@@ -118,7 +118,7 @@ hipError_t sp_launch_gemm_f32(const float* X, const float* W, float* out, int M,
 hipError_t sp_launch_gateup_f32(const float* X, const float* W, float* act, int M, int F, int K, hipStream_t st);
 hipError_t sp_launch_attn_f32(const float* q, const RowInfo* rows, const ReqTables* tables, KvGeom g, int layer, float* out,
                               int M, int n_q, int n_kv, int d_head, hipStream_t st);
-// bf16 MFMA kernels.  Returns the split count used in *S_out (partials [S][M][N]).  packed: the
+// bf16 MFMA kernels: the rows X and the gate/up products are in fragment order (frag_at).  Returns the split count used in *S_out (partials [S][M][N]).  packed: the
 // weights are in MFMA fragment order (sp_launch_pack_weights).
 hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st,

@@ -57,8 +57,11 @@ __device__ __forceinline__ f32x4_t fold4(const float* p, int S, size_t stride) {
 //          level is one future position (Sec. 3.2).  The angle is formed in double so that positions of tens of
 //          thousands keep full float accuracy in cos and sin.
 //   else:  h[row] += sum_s part[s][row].
-// Then xn[row] = h * rsqrt(mean(h^2)+eps) * gain.  The first two passes stay in registers.
+// Then xn[row] = h * rsqrt(mean(h^2)+eps) * gain, in fragment order where the matrix-core kernels read it (frag).  The
+// first two passes stay in registers.
 #define ENTER_ROWS 4       // rows a workgroup of descriptors and rotary tables takes (few: double precision is slow)
+// Workgroups of the rows: one each, in fragment order in whole groups of 64 (eight rows for each of the eight XCDs).
+__host__ __device__ inline int norm_blocks(int M, bool frag) { return frag ? (M + 63) / 64 * 64 : M; }
 struct NoPlan { int unused; };
 template <bool FIRST> struct PlanArg { typedef NoPlan type; };
 template <> struct PlanArg<true> { typedef AttnPlan type; };
@@ -68,13 +71,15 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
                                                     const T* gain, T* xn, int M, int d, float eps, const T* x,
                                                     typename PlanArg<FIRST>::type b, AttnPlan* plan_dev,
                                                     const ReqMeta* meta, const ReqTables* tables, RowInfo* rows,
-                                                    float* cs, int d_head, float theta) {
+                                                    float* cs, int d_head, float theta, bool frag) {
   __shared__ float s_red[16];
-  const int row = blockIdx.x;
+  const int row_blocks = norm_blocks(M, frag);
+  // fragment order puts eight rows into a 128-byte line: they go to the same XCD, whose L2 puts the line together
+  const int row = frag ? (((blockIdx.x >> 6) * 8 + (blockIdx.x & 7)) * 8 + ((blockIdx.x >> 3) & 7)) : blockIdx.x;
   if constexpr (FIRST) {
     const int half = d_head >> 1;
-    if (row >= M) {
-      const int r = (row - M) * ENTER_ROWS + (int)threadIdx.x / half, tt = (int)threadIdx.x % half;
+    if ((int)blockIdx.x >= row_blocks) {
+      const int r = ((int)blockIdx.x - row_blocks) * ENTER_ROWS + (int)threadIdx.x / half, tt = (int)threadIdx.x % half;
       if (r < M && (int)threadIdx.x < ENTER_ROWS * half) {
         int seg = 0;
         while (seg + 1 < b.n_seg && r >= b.seg_row0[seg + 1]) ++seg;
@@ -93,7 +98,7 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
         cs[(size_t)r * d_head + half + tt] = (float)sin(ang);
       }
       // the call's plan goes to device memory for the kernels that follow
-      if (plan_dev && row == M) {
+      if (plan_dev && (int)blockIdx.x == row_blocks) {
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&b);
         uint32_t* dst = reinterpret_cast<uint32_t*>(plan_dev);
         for (int i = threadIdx.x; i < (int)(sizeof(AttnPlan) / 4); i += blockDim.x) dst[i] = src[i];
@@ -101,6 +106,7 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
       return;
     }
   }
+  if (row >= M) return;
   float* hr = h + (size_t)row * d;
   const int c0 = threadIdx.x * 4, step = blockDim.x * 4;
   f32x4_t keep[2];
@@ -127,10 +133,11 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     const int c = c0 + p * step;
-    if (c < d) Vec4<T>::st(xn + (size_t)row * d + c, keep[p] * scale * Vec4<T>::ld(gain + c));
+    if (c < d) Vec4<T>::st(xn + (frag ? frag_at(row, c, d) : (size_t)row * d + c), keep[p] * scale * Vec4<T>::ld(gain + c));
   }
   for (int c = c0 + 2 * step; c < d; c += step)
-    Vec4<T>::st(xn + (size_t)row * d + c, *reinterpret_cast<const f32x4_t*>(hr + c) * scale * Vec4<T>::ld(gain + c));
+    Vec4<T>::st(xn + (frag ? frag_at(row, c, d) : (size_t)row * d + c),
+                *reinterpret_cast<const f32x4_t*>(hr + c) * scale * Vec4<T>::ld(gain + c));
 }
 
 // Threads work in groups of d_head/8, one group per (row, head) over the projection's
@@ -241,7 +248,7 @@ static inline int grid_for(size_t n, int block, int cap = 4096) {
 
 hipError_t sp_launch_enter_norm(int dtype, const void* x, const AttnPlan& plan, AttnPlan* plan_dev,
                                 const ReqMeta* meta, const ReqTables* tables, RowInfo* rows, float* cs, int d_head,
-                                float theta, float* h, const void* gain, void* xn, int M, int d, float eps,
+                                float theta, float* h, const void* gain, void* xn, bool frag, int M, int d, float eps,
                                 hipStream_t st) {
   // 1024 threads per row up to two rows per CU; with more rows 512, so that four rows per CU are in flight (638 rows of
   // 4096, with the tables apart: 13.9 -> 8.4 us) -- as long as a row takes no more than the two passes that stay in
@@ -251,25 +258,25 @@ hipError_t sp_launch_enter_norm(int dtype, const void* x, const AttnPlan& plan, 
   static_assert(sizeof(AttnPlan) % 4 == 0 && sizeof(AttnPlan) < 3900, "the plan travels as a kernel argument");
   if (dtype == 0)
     hipLaunchKernelGGL((k_add_norm<float, true>), dim3(M + extra), dim3(nth), 0, st, h, nullptr, 0, 0, (const float*)gain,
-                       (float*)xn, M, d, eps, (const float*)x, plan, plan_dev, meta, tables, rows, cs, d_head, theta);
+                       (float*)xn, M, d, eps, (const float*)x, plan, plan_dev, meta, tables, rows, cs, d_head, theta, false);
   else
-    hipLaunchKernelGGL((k_add_norm<bf16_t, true>), dim3(M + extra), dim3(nth), 0, st, h, nullptr, 0, 0,
+    hipLaunchKernelGGL((k_add_norm<bf16_t, true>), dim3(norm_blocks(M, frag) + extra), dim3(nth), 0, st, h, nullptr, 0, 0,
                        (const bf16_t*)gain, (bf16_t*)xn, M, d, eps, (const bf16_t*)x, plan, plan_dev, meta, tables, rows,
-                       cs, d_head, theta);
+                       cs, d_head, theta, frag);
   return hipGetLastError();
 }
 
 hipError_t sp_launch_add_norm(int dtype, float* h, const float* part, int S, size_t part_stride, const void* gain,
-                              void* xn, int M, int d, float eps, hipStream_t st) {
+                              void* xn, bool frag, int M, int d, float eps, hipStream_t st) {
   const NoPlan none{0};
   if (dtype == 0)
     hipLaunchKernelGGL((k_add_norm<float, false>), dim3(M), dim3(1024), 0, st, h, part, S, part_stride,
                        (const float*)gain, (float*)xn, M, d, eps, nullptr, none, nullptr, nullptr, nullptr, nullptr,
-                       nullptr, 0, 0.f);
+                       nullptr, 0, 0.f, false);
   else
-    hipLaunchKernelGGL((k_add_norm<bf16_t, false>), dim3(M), dim3(1024), 0, st, h, part, S, part_stride,
+    hipLaunchKernelGGL((k_add_norm<bf16_t, false>), dim3(norm_blocks(M, frag)), dim3(1024), 0, st, h, part, S, part_stride,
                        (const bf16_t*)gain, (bf16_t*)xn, M, d, eps, nullptr, none, nullptr, nullptr, nullptr, nullptr,
-                       nullptr, 0, 0.f);
+                       nullptr, 0, 0.f, frag);
   return hipGetLastError();
 }
 

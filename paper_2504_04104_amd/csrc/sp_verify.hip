@@ -19,7 +19,7 @@
 
 template <typename T>
 __global__ void __launch_bounds__(1024) k_row_norm(const T* __restrict__ x, const T* __restrict__ gain,
-                                                    T* __restrict__ xn, int d, float eps) {
+                                                    T* __restrict__ xn, int d, float eps, bool frag) {
   __shared__ float s_red[16];
   const int row = blockIdx.x;
   const T* xr = x + (size_t)row * d;
@@ -33,7 +33,7 @@ __global__ void __launch_bounds__(1024) k_row_norm(const T* __restrict__ x, cons
   for (int w = 0; w < 16; ++w) tot += s_red[w];
   const float rs = rsqrtf(tot / (float)d + eps);
   for (int c = threadIdx.x; c < d; c += 1024)
-    Elt<T>::st(xn + (size_t)row * d + c, Elt<T>::ld(xr + c) * rs * Elt<T>::ld(gain + c));
+    Elt<T>::st(xn + (frag ? frag_at(row, c, d) : (size_t)row * d + c), Elt<T>::ld(xr + c) * rs * Elt<T>::ld(gain + c));
 }
 
 // The root's children in node order: s_node[0..nc), their tokens in s_tok.  Called by all threads (256 or more).
@@ -670,12 +670,12 @@ hipError_t sp_launch_verify_sample(ReqMeta* meta, const ReqTables* tables, const
   return hipGetLastError();
 }
 
-hipError_t sp_launch_row_norm(int dtype, const void* x, const void* gain, void* xn, int M, int d, float eps,
+hipError_t sp_launch_row_norm(int dtype, const void* x, const void* gain, void* xn, bool frag, int M, int d, float eps,
                               hipStream_t st) {
   if (dtype == 0)
-    hipLaunchKernelGGL(k_row_norm<float>, dim3(M), dim3(1024), 0, st, (const float*)x, (const float*)gain, (float*)xn, d, eps);
+    hipLaunchKernelGGL(k_row_norm<float>, dim3(M), dim3(1024), 0, st, (const float*)x, (const float*)gain, (float*)xn, d, eps, false);
   else
-    hipLaunchKernelGGL(k_row_norm<bf16_t>, dim3(M), dim3(1024), 0, st, (const bf16_t*)x, (const bf16_t*)gain, (bf16_t*)xn, d, eps);
+    hipLaunchKernelGGL(k_row_norm<bf16_t>, dim3(M), dim3(1024), 0, st, (const bf16_t*)x, (const bf16_t*)gain, (bf16_t*)xn, d, eps, frag);
   return hipGetLastError();
 }
 
