@@ -659,46 +659,53 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   }
 
   const size_t strideD = (size_t)M * d, strideQ = (size_t)M * nqkv;
+  const bool few = s->fast && sp_few_takes(M, d, dq, F, s->packed, s->n_cu);
+  // Activations between the products in fragment order, but up to four rows row-major where no product takes them by
+  // direct-to-LDS loads (8B shape, one node: 105.7 -> 104.0 us; eight rows gain from the fragments, 101.5 -> 99.8 us a layer).
+  const bool frag = s->fast && !(M <= 4 && (s->packed || (few && !sp_gemm_mid_takes_gateup(M, F, d, false, s->n_cu))));
   // projections: few rows stream the weights (HBM-bound); many rows use the register-blocked kernel
   const bool wide = s->fast && M > 128 && nqkv % 256 == 0 && d % 256 == 0 && F % 128 == 0 && dq % 128 == 0;
   auto gemm = [&](const void* X, const void* Wm, int N_, int K_, int* S_, bool resident = false) -> hipError_t {
-    if (sp_gemm_mid_takes(M, N_, K_, s->n_cu))
+    if (sp_gemm_mid_takes(M, N_, K_, s->packed, s->n_cu))
       return sp_launch_gemm_mid((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, s->n_cu, 16,
                                 w.part_floats, S_, st, resident);
     if (wide)
       return sp_launch_gemm_wide((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, s->n_cu,
                                  w.part_floats, S_, st);
     return sp_launch_gemm_bf16((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, 16, w.part_floats,
-                               S_, st, resident);
+                               S_, st, resident, frag);
   };
   // Everything behind the kernel that opens the call (rows enter, first RMSNorm, plan to device
   // memory), the write-out included: it takes the result's pointer from the plan.  No argument of these launches depends on the
   // caller's pointers or on the plan's contents, only on M and on the grid sizes the plan implies.
 #define SP_STEP(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) return e_; } while (0)
   // One row tile: complete projections with RoPE, residual, norm and write-out as their epilogues.
-  const bool few = s->fast && sp_few_takes(M, d, dq, F, s->packed, s->n_cu);
   auto run_layers_few = [&]() -> hipError_t {
     float* ssq = w.part;                            // [M][d / 16]
     for (int l = 0; l < c.n_layers; ++l) {
       const sp_layer_weights& L = s->W[l];
       { ProfScope p(s, SP_K_GEMM_QKV, st);
-        SP_STEP(sp_launch_few_qkv((const bf16_t*)w.xn, (const bf16_t*)L.wqkv, s->packed, l > 0 ? ssq : nullptr, c.rms_eps,
+        SP_STEP(sp_launch_few_qkv((const bf16_t*)w.xn, frag, (const bf16_t*)L.wqkv, s->packed, l > 0 ? ssq : nullptr, c.rms_eps,
                                   w.rows, w.cs, (bf16_t*)w.qbuf, s->geom, l, M, d, nq, nkv, s->n_cu, st)); }
       { ProfScope p(s, SP_K_ATTENTION, st);
         SP_STEP(sp_launch_attn_bf16((const bf16_t*)w.qbuf, s->d_tables, s->geom, l, plan, w.plan, w.attn_part,
-                                    (bf16_t*)w.attn, M, nq, nkv, dh, st)); }
+                                    (bf16_t*)w.attn, frag, M, nq, nkv, dh, st)); }
       { ProfScope p(s, SP_K_GEMM_O, st);
-        SP_STEP(sp_launch_few_residual((const bf16_t*)w.attn, (const bf16_t*)L.wo, s->packed, s->o_resident, w.h,
+        SP_STEP(sp_launch_few_residual((const bf16_t*)w.attn, frag, (const bf16_t*)L.wo, s->packed, s->o_resident, w.h,
                                        (const bf16_t*)L.norm2, (bf16_t*)w.xn, ssq, M, d, dq, s->n_cu, st)); }
       { ProfScope p(s, SP_K_GEMM_GATEUP, st);
-        SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d,
-                                           s->n_cu, ssq, c.rms_eps, st)); }
+        if (sp_gemm_mid_takes_gateup(M, F, d, s->packed, s->n_cu))
+          SP_STEP(sp_launch_gemm_mid_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d,
+                                            s->n_cu, ssq, c.rms_eps, st));
+        else
+          SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, frag, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d,
+                                             s->n_cu, ssq, c.rms_eps, st)); }
       { ProfScope p(s, SP_K_GEMM_DOWN, st);
         if (l + 1 < c.n_layers)
-          SP_STEP(sp_launch_few_residual((const bf16_t*)w.act, (const bf16_t*)L.wd, s->packed, false, w.h,
+          SP_STEP(sp_launch_few_residual((const bf16_t*)w.act, frag, (const bf16_t*)L.wd, s->packed, false, w.h,
                                          (const bf16_t*)s->W[l + 1].norm1, (bf16_t*)w.xn, ssq, M, d, F, s->n_cu, st));
         else
-          SP_STEP(sp_launch_few_out((const bf16_t*)w.act, (const bf16_t*)L.wd, s->packed, w.h, w.plan, M, d, F, s->n_cu, st)); }
+          SP_STEP(sp_launch_few_out((const bf16_t*)w.act, frag, (const bf16_t*)L.wd, s->packed, w.h, w.plan, M, d, F, s->n_cu, st)); }
     }
     return hipSuccess;
   };
@@ -709,7 +716,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       const sp_layer_weights& L = s->W[l];
       if (l > 0) {
         ProfScope p(s, SP_K_NORM, st);
-        SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S_prev, strideD, L.norm1, w.xn, s->fast, M, d, c.rms_eps, st));
+        SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S_prev, strideD, L.norm1, w.xn, frag, M, d, c.rms_eps, st));
       }
       int S = 1;
       { ProfScope p(s, SP_K_GEMM_QKV, st);
@@ -720,7 +727,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       if (s->fast) {
         ProfScope p(s, SP_K_ATTENTION, st);
         SP_STEP(sp_launch_attn_bf16((const bf16_t*)w.qbuf, s->d_tables, s->geom, l, plan, w.plan, w.attn_part,
-                                    (bf16_t*)w.attn, M, nq, nkv, dh, st));
+                                    (bf16_t*)w.attn, frag, M, nq, nkv, dh, st));
       } else {
         ProfScope p(s, SP_K_ATTENTION, st);
         if (s->f32) SP_STEP(sp_launch_attn_f32((const float*)w.qbuf, w.rows, s->d_tables, s->geom, l, (float*)w.attn, M, nq, nkv, dh, st));
@@ -731,12 +738,12 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
         if (s->fast) SP_STEP(gemm(w.attn, L.wo, d, dq, &S, s->o_resident));
         else SP_STEP(other_gemm(s, w.attn, L.wo, w.part, M, d, dq, st)); }
       { ProfScope p(s, SP_K_NORM, st);
-        SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S, strideD, L.norm2, w.xn, s->fast, M, d, c.rms_eps, st)); }
+        SP_STEP(sp_launch_add_norm(dt, w.h, w.part, S, strideD, L.norm2, w.xn, frag, M, d, c.rms_eps, st)); }
       { ProfScope p(s, SP_K_GEMM_GATEUP, st);
         if (s->fast) {
-          if (sp_gemm_mid_takes_gateup(M, F, d, s->n_cu)) SP_STEP(sp_launch_gemm_mid_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, st));
+          if (sp_gemm_mid_takes_gateup(M, F, d, s->packed, s->n_cu)) SP_STEP(sp_launch_gemm_mid_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, nullptr, 0.f, st));
           else if (wide) SP_STEP(sp_launch_gemm_wide_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, st));
-          else SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, nullptr, 0.f, st));
+          else SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, frag, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, nullptr, 0.f, st));
         } else if (s->f32) {
           SP_STEP(sp_launch_gateup_f32((const float*)w.xn, (const float*)L.wgu, (float*)w.act, M, F, d, st));
         } else {
@@ -755,7 +762,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
 
   { ProfScope p(s, SP_K_NORM, st);
     SP_TRY(sp_launch_enter_norm(dt, x_in, plan, w.plan, s->d_meta, s->d_tables, w.rows, w.cs, dh,
-                                c.rope_theta, w.h, s->W[0].norm1, w.xn, s->fast, M, d, c.rms_eps, st)); }
+                                c.rope_theta, w.h, s->W[0].norm1, w.xn, frag, M, d, c.rms_eps, st)); }
 
   // A shape that comes back replays its graph; one seen for the second time is captured.  Not while a
   // kernel kind is being timed (the events sit between the launches) and not inside a caller's capture.

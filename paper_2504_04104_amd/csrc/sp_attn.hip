@@ -31,7 +31,8 @@ struct AttnArgs {
   KvGeom g;
   int layer, n_q, n_kv;
   float* part_o;            // [units][DH], followed by [units][2] (running max, sum)
-  bf16_t* out;              // rows of n_q * DH columns in fragment order
+  bf16_t* out;              // rows of n_q * DH columns, in fragment order or (frag false) row-major
+  bool frag;
   const AttnPlan* plan;     // device copy of the call's plan (written by the kernel that opens the forward)
 };
 
@@ -328,7 +329,7 @@ __global__ void __launch_bounds__(64 * AW) k_attn_bf16(AttnArgs a) {
     pk.y = pack_bf16x2(e0[1] * inv, e1[1] * inv);
     pk.z = pack_bf16x2(e0[2] * inv, e1[2] * inv);
     pk.w = pack_bf16x2(e0[3] * inv, e1[3] * inv);
-    *reinterpret_cast<u32x4_t*>(a.out + frag_at(row0 + nl, head * DH + G * 32 + 8 * kg, a.n_q * DH)) = pk;
+    *reinterpret_cast<u32x4_t*>(a.out + row_at(a.frag, row0 + nl, head * DH + G * 32 + 8 * kg, a.n_q * DH)) = pk;
   } else {
     const size_t unit = (size_t)sg_unit0 + (size_t)ch * seg_rows * a.n_q + (size_t)nl * a.n_q + head;
     float* po = a.part_o + unit * DH;
@@ -421,17 +422,18 @@ __global__ void __launch_bounds__(256) k_attn_merge(AttnArgs a, int M) {
     }
   }
   const float inv = 1.f / lsum;
-  *reinterpret_cast<uint32_t*>(a.out + frag_at(row, head * DH + 2 * lane, a.n_q * DH)) = pack_bf16x2(acc0 * inv, acc1 * inv);
+  *reinterpret_cast<uint32_t*>(a.out + row_at(a.frag, row, head * DH + 2 * lane, a.n_q * DH)) = pack_bf16x2(acc0 * inv, acc1 * inv);
 }
 
 hipError_t sp_launch_attn_bf16(const bf16_t* q, const ReqTables* tables, KvGeom g, int layer, const AttnPlan& plan,
-                               const AttnPlan* plan_dev, float* part, bf16_t* out, int M, int n_q, int n_kv,
-                               int d_head, hipStream_t st) {
+                               const AttnPlan* plan_dev, float* part, bf16_t* out, bool frag, int M,
+                               int n_q, int n_kv, int d_head, hipStream_t st) {
   if (d_head != DH || g.row_bytes != 256) return hipErrorInvalidValue;
   AttnArgs a;
   a.q = q; a.tables = tables; a.g = g; a.layer = layer; a.n_q = n_q; a.n_kv = n_kv;
   a.part_o = part;
   a.out = out;
+  a.frag = frag;
   a.plan = plan_dev;
   dim3 grid(plan.total_items * n_kv);
   bool stream = true;                     // one block of query rows per request: K/V rows are read once

@@ -124,10 +124,12 @@ __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u 
 // workgroup of a projection reads all of its input rows out of L2, and a load instruction that covers 1 KB of consecutive
 // addresses gets 120 GB/s per CU from there (31 TB/s over the chip), one that covers 128 bytes of each of eight rows of
 // 8 KB 78, and one that covers 64 bytes of each of sixteen rows 38 (256 workgroups of eight waves that read 0.5 to 18 MB
-// in step).  Element index of (row m, column k) in rows of K columns:
+// in step).  Up to four rows of a one-tile call with packed weights stay row-major (frag false): a k step of a single row
+// is then half a line instead of a piece of each of four.  Element index of (row m, column k) in rows of K columns:
 __device__ __forceinline__ size_t frag_at(int m, int k, int K) {
   return ((size_t)(m >> 4) * (K >> 5) + (k >> 5)) * 512 + (((k >> 3) & 3) * 16 + (m & 15)) * 8 + (k & 7);
 }
+__device__ __forceinline__ size_t row_at(bool frag, int m, int k, int K) { return frag ? frag_at(m, k, K) : (size_t)m * K + k; }
 
 // A buffer over `p` for raw buffer loads: 2 GB long, or, where `on` is false, empty (its loads return zeros without a
 // memory access, so that a loop's loads need no branch around them past the end).
@@ -135,9 +137,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p, bool 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, on ? 0x7fffffff : 0, 0x00020000);
 }
 // 16 bytes per lane straight from memory to LDS: lane l's go to l * 16 bytes behind `dst`, which is the same in all lanes.
+// NT: non-temporal.
+template <bool NT = false>
 __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buf, char* dst, int lane_offset, int offset) {
 #ifdef __HIP_DEVICE_COMPILE__      // (the host pass of the compiler does not know the builtin)
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)dst, 16, lane_offset, offset, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)dst, 16, lane_offset, offset, 0, NT ? 2 : 0);
 #endif
 }
 // Waits until at most n of the wave's vector memory accesses are outstanding.

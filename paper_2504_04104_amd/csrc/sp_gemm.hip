@@ -87,7 +87,7 @@
 // strips in fixed 32-column workgroups cannot do when d_ff / 32 is not a multiple of the CU count (d_ff = 14336:
 // 1.75 workgroups per CU), and the panel is staged once per CU instead of once per four waves.
 template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, int NWAVES = 4, bool EVEN = false, bool WNT = true,
-          bool STATS = false, bool TWO = false>
+          bool STATS = false, bool TWO = false, bool FRAG = true>
 __global__ void __launch_bounds__(64 * NWAVES)
 k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
             bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int cpw = 0, int rot = 0,
@@ -148,7 +148,11 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   for (int p = 0; p < PASSES; ++p) {
     const int u = p * NTH + tid;
     xo[p] = (unsigned)min(blockIdx.z * MT + u / UPT, (M - 1) >> 4) * (unsigned)(K * 16) + (u % UPT) * 8;
+    // few rows may come row-major
+    if (!FRAG) xo[p] = (unsigned)(min(u & 15, M - 1) * K + ((u % UPT) >> 4) * 8);
   }
+  constexpr int XCHUNK = FRAG ? KC * 16 : KC;
+  static_assert(FRAG || MT == 1, "row-major rows: one tile only");
 
   u32x4_t wb[NB][NW][KSTEPS];
   u32x4_t xnxt[PASSES];
@@ -160,7 +164,7 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 
 #define SP_LOAD_X(C)                                                                                   \
   _Pragma("unroll") for (int p = 0; p < PASSES; ++p) {                                                  \
-    xnxt[p] = *reinterpret_cast<const u32x4_t*>(X + (size_t)SP_PC(C) * (KC * 16) + xo[p]);               \
+    xnxt[p] = *reinterpret_cast<const u32x4_t*>(X + (size_t)SP_PC(C) * XCHUNK + xo[p]);                  \
   }
 #define SP_STORE_X(BUF)                                                                                 \
   _Pragma("unroll") for (int p = 0; p < PASSES; ++p)                                                    \
@@ -358,7 +362,7 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
       uint2 pk;
       pk.x = pack_bf16x2(o[0], o[1]);
       pk.y = pack_bf16x2(o[2], o[3]);
-      *reinterpret_cast<uint2*>(act + frag_at(m, ncol, N)) = pk;
+      *reinterpret_cast<uint2*>(act + row_at(FRAG, m, ncol, N)) = pk;
     } else {
       float* o = out + ((size_t)blockIdx.y * M + m) * N + ncol;
       *reinterpret_cast<f32x4_t*>(o) = acc[0][mt];
@@ -375,10 +379,16 @@ static inline int rot_for(int S, int K) { return (SP_GEMM_ROT && S > 1 && K <= 8
 
 template <int NCG, bool GATEUP, int KCV, bool PACKED, bool ARGMAX = false>
 static hipError_t launch_mt(int MT, dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out,
-                            bf16_t* act, int M, int N, int K, int S, const float* ssq = nullptr, float eps = 0.f) {
+                            bf16_t* act, int M, int N, int K, int S, const float* ssq = nullptr, float eps = 0.f, bool frag = true) {
 #define SP_GO(MTV, KCX)                                                                                        \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, NCG, GATEUP, KCX, SP_GEMM_PF, PACKED, ARGMAX>), grid, dim3(256), 0, st, X, \
                      W, out, act, M, N, K, K / KCX, S, 0, (!GATEUP && !ARGMAX) ? rot_for(S, K) : 0, ssq, eps)
+  if constexpr (!ARGMAX && !(GATEUP && NCG == 4))
+    if (!frag) {
+      hipLaunchKernelGGL((k_gemm_bf16<1, NCG, GATEUP, KCV, SP_GEMM_PF, PACKED, ARGMAX, 4, false, true, false, false, false>), grid, dim3(256), 0,
+                         st, X, W, out, act, M, N, K, K / KCV, S, 0, GATEUP ? 0 : rot_for(S, K), ssq, eps);
+      return hipGetLastError();
+    }
   if (!ARGMAX && MT == 4 && GATEUP && NCG == 4) {      // the 64 + 64 column gate/up workgroup at 49-64 rows
     hipLaunchKernelGGL((k_gemm_bf16<4, 4, true, 128, SP_GEMM_PF, PACKED, false>), grid, dim3(256), 0, st, X, W, out, act, M, N, K, K / 128, S);
     return hipGetLastError();
@@ -409,7 +419,7 @@ static inline void row_blocks(int M, int* MT, int* mblocks) {
 }
 
 hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
-                               int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident) {
+                               int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident, bool frag) {
   int MT, mblocks;
   row_blocks(M, &MT, &mblocks);
   // 17-64 rows: workgroups of eight waves over 128 columns, one per CU -- the same waves per CU as two
@@ -424,7 +434,7 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   const bool six = SP_GEMM_PLAIN6 && eight && MT <= 4 && N % 96 == 0 && (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 128) != 0 &&
                    (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 96) == 0;
   const int TILE = six ? 96 : eight ? 128 : 16 * SP_GEMM_NCG_PLAIN;
-  if (M < 1 || M > 128 || (MT == 8 && !eight) || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
+  if (M < 1 || M > 128 || (!frag && M > 8) || (MT == 8 && !eight) || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
   const int chunks = K / SP_GEMM_KC_PLAIN;
   const int tiles = N / TILE;
   // Enough workgroups to keep every CU streaming, within the partial-sum buffer.  Every slice costs M*N*4 bytes
@@ -486,8 +496,8 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
 #undef SP_GOR
     return hipGetLastError();
   }
-  if (packed) return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, true>(MT, grid, st, X, W, out, nullptr, M, N, K, S);
-  return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, false>(MT, grid, st, X, W, out, nullptr, M, N, K, S);
+  if (packed) return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, true>(MT, grid, st, X, W, out, nullptr, M, N, K, S, nullptr, 0.f, frag);
+  return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, false>(MT, grid, st, X, W, out, nullptr, M, N, K, S, nullptr, 0.f, frag);
 }
 
 template <bool PACKED>
@@ -521,11 +531,11 @@ static hipError_t launch_even7(int MT, int n_wg, hipStream_t st, const bf16_t* X
   return hipGetLastError();
 }
 
-hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F,
+hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, bool frag, const bf16_t* W, bool packed, bf16_t* act, int M, int F,
                                       int K, int n_cu, const float* ssq, float eps, hipStream_t st) {
   int MT, mblocks;
   row_blocks(M, &MT, &mblocks);
-  if (ssq && MT != 1) return hipErrorInvalidValue;
+  if ((ssq || !frag) && MT != 1) return hipErrorInvalidValue;
   if (M < 1 || F % 64 || K % SP_GEMM_KC_GATEUP || K % 128) return hipErrorInvalidValue;
   // 17-48 rows and a d_ff that gives every CU the same 56 or 64 columns: one eight-wave workgroup per CU (more rows:
   // sp_gemm_mid.hip)
@@ -550,8 +560,8 @@ hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool pac
   }
   const int TILE = tile_cols(MT, true);
   const dim3 grid(F / TILE, 1, mblocks);
-  if (packed) return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, true>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, ssq, eps);
-  return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, false>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, ssq, eps);
+  if (packed) return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, true>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, ssq, eps, frag);
+  return launch_mt<SP_GEMM_NCG_GATEUP, true, SP_GEMM_KC_GATEUP, false>(MT, grid, st, X, W, nullptr, act, M, F, K, 1, ssq, eps, frag);
 }
 
 // Output head: per row the top column of every 64-column tile, as (value, index) pairs

@@ -31,9 +31,10 @@
 #define FEW_OUT 2          // residual of the last layer: the rows leave the stage
 
 struct FewArgs {
-  const bf16_t* X;         // [M][K] in fragment order
+  const bf16_t* X;         // [M][K], in fragment order or row-major
   const bf16_t* W;         // [N][K], row-major or in fragment order
   int M, N, K;
+  bool frag;
   const float* ssq_in;     // [M][K / 16] sums of squares of the rows behind X (nullptr: X is normalised already)
   float eps;
   // QKV
@@ -45,12 +46,12 @@ struct FewArgs {
   // O, down
   float* h;                // [M][N]
   const bf16_t* gain;      // [N] gain of the norm that follows
-  bf16_t* xn;              // [M][N] in fragment order
+  bf16_t* xn;              // [M][N], as X
   float* ssq_out;          // [M][N / 16]
   const AttnPlan* plan;    // FEW_OUT: x_out
 };
 
-template <int D, int NS, int MODE, bool PACKED, bool WNT>
+template <int D, int NS, int MODE, bool PACKED, bool WNT, bool FRAG>
 __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
   __shared__ __attribute__((aligned(16))) f32x4_t s_acc[NS][FEW_WAVES][64];
   __shared__ __attribute__((aligned(16))) float s_tot[16];
@@ -71,7 +72,8 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
   const int b = blockIdx.x * NS + (wave < NS ? wave : 0), head = b >> 3, t0 = (b & 7) * 8;
   constexpr int WSTEP = PACKED ? 512 : 32;
   // rows past M repeat the last row and multiply into output rows that are never stored
-  const bf16_t* x = a.X + (size_t)wave * n * 512 + (kg * 16 + min(r, M - 1)) * 8;
+  constexpr int XSTEP = FRAG ? 512 : 32;
+  const bf16_t* x = a.X + (size_t)wave * n * XSTEP + (FRAG ? (kg * 16 + min(r, M - 1)) * 8 : min(r, M - 1) * K + kg * 8);
   u32x4_t wf[NS][D], xf[D];
   f32x4_t acc[NS];
 #pragma unroll
@@ -84,7 +86,7 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
       const u32x4_t* wp_ = reinterpret_cast<const u32x4_t*>(w[i] + (size_t)p_ * WSTEP);                 \
       wf[i][j] = WNT ? __builtin_nontemporal_load(wp_) : *wp_;                                  \
     }                                                                                           \
-    xf[j] = *reinterpret_cast<const u32x4_t*>(x + (size_t)p_ * 512);                           \
+    xf[j] = *reinterpret_cast<const u32x4_t*>(x + p_ * XSTEP);                                 \
   }
 #define SP_MM(j)                                                                                \
   _Pragma("unroll") for (int i = 0; i < NS; ++i)                                                \
@@ -173,7 +175,7 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
     *reinterpret_cast<f32x4_t*>(a.h + (size_t)r * a.N + col) = y;
     pk.x = pack_bf16x2(y[0] * bf16_lo(gn.x), y[1] * bf16_hi(gn.x));
     pk.y = pack_bf16x2(y[2] * bf16_lo(gn.y), y[3] * bf16_hi(gn.y));
-    *reinterpret_cast<uint2*>(a.xn + frag_at(r, col, a.N)) = pk;
+    *reinterpret_cast<uint2*>(a.xn + row_at(FRAG, r, col, a.N)) = pk;
   }
 }
 
@@ -205,10 +207,10 @@ bool sp_few_takes(int M, int d, int dq, int F, bool packed, int n_cu) {
 }
 
 // Eight fragments in flight per wave; shapes whose k slices are shorter, or no multiple of that, take fewer.
-template <int MODE, bool PACKED, bool WNT>
-static hipError_t launch_few(const FewArgs& a, int n_cu, hipStream_t st) {
+template <int MODE, bool PACKED, bool WNT, bool FRAG>
+static hipError_t launch_few_as(const FewArgs& a, int n_cu, hipStream_t st) {
   const int n = a.K / (32 * FEW_WAVES);
-#define SP_GO(DV, NSV) hipLaunchKernelGGL((k_gemm_few<DV, NSV, MODE, PACKED, WNT>), dim3(a.N / 16 / NSV), dim3(64 * FEW_WAVES), 0, st, a)
+#define SP_GO(DV, NSV) hipLaunchKernelGGL((k_gemm_few<DV, NSV, MODE, PACKED, WNT, FRAG>), dim3(a.N / 16 / NSV), dim3(64 * FEW_WAVES), 0, st, a)
   if (MODE != FEW_QKV && two_strips(a.N, a.K, n_cu)) SP_GO(8, 2);
   else if (n % 8 == 0) SP_GO(8, 1);
   else if (n % 2 == 0) SP_GO(2, 1);
@@ -216,31 +218,35 @@ static hipError_t launch_few(const FewArgs& a, int n_cu, hipStream_t st) {
 #undef SP_GO
   return hipGetLastError();
 }
+template <int MODE, bool PACKED, bool WNT>
+static hipError_t launch_few(const FewArgs& a, int n_cu, hipStream_t st) {
+  return a.frag ? launch_few_as<MODE, PACKED, WNT, true>(a, n_cu, st) : launch_few_as<MODE, PACKED, WNT, false>(a, n_cu, st);
+}
 
-hipError_t sp_launch_few_qkv(const bf16_t* X, const bf16_t* W, bool packed, const float* ssq, float eps, const RowInfo* rows,
+hipError_t sp_launch_few_qkv(const bf16_t* X, bool frag, const bf16_t* W, bool packed, const float* ssq, float eps, const RowInfo* rows,
                              const float* cs, bf16_t* qbuf, KvGeom g, int layer, int M, int K, int n_q, int n_kv,
                              int n_cu, hipStream_t st) {
   if (M < 1 || M > 16 || K % 256 || g.row_bytes != 256) return hipErrorInvalidValue;
   FewArgs a = {};
-  a.X = X; a.W = W; a.M = M; a.N = (n_q + 2 * n_kv) * 128; a.K = K; a.ssq_in = ssq; a.eps = eps;
+  a.X = X; a.frag = frag; a.W = W; a.M = M; a.N = (n_q + 2 * n_kv) * 128; a.K = K; a.ssq_in = ssq; a.eps = eps;
   a.rows = rows; a.cs = cs; a.qbuf = qbuf; a.g = g; a.layer = layer; a.n_q = n_q; a.n_kv = n_kv;
   return packed ? launch_few<FEW_QKV, true, true>(a, n_cu, st) : launch_few<FEW_QKV, false, true>(a, n_cu, st);
 }
 
-hipError_t sp_launch_few_residual(const bf16_t* X, const bf16_t* W, bool packed, bool resident, float* h, const bf16_t* gain,
+hipError_t sp_launch_few_residual(const bf16_t* X, bool frag, const bf16_t* W, bool packed, bool resident, float* h, const bf16_t* gain,
                                   bf16_t* xn, float* ssq_out, int M, int N, int K, int n_cu,
                                   hipStream_t st) {
   if (M < 1 || M > 16 || K % 256 || N % 16) return hipErrorInvalidValue;
   FewArgs a = {};
-  a.X = X; a.W = W; a.M = M; a.N = N; a.K = K; a.h = h; a.gain = gain; a.xn = xn; a.ssq_out = ssq_out;
+  a.X = X; a.frag = frag; a.W = W; a.M = M; a.N = N; a.K = K; a.h = h; a.gain = gain; a.xn = xn; a.ssq_out = ssq_out;
   if (resident) return packed ? launch_few<FEW_RESIDUAL, true, false>(a, n_cu, st) : launch_few<FEW_RESIDUAL, false, false>(a, n_cu, st);
   return packed ? launch_few<FEW_RESIDUAL, true, true>(a, n_cu, st) : launch_few<FEW_RESIDUAL, false, true>(a, n_cu, st);
 }
 
-hipError_t sp_launch_few_out(const bf16_t* X, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
+hipError_t sp_launch_few_out(const bf16_t* X, bool frag, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
                              int N, int K, int n_cu, hipStream_t st) {
   if (M < 1 || M > 16 || K % 256 || N % 16) return hipErrorInvalidValue;
   FewArgs a = {};
-  a.X = X; a.W = W; a.M = M; a.N = N; a.K = K; a.h = const_cast<float*>(h); a.plan = plan_dev;
+  a.X = X; a.frag = frag; a.W = W; a.M = M; a.N = N; a.K = K; a.h = const_cast<float*>(h); a.plan = plan_dev;
   return packed ? launch_few<FEW_OUT, true, true>(a, n_cu, st) : launch_few<FEW_OUT, false, true>(a, n_cu, st);
 }

@@ -13,6 +13,8 @@
 //
 //   out[y][m][n] = sum_{k in slice y} X[m][k] * W[n][k]        (f32 partial sums)
 //   gate/up:      act[m][f] = silu(X Wg^T) * (X Wu^T)
+#include <type_traits>
+
 #include "sp_launch.h"
 
 #define MID_NS 2                         // strips of 16 weight rows per wave
@@ -21,10 +23,10 @@
 
 // MT row tiles; CW waves side by side, KQ that share their strips and cut a chunk's k steps between them; chunks of KC k;
 // activation panels D chunks ahead, weights PF chunks ahead; NPR waves that bring the panels in.
-template <int MT, int CW, int KQ, bool GATEUP, bool PACKED, bool WNT, int KC, int D, int PF, int NPR>
+template <int MT, int CW, int KQ, bool GATEUP, bool PACKED, bool WNT, int KC, int D, int PF, int NPR, bool WL>
 __global__ void __launch_bounds__(64 * (CW * KQ + NPR))
 k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
-           bf16_t* __restrict__ act, int M, int N, int K, int S, int cpw) {
+           bf16_t* __restrict__ act, int M, int N, int K, int S, int cpw, const float* ssq = nullptr, float eps = 0.f) {
   constexpr int NS = MID_NS;
   constexpr int NMM = CW * KQ, NTH = 64 * (NMM + NPR);  // waves that multiply, threads
   constexpr int CS = KC / 32, KSTEPS = CS / KQ;         // k steps of a chunk, and of a wave in it
@@ -37,6 +39,15 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   constexpr int WCOLS = 16 * NS * CW, LSF = WCOLS + 4;  // columns, and floats per LDS row of the plain products
   constexpr int OUT_BYTES = GATEUP ? 0 : ROWS * LSF * 4;
   constexpr int END_BYTES = FOLD_BYTES > OUT_BYTES ? FOLD_BYTES : OUT_BYTES;
+  // Row-major weights: a wave's rows come in as whole 128-byte lines (64 k), straight to LDS, and are read back as
+  // fragments; one array per set, so that the compiler knows which loads a read has to wait for.
+  constexpr int WSET = !WL ? 16 : NMM * NS * KSTEPS * 1024;
+  static_assert(PACKED || KSTEPS % 2 == 0, "whole lines of row-major weights");
+  __shared__ __attribute__((aligned(16))) char wl0[WSET];
+  __shared__ __attribute__((aligned(16))) char wl1[WSET];
+  __shared__ __attribute__((aligned(16))) char wl2[NB > 2 ? WSET : 16];
+#define SP_WSET(B) ((B) == 0 ? wl0 : (B) == 1 ? wl1 : wl2)
+  static_assert(!WL || NB <= 3, "weight sets");
   static_assert(BLOCKS % NPR == 0 && CS % KQ == 0 && KQ <= 2 && (D - 1) * NX < 64 && PF >= 1 && PF <= 3, "shape of the pipeline");
   __shared__ __attribute__((aligned(16))) char lds[NP * PANEL > END_BYTES ? NP * PANEL : END_BYTES];
 
@@ -66,6 +77,13 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   for (int a = 0; a < NS; ++a)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[a][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+
+  // one row tile of gate/up: the rows may come without their RMSNorm, whose scale is then a factor of the products
+  constexpr bool SCALED = GATEUP && MT == 1;
+  __shared__ float s_tot[SCALED ? 16 : 1];
+  RowSquares<64 * (SCALED ? NMM : 1)> sq;
+  static_assert(!SCALED || 16 % NMM == 0, "the multiplying waves share the rows evenly");
+  if (SCALED && mm && ssq) sq.load(ssq, K / 16, M);
 
   // One barrier per chunk.  Behind that of chunk C, panel C is complete and nobody reads panel C - 1 any more, whose
   // place panel C + D takes.  Loads past the last chunk go to an empty buffer: they cost an issue slot and keep every
@@ -99,7 +117,7 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   } else {
     // addresses as a uniform base per strip and an offset per lane (bytes), which up and gate strip share
     const bf16_t* w[NS];
-    int wl[GS];
+    int wl[GS][PACKED ? 1 : 2];
 #pragma unroll
     for (int a = 0; a < NS; ++a) {
       const int row0 = (GATEUP && a >= GS ? N : 0) + col0 + (a % GS) * 16;
@@ -108,32 +126,52 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
 #pragma unroll
     for (int g = 0; g < GS; ++g) {
       // a short last group re-reads its last row; its surplus products are dropped at the end
-      const int rr = GATEUP ? min(r, cpw - (cw * GS + g) * 16 - 1) : r;
-      const int in = (col0 & 15) + rr;    // row inside the strip's first fragment block, or in the one after it
-      wl[g] = PACKED ? (in >> 4) * (K * 32) + (kg * 16 + (in & 15)) * 16 : (rr * K + kg * 8) * 2;
+      const int last = GATEUP ? cpw - (cw * GS + g) * 16 - 1 : 15;
+      if (PACKED) {
+        const int in = (col0 & 15) + min(r, last);   // row inside the strip's first fragment block, or in the one after it
+        wl[g][0] = (in >> 4) * (K * 32) + (kg * 16 + (in & 15)) * 16;
+      } else {
+        // eight rows of 128 bytes per load; within a row the eight 16-byte units are exchanged by the row's number, which
+        // spreads a fragment's units over the LDS banks
+#pragma unroll
+        for (int h = 0; h < 2; ++h) wl[g][PACKED ? 0 : h] = min(h * 8 + (lane >> 3), last) * (K * 2) + ((lane & 7) ^ (lane >> 3)) * 16;
+      }
     }
-    u32x4_t wb[NB][NS][KSTEPS];
+    u32x4_t wb[!WL ? NB : 1][NS][KSTEPS];
+    const int wbase = wave * (NS * KSTEPS * 1024), wread = wbase + (PACKED ? lane * 16 : (r >> 3) * 1024 + (r & 7) * 128);
 #define SP_LOAD_W(B, C)                                                                                 \
   {                                                                                                     \
     const bool on_ = (C) < c_end;                                                                       \
     const int pc_ = SP_PC(C);                                                                           \
     _Pragma("unroll") for (int a = 0; a < NS; ++a) {                                                    \
       const auto buf_ = buffer_at(w[a], on_);                                                           \
-      _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s)                                                \
-        wb[B][a][s] = __builtin_amdgcn_raw_buffer_load_b128(                                            \
-            buf_, wl[a % GS], PACKED ? (pc_ * CS + s) * 1024 : (pc_ * KC + s * 32) * 2, WNT ? 2 : 0);   \
+      _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s) {                                              \
+        if (!WL)                                                                                        \
+          wb[!WL ? (B) : 0][a][s] = __builtin_amdgcn_raw_buffer_load_b128(buf_, wl[a % GS][0], (pc_ * CS + s) * 1024, WNT ? 2 : 0); \
+        else if (PACKED)                                                                                \
+          load_to_lds<WNT>(buf_, SP_WSET(B) + wbase + (a * KSTEPS + s) * 1024, wl[a % GS][0], (pc_ * CS + s) * 1024); \
+        else    /* load s: rows (s % 2) * 8 .. + 7, k group s / 2 */                                    \
+          load_to_lds<WNT>(buf_, SP_WSET(B) + wbase + (a * KSTEPS + s) * 1024, wl[a % GS][PACKED ? 0 : s % 2], (pc_ * KC + s / 2 * 64) * 2); \
+      }                                                                                                 \
     }                                                                                                   \
     __builtin_amdgcn_sched_barrier(0);                                                                  \
+  }
+  // row-major: fragments of set B, strip a, k step s, out of LDS
+#define SP_READ_W(B)                                                                                    \
+  if (WL) {                                                                                             \
+    _Pragma("unroll") for (int a = 0; a < NS; ++a) _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s)   \
+      wb[0][a][s] = *reinterpret_cast<const u32x4_t*>(SP_WSET(B) + wread + (PACKED ? (a * KSTEPS + s) * 1024 : (a * KSTEPS + s / 2 * 2) * 1024 + ((s % 2 * 4 + kg) ^ (r & 7)) * 16)); \
   }
     int pan = lane * 16;
 #define SP_CHUNK(B, C)                                                                                  \
   if ((C) < c_end) {                                                                                    \
     bare_barrier();                                                                                     \
     SP_LOAD_W(((B) + PF) % NB, (C) + PF)                                                                \
+    SP_READ_W(B)                                                                                        \
     _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s) _Pragma("unroll") for (int mt = 0; mt < MT; ++mt) { \
       const bf16x8_t b = *reinterpret_cast<const bf16x8_t*>(lds + pan + (mt * CS + kq * KSTEPS + s) * 1024); \
       _Pragma("unroll") for (int a = 0; a < NS; ++a) acc[a][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16( \
-          *reinterpret_cast<const bf16x8_t*>(&wb[B][a][s]), b, acc[a][mt], 0, 0, 0);                    \
+          *reinterpret_cast<const bf16x8_t*>(&wb[!WL ? (B) : 0][a][s]), b, acc[a][mt], 0, 0, 0);     \
     }                                                                                                   \
     pan = pan + PANEL >= NP * PANEL ? pan + PANEL - NP * PANEL : pan + PANEL;                           \
     __builtin_amdgcn_sched_barrier(0);                                                                  \
@@ -148,9 +186,12 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
     }
 #undef SP_CHUNK
 #undef SP_LOAD_W
+#undef SP_READ_W
+#undef SP_WSET
   }
 #undef SP_PC
 
+  if (SCALED && mm && ssq) sq.post(ssq, K / 16, M, s_tot);
   if (KQ > 1) {
     // Fold the two waves that share their strips: strip by strip, a wave leaves the row tiles that are not its own (tile
     // mt belongs to wave mt % 2) and adds the other's products of its own tiles, in order.
@@ -178,6 +219,9 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   // lane holds, for row m = mt*16 + l%16 of its own tiles, columns (strip base) + 4*(l/16) + 0..3
   if (GATEUP) {
     if (!mm) return;
+    static_assert(!SCALED || KQ > 1, "the fold's barrier stands between the row sums and their use");
+    float row_scale = 1.f;
+    if (SCALED && ssq) row_scale = rsqrtf(s_tot[min(r, M - 1)] / (float)K + eps);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const int m = mt * 16 + r;
@@ -188,7 +232,8 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
         float o[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float gte = acc[g][mt][i], up = acc[GS + g < NS ? GS + g : 0][mt][i];
+          const float gte = SCALED ? acc[g][mt][i] * row_scale : acc[g][mt][i];
+          const float up = SCALED ? acc[GS + g < NS ? GS + g : 0][mt][i] * row_scale : acc[GS + g < NS ? GS + g : 0][mt][i];
           o[i] = gte / (1.f + __expf(-gte)) * up;
         }
         uint2 pk;
@@ -223,36 +268,58 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
 }
 
 // row tiles of a launch: the kernel is compiled for these heights
-static inline int mid_tiles(int M) { return M <= 64 ? 4 : M <= 96 ? 6 : M <= 128 ? 8 : 10; }
-
-template <int NSTRIPS, bool PACKED, bool WNT>
-static hipError_t launch_plain(dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out, int M, int N, int K, int S) {
-#define SP_GO(MTV, KCV, DV, PFV)                                                                                          \
-  hipLaunchKernelGGL((k_gemm_mid<MTV, NSTRIPS / 2, 2, false, PACKED, WNT, KCV, DV, PFV, MID_NPR>), grid,                  \
-                     dim3(64 * (NSTRIPS + MID_NPR)), 0, st, X, W, out, nullptr, M, N, K, S, 0)
-  switch (mid_tiles(M)) {
-    case 4: SP_GO(4, 128, 2, 2); break;
-    case 6: SP_GO(6, 128, 2, 2); break;
-    case 8: SP_GO(8, 128, 2, 2); break;
-    default: SP_GO(10, 64, 3, 3); break;
+static inline int mid_tiles(int M) { return M <= 64 ? (M + 15) / 16 : M <= 96 ? 6 : M <= 128 ? 8 : 10; }
+#define SP_BY_TILES(GO)       \
+  switch (mid_tiles(M)) {     \
+    case 1: GO(1) break;      \
+    case 2: GO(2) break;      \
+    case 3: GO(3) break;      \
+    case 4: GO(4) break;      \
+    case 6: GO(6) break;      \
+    case 8: GO(8) break;      \
+    default: GO(10) break;    \
   }
+
+// Chunk length, how far panels and weights are ahead, loading waves, and whether the weights go through LDS, within
+// 160 KB of LDS and 168 registers.
+template <int KC_, int D_, int PF_, bool WL_> struct MidPipe {
+  static constexpr int KC = KC_, D = D_, PF = PF_;
+  static constexpr bool WL = WL_;
+};
+template <int MT, bool PACKED, bool SHORT> struct PlainPipe
+    : std::conditional_t<!PACKED, std::conditional_t<(MT <= 4), MidPipe<128, 2, 2, true>, std::conditional_t<(MT <= 6), MidPipe<128, 2, 1, true>, MidPipe<128, 1, 1, true>>>,
+                         std::conditional_t<(MT > 8 || (MT == 8 && SHORT)), MidPipe<64, 3, 2, true>,
+                                            std::conditional_t<(MT <= 6), MidPipe<128, 2, 1, true>, MidPipe<128, 2, 2, false>>>> {};
+template <int MT, int KQ, bool PACKED> struct GateupPipe
+    : std::conditional_t<KQ == 1, std::conditional_t<(MT <= 8 || !PACKED), MidPipe<64, MT <= 8 ? 3 : 2, MT <= 8 && PACKED ? 2 : 1, true>, MidPipe<128, 2, 1, false>>,
+                         std::conditional_t<(MT <= 6), MidPipe<128, 2, (MT <= 4 && !PACKED) ? 2 : 1, true>,
+                                            std::conditional_t<PACKED, MidPipe<128, 2, 2, false>, MidPipe<128, 1, 1, true>>>> {};
+
+template <int NSTRIPS, bool PACKED, bool WNT, bool SHORT>
+static hipError_t launch_plain(dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out, int M, int N, int K, int S) {
+#define SP_GO(MTV)                                                                                                        \
+  {                                                                                                                       \
+    typedef PlainPipe<MTV, PACKED, SHORT> P;                                                                              \
+    hipLaunchKernelGGL((k_gemm_mid<MTV, NSTRIPS / 2, 2, false, PACKED, WNT, P::KC, P::D, P::PF, MID_NPR, P::WL>), grid,   \
+                       dim3(64 * (NSTRIPS + MID_NPR)), 0, st, X, W, out, nullptr, M, N, K, S, 0, nullptr, 0.f);           \
+  }
+  SP_BY_TILES(SP_GO)
 #undef SP_GO
   return hipGetLastError();
 }
 
 // gate/up: CW groups of 16 columns
 template <int CW, int KQ, bool PACKED>
-static hipError_t launch_gateup(int n_cu, hipStream_t st, const bf16_t* X, const bf16_t* W, bf16_t* act, int M, int F, int K) {
-  constexpr int NPR = KQ == 2 ? MID_NPR : 1, PF = KQ == 2 ? 2 : 1;
-#define SP_GO(MTV)                                                                                                   \
-  hipLaunchKernelGGL((k_gemm_mid<MTV, CW, KQ, true, PACKED, true, 128, 2, PF, NPR>), dim3(n_cu), dim3(64 * (CW * KQ + NPR)), 0, \
-                     st, X, W, nullptr, act, M, F, K, 1, F / n_cu)
-  switch (mid_tiles(M)) {
-    case 4: SP_GO(4); break;
-    case 6: SP_GO(6); break;
-    case 8: SP_GO(8); break;
-    default: SP_GO(10); break;
-  }
+static hipError_t launch_gateup(int n_cu, hipStream_t st, const bf16_t* X, const bf16_t* W, bf16_t* act, int M, int F, int K,
+                                const float* ssq, float eps) {
+  constexpr int NPR = KQ == 2 ? MID_NPR : 1;
+#define SP_GO(MTV)                                                                                                        \
+  if constexpr (MTV > 1 || KQ > 1) {                                                                                      \
+    typedef GateupPipe<MTV, KQ, PACKED> P;                                                                                \
+    hipLaunchKernelGGL((k_gemm_mid<MTV, CW, KQ, true, PACKED, true, P::KC, P::D, P::PF, NPR, P::WL>), dim3(n_cu),         \
+                       dim3(64 * (CW * KQ + NPR)), 0, st, X, W, nullptr, act, M, F, K, 1, F / n_cu, ssq, eps);            \
+  } else return hipErrorInvalidValue;
+  SP_BY_TILES(SP_GO)
 #undef SP_GO
   return hipGetLastError();
 }
@@ -283,24 +350,24 @@ static MidCut mid_cut(int M, int N, int K, int n_cu) {
 // chunk do not earn back (97 rows: 768 wide 60.5 / 62.9, 1024 wide 69.5 / 71.8; with two chunks in QKV alone, 2048 wide,
 // 94.5 / 92.5), nor do two slices of a wide matrix (12288 wide 451 / 470, row-major 605 / 638).  65-96 and 129-160 rows:
 // level (768 wide) to 8 % faster throughout.
-bool sp_gemm_mid_takes(int M, int N, int K, int n_cu) {
-  if (M <= 48 || M > 160 || N % 128 || K % MID_KC) return false;
+bool sp_gemm_mid_takes(int M, int N, int K, bool packed, int n_cu) {
+  if (M < 1 || M > 160 || N % 128 || K % MID_KC) return false;
   const MidCut cut = mid_cut(M, N, K, n_cu);
-  if (M <= 64) return K > 8192 && cut.cols == 128 && cut.S >= 3;
-  if (M > 96 && M <= 128) return cut.S >= 3 && K / MID_KC >= 2 * (cut.S < 16 ? cut.S : 16);
+  if (!packed) return cut.S >= 1;
+  if (M <= 64) return M > 16 && K >= 1024 * cut.S && cut.S >= 1;
   return true;
 }
-// columns of a CU's share of the gate/up product: 48 < cpw <= 64 (four groups, two waves each) or, from 65 rows on,
+// columns of a CU's share of the gate/up product: 48 < cpw <= 64 (four groups, two waves each) or, from two row tiles on,
 // 96 < cpw <= 112 (seven groups, one wave each)
-bool sp_gemm_mid_takes_gateup(int M, int F, int K, int n_cu) {
-  if (M <= 48 || M > 160 || K % 128 || n_cu < 1 || F % n_cu || (F / n_cu) % 8) return false;
+bool sp_gemm_mid_takes_gateup(int M, int F, int K, bool packed, int n_cu) {
+  if (M < (packed ? 17 : 1) || M > 160 || K % 128 || n_cu < 1 || F % n_cu || (F / n_cu) % 8) return false;
   const int cpw = F / n_cu;
-  return (cpw > 48 && cpw <= 64) || (M > 64 && cpw > 96 && cpw <= 112);
+  return (cpw > 48 && cpw <= 64) || (M > 16 && cpw > 96 && cpw <= 112);
 }
 
 hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,
                               int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident) {
-  if (!sp_gemm_mid_takes(M, N, K, n_cu)) return hipErrorInvalidValue;
+  if (!sp_gemm_mid_takes(M, N, K, packed, n_cu)) return hipErrorInvalidValue;
   const MidCut cut = mid_cut(M, N, K, n_cu);
   const bool six = cut.cols == 96;
   const int tiles = N / cut.cols, chunks = K / MID_KC;
@@ -312,16 +379,21 @@ hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, flo
   if ((size_t)S * M * N > part_capacity_floats) return hipErrorInvalidValue;
   *S_out = S;
   const dim3 grid(tiles, S);
-  if (six && resident) return packed ? launch_plain<6, true, false>(grid, st, X, W, out, M, N, K, S) : launch_plain<6, false, false>(grid, st, X, W, out, M, N, K, S);
-  if (six) return packed ? launch_plain<6, true, true>(grid, st, X, W, out, M, N, K, S) : launch_plain<6, false, true>(grid, st, X, W, out, M, N, K, S);
-  if (resident) return packed ? launch_plain<8, true, false>(grid, st, X, W, out, M, N, K, S) : launch_plain<8, false, false>(grid, st, X, W, out, M, N, K, S);
-  return packed ? launch_plain<8, true, true>(grid, st, X, W, out, M, N, K, S) : launch_plain<8, false, true>(grid, st, X, W, out, M, N, K, S);
+#define SP_GO(STRIPS, PK, NT, SH) return launch_plain<STRIPS, PK, NT, SH>(grid, st, X, W, out, M, N, K, S)
+#define SP_BY_CACHE(STRIPS, PK, SH) { if (resident) SP_GO(STRIPS, PK, false, SH); else SP_GO(STRIPS, PK, true, SH); }
+#define SP_BY_STRIPS(PK, SH) { if (six) SP_BY_CACHE(6, PK, SH) else SP_BY_CACHE(8, PK, SH) }
+  if (!packed) SP_BY_STRIPS(false, false)
+  if (K / S <= 2048) SP_BY_STRIPS(true, true)
+  SP_BY_STRIPS(true, false)
+#undef SP_BY_STRIPS
+#undef SP_BY_CACHE
+#undef SP_GO
 }
 
 hipError_t sp_launch_gemm_mid_gateup(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F, int K, int n_cu,
-                                     hipStream_t st) {
-  if (!sp_gemm_mid_takes_gateup(M, F, K, n_cu)) return hipErrorInvalidValue;
+                                     const float* ssq, float eps, hipStream_t st) {
+  if (!sp_gemm_mid_takes_gateup(M, F, K, packed, n_cu) || (ssq && M > 16)) return hipErrorInvalidValue;
   if (F / n_cu > 64)
-    return packed ? launch_gateup<7, 1, true>(n_cu, st, X, W, act, M, F, K) : launch_gateup<7, 1, false>(n_cu, st, X, W, act, M, F, K);
-  return packed ? launch_gateup<4, 2, true>(n_cu, st, X, W, act, M, F, K) : launch_gateup<4, 2, false>(n_cu, st, X, W, act, M, F, K);
+    return packed ? launch_gateup<7, 1, true>(n_cu, st, X, W, act, M, F, K, ssq, eps) : launch_gateup<7, 1, false>(n_cu, st, X, W, act, M, F, K, ssq, eps);
+  return packed ? launch_gateup<4, 2, true>(n_cu, st, X, W, act, M, F, K, ssq, eps) : launch_gateup<4, 2, false>(n_cu, st, X, W, act, M, F, K, ssq, eps);
 }

@@ -119,40 +119,42 @@ hipError_t sp_launch_gateup_f32(const float* X, const float* W, float* act, int 
 hipError_t sp_launch_attn_f32(const float* q, const RowInfo* rows, const ReqTables* tables, KvGeom g, int layer, float* out,
                               int M, int n_q, int n_kv, int d_head, hipStream_t st);
 // bf16 MFMA kernels: the rows X and the gate/up products are in fragment order (frag_at).  Returns the split count used in *S_out (partials [S][M][N]).  packed: the
-// weights are in MFMA fragment order (sp_launch_pack_weights).
+// weights are in MFMA fragment order (sp_launch_pack_weights); frag false (at most eight rows): X is row-major.
 hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st,
-                               bool resident = false);
+                               bool resident = false, bool frag = true);
 hipError_t sp_launch_gemm_logits_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* logits, float* stats, float inv_T,
                                       int M, int V, int K, int* tile_cols, hipStream_t st);
 // act[m][f] = silu(X Wg^T) * (X Wu^T), W = [gate rows ; up rows]
 hipError_t sp_launch_gemm_argmax_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* pairs, int M, int V, int K,
                                       size_t pair_capacity_floats, int* tiles_out, hipStream_t st);
-// ssq (nullable, M <= 16 only): [M][K / 16] sums of squares of the rows, X is then not normalised yet
-hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F,
+// ssq (nullable, M <= 16 only): [M][K / 16] sums of squares of the rows, X is then not normalised yet.  frag false (M <= 16
+// only): X and the products are row-major.
+hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, bool frag, const bf16_t* W, bool packed, bf16_t* act, int M, int F,
                                       int K, int n_cu, const float* ssq, float eps, hipStream_t st);
 // One row tile (M <= 16), fast path: complete projections with what follows them as their epilogue (sp_gemm_few.hip);
-// `takes` says for which sizes these are to be called (d = d_model, dq = n_q * d_head).
+// `takes` says for which sizes these are to be called (d = d_model, dq = n_q * d_head).  frag: how X and the rows left for
+// the next product lie.
 bool sp_few_takes(int M, int d, int dq, int F, bool packed, int n_cu);
 // ssq (nullable): [M][d / 16] sums of squares of the rows, X is then not normalised yet.
-hipError_t sp_launch_few_qkv(const bf16_t* X, const bf16_t* W, bool packed, const float* ssq, float eps, const RowInfo* rows,
+hipError_t sp_launch_few_qkv(const bf16_t* X, bool frag, const bf16_t* W, bool packed, const float* ssq, float eps, const RowInfo* rows,
                              const float* cs, bf16_t* qbuf, KvGeom g, int layer, int M, int K, int n_q, int n_kv,
                              int n_cu, hipStream_t st);
 // h += X W^T; xn = bf16(h * gain); ssq_out[M][N / 16]
-hipError_t sp_launch_few_residual(const bf16_t* X, const bf16_t* W, bool packed, bool resident, float* h, const bf16_t* gain,
+hipError_t sp_launch_few_residual(const bf16_t* X, bool frag, const bf16_t* W, bool packed, bool resident, float* h, const bf16_t* gain,
                                   bf16_t* xn, float* ssq_out, int M, int N, int K, int n_cu,
                                   hipStream_t st);
 // rows of the plan's x_out = bf16(h + X W^T)
-hipError_t sp_launch_few_out(const bf16_t* X, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
+hipError_t sp_launch_few_out(const bf16_t* X, bool frag, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
                              int N, int K, int n_cu, hipStream_t st);
 // 49-160 rows (sp_gemm_mid.hip): one workgroup per CU, two strips of weight rows per wave; `takes` says for which
 // sizes these are to be called (gate/up: where every CU gets the same 56 or 64 columns)
-bool sp_gemm_mid_takes(int M, int N, int K, int n_cu);
-bool sp_gemm_mid_takes_gateup(int M, int F, int K, int n_cu);
+bool sp_gemm_mid_takes(int M, int N, int K, bool packed, int n_cu);
+bool sp_gemm_mid_takes_gateup(int M, int F, int K, bool packed, int n_cu);
 hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,
                               int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident);
 hipError_t sp_launch_gemm_mid_gateup(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F, int K, int n_cu,
-                                     hipStream_t st);
+                                     const float* ssq, float eps, hipStream_t st);
 // Many rows (more than the kernels above take): workgroups of 128 or 256 rows x 256 columns, weights kept in registers per wave.
 // Needs N % 256 == 0 (gate/up: F % 128 == 0) and K % 64 == 0.
 hipError_t sp_launch_gemm_wide(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
@@ -168,5 +170,5 @@ hipError_t sp_launch_attn_simple(int dtype, const void* q, const RowInfo* rows, 
 
 // plan: host copy (grid sizes); plan_dev: the device copy the kernels read
 hipError_t sp_launch_attn_bf16(const bf16_t* q, const ReqTables* tables, KvGeom g, int layer, const AttnPlan& plan,
-                               const AttnPlan* plan_dev, float* part /*workspace*/, bf16_t* out, int M, int n_q,
-                               int n_kv, int d_head, hipStream_t st);
+                               const AttnPlan* plan_dev, float* part /*workspace*/, bf16_t* out, bool frag, int M,
+                               int n_q, int n_kv, int d_head, hipStream_t st);

@@ -60,8 +60,10 @@ __device__ __forceinline__ f32x4_t fold4(const float* p, int S, size_t stride) {
 // Then xn[row] = h * rsqrt(mean(h^2)+eps) * gain, in fragment order where the matrix-core kernels read it (frag).  The
 // first two passes stay in registers.
 #define ENTER_ROWS 4       // rows a workgroup of descriptors and rotary tables takes (few: double precision is slow)
-// Workgroups of the rows: one each, in fragment order in whole groups of 64 (eight rows for each of the eight XCDs).
-__host__ __device__ inline int norm_blocks(int M, bool frag) { return frag ? (M + 63) / 64 * 64 : M; }
+// Workgroups of the rows: one each.  Fragment order puts eight rows into a 128-byte line: they go to the same XCD, whose L2
+// puts the line together, in whole groups of 64 rows (145 rows 7.1 -> 6.8 us).  Up to 64 rows that would leave XCDs, and
+// their share of the bandwidth for the partial sums, idle (24 rows 9.1 us against 7.2): consecutive workgroups there.
+__host__ __device__ inline int norm_blocks(int M, bool frag) { return frag && M > 64 ? (M + 63) / 64 * 64 : M; }
 struct NoPlan { int unused; };
 template <bool FIRST> struct PlanArg { typedef NoPlan type; };
 template <> struct PlanArg<true> { typedef AttnPlan type; };
@@ -74,8 +76,7 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
                                                     float* cs, int d_head, float theta, bool frag) {
   __shared__ float s_red[16];
   const int row_blocks = norm_blocks(M, frag);
-  // fragment order puts eight rows into a 128-byte line: they go to the same XCD, whose L2 puts the line together
-  const int row = frag ? (((blockIdx.x >> 6) * 8 + (blockIdx.x & 7)) * 8 + ((blockIdx.x >> 3) & 7)) : blockIdx.x;
+  const int row = row_blocks != M ? (((blockIdx.x >> 6) * 8 + (blockIdx.x & 7)) * 8 + ((blockIdx.x >> 3) & 7)) : blockIdx.x;
   if constexpr (FIRST) {
     const int half = d_head >> 1;
     if ((int)blockIdx.x >= row_blocks) {
@@ -133,10 +134,10 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     const int c = c0 + p * step;
-    if (c < d) Vec4<T>::st(xn + (frag ? frag_at(row, c, d) : (size_t)row * d + c), keep[p] * scale * Vec4<T>::ld(gain + c));
+    if (c < d) Vec4<T>::st(xn + row_at(frag, row, c, d), keep[p] * scale * Vec4<T>::ld(gain + c));
   }
   for (int c = c0 + 2 * step; c < d; c += step)
-    Vec4<T>::st(xn + (frag ? frag_at(row, c, d) : (size_t)row * d + c),
+    Vec4<T>::st(xn + row_at(frag, row, c, d),
                 *reinterpret_cast<const f32x4_t*>(hr + c) * scale * Vec4<T>::ld(gain + c));
 }
 

@@ -33,7 +33,7 @@ __global__ void __launch_bounds__(1024) k_row_norm(const T* __restrict__ x, cons
   for (int w = 0; w < 16; ++w) tot += s_red[w];
   const float rs = rsqrtf(tot / (float)d + eps);
   for (int c = threadIdx.x; c < d; c += 1024)
-    Elt<T>::st(xn + (frag ? frag_at(row, c, d) : (size_t)row * d + c), Elt<T>::ld(xr + c) * rs * Elt<T>::ld(gain + c));
+    Elt<T>::st(xn + row_at(frag, row, c, d), Elt<T>::ld(xr + c) * rs * Elt<T>::ld(gain + c));
 }
 
 // The root's children in node order: s_node[0..nc), their tokens in s_tok.  Called by all threads (256 or more).
