@@ -661,8 +661,10 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   const size_t strideD = (size_t)M * d, strideQ = (size_t)M * nqkv;
   const bool few = s->fast && sp_few_takes(M, d, dq, F, s->packed, s->n_cu);
   // Activations between the products in fragment order, but up to four rows row-major where no product takes them by
-  // direct-to-LDS loads (8B shape, one node: 105.7 -> 104.0 us; eight rows gain from the fragments, 101.5 -> 99.8 us a layer).
-  const bool frag = s->fast && !(M <= 4 && (s->packed || (few && !sp_gemm_mid_takes_gateup(M, F, d, false, s->n_cu))));
+  // direct-to-LDS loads (8B shape, one node: 105.7 -> 104.0 us; eight rows gain from the fragments, 101.5 -> 99.8 us a layer),
+  // and in the many-row kernel beside row-major weights.
+  const bool frag = s->fast && !(M <= 4 && (s->packed || (few && !sp_gemm_mid_takes_gateup(M, F, d, false, s->n_cu)))) &&
+                    (s->packed || M <= 160);
   // projections: few rows stream the weights (HBM-bound); many rows use the register-blocked kernel
   const bool wide = s->fast && M > 128 && nqkv % 256 == 0 && d % 256 == 0 && F % 128 == 0 && dq % 128 == 0;
   auto gemm = [&](const void* X, const void* Wm, int N_, int K_, int* S_, bool resident = false) -> hipError_t {
@@ -670,7 +672,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       return sp_launch_gemm_mid((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, s->n_cu, 16,
                                 w.part_floats, S_, st, resident);
     if (wide)
-      return sp_launch_gemm_wide((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, s->n_cu,
+      return sp_launch_gemm_wide((const bf16_t*)X, frag, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, s->n_cu,
                                  w.part_floats, S_, st);
     return sp_launch_gemm_bf16((const bf16_t*)X, (const bf16_t*)Wm, s->packed, w.part, M, N_, K_, 16, w.part_floats,
                                S_, st, resident, frag);
@@ -742,7 +744,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       { ProfScope p(s, SP_K_GEMM_GATEUP, st);
         if (s->fast) {
           if (sp_gemm_mid_takes_gateup(M, F, d, s->packed, s->n_cu)) SP_STEP(sp_launch_gemm_mid_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, nullptr, 0.f, st));
-          else if (wide) SP_STEP(sp_launch_gemm_wide_gateup((const bf16_t*)w.xn, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, st));
+          else if (wide) SP_STEP(sp_launch_gemm_wide_gateup((const bf16_t*)w.xn, frag, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, st));
           else SP_STEP(sp_launch_gemm_gateup_bf16((const bf16_t*)w.xn, frag, (const bf16_t*)L.wgu, s->packed, (bf16_t*)w.act, M, F, d, s->n_cu, nullptr, 0.f, st));
         } else if (s->f32) {
           SP_STEP(sp_launch_gateup_f32((const float*)w.xn, (const float*)L.wgu, (float*)w.act, M, F, d, st));

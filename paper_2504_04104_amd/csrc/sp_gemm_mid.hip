@@ -159,6 +159,7 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   // row-major: fragments of set B, strip a, k step s, out of LDS
 #define SP_READ_W(B)                                                                                    \
   if (WL) {                                                                                             \
+    SP_WAIT_VMEM(PF * NS * KSTEPS);       /* the sets behind this one */                                \
     _Pragma("unroll") for (int a = 0; a < NS; ++a) _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s)   \
       wb[0][a][s] = *reinterpret_cast<const u32x4_t*>(SP_WSET(B) + wread + (PACKED ? (a * KSTEPS + s) * 1024 : (a * KSTEPS + s / 2 * 2) * 1024 + ((s % 2 * 4 + kg) ^ (r & 7)) * 16)); \
   }
@@ -268,7 +269,7 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
 }
 
 // row tiles of a launch: the kernel is compiled for these heights
-static inline int mid_tiles(int M) { return M <= 64 ? (M + 15) / 16 : M <= 96 ? 6 : M <= 128 ? 8 : 10; }
+static inline int mid_tiles(int M) { return M <= 64 ? (M + 15) / 16 : M <= 96 ? 6 : M <= 128 ? 8 : M <= 160 ? 10 : 12; }
 #define SP_BY_TILES(GO)       \
   switch (mid_tiles(M)) {     \
     case 1: GO(1) break;      \
@@ -277,7 +278,8 @@ static inline int mid_tiles(int M) { return M <= 64 ? (M + 15) / 16 : M <= 96 ? 
     case 4: GO(4) break;      \
     case 6: GO(6) break;      \
     case 8: GO(8) break;      \
-    default: GO(10) break;    \
+    case 10: GO(10) break;    \
+    default: GO(12) break;    \
   }
 
 // Chunk length, how far panels and weights are ahead, loading waves, and whether the weights go through LDS, within
@@ -293,16 +295,17 @@ template <int MT, bool PACKED, bool SHORT> struct PlainPipe
 template <int MT, int KQ, bool PACKED> struct GateupPipe
     : std::conditional_t<KQ == 1, std::conditional_t<(MT <= 8 || !PACKED), MidPipe<64, MT <= 8 ? 3 : 2, MT <= 8 && PACKED ? 2 : 1, true>, MidPipe<128, 2, 1, false>>,
                          std::conditional_t<(MT <= 6), MidPipe<128, 2, (MT <= 4 && !PACKED) ? 2 : 1, true>,
-                                            std::conditional_t<PACKED, MidPipe<128, 2, 2, false>, MidPipe<128, 1, 1, true>>>> {};
+                                            std::conditional_t<(MT > 10), MidPipe<64, 3, 3, false>,
+                                                               std::conditional_t<PACKED, MidPipe<128, 2, 2, false>, MidPipe<128, 1, 1, true>>>>> {};
 
 template <int NSTRIPS, bool PACKED, bool WNT, bool SHORT>
 static hipError_t launch_plain(dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out, int M, int N, int K, int S) {
 #define SP_GO(MTV)                                                                                                        \
-  {                                                                                                                       \
+  if constexpr (MTV <= 10) {                                                                                              \
     typedef PlainPipe<MTV, PACKED, SHORT> P;                                                                              \
     hipLaunchKernelGGL((k_gemm_mid<MTV, NSTRIPS / 2, 2, false, PACKED, WNT, P::KC, P::D, P::PF, MID_NPR, P::WL>), grid,   \
                        dim3(64 * (NSTRIPS + MID_NPR)), 0, st, X, W, out, nullptr, M, N, K, S, 0, nullptr, 0.f);           \
-  }
+  } else return hipErrorInvalidValue;
   SP_BY_TILES(SP_GO)
 #undef SP_GO
   return hipGetLastError();
@@ -314,7 +317,7 @@ static hipError_t launch_gateup(int n_cu, hipStream_t st, const bf16_t* X, const
                                 const float* ssq, float eps) {
   constexpr int NPR = KQ == 2 ? MID_NPR : 1;
 #define SP_GO(MTV)                                                                                                        \
-  if constexpr (MTV > 1 || KQ > 1) {                                                                                      \
+  if constexpr ((MTV > 1 || KQ > 1) && (MTV <= 10 || (KQ == 2 && PACKED))) {                                              \
     typedef GateupPipe<MTV, KQ, PACKED> P;                                                                                \
     hipLaunchKernelGGL((k_gemm_mid<MTV, CW, KQ, true, PACKED, true, P::KC, P::D, P::PF, NPR, P::WL>), dim3(n_cu),         \
                        dim3(64 * (CW * KQ + NPR)), 0, st, X, W, nullptr, act, M, F, K, 1, F / n_cu, ssq, eps);            \
@@ -360,9 +363,9 @@ bool sp_gemm_mid_takes(int M, int N, int K, bool packed, int n_cu) {
 // columns of a CU's share of the gate/up product: 48 < cpw <= 64 (four groups, two waves each) or, from two row tiles on,
 // 96 < cpw <= 112 (seven groups, one wave each)
 bool sp_gemm_mid_takes_gateup(int M, int F, int K, bool packed, int n_cu) {
-  if (M < (packed ? 17 : 1) || M > 160 || K % 128 || n_cu < 1 || F % n_cu || (F / n_cu) % 8) return false;
+  if (M < (packed ? 17 : 1) || M > 192 || K % 128 || n_cu < 1 || F % n_cu || (F / n_cu) % 8) return false;
   const int cpw = F / n_cu;
-  return (cpw > 48 && cpw <= 64) || (M > 16 && cpw > 96 && cpw <= 112);
+  return cpw > 48 && cpw <= 64 ? M <= 160 || packed : M > 16 && M <= 160 && cpw > 96 && cpw <= 112;
 }
 
 hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,

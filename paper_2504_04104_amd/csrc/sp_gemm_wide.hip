@@ -15,6 +15,7 @@
 #ifndef WKC
 #define WKC 64                  // k per staged chunk
 #endif
+#define WXS (WKC * 2 + 16)      // LDS row stride of a row-major panel in bytes
 
 // Loads run NB-1 chunks ahead of the math in NB weight register sets, with NB LDS panels.  The
 // memory counter retires loads in issue order, so activations and weights of one chunk are
@@ -22,7 +23,7 @@
 // never forces a younger weight load.  Chunk indices past the end are clamped (a few redundant
 // loads at the tail keep every chunk one straight-line block, which lets the LDS reads be
 // scheduled among the MFMAs).
-template <int SPW, int MT, bool GATEUP, bool PACKED>
+template <int SPW, int MT, bool GATEUP, bool PACKED, bool XF>
 __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W,
                                           float* __restrict__ out, bf16_t* __restrict__ act, int M, int N, int K,
                                           int tile, int m_base, int c_begin, int c_end, char* lds_raw) {
@@ -31,10 +32,13 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
   constexpr int KSTEPS = WKC / 32;
   constexpr int ITEMS = KSTEPS * MT;               // (k step, row tile) pairs of a chunk
   constexpr int BQ = 4;                            // activation fragments read ahead of their MFMAs
-  constexpr int UPT = WKC * 2, UNITS = MT * UPT;   // 16-byte units of a row tile's chunk, and of a panel (fragment order)
+  // XF: the activations lie in fragment order.  From 161 rows on beside row-major weights they are row-major (the 256-row
+  // body loses 3-5 % with fragments there: gate/up of 512 rows 120 -> 127 us).
+  constexpr int UPT = WKC * 2, UNITS = MT * UPT;   // 16-byte units of a row tile's chunk, and of a panel
   constexpr int PASSES = UNITS / 256;
+  constexpr int PANEL = XF ? UNITS * 16 : MT * 16 * WXS;
   constexpr int GS = GATEUP ? SPW / 2 : SPW;       // strips per wave and matrix half
-  char (*lds)[UNITS * 16] = reinterpret_cast<char (*)[UNITS * 16]>(lds_raw);
+  char (*lds)[PANEL] = reinterpret_cast<char (*)[PANEL]>(lds_raw);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // known uniform: addresses split into scalar + lane part
@@ -52,13 +56,17 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
   }
   const unsigned wl = PACKED ? lane * 8 : r * K + kg * 8;
 #define SP_WOFF(C, s) (PACKED ? ((size_t)(C) * (WKC / 32) + (s)) * 512 : (size_t)(C)*WKC + (s) * 32)
-  // activations: per-thread offset (elements; row tiles past the last one repeat it) + uniform chunk origin
+  // activations: per-thread offset (elements; row tiles or rows past the last one repeat it) + uniform chunk origin
   unsigned xo[PASSES];
+  const int xl = XF ? tid * 16 : (tid >> 3) * WXS + (tid & 7) * 16;      // in a panel; passes are XPASS bytes apart
+  constexpr int XCHUNK = XF ? WKC * 16 : WKC, XPASS = XF ? 4096 : 32 * WXS;
 #pragma unroll
   for (int p = 0; p < PASSES; ++p) {
     const int u = p * 256 + tid;
-    xo[p] = (unsigned)min((m_base >> 4) + u / UPT, (M - 1) >> 4) * (unsigned)(K * 16) + (u % UPT) * 8;
+    xo[p] = XF ? (unsigned)min((m_base >> 4) + u / UPT, (M - 1) >> 4) * (unsigned)(K * 16) + (u % UPT) * 8
+               : (unsigned)min(m_base + (u >> 3), M - 1) * (unsigned)K + (tid & 7) * 8;
   }
+  const unsigned bl = XF ? lane * 16 : r * WXS + kg * 16;                // a fragment in its row tile
 
   u32x4_t wb[NB][SPW][KSTEPS];
   u32x4_t xb[NBX][PASSES];
@@ -70,13 +78,13 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
 
 #define SP_LOAD_X(B, C)                                                                                 \
   {                                                                                                     \
-    const bf16_t* xs = X + (size_t)min((C), c_last) * (WKC * 16);                                       \
+    const bf16_t* xs = X + (size_t)min((C), c_last) * XCHUNK;                                           \
     _Pragma("unroll") for (int p = 0; p < PASSES; ++p)                                                  \
         xb[B][p] = *reinterpret_cast<const u32x4_t*>(xs + xo[p]);                                       \
   }
 #define SP_STORE_X(B, BUF)                                                                              \
   _Pragma("unroll") for (int p = 0; p < PASSES; ++p)                                                    \
-      *reinterpret_cast<u32x4_t*>(&lds[BUF][(p * 256 + tid) * 16]) = xb[B][p];
+      *reinterpret_cast<u32x4_t*>(&lds[BUF][p * XPASS + xl]) = xb[B][p];
 #define SP_LOAD_W(B, C)                                                                                 \
   {                                                                                                     \
     const int cw = min((C), c_last);                                                                    \
@@ -86,7 +94,7 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
   }
   // item j of a chunk: k step j / MT, row tile j % MT
 #define SP_LDS_B(BUF, j)                                                                                \
-  (*reinterpret_cast<const bf16x8_t*>(&lds[BUF][(((j) % MT) * KSTEPS + (j) / MT) * 1024 + lane * 16]))
+  (*reinterpret_cast<const bf16x8_t*>(&lds[BUF][XF ? (((j) % MT) * KSTEPS + (j) / MT) * 1024 + bl : ((j) % MT) * 16 * WXS + ((j) / MT) * 64 + bl]))
   // Chunk C, weights in register set B, activations in LDS panel B.  The activations of chunk
   // C+2 go from their register set BX to their panel; that set then takes chunk C+2+NBX and
   // weight set B-1 the weights of chunk C+NB-1.  The last BQ fragment reads already address the
@@ -165,7 +173,7 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
         uint2 pk;
         pk.x = pack_bf16x2(o[0], o[1]);
         pk.y = pack_bf16x2(o[2], o[3]);
-        *reinterpret_cast<uint2*>(act + frag_at(m, n0 + a * 16 + 4 * kg, N)) = pk;
+        *reinterpret_cast<uint2*>(act + row_at(XF, m, n0 + a * 16 + 4 * kg, N)) = pk;
       }
     } else {
 #pragma unroll
@@ -178,7 +186,7 @@ __device__ __forceinline__ void wide_body(const bf16_t* __restrict__ X, const bf
 #ifndef SP_WIDE_OCC8
 #define SP_WIDE_OCC8 1
 #endif
-template <int SPW, int MTMAX, bool GATEUP, bool PACKED>
+template <int SPW, int MTMAX, bool GATEUP, bool PACKED, bool XF>
 __global__ void __launch_bounds__(256, MTMAX > 8 ? 1 : SP_WIDE_OCC8)
 k_gemm_wide(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
             bf16_t* __restrict__ act, int M, int N, int K, int n_tiles, int S) {
@@ -203,29 +211,230 @@ k_gemm_wide(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   const int c_end = (int)(((long long)(blockIdx.y + 1) * chunks_total) / S);
   if (c_begin >= c_end) return;                     // whole workgroup (S never exceeds the chunk count)
   const int rows = M - m_base;                      // uniform over the workgroup
-  if (MTMAX > 12 && rows > 192) wide_body<SPW, MTMAX, GATEUP, PACKED>(X, W, out, act, M, N, K, tile, m_base, c_begin, c_end, lds_raw);
-  else if (MTMAX > 8 && rows > 128) wide_body<SPW, 12, GATEUP, PACKED>(X, W, out, act, M, N, K, tile, m_base, c_begin, c_end, lds_raw);
-  else if (rows > 64) wide_body<SPW, 8, GATEUP, PACKED>(X, W, out, act, M, N, K, tile, m_base, c_begin, c_end, lds_raw);
-  else wide_body<SPW, 4, GATEUP, PACKED>(X, W, out, act, M, N, K, tile, m_base, c_begin, c_end, lds_raw);
+  if (MTMAX > 12 && rows > 192) wide_body<SPW, MTMAX, GATEUP, PACKED, XF>(X, W, out, act, M, N, K, tile, m_base, c_begin, c_end, lds_raw);
+  else if (MTMAX > 8 && rows > 128) wide_body<SPW, 12, GATEUP, PACKED, XF>(X, W, out, act, M, N, K, tile, m_base, c_begin, c_end, lds_raw);
+  else if (rows > 64) wide_body<SPW, 8, GATEUP, PACKED, XF>(X, W, out, act, M, N, K, tile, m_base, c_begin, c_end, lds_raw);
+  else wide_body<SPW, 4, GATEUP, PACKED, XF>(X, W, out, act, M, N, K, tile, m_base, c_begin, c_end, lds_raw);
 }
 
 // Launch with the activation panels as dynamic LDS (more than the 64 KB a kernel may declare
 // statically).
-template <int SPW, int MT, bool GATEUP, bool PACKED>
+template <int SPW, int MT, bool GATEUP, bool PACKED, bool XF>
 static hipError_t launch_wide(dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out, bf16_t* act,
                               int M, int N, int K, int n_tiles, int S) {
-  constexpr int LDS_BYTES = (MT > 8 ? 3 : 4) * MT * 16 * WKC * 2;    // NB panels of the tallest body
+  constexpr int LDS_BYTES = (MT > 8 ? 3 : 4) * MT * 16 * (XF ? WKC * 2 : WXS);    // NB panels of the tallest body
   static bool ready = false;
   if (!ready) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_wide<SPW, MT, GATEUP, PACKED>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_wide<SPW, MT, GATEUP, PACKED, XF>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
     if (e != hipSuccess) return e;
     ready = true;
   }
-  hipLaunchKernelGGL((k_gemm_wide<SPW, MT, GATEUP, PACKED>), grid, dim3(256), LDS_BYTES, st, X, W, out, act, M, N, K,
+  hipLaunchKernelGGL((k_gemm_wide<SPW, MT, GATEUP, PACKED, XF>), grid, dim3(256), LDS_BYTES, st, X, W, out, act, M, N, K,
                      n_tiles, S);
   return hipGetLastError();
 }
+
+// ---- fragment-order weights, many rows ------------------------------------------------------------------------------
+// Four waves side by side over 256 weight rows (gate/up: 128 columns, gate and up rows) and RT tiles of 32 activation rows.
+// v_mfma_f32_32x32x16_bf16 issues back to back from one wave per SIMD, which the 16 x 16 shape does not (57 % of its rate),
+// and gives the same sums; the panels come in by direct-to-LDS loads three chunks of 32 k ahead, as do the weights in
+// registers.  Up to RT = 5 two workgroups share a CU.  What sets the time of the products is how many rounds of workgroups
+// a shape makes, so the height is chosen by that (wide_plan).  gate/up 8B shape, 128- and 256-row blocks of the kernel above /
+// here: 320 rows 106.7 / 88.4 us, 512 rows 114.1 / 103.7, 638 rows 161.9 / 133.2, 1024 rows 213 / 202; O of 638 rows in five /
+// four slices 34.4 / 30.9.
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+
+template <int RT, bool GATEUP>
+__global__ void __launch_bounds__(256, RT <= 5 ? 2 : 1)
+k_gemm_wide32(const bf16_t* X, const bf16_t* W, float* out, bf16_t* act, int M, int N, int K, int n_tiles, int m_blocks, int S) {
+  constexpr int NB = 4, D = 3;                      // panels and weight sets, chunks ahead
+  constexpr int BQ = RT == 5 || RT == 7 ? RT : RT == 3 || RT == 6 ? 3 : 4;    // activation fragments read ahead of their MFMAs
+  constexpr int BLOCKS = RT * 2, NX = (BLOCKS + 3) / 4, NW = 4;     // fragment blocks of a panel, loads per wave and chunk
+  constexpr int PANEL = BLOCKS * 1024;
+  constexpr int ITEMS = 2 * RT;                     // (16 k, row tile) pairs of a chunk
+  static_assert(ITEMS % BQ == 0, "the fragment queue keeps its place from chunk to chunk");
+  // arrays of their own, so that the compiler knows which loads a read has to wait for
+  __shared__ __attribute__((aligned(16))) char p0[PANEL];
+  __shared__ __attribute__((aligned(16))) char p1[PANEL];
+  __shared__ __attribute__((aligned(16))) char p2[PANEL];
+  __shared__ __attribute__((aligned(16))) char p3[PANEL];
+#define SP_PAN(i) ((i) == 0 ? p0 : (i) == 1 ? p1 : (i) == 2 ? p2 : p3)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 31, hf = lane >> 5;
+  // the row blocks of a column tile get ids that are equal modulo 8: the same XCD, whose L2 holds the tile's weights
+  const int lin = blockIdx.x, j8 = lin >> 3;
+  const int tile = (j8 / m_blocks) * 8 + (lin & 7), mblk = j8 % m_blocks;
+  if (tile >= n_tiles) return;                      // whole workgroup (the grid is padded to a multiple of 8)
+  const int chunks = K / 32;
+  const int c_begin = (int)(((long long)blockIdx.y * chunks) / S);
+  const int c_end = (int)(((long long)(blockIdx.y + 1) * chunks) / S);
+  // the wave's two tiles of 32 weight rows: consecutive, or (gate/up) gate rows and the up rows of the same columns
+  const int col0 = tile * (GATEUP ? 128 : 256) + wave * (GATEUP ? 32 : 64);
+  const bf16_t* w[2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) w[a] = W + (size_t)((GATEUP ? a * N + col0 : col0 + a * 32) >> 4) * (K / 32) * 512;
+  // lane (r, hf) of an operand: row r, k = 16 * kk + 8 * hf .. + 7
+  const int wl = (r >> 4) * (K * 32) + hf * 256 + (r & 15) * 16;
+  const int ll = (r >> 4) * 1024 + hf * 256 + (r & 15) * 16;
+  const int t0 = mblk * RT * 2, t_last = (M - 1) >> 4;
+  int xo[NX], xl[NX];                               // (row tiles and blocks past the last one repeat it)
+#pragma unroll
+  for (int j = 0; j < NX; ++j) {
+    const int b = min(wave * NX + j, BLOCKS - 1);
+    xl[j] = b * 1024;
+    xo[j] = min(t0 + b, t_last) * (K * 32);
+  }
+  const int lane16 = lane * 16;
+  u32x4_t wb[NB][2][2];
+  f32x16_t acc[2][RT];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][t][i] = 0.f;
+  // The waits count on the order of the loads, a chunk's panel before its weights.  (X and W are not __restrict__: loads of
+  // what the compiler takes for constant would be moved past waits and barriers.)
+#define SP_LOADS(I, C)                                                                                  \
+  {                                                                                                     \
+    const bool on_ = (C) < c_end;                                                                       \
+    const auto xb_ = buffer_at(X, on_);                                                                 \
+    _Pragma("unroll") for (int j = 0; j < NX; ++j) load_to_lds(xb_, SP_PAN(I) + xl[j], lane16, (C) * 1024 + xo[j]); \
+    __builtin_amdgcn_sched_barrier(0);                                                                  \
+    _Pragma("unroll") for (int a = 0; a < 2; ++a) {                                                     \
+      const auto wr_ = buffer_at(w[a], on_);                                                            \
+      _Pragma("unroll") for (int kk = 0; kk < 2; ++kk)                                                  \
+        wb[I][a][kk] = __builtin_amdgcn_raw_buffer_load_b128(wr_, wl, (C) * 1024 + kk * 512, 0);        \
+    }                                                                                                   \
+  }
+#define SP_LDS_B(I, j) (*reinterpret_cast<const bf16x8_t*>(SP_PAN(I) + ((j) % RT) * 2048 + ((j) / RT) * 512 + ll))
+  // Chunk C out of panel and weight set I.  What may still be on its way behind the wait: the weights of C + 1 and all loads
+  // of C + 2.  Behind the barrier panels C and C + 1 are complete (the last BQ fragment reads
+  // already address the next panel) and nobody reads panel C - 1 any more, whose place the loads of chunk C + 3 take.
+#define SP_CHUNK(I, C)                                                                                  \
+  {                                                                                                     \
+    SP_WAIT_VMEM(NX + 2 * NW);                                                                          \
+    bare_barrier();                                                                                     \
+    SP_LOADS((I + D) % NB, (C) + D)                                                                     \
+    __builtin_amdgcn_sched_barrier(0);                                                                  \
+    _Pragma("unroll") for (int j = 0; j < ITEMS; ++j) {                                                 \
+      const bf16x8_t b = bq[j % BQ];                                                                    \
+      if (j + BQ < ITEMS) bq[j % BQ] = SP_LDS_B(I, j + BQ); else bq[j % BQ] = SP_LDS_B((I + 1) % NB, j + BQ - ITEMS); \
+      _Pragma("unroll") for (int a = 0; a < 2; ++a) acc[a][j % RT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16( \
+          *reinterpret_cast<const bf16x8_t*>(&wb[I][a][j / RT]), b, acc[a][j % RT], 0, 0, 0);           \
+    }                                                                                                   \
+    _Pragma("unroll") for (int j = 0; j < ITEMS; ++j) {                                                 \
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                                \
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                \
+    }                                                                                                   \
+    __builtin_amdgcn_sched_barrier(0);                                                                  \
+  }
+#pragma unroll
+  for (int i = 0; i < D; ++i) { SP_LOADS(i, c_begin + i) __builtin_amdgcn_sched_barrier(0); }
+  SP_WAIT_VMEM(2 * (NX + NW) + NW);
+  bare_barrier();
+  bf16x8_t bq[BQ];
+#pragma unroll
+  for (int j = 0; j < BQ; ++j) bq[j] = SP_LDS_B(0, j);
+  for (int c = c_begin; c < c_end; c += 4) {
+    SP_CHUNK(0, c)
+    if (c + 1 < c_end) SP_CHUNK(1, c + 1)
+    if (c + 2 < c_end) SP_CHUNK(2, c + 2)
+    if (c + 3 < c_end) SP_CHUNK(3, c + 3)
+  }
+#undef SP_CHUNK
+#undef SP_LDS_B
+#undef SP_LOADS
+  SP_WAIT_VMEM(0);
+
+  // lane (r, hf) holds, for row t * 32 + r, columns 8 * g + 4 * hf + 0..3 of each tile of 32 (g = 0..3)
+  if (GATEUP) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const int m = t0 * 16 + t * 32 + r;
+      if (m >= M) continue;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float gte = acc[0][t][g * 4 + i], up = acc[1][t][g * 4 + i];
+          o[i] = gte / (1.f + __expf(-gte)) * up;
+        }
+        uint2 pk;
+        pk.x = pack_bf16x2(o[0], o[1]);
+        pk.y = pack_bf16x2(o[2], o[3]);
+        *reinterpret_cast<uint2*>(act + frag_at(m, col0 + g * 8 + 4 * hf, N)) = pk;
+      }
+    }
+    return;
+  }
+  // Partial sums leave as 256 bytes of a row each, put together in a panel per wave (16-byte units of a row exchanged by
+  // its number against bank conflicts).
+  __syncthreads();
+  static_assert(GATEUP || PANEL >= 32 * 256, "32 rows of a wave's 64 columns fit a panel");
+  char* buf = SP_PAN(wave);
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4_t v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = acc[a][t][g * 4 + i];
+        *reinterpret_cast<f32x4_t*>(buf + r * 256 + ((a * 8 + g * 2 + hf) ^ (r & 15)) * 16) = v;
+      }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = i * 4 + (lane >> 4), m = t0 * 16 + t * 32 + row;
+      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(buf + row * 256 + ((lane & 15) ^ (row & 15)) * 16);
+      if (m < M) *reinterpret_cast<f32x4_t*>(out + ((size_t)blockIdx.y * M + m) * N + col0 + (lane & 15) * 4) = v;
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+#undef SP_PAN
+}
+
+// Height of the row blocks and number of k slices.  us[RT][n]: what n workgroups of a height take on a CU over 4096 k (8B
+// gate/up, measured with 224 workgroups and more); two of up to 160 rows share a CU.  A slice costs its partial sums, M * N
+// floats written here and read by the kernel that folds them, at 3.5 TB/s for the two.
+struct WidePlan { int RT, S; };
+static WidePlan wide_plan(int M, int n_tiles, int K, size_t row_bytes, int n_cu, int max_s) {
+  static const float one[9] = {0, 0, 0, 0, 81, 87, 95, 100, 104}, two[6] = {0, 0, 0, 0, 112, 130};
+  WidePlan best = {8, 1};
+  float best_us = 0.f;
+  for (int RT = 4; RT <= 8; ++RT)
+    for (int S = 1; S <= max_s; ++S) {
+      const int wgs = n_tiles * ((M + RT * 32 - 1) / (RT * 32)) * S, n = (wgs + n_cu - 1) / n_cu;
+      const float loop = RT <= 5 ? (n / 2) * two[RT] + (n % 2) * one[RT] : n * one[RT];
+      const float us = loop * (float)K / (4096.f * (float)S) + (float)S * (float)M * (float)row_bytes * 2.f / 3.5e6f;
+      if (best_us == 0.f || us < best_us) { best_us = us; best = {RT, S}; }
+    }
+  return best;
+}
+template <bool GATEUP>
+static hipError_t launch_wide32(const WidePlan& p, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out, bf16_t* act, int M,
+                                int N, int K, int n_tiles) {
+  const int m_blocks = (M + p.RT * 32 - 1) / (p.RT * 32);
+  const dim3 grid((n_tiles + 7) / 8 * 8 * m_blocks, p.S);
+#define SP_GO(RTV) hipLaunchKernelGGL((k_gemm_wide32<RTV, GATEUP>), grid, dim3(256), 0, st, X, W, out, act, M, N, K, n_tiles, m_blocks, p.S)
+  switch (p.RT) {
+    case 4: SP_GO(4); break;
+    case 5: SP_GO(5); break;
+    case 6: SP_GO(6); break;
+    case 7: SP_GO(7); break;
+    default: SP_GO(8); break;
+  }
+#undef SP_GO
+  return hipGetLastError();
+}
+// From how many rows: gate/up 256 rows 72.0 above / 81.2 us here, 288 rows 105.9 / 86.8; plain products in blocks of 128 rows are
+// level or better up to 384 rows (320 rows: QKV 30.0 / 30.0, O 21.4 / 24.7, down 50.2 / 50.9).
+static bool wide32_takes(int M, bool packed, bool gateup) { return packed && M > (gateup ? 256 : 384); }
 
 // rows per workgroup: 256 once there are enough rows to fill them, else 128
 #ifndef SP_WIDE_ROWS
@@ -233,10 +442,18 @@ static hipError_t launch_wide(dim3 grid, hipStream_t st, const bf16_t* X, const 
 #endif
 static inline int wide_rows(int M) { return SP_WIDE_ROWS(M); }
 
-hipError_t sp_launch_gemm_wide(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
+hipError_t sp_launch_gemm_wide(const bf16_t* X, bool frag, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int n_cu, size_t part_capacity_floats, int* S_out, hipStream_t st) {
   constexpr int SPW = 4;
-  if (M < 1 || N % (64 * SPW) || K % WKC) return hipErrorInvalidValue;
+  if (M < 1 || N % (64 * SPW) || K % WKC || (packed && !frag)) return hipErrorInvalidValue;
+  if (wide32_takes(M, packed, false)) {
+    int max_s = K / 32 < 8 ? K / 32 : 8;
+    while (max_s > 1 && (size_t)max_s * M * N > part_capacity_floats) --max_s;
+    if ((size_t)max_s * M * N > part_capacity_floats) return hipErrorInvalidValue;
+    const WidePlan p = wide_plan(M, N / 256, K, (size_t)N * 4, n_cu, max_s);
+    *S_out = p.S;
+    return launch_wide32<false>(p, st, X, W, out, nullptr, M, N, K, N / 256);
+  }
   const int WROWS = wide_rows(M);
   const int n_tiles = N / (64 * SPW), m_blocks = (M + WROWS - 1) / WROWS;
   const int chunks = K / WKC;
@@ -249,25 +466,29 @@ hipError_t sp_launch_gemm_wide(const bf16_t* X, const bf16_t* W, bool packed, fl
   *S_out = S;
   const int tiles8 = (n_tiles + 7) / 8 * 8;
   const dim3 grid(tiles8 * m_blocks, S);
-  if (WROWS == 256)
-    return packed ? launch_wide<SPW, 16, false, true>(grid, st, X, W, out, nullptr, M, N, K, n_tiles, S)
-                  : launch_wide<SPW, 16, false, false>(grid, st, X, W, out, nullptr, M, N, K, n_tiles, S);
-  return packed ? launch_wide<SPW, 8, false, true>(grid, st, X, W, out, nullptr, M, N, K, n_tiles, S)
-                : launch_wide<SPW, 8, false, false>(grid, st, X, W, out, nullptr, M, N, K, n_tiles, S);
+#define SP_GO(MT, PK, XF) return launch_wide<SPW, MT, false, PK, XF>(grid, st, X, W, out, nullptr, M, N, K, n_tiles, S)
+#define SP_BY_ORDER(MT) { if (packed) SP_GO(MT, true, true); else if (frag) SP_GO(MT, false, true); else SP_GO(MT, false, false); }
+  if (WROWS == 256) SP_BY_ORDER(16)
+  SP_BY_ORDER(8)
+#undef SP_BY_ORDER
+#undef SP_GO
 }
 
-hipError_t sp_launch_gemm_wide_gateup(const bf16_t* X, const bf16_t* W, bool packed, bf16_t* act, int M, int F, int K,
-                                      hipStream_t st) {
+hipError_t sp_launch_gemm_wide_gateup(const bf16_t* X, bool frag, const bf16_t* W, bool packed, bf16_t* act, int M, int F, int K,
+                                      int n_cu, hipStream_t st) {
   constexpr int SPW = 4;                            // two gate strips and two up strips per wave
   constexpr int TW = 64 * (SPW / 2);                // activation columns per workgroup
-  if (M < 1 || F % TW || K % WKC) return hipErrorInvalidValue;
+  if (M < 1 || F % TW || K % WKC || (packed && !frag)) return hipErrorInvalidValue;
+  if (wide32_takes(M, packed, true))
+    return launch_wide32<true>(wide_plan(M, F / TW, K, 0, n_cu, 1), st, X, W, nullptr, act, M, F, K, F / TW);
   const int WROWS = wide_rows(M);
   const int n_tiles = F / TW, m_blocks = (M + WROWS - 1) / WROWS;
   const int tiles8 = (n_tiles + 7) / 8 * 8;
   const dim3 grid(tiles8 * m_blocks, 1);
-  if (WROWS == 256)
-    return packed ? launch_wide<SPW, 16, true, true>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1)
-                  : launch_wide<SPW, 16, true, false>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1);
-  return packed ? launch_wide<SPW, 8, true, true>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1)
-                : launch_wide<SPW, 8, true, false>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1);
+#define SP_GO(MT, PK, XF) return launch_wide<SPW, MT, true, PK, XF>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1)
+#define SP_BY_ORDER(MT) { if (packed) SP_GO(MT, true, true); else if (frag) SP_GO(MT, false, true); else SP_GO(MT, false, false); }
+  if (WROWS == 256) SP_BY_ORDER(16)
+  SP_BY_ORDER(8)
+#undef SP_BY_ORDER
+#undef SP_GO
 }

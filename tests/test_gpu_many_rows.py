@@ -1,0 +1,44 @@
+"""Many rows over weights in fragment order: the 32 x 32 kernel at the row counts that select each of its heights (the
+8B stage's column counts over a short k range: d_ff = 14336 makes 112 column tiles, so that the rounds of workgroups decide
+as they do at full depth), one and two workgroups per CU, ragged last tiles, several k slices of the plain products; and
+161-192 rows of gate/up in the kernel of the fewer rows.  Row-major weights stay in blocks of 128 and 256 rows."""
+import numpy as np
+import pytest
+
+import workloads as wl
+import paper_2504_04104_amd as sp
+from gpu_harness import Pair, elementwise_figure, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+# rows: 161 and 192 (twelve row tiles), 257 and 320 (160-row blocks), 321 and 384 (192), 400 (224), 512 (256), 513 and
+# 639 (160, two per CU; the last tile of 639 one row short)
+@pytest.mark.parametrize("rows,packed", [(161, True), (192, True), (192, False), (257, True), (320, True), (321, True), (384, True),
+                                         (385, True), (400, True), (512, True), (513, True), (513, False), (639, True)])
+def test_row_blocks(rows, packed):
+    """Increment y - x of small inputs element by element (2e-2 of the value plus 5e-2 of the rms: about six tensors on
+    the way are stored in bf16), cache rows at 2e-2 of the largest."""
+    shape = wl.ModelShape(n_layers=1, d_model=512, n_q_heads=32, n_kv_heads=8, d_head=128, d_ff=14336)
+    check(shape, rows, packed)
+
+
+@pytest.mark.parametrize("rows", [385, 640, 700])
+def test_k_slices_of_the_plain_products(rows):
+    """K = 4096 in O and 3072 in the down projection with 512 to 768 columns: up to eight slices."""
+    check(wl.ModelShape(n_layers=1, d_model=768, n_q_heads=32, n_kv_heads=4, d_head=128, d_ff=3072), rows, True)
+
+
+def check(shape, rows, packed):
+    n_req = (rows + 249) // 250
+    counts = [rows // n_req + (r < rows % n_req) for r in range(n_req)]
+    pair = Pair(shape, 29, {r: 19 + r for r in range(n_req)}, max_batch_nodes=704, flags=sp.SP_FLAG_PACKED_WEIGHTS if packed else 0)
+    for r, n in enumerate(counts):
+        pair.insert(r, wl.tree_uniform_parents(29, n, 9, name=("many", rows, r)))
+    x = wl.hidden_rows(shape, 29, ("many", rows), rows) * np.float32(2.0 ** -6)
+    y, ref = pair.forward(list(range(n_req)), [0] * n_req, counts, x)
+    assert rel_err(y - x, ref - x) <= 2e-2, rows
+    assert elementwise_figure(y.astype(np.float64) - x, ref - x, 2e-2, 5e-2) <= 1.0, rows
+    for r in range(n_req):
+        pair.check_kv(r, 2e-2)
+    pair.close()
