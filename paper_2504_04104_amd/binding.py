@@ -152,6 +152,16 @@ def _i32(a: Optional[Sequence[int]]):
     return arr, arr.ctypes.data_as(C.POINTER(C.c_int32))
 
 
+def _f32(a: Optional[Sequence[float]]):
+    if a is None:
+        return None, None
+    if type(a) is list and set(map(type, a)) == {float}:
+        buf = array.array("f", a)                # as _i32: plain lists take the short way
+        return buf, (C.c_float * len(buf)).from_buffer(buf)
+    arr = np.ascontiguousarray(np.asarray(a, dtype=np.float32))
+    return arr, arr.ctypes.data_as(C.POINTER(C.c_float))
+
+
 def _check(rc: int, what: str):
     if rc != 0:
         raise SpError(rc, what)
@@ -198,7 +208,10 @@ class Stage:
 
     # -- plumbing -----------------------------------------------------------------
     def _stream(self):
-        return C.c_void_p(self.torch.cuda.current_stream(self.device).cuda_stream)
+        # the raw handle of the device's current stream: a Stream object for it costs 1.5 us a call
+        if self.device.index is not None:
+            return self.torch._C._cuda_getCurrentRawStream(self.device.index)
+        return self.torch.cuda.current_stream(self.device).cuda_stream
 
     def close(self):
         if getattr(self, "handle", None):
@@ -248,10 +261,7 @@ class Stage:
                     probs: Optional[Sequence[float]] = None) -> int:
         pa, pp = _i32(parents)
         ta, tp = _i32(tokens)
-        fa = fp = None
-        if probs is not None:
-            fa = np.ascontiguousarray(np.asarray(probs, dtype=np.float32))
-            fp = fa.ctypes.data_as(C.POINTER(C.c_float))
+        fa, fp = _f32(probs)
         first = C.c_int32(-1)
         _check(self.lib.sp_tree_insert(self.handle, req, len(pa), pp, tp, fp, C.byref(first), self._stream()),
                "sp_tree_insert")
@@ -265,15 +275,11 @@ class Stage:
         na, npn = _i32([len(p) for p in parents_per_req])
         pa, pp = _i32([x for p in parents_per_req for x in p])
         ta, tp = _i32([x for t in tokens_per_req for x in t]) if tokens_per_req is not None else (None, None)
-        qa = fp = None
-        if probs_per_req is not None:
-            qa = np.ascontiguousarray(np.asarray([x for q in probs_per_req for x in q], dtype=np.float32))
-            fp = qa.ctypes.data_as(C.POINTER(C.c_float))
-        first = np.zeros(max(len(ra), 1), dtype=np.int32)
-        _check(self.lib.sp_tree_insert_batch(self.handle, len(ra), rp, npn, pp, tp, fp,
-                                             first.ctypes.data_as(C.POINTER(C.c_int32)), self._stream()),
+        qa, fp = _f32([x for q in probs_per_req for x in q]) if probs_per_req is not None else (None, None)
+        first = (C.c_int32 * max(len(ra), 1))()
+        _check(self.lib.sp_tree_insert_batch(self.handle, len(ra), rp, npn, pp, tp, fp, first, self._stream()),
                "sp_tree_insert_batch")
-        return [int(v) for v in first[:len(ra)]]
+        return first[:len(ra)]
 
     def stage_forward(self, req_ids: Sequence[int], first_node: Sequence[int], n_nodes: Sequence[int], x_in, x_out=None):
         ra, rp = _i32(req_ids)
@@ -302,11 +308,11 @@ class Stage:
                    "sp_kv_compact")
             return 0, []
         ra, rp = _i32(row_nodes)
-        out = np.full(max(len(ra), 1), -2, dtype=np.int32)
+        out = (C.c_int32 * max(len(ra), 1))()
         assert x_rows.is_cuda and x_rows.is_contiguous() and x_rows.dtype == self.tdtype
         _check(self.lib.sp_kv_compact(self.handle, req, C.c_void_p(x_rows.data_ptr()), len(ra), rp, C.byref(n_out),
-                                      out.ctypes.data_as(C.POINTER(C.c_int32)), self._stream()), "sp_kv_compact")
-        return n_out.value, out[:n_out.value].tolist()
+                                      out, self._stream()), "sp_kv_compact")
+        return n_out.value, out[:n_out.value]
 
     def tree_prune_verified(self, req_ids: Sequence[int], nodes_dev, stride: int = 1):
         """Prune + cache compaction by the verified nodes a device tensor holds (int32; the result of
@@ -319,13 +325,10 @@ class Stage:
         ra, rp = _i32(req_ids)
         ma, mp = _i32(modes)
         na, np_ = _i32(nodes)
-        live = np.zeros(len(ra), np.int32)
-        commit = np.zeros(len(ra), np.int32)
-        _check(self.lib.sp_tree_prune_batch(self.handle, len(ra), rp, mp, np_,
-                                            live.ctypes.data_as(C.POINTER(C.c_int32)),
-                                            commit.ctypes.data_as(C.POINTER(C.c_int32)), self._stream()),
+        live, commit = (C.c_int32 * len(ra))(), (C.c_int32 * len(ra))()
+        _check(self.lib.sp_tree_prune_batch(self.handle, len(ra), rp, mp, np_, live, commit, self._stream()),
                "sp_tree_prune_batch")
-        return live.tolist(), commit.tolist()
+        return live[:], commit[:]
 
     def kv_compact_batch(self, req_ids):
         ra, rp = _i32(req_ids)
@@ -391,7 +394,10 @@ class Stage:
         _check(self.lib.sp_tree_expand(self.handle, req, len(ba), bp, k, cand_tokens.data_ptr(), cand_probs.data_ptr(),
                                        w, base, base + 4 * room, base + 8 * room, base + 12 * room, self._stream()),
                "sp_tree_expand")
-        host = out.cpu().numpy()
+        pinned = torch.empty(3 * room + 1, dtype=torch.int32, pin_memory=True)
+        pinned.copy_(out, non_blocking=True)
+        torch.cuda.current_stream(self.device).synchronize()
+        host = pinned.numpy()
         n = int(host[3 * room])
         return (host[:n].tolist(), host[room:room + n].tolist(),
                 host[2 * room:2 * room + n].view(np.float32).tolist())
