@@ -3,22 +3,43 @@
 // launch is a chain of memory latencies, so what counts is how few of them stand in a row: the waves of a workgroup cut
 // the k range (or the cache slots) between them and have several loads each in flight, and are folded through LDS.
 // Measured on the two-layer d = 256 stage, 16 nodes, context 128 (one thread column per output and one wave per row
-// and head before): products of 256 and 688 k 12.0 and 18.3 -> 4.6 and 4.7 us, attention 27.8 -> 5.5 us.
+// and head before): products of 256 and 688 k 12.0 and 18.3 -> 4.6 and 4.7 us, attention 27.8 -> 5.5 us.  For the same
+// reason a layer is five launches: RMSNorm, rotation, cache append, residual and write-out are prologues and epilogues of
+// the products: 2 layers, 16 nodes, a call 80 -> 70 us (70.1 -> 60.7 back to back), 64 nodes 104 -> 94.
 #include <type_traits>
 
 #include "sp_launch.h"
 
 #define F_WAVES 8
-#define F_D 4              // 16-byte pieces of every operand in flight per lane
 
-// out[m][n] = sum_k X[m][k] W[n][k]; GATEUP: act[m][f] = silu(X Wg^T) * (X Wu^T), W = [N gate rows ; N up rows].
+// What becomes of the products y[m][n] = sum_k X[m][k] W[n][k]:
+enum F32Mode {
+  F_PLAIN,      // out = y
+  F_QKV,        // X = rmsnorm(h): queries and keys rotated, values copied; queries to out [M][n_q * d_head], the rest to the cache
+  F_GATEUP,     // X = rmsnorm(h): out = silu(X Wg^T) * (X Wu^T), W = [N gate rows ; N up rows]
+  F_RESIDUAL,   // out += y (out is h; X is another buffer)
+  F_OUT         // the plan's x_out = h + y (out is h)
+};
+struct F32Args {
+  const float* gain; float eps;                                                              // F_QKV, F_GATEUP
+  const RowInfo* rows; const float* cs; KvGeom g; int layer, n_q, n_kv, d_head;              // F_QKV
+  const AttnPlan* plan;                                                                      // F_OUT
+};
+
+// RMSNorm as a prologue: rows come as h[m][k] * gain[k], their squares are summed on the way (every workgroup reads whole
+// rows, each of its waves and lanes another part), and rsqrt(mean + eps) multiplies the finished sums.
+// F_QKV: the 16 columns of a workgroup are eight rotation pairs, t0 .. t0 + 7 and the same d_head / 2 further on, so a
+// lane's partner value is its neighbour's in lane ^ 32.
 // A workgroup covers 16 columns and 16 * MT rows.  A lane's 16-byte piece holds four consecutive k of its row; MFMA i of
 // the four takes element i of every lane's piece, so lane group kg contributes k = 16 * step + 4 * kg + i on both sides.
-template <int MT, bool GATEUP>
+template <int MT, int MODE>
 __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restrict__ X, const float* __restrict__ W,
-                                                           float* __restrict__ out, int M, int N, int K) {
+                                                           float* __restrict__ out, int M, int N, int K, F32Args fa) {
+  constexpr bool GATEUP = MODE == F_GATEUP, NORM = MODE == F_QKV || MODE == F_GATEUP;
   constexpr int NS = GATEUP ? 2 : 1;
+  constexpr int F_D = MT * NS == 8 ? 2 : 4;     // 16-byte pieces of every operand in flight per lane (four of the largest spill)
   __shared__ __attribute__((aligned(16))) f32x4_t s_acc[F_WAVES][NS * MT][64];
+  __shared__ double s_ss[F_WAVES][NORM ? MT : 1][16];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int r = lane & 15, kg = lane >> 4;
   const int n0 = blockIdx.x * 16, m0 = blockIdx.y * (16 * MT);
@@ -29,13 +50,22 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
   const float* x[MT];
 #pragma unroll
   for (int a = 0; a < NS; ++a) w[a] = W + (size_t)(a * N + min(n0 + r, N - 1)) * K;
+  int head = 0, t0 = 0, half = 0;
+  if constexpr (MODE == F_QKV) {
+    half = fa.d_head >> 1;
+    head = n0 / fa.d_head;
+    t0 = (n0 - head * fa.d_head) >> 1;
+    w[0] = W + (size_t)(head * fa.d_head + t0 + (r & 7) + (r >> 3) * half) * K;
+  }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) x[mt] = X + (size_t)min(m0 + mt * 16 + r, M - 1) * K;
   // Several short chains of additions per result instead of one long one, and their sums taken in 64 bits: the error
   // against 64-bit arithmetic stays below that of the plain kernel (64 lanes with a few terms each, added pairwise),
   // which float32 sums of the chains miss by 2 % (the matrix unit rounds inside its four-term step).
   constexpr int CH = MT == 1 ? 8 : 4;
-  f32x4_t acc[CH][NS][MT];
+  f32x4_t acc[CH][NS][MT], sq[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) sq[mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int c = 0; c < CH; ++c)
 #pragma unroll
@@ -43,7 +73,7 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) acc[c][a][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
   for (int s0 = s_begin; s0 < s_end; s0 += F_D) {
-    f32x4_t wf[F_D][NS], xf[F_D][MT];
+    f32x4_t wf[F_D][NS], xf[F_D][MT], gn[NORM ? F_D : 1];
 #pragma unroll
     for (int j = 0; j < F_D; ++j) {
       const int p = (s0 + j) * 4 + kg;
@@ -59,6 +89,16 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
         const f32x4_t v = *reinterpret_cast<const f32x4_t*>(x[mt] + pc * 4);
         xf[j][mt] = in ? v : (f32x4_t){0.f, 0.f, 0.f, 0.f};
       }
+      if constexpr (NORM) gn[j] = *reinterpret_cast<const f32x4_t*>(fa.gain + pc * 4);
+    }
+    if constexpr (NORM) {
+#pragma unroll
+      for (int j = 0; j < F_D; ++j)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          sq[mt] += xf[j][mt] * xf[j][mt];
+          xf[j][mt] *= gn[j];
+        }
     }
 #pragma unroll
     for (int j = 0; j < F_D; ++j)
@@ -85,6 +125,15 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
       }
       s_acc[wave][a * MT + mt][lane] = t;
     }
+  if constexpr (NORM) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      double t = ((double)sq[mt][0] + (double)sq[mt][1]) + ((double)sq[mt][2] + (double)sq[mt][3]);
+      t += __shfl_xor(t, 16, 64);
+      t += __shfl_xor(t, 32, 64);
+      if (lane < 16) s_ss[wave][mt][lane] = t;
+    }
+  }
   __syncthreads();
   if (wave >= MT) return;
   // wave mt finishes row tile mt: row r, columns n0 + 4 * kg .. + 3
@@ -102,19 +151,52 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
       y[a][i] = (float)d;
     }
   }
+  if constexpr (NORM) {
+    double t = 0.0;
+#pragma unroll
+    for (int v = 0; v < F_WAVES; ++v) t += s_ss[v][wave][r];
+    const float scale = rsqrtf((float)t / (float)K + fa.eps);
+#pragma unroll
+    for (int a = 0; a < NS; ++a) y[a] *= scale;
+  }
   const int m = m0 + wave * 16 + r, n = n0 + 4 * kg;
-  if (m >= M) return;
   f32x4_t o = y[0];
+  if constexpr (MODE == F_QKV) {
+    f32x4_t b;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = __shfl_xor(o[i], 32, 64);
+    if (m >= M) return;
+    const int t = t0 + 4 * (kg & 1), col = t + (kg >> 1) * half;
+    const RowInfo ri = fa.rows[m];
+    const size_t slot = sp_phys_slot(fa.g, ri.req, ri.base, ri.P + ri.node);
+    if (head < fa.n_q + fa.n_kv) {
+      const float* c = fa.cs + (size_t)m * fa.d_head;
+      const f32x4_t co = *reinterpret_cast<const f32x4_t*>(c + t), si = *reinterpret_cast<const f32x4_t*>(c + half + t);
+      o = kg < 2 ? o * co - b * si : o * co + b * si;
+    }
+    float* dst = out + ((size_t)m * fa.n_q + head) * fa.d_head;
+    if (head >= fa.n_q) {
+      const int value = head >= fa.n_q + fa.n_kv, kvh = head - fa.n_q - value * fa.n_kv;
+      dst = reinterpret_cast<float*>(fa.g.kv + ((size_t)(fa.layer * 2 + value) * fa.n_kv + kvh) * fa.g.plane_bytes +
+                                     slot * fa.g.row_bytes);
+    }
+    *reinterpret_cast<f32x4_t*>(dst + col) = o;
+    return;
+  }
+  if (m >= M) return;
   if (GATEUP) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = y[0][i] / (1.f + __expf(-y[0][i])) * y[NS - 1][i];
   }
-  float* dst = out + (size_t)m * N + n;
+  const float* h = out + (size_t)m * N + n;
+  float* dst = (MODE == F_OUT ? reinterpret_cast<float*>(fa.plan->x_out) : out) + (size_t)m * N + n;
+  constexpr bool ADD = MODE == F_RESIDUAL || MODE == F_OUT;
   if (n + 4 <= N && (N & 3) == 0) {
+    if (ADD) o = *reinterpret_cast<const f32x4_t*>(h) + o;
     *reinterpret_cast<f32x4_t*>(dst) = o;
   } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) if (n + i < N) dst[i] = o[i];
+    for (int i = 0; i < 4; ++i) if (n + i < N) dst[i] = ADD ? h[i] + o[i] : o[i];
   }
 }
 
@@ -224,21 +306,39 @@ __global__ void __launch_bounds__(256) k_attn_f32(const float* __restrict__ q, c
   out[((size_t)row * n_q + head) * DH + threadIdx.x] = num / den;
 }
 
-template <bool GATEUP>
-static hipError_t launch_gemm_f32(const float* X, const float* W, float* out, int M, int N, int K, hipStream_t st) {
+template <int MODE>
+static hipError_t launch_gemm_f32(const float* X, const float* W, float* out, int M, int N, int K, const F32Args& fa,
+                                  hipStream_t st) {
   if (M < 1 || N < 1 || K < 4 || K % 4) return hipErrorInvalidValue;
   const int tiles = (M + 15) / 16, mt = tiles >= 4 ? 4 : tiles >= 2 ? 2 : 1;     // row tiles that share a read of the weights
   const dim3 grid((N + 15) / 16, (tiles + mt - 1) / mt);
-#define SP_GO(MTV) hipLaunchKernelGGL((k_gemm_f32<MTV, GATEUP>), grid, dim3(64 * F_WAVES), 0, st, X, W, out, M, N, K)
+#define SP_GO(MTV) hipLaunchKernelGGL((k_gemm_f32<MTV, MODE>), grid, dim3(64 * F_WAVES), 0, st, X, W, out, M, N, K, fa)
   if (mt == 1) SP_GO(1); else if (mt == 2) SP_GO(2); else SP_GO(4);
 #undef SP_GO
   return hipGetLastError();
 }
 hipError_t sp_launch_gemm_f32(const float* X, const float* W, float* out, int M, int N, int K, hipStream_t st) {
-  return launch_gemm_f32<false>(X, W, out, M, N, K, st);
+  return launch_gemm_f32<F_PLAIN>(X, W, out, M, N, K, F32Args{}, st);
 }
-hipError_t sp_launch_gateup_f32(const float* X, const float* W, float* act, int M, int F, int K, hipStream_t st) {
-  return launch_gemm_f32<true>(X, W, act, M, F, K, st);
+hipError_t sp_launch_qkv_f32(const float* h, const float* gain, float eps, const float* W, const RowInfo* rows, const float* cs,
+                             float* qbuf, KvGeom g, int layer, int M, int d, int n_q, int n_kv, int d_head, hipStream_t st) {
+  if (d_head < 16 || d_head % 16) return hipErrorInvalidValue;      // eight pairs to a workgroup
+  F32Args fa{};
+  fa.gain = gain; fa.eps = eps; fa.rows = rows; fa.cs = cs; fa.g = g; fa.layer = layer;
+  fa.n_q = n_q; fa.n_kv = n_kv; fa.d_head = d_head;
+  return launch_gemm_f32<F_QKV>(h, W, qbuf, M, (n_q + 2 * n_kv) * d_head, d, fa, st);
+}
+hipError_t sp_launch_gateup_f32(const float* h, const float* gain, float eps, const float* W, float* act, int M, int F, int K,
+                                hipStream_t st) {
+  F32Args fa{};
+  fa.gain = gain; fa.eps = eps;
+  return launch_gemm_f32<F_GATEUP>(h, W, act, M, F, K, fa, st);
+}
+hipError_t sp_launch_residual_f32(const float* X, const float* W, float* h, const AttnPlan* plan_out, int M, int N, int K,
+                                  hipStream_t st) {
+  F32Args fa{};
+  fa.plan = plan_out;
+  return plan_out ? launch_gemm_f32<F_OUT>(X, W, h, M, N, K, fa, st) : launch_gemm_f32<F_RESIDUAL>(X, W, h, M, N, K, fa, st);
 }
 
 hipError_t sp_launch_attn_f32(const float* q, const RowInfo* rows, const ReqTables* tables, KvGeom g, int layer, float* out,

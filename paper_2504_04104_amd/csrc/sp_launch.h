@@ -115,7 +115,15 @@ hipError_t sp_launch_gemm_simple(int dtype, const void* X, const void* W, float*
                                  hipStream_t st);
 // float32 on the matrix cores (K % 4 == 0, rows 16-byte aligned)
 hipError_t sp_launch_gemm_f32(const float* X, const float* W, float* out, int M, int N, int K, hipStream_t st);
-hipError_t sp_launch_gateup_f32(const float* X, const float* W, float* act, int M, int F, int K, hipStream_t st);
+// the float32 layer's products with what stands before and after them (h: the residual stream [M][d], float32):
+// qkv of rmsnorm(h), rotated, to qbuf and the cache; silu(gate) * up of rmsnorm(h); h += X W^T, or with plan_out the plan's
+// x_out = h + X W^T
+hipError_t sp_launch_qkv_f32(const float* h, const float* gain, float eps, const float* W, const RowInfo* rows, const float* cs,
+                             float* qbuf, KvGeom g, int layer, int M, int d, int n_q, int n_kv, int d_head, hipStream_t st);
+hipError_t sp_launch_gateup_f32(const float* h, const float* gain, float eps, const float* W, float* act, int M, int F, int K,
+                                hipStream_t st);
+hipError_t sp_launch_residual_f32(const float* X, const float* W, float* h, const AttnPlan* plan_out /*nullable*/, int M, int N,
+                                  int K, hipStream_t st);
 hipError_t sp_launch_attn_f32(const float* q, const RowInfo* rows, const ReqTables* tables, KvGeom g, int layer, float* out,
                               int M, int n_q, int n_kv, int d_head, hipStream_t st);
 // bf16 MFMA kernels: the rows X and the gate/up products are in fragment order (frag_at).  Returns the split count used in *S_out (partials [S][M][N]).  packed: the

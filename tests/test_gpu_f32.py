@@ -34,6 +34,22 @@ def test_f32_tiles(shape, n, prefix, page_slots):
     pair.close()
 
 
+@pytest.mark.parametrize("n", [1, 16, 33, 65])
+@pytest.mark.parametrize("shape", SHAPES.values(), ids=SHAPES.keys())
+def test_f32_rows_of_any_scale(shape, n):
+    """Rows from 2^-12 to 2^12 of the usual size in one call: each takes its own RMSNorm scale after the products.  A row's
+    increment within 2e-5 of its largest value (as above) plus the roundings of x + increment, two additions a layer at
+    half a unit of 2^-23 of the row's largest value, doubled."""
+    pair = Pair(shape, 29, {0: 37}, max_batch_nodes=80)
+    pair.insert(0, wl.tree_deep(29, n, 20))
+    scale = np.float32(2.0) ** ((np.arange(n) * 7) % 25 - 12).astype(np.float32)
+    x = wl.hidden_rows(shape, 29, ("f32 scales", n), n) * scale[:, None]
+    y, ref = pair.forward([0], [0], [n], x)
+    pair.close()
+    err = np.abs((y - x) - (ref - x)).max(1)
+    assert (err <= 2e-5 * np.abs(ref - x).max(1) + 4 * 2.0 ** -23 * np.abs(ref).max(1)).all()
+
+
 @pytest.mark.parametrize("page_slots", [0, 32], ids=["contiguous", "pages32"])
 @pytest.mark.parametrize("shape", SHAPES.values(), ids=SHAPES.keys())
 def test_f32_infinite_value_row(shape, page_slots):
