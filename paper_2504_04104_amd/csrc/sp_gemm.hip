@@ -1,14 +1,13 @@
-// bf16 projections for few rows (M = tree nodes in flight, typically <= 64) on the
-// CDNA4 matrix cores (QKV, O and down of up to 16 rows have a kernel of their own, sp_gemm_few.hip, and most products
-// from 49 rows on, sp_gemm_mid.hip).  With so few rows every weight is used once, so the kernel is a
-// weight streamer (decode is bound by loading parameters, Sec. 2.2): each wave pulls
-// its 16 weight rows straight from HBM into registers in MFMA operand layout (one
-// 16-byte load per lane per k-step, PF chunks ahead of the math), while the M x K
-// activation panel -- shared by every wave -- is staged once per workgroup through LDS.
-// Up to 16 rows a workgroup is four waves over 64 columns (the panel is small, more workgroups
-// stream better); from 17 rows on it is eight waves over 128 columns, or over the CU's even share
-// of the gate/up columns, one workgroup per CU, because the panel's way from L2 into the CU is
-// then what the rows cost.  The weights carry the non-temporal hint.
+// bf16 products of few rows (M = tree nodes in flight) on the CDNA4 matrix cores, as far as no kernel of their own takes
+// them: QKV, O and down over weights in fragment order up to 16 rows where sp_gemm_few.hip does not, and 17-64 rows with k
+// slices too short for sp_gemm_mid.hip; gate/up up to 128 rows of widths that are no even share per CU; the output head and
+// the logits, over weights in either order.  With so few rows every weight is used once, so the kernel is a weight streamer (decode is bound by loading
+// parameters, Sec. 2.2): each wave pulls its 16 weight rows straight from HBM into registers in MFMA operand layout (one
+// 16-byte load per lane per k-step, PF chunks ahead of the math), while the M x K activation panel -- shared by every wave
+// -- is staged once per workgroup through LDS.  Up to 16 rows a workgroup is four waves over 64 columns (the panel is
+// small, more workgroups stream better); from 17 rows on plain products take eight waves over 128 columns, one workgroup
+// per CU, because the panel's way from L2 into the CU is then what the rows cost: it comes in fragment order, whose 1 KB
+// loads that path moves at 120 B/ns per CU (16 rows of 64 bytes: 38).  The weights carry the non-temporal hint.
 //
 //   out[y][m][n] = sum_{k in slice y} X[m][k] * W[n][k]        (f32 partial sums)
 //
@@ -36,17 +35,8 @@
 #ifndef SP_GEMM_ARGMAX8
 #define SP_GEMM_ARGMAX8 1         // the output head's top-column kernel in the eight-wave shape
 #endif
-#ifndef SP_GEMM_EVEN7
-#define SP_GEMM_EVEN7 1           // gate/up, one workgroup per CU over 96 < d_ff / CUs <= 112 columns (seven waves)
-#endif
-#ifndef SP_GEMM_PF_EVEN
-#define SP_GEMM_PF_EVEN 3         // the eight-wave gate/up kernel has the registers for a third chunk (45.5 -> 44.9 us)
-#endif
 #ifndef SP_GEMM_PF_EIGHT
 #define SP_GEMM_PF_EIGHT SP_GEMM_PF   // the eight-wave plain kernels are faster with two
-#endif
-#ifndef SP_GEMM_EVEN_MIN_MT
-#define SP_GEMM_EVEN_MIN_MT 2     // row tiles from which gate/up takes one workgroup per CU where d_ff allows
 #endif
 #ifndef SP_GEMM_NCG_PLAIN
 #define SP_GEMM_NCG_PLAIN 4       // column groups (of 16 weight rows) per workgroup
@@ -58,8 +48,7 @@
 // Plain products split over k, K up to 8192 (the QKV and O shapes): workgroups walk their k slice from
 // different starting chunks.  At 32 and 64 rows 8192 x 8192 29.2 -> 24.8 and 31.0 -> 27.9 us, the other shapes
 // within 1 %; nothing gained with K = 14336 or 28672 (down) and in gate/up over weights in fragment order: those keep
-// the plain order.  Gate/up over row-major weights, one workgroup per CU, takes staggered starts too (its rows are 8 or
-// 16 KB apart): 8B shape at 37 rows 58.8 -> 52.7 us, 70B shape at 20 rows 183 -> 176 us (16 rows and fewer: level).
+// the plain order.
 #define SP_GEMM_ROT 1
 #endif
 #ifndef SP_GEMM_TARGET_WGS_ROWS
@@ -75,65 +64,39 @@
 // ARGMAX (output head of the last stage, Algorithm 1 "verify new token"): instead of the
 // products, a workgroup leaves per row the largest of its 16*NCG columns and that column's
 // index (the lowest one among equal maxima) as a (float, int) pair at out[(m * tiles + tile) * 2].
-// TWO (plain products of eight row tiles): a wave holds two strips of 16 weight rows, 64 rows apart, so that a workgroup
-// of four waves covers 128 columns.
 // STATS (logits of a stochastic verification): beside the products, a workgroup leaves per row the maximum mx of its
 // 16*NCG columns and the sum of exp((l - mx) * inv_T) over them as a float pair at stats[(m * tiles + tile) * 2].
-// EVEN (gate/up): one workgroup per CU covers cpw = d_ff / CUs activation columns, a multiple of 8, in NCG column
-// groups of 16 columns and a last one of cpw - 16 * (NCG - 1) -- eight waves as four groups times two k-halves for
-// 48 < cpw <= 64, seven waves as seven groups for 96 < cpw <= 112 (the upper lanes of a short last group re-read
-// its last row and their results are dropped; 8 rows of the fragment layout are one 128-byte line, so nothing is
-// fetched twice).  Every CU then streams the same bytes, which 16-row
-// strips in fixed 32-column workgroups cannot do when d_ff / 32 is not a multiple of the CU count (d_ff = 14336:
-// 1.75 workgroups per CU), and the panel is staged once per CU instead of once per four waves.
-template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, int NWAVES = 4, bool EVEN = false, bool WNT = true,
-          bool STATS = false, bool TWO = false, bool FRAG = true>
+template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, int NWAVES = 4, bool WNT = true,
+          bool STATS = false, bool FRAG = true>
 __global__ void __launch_bounds__(64 * NWAVES)
 k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
-            bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int cpw = 0, int rot = 0,
+            bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int rot = 0,
             const float* ssq = nullptr, float eps = 0.f, float* stats = nullptr, float inv_T = 0.f) {
-  static_assert(!(TWO && (GATEUP || ARGMAX || STATS)), "two strips per wave: plain products only");
-  static_assert(!EVEN || GATEUP, "even split: gate/up only");
   constexpr int NTH = 64 * NWAVES;
   constexpr int NKH = NWAVES / NCG;       // waves sharing a column group split each chunk's k-steps
   constexpr int KSTEPS = (KC / 32) / NKH;
-  constexpr int NW = (GATEUP || TWO) ? 2 : 1;
+  constexpr int NW = GATEUP ? 2 : 1;
   constexpr int ROWS = MT * 16;
   constexpr int UPT = KC * 2;             // 16-byte units of a row tile's chunk (KC / 32 fragment blocks, consecutive in X)
   constexpr int UNITS = MT * UPT;
   constexpr int PASSES = (UNITS + NTH - 1) / NTH;  // the last staging pass may cover fewer units
   constexpr bool RAGGED_PASS = UNITS % NTH != 0;
   constexpr int NB = PF + 1;              // weight register buffers
-  // two panels in fragment order, as X: the fragment reads are conflict-free without padding.  Plain products of eight
-  // row tiles put their rows together here at the end.
-  constexpr int WCOLS = 16 * NCG * (TWO ? 2 : 1);
-  constexpr int LSF = WCOLS + 4;                        // floats per row of those
-  constexpr int OUT_BYTES = MT == 8 && !GATEUP && !ARGMAX ? ROWS * LSF * 4 : 0;
-  constexpr int LDS_BYTES = 2 * UNITS * 16 > OUT_BYTES ? 2 * UNITS * 16 : OUT_BYTES;
-  __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
+  // two panels in fragment order, as X: the fragment reads are conflict-free without padding
+  __shared__ __attribute__((aligned(16))) char lds[2 * UNITS * 16];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int cg = wave % NCG, kh = wave / NCG;
   const int r = lane & 15, kg = lane >> 4;
-  const int n0 = EVEN ? blockIdx.x * cpw + cg * 16 : blockIdx.x * (16 * NCG * (TWO ? 2 : 1)) + cg * 16;
-  const int vr = EVEN ? min(16, cpw - cg * 16) : 16;     // valid columns of this wave's group (8 or 16)
-  const int pair_off = TWO ? 16 * NCG : N;   // rows between a wave's two strips (gate/up: the up rows follow the N gate rows)
+  const int n0 = blockIdx.x * (16 * NCG) + cg * 16;
   const int m_base = blockIdx.z * ROWS;
   const int c_begin = (int)(((long long)blockIdx.y * chunks_total) / S);
   const int c_end = (int)(((long long)(blockIdx.y + 1) * chunks_total) / S);
 
-  // EVEN: a group starts at a multiple of 8, so its 16 rows may lie in two fragment blocks: per-lane row addresses
-  const int wr0 = n0 + min(r, vr - 1), wr1 = pair_off + wr0;
-  const bf16_t* w0 =
-      EVEN ? (PACKED ? W + ((size_t)(wr0 >> 4) * (K / 32) + kh * KSTEPS) * 512 + (kg * 16 + (wr0 & 15)) * 8
-                     : W + (size_t)wr0 * K + kg * 8 + kh * (KSTEPS * 32))
-           : (PACKED ? W + ((size_t)(n0 / 16) * (K / 32) + kh * KSTEPS) * 512 + lane * 8
-                     : W + (size_t)(n0 + r) * K + kg * 8 + kh * (KSTEPS * 32));
-  const bf16_t* w1 =                                                                                // second strip
-      EVEN ? (PACKED ? W + ((size_t)(wr1 >> 4) * (K / 32) + kh * KSTEPS) * 512 + (kg * 16 + (wr1 & 15)) * 8
-                     : W + (size_t)wr1 * K + kg * 8 + kh * (KSTEPS * 32))
-           : (PACKED ? W + ((size_t)((pair_off + n0) / 16) * (K / 32) + kh * KSTEPS) * 512 + lane * 8
-                     : W + (size_t)(pair_off + n0 + r) * K + kg * 8 + kh * (KSTEPS * 32));
+  const bf16_t* w0 = PACKED ? W + ((size_t)(n0 / 16) * (K / 32) + kh * KSTEPS) * 512 + lane * 8
+                            : W + (size_t)(n0 + r) * K + kg * 8 + kh * (KSTEPS * 32);
+  const bf16_t* w1 = PACKED ? W + ((size_t)((N + n0) / 16) * (K / 32) + kh * KSTEPS) * 512 + lane * 8     // the up rows
+                            : W + (size_t)(N + n0 + r) * K + kg * 8 + kh * (KSTEPS * 32);
 #define SP_WOFF(C, s) (PACKED ? ((size_t)(C) * (KC / 32) + (s)) * 512 : (size_t)(C)*KC + (s) * 32)
   // rot: workgroups start at different chunks of their k slice and wrap around, so that the workgroups of one
   // slice, whose weight rows lie a fixed distance apart, are not all at the same offset of their rows at the
@@ -256,7 +219,6 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 
   // lane holds, for activation row m = mt*16 + l%16, output columns n0 + 4*(l/16) + 0..3
   const int ncol = n0 + 4 * kg;
-  if (EVEN && 4 * kg >= vr) return;       // columns past a short last group
   if (ARGMAX) {
     static_assert(!ARGMAX || (NKH == 1 && !GATEUP), "one wave per column group");
     float* s_val = reinterpret_cast<float*>(lds);          // [NCG][ROWS]; the panels are no longer read
@@ -319,29 +281,6 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
       *reinterpret_cast<float2*>(stats + ((size_t)(m_base + tid) * gridDim.x + blockIdx.x) * 2) = make_float2(mx, z);
     }
   }
-  if (!GATEUP && !STATS && MT == 8) {
-    // Eight row tiles: partial sums leave in whole rows of the workgroup's columns.  The waves' 16-column pieces are put
-    // together in LDS (the panels are no longer read: every wave has passed the barrier that ends its last chunk), and a
-    // store instruction then writes 1 KB of consecutive addresses instead of 64 bytes in each of 16 rows.
-    static_assert(NKH == 1 || GATEUP, "plain products: one wave per column group");
-    float* tile = reinterpret_cast<float*>(lds);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int a = 0; a < NW; ++a)
-        *reinterpret_cast<f32x4_t*>(tile + (mt * 16 + r) * LSF + a * (16 * NCG) + cg * 16 + 4 * kg) = acc[a][mt];
-    __syncthreads();
-    constexpr int UPRW = WCOLS / 4;                       // 16-byte units per row
-    const int col0 = blockIdx.x * WCOLS;
-    for (int idx = tid; idx < ROWS * UPRW; idx += NTH) {
-      const int row = idx / UPRW, u = idx - row * UPRW;
-      const int m = m_base + row;
-      if (m < M)
-        *reinterpret_cast<f32x4_t*>(out + ((size_t)blockIdx.y * M + m) * N + col0 + u * 4) =
-            *reinterpret_cast<const f32x4_t*>(tile + row * LSF + u * 4);
-    }
-    return;
-  }
   float row_scale = 1.f;
   if (SCALED && ssq) {
     if (NKH != 2) __syncthreads();      // (the fold of the k-halves has passed a barrier)
@@ -371,9 +310,9 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 }
 
 // ---- launchers -------------------------------------------------------------------
-// Up to 64 rows run as one block of MT = ceil(M/16) tiles; more rows (shapes that sp_gemm_mid.hip does not take, the
-// output head) run in blocks of 128 (MT = 8, always with the 128-wide chunk so that the two LDS panels
-// fit), each block streaming the weights once.
+// Up to 64 rows run as one block of MT = ceil(M/16) tiles; more rows (gate/up of other widths, the output head) run in
+// blocks of 128 (MT = 8, always with the 128-wide chunk so that the two LDS panels fit), each block streaming the weights
+// once.
 // staggered starting chunks: plain products that are split over k, K up to 8192 (see SP_GEMM_ROT)
 static inline int rot_for(int S, int K) { return (SP_GEMM_ROT && S > 1 && K <= 8192) ? 1 : 0; }
 
@@ -382,11 +321,11 @@ static hipError_t launch_mt(int MT, dim3 grid, hipStream_t st, const bf16_t* X, 
                             bf16_t* act, int M, int N, int K, int S, const float* ssq = nullptr, float eps = 0.f, bool frag = true) {
 #define SP_GO(MTV, KCX)                                                                                        \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, NCG, GATEUP, KCX, SP_GEMM_PF, PACKED, ARGMAX>), grid, dim3(256), 0, st, X, \
-                     W, out, act, M, N, K, K / KCX, S, 0, (!GATEUP && !ARGMAX) ? rot_for(S, K) : 0, ssq, eps)
-  if constexpr (!ARGMAX && !(GATEUP && NCG == 4))
+                     W, out, act, M, N, K, K / KCX, S, (!GATEUP && !ARGMAX) ? rot_for(S, K) : 0, ssq, eps)
+  if constexpr (!ARGMAX && (GATEUP ? NCG != 4 : PACKED))
     if (!frag) {
-      hipLaunchKernelGGL((k_gemm_bf16<1, NCG, GATEUP, KCV, SP_GEMM_PF, PACKED, ARGMAX, 4, false, true, false, false, false>), grid, dim3(256), 0,
-                         st, X, W, out, act, M, N, K, K / KCV, S, 0, GATEUP ? 0 : rot_for(S, K), ssq, eps);
+      hipLaunchKernelGGL((k_gemm_bf16<1, NCG, GATEUP, KCV, SP_GEMM_PF, PACKED, ARGMAX, 4, true, false, false>), grid, dim3(256), 0,
+                         st, X, W, out, act, M, N, K, K / KCV, S, GATEUP ? 0 : rot_for(S, K), ssq, eps);
       return hipGetLastError();
     }
   if (!ARGMAX && MT == 4 && GATEUP && NCG == 4) {      // the 64 + 64 column gate/up workgroup at 49-64 rows
@@ -420,21 +359,16 @@ static inline void row_blocks(int M, int* MT, int* mblocks) {
 
 hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st, bool resident, bool frag) {
-  int MT, mblocks;
-  row_blocks(M, &MT, &mblocks);
+  const int MT = (M + 15) / 16;
   // 17-64 rows: workgroups of eight waves over 128 columns, one per CU -- the same waves per CU as two
   // four-wave workgroups of 64 columns, but the panel slice is staged once for all eight
   const bool eight = SP_GEMM_PLAIN8 && N % 128 == 0 && MT >= 2;
-  // 97-128 rows where sp_gemm_mid.hip does not take the product (slices of one chunk, two slices of a wide matrix): the
-  // same, and for large matrices four waves with two strips each, two workgroups per CU: the panel is then read once per
-  // 128 columns, which is worth the partial sums of twice the slices (12288 wide, 97 rows: QKV 79 -> 76 us per launch)
-  const bool two = MT == 8 && (double)N * (double)K >= 64.0 * 1048576.0;
   // ... or six waves over 96 columns where that divides the CUs evenly and 128 columns do not (N = 6144 on 256 CUs:
   // 64 tiles x 4 slices of equal length instead of 48 x 5 of 6 or 7 chunks)
-  const bool six = SP_GEMM_PLAIN6 && eight && MT <= 4 && N % 96 == 0 && (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 128) != 0 &&
+  const bool six = SP_GEMM_PLAIN6 && eight && N % 96 == 0 && (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 128) != 0 &&
                    (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 96) == 0;
   const int TILE = six ? 96 : eight ? 128 : 16 * SP_GEMM_NCG_PLAIN;
-  if (M < 1 || M > 128 || (!frag && M > 8) || (MT == 8 && !eight) || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
+  if (M < 1 || M > 64 || (!frag && M > 8) || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
   const int chunks = K / SP_GEMM_KC_PLAIN;
   const int tiles = N / TILE;
   // Enough workgroups to keep every CU streaming, within the partial-sum buffer.  Every slice costs M*N*4 bytes
@@ -442,9 +376,9 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   // workgroups per CU (measured on the whole 64-row step: 0.608 ms against 0.617 ms with three; a count between
   // two and three per CU, which leaves the CUs unevenly loaded, 0.638 ms; two waves per column group with half
   // the slices again: 0.612 ms).
-  int S = (eight && !two ? SP_GEMM_TARGET_WGS_ROWS / 2 : SP_GEMM_TARGET_WGS_ROWS) / (tiles * mblocks);
+  int S = (eight ? SP_GEMM_TARGET_WGS_ROWS / 2 : SP_GEMM_TARGET_WGS_ROWS) / tiles;
   // One row tile, whose partial sums are small: three workgroups per CU where two per CU would be an uneven round (12288
-  // columns: 192 tiles x 4 instead of x 2; one layer, row-major, with those in QKV 128.8 -> 124.7 us at one row and 140.3
+  // columns: 192 tiles x 4 instead of x 2; measured over row-major weights, one layer with those in QKV 128.8 -> 124.7 us at one row and 140.3
   // -> 136.7 at 16, with those in O and down 430 -> 398 and 461 -> 428).  Not throughout: 7168 and 5120 columns in 112 x 7
   // and 80 x 10 workgroups, a few more than three per CU, 156 -> 165 us at one row.
   if (MT == 1 && S >= 1 && 4 * S * tiles <= 3 * SP_GEMM_TARGET_WGS_ROWS) S = (SP_GEMM_TARGET_WGS_ONE + tiles - 1) / tiles;
@@ -454,19 +388,11 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   if (S < 1) S = 1;
   if ((size_t)S * M * N > part_capacity_floats) return hipErrorInvalidValue;
   *S_out = S;
-  const dim3 grid(tiles, S, mblocks);
-  if (two) {
-#define SP_GO2(PK)                                                                                               \
-  hipLaunchKernelGGL((k_gemm_bf16<8, 4, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, 4, false, true, false, true>), grid, \
-                     dim3(256), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K))
-    if (packed) SP_GO2(true); else SP_GO2(false);
-#undef SP_GO2
-    return hipGetLastError();
-  }
+  const dim3 grid(tiles, S);
   if (six) {
 #define SP_GO6(MTV, PK)                                                                                          \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, 6, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, 6>), grid, dim3(384), 0, \
-                     st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K))
+                     st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, rot_for(S, K))
     if (packed) { if (MT == 2) SP_GO6(2, true); else if (MT == 3) SP_GO6(3, true); else SP_GO6(4, true); }
     else { if (MT == 2) SP_GO6(2, false); else if (MT == 3) SP_GO6(3, false); else SP_GO6(4, false); }
 #undef SP_GO6
@@ -474,61 +400,27 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   }
   if (eight) {
 #define SP_GO8(MTV, PK)                                                                                          \
-  if (resident)                                                                                                  \
-    hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, PK, false, 8, false, false>), \
-                       grid, dim3(512), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K)); \
+  if (PK && resident)                                                                                            \
+    hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, true, false, 8, false>),  \
+                       grid, dim3(512), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, rot_for(S, K)); \
   else                                                                                                           \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, PK, false, 8>), grid, dim3(512), 0, \
-                     st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K))
-    if (packed) { if (MT == 2) SP_GO8(2, true); else if (MT == 3) SP_GO8(3, true); else if (MT == 4) SP_GO8(4, true); else SP_GO8(8, true); }
-    else { if (MT == 2) SP_GO8(2, false); else if (MT == 3) SP_GO8(3, false); else if (MT == 4) SP_GO8(4, false); else SP_GO8(8, false); }
+                     st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, rot_for(S, K))
+    if (packed) { if (MT == 2) SP_GO8(2, true); else if (MT == 3) SP_GO8(3, true); else SP_GO8(4, true); }
+    else { if (MT == 2) SP_GO8(2, false); else if (MT == 3) SP_GO8(3, false); else SP_GO8(4, false); }
 #undef SP_GO8
     return hipGetLastError();
   }
-  // One row tile of a matrix that is to stay in the Infinity Cache: ordinary weight loads from 9 rows on (one layer,
-  // row-major, 4096 wide, 16 rows 133.2 -> 131.4 us, 5120 171.6 -> 165.1, 8192 392.6 -> 385.5); with fewer it is level (packed,
-  // 4608 wide, 8 rows 144.5 -> 146.5, row-major 5120 one row 156.0 -> 154.0).
-  if (resident && MT == 1 && M > 8) {
-#define SP_GOR(PK)                                                                                                    \
-  hipLaunchKernelGGL((k_gemm_bf16<1, SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, 4, false, false>), \
-                     grid, dim3(256), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, 0, rot_for(S, K))
-    if (packed) SP_GOR(true); else SP_GOR(false);
-#undef SP_GOR
+  // One row tile of a matrix that is to stay in the Infinity Cache: ordinary weight loads from 9 rows on (measured over
+  // row-major weights, which sp_gemm_mid.hip takes now: one layer of 5120 and 8192 columns at 16 rows 171.6 -> 165.1 and
+  // 392.6 -> 385.5 us); with fewer it is level (4608 wide, 8 rows 144.5 -> 146.5).
+  if (resident && packed && M > 8) {
+    hipLaunchKernelGGL((k_gemm_bf16<1, SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, true, false, 4, false>),
+                       grid, dim3(256), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, rot_for(S, K));
     return hipGetLastError();
   }
   if (packed) return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, true>(MT, grid, st, X, W, out, nullptr, M, N, K, S, nullptr, 0.f, frag);
-  return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, false>(MT, grid, st, X, W, out, nullptr, M, N, K, S, nullptr, 0.f, frag);
-}
-
-template <bool PACKED>
-static hipError_t launch_even(int MT, int n_wg, hipStream_t st, const bf16_t* X, const bf16_t* W, bf16_t* act, int M,
-                              int F, int K, int cpw) {
-#define SP_GO(MTV)                                                                                              \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 4, true, SP_GEMM_KC_GATEUP, SP_GEMM_PF_EVEN, PACKED, false, 8, true>),   \
-                     dim3(n_wg), dim3(512), 0, st, X, W, nullptr, act, M, F, K, K / SP_GEMM_KC_GATEUP, 1, cpw, PACKED ? 0 : 1)
-  switch (MT) {
-    case 2: SP_GO(2); break;
-    default: SP_GO(3); break;
-  }
-#undef SP_GO
-  return hipGetLastError();
-}
-// the same for 96 < cpw <= 112 (the 70B shape's d_ff = 28672 on 256 CUs): seven column groups, one wave each
-template <bool PACKED>
-static hipError_t launch_even7(int MT, int n_wg, hipStream_t st, const bf16_t* X, const bf16_t* W, bf16_t* act, int M,
-                               int F, int K, int cpw) {
-  // three weight chunks in flight up to 64 rows (148 -> 145 us per launch), two with 128 (three: 171 -> 179 us)
-#define SP_GO(MTV, PFV)                                                                                         \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 7, true, 128, PFV, PACKED, false, 7, true>), dim3(n_wg), dim3(448), 0, st, X, \
-                     W, nullptr, act, M, F, K, K / 128, 1, cpw, PACKED ? 0 : 1)
-  switch (MT) {
-    case 2: SP_GO(2, 3); break;
-    case 3: SP_GO(3, 3); break;
-    case 4: SP_GO(4, 3); break;
-    default: SP_GO(8, 2); break;
-  }
-#undef SP_GO
-  return hipGetLastError();
+  return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, false>(MT, grid, st, X, W, out, nullptr, M, N, K, S);
 }
 
 hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, bool frag, const bf16_t* W, bool packed, bf16_t* act, int M, int F,
@@ -537,19 +429,7 @@ hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, bool frag, const bf16_t* 
   row_blocks(M, &MT, &mblocks);
   if ((ssq || !frag) && MT != 1) return hipErrorInvalidValue;
   if (M < 1 || F % 64 || K % SP_GEMM_KC_GATEUP || K % 128) return hipErrorInvalidValue;
-  // 17-48 rows and a d_ff that gives every CU the same 56 or 64 columns: one eight-wave workgroup per CU (more rows:
-  // sp_gemm_mid.hip)
-  if (MT >= SP_GEMM_EVEN_MIN_MT && MT <= 3 && n_cu > 0 && F % n_cu == 0 && (F / n_cu) % 8 == 0 && F / n_cu > 48 &&
-      F / n_cu <= 64 && SP_GEMM_KC_GATEUP == 256) {
-    return packed ? launch_even<true>(MT, n_cu, st, X, W, act, M, F, K, F / n_cu)
-                  : launch_even<false>(MT, n_cu, st, X, W, act, M, F, K, F / n_cu);
-  }
-  if (SP_GEMM_EVEN7 && MT >= 2 && mblocks == 1 && n_cu > 0 && F % n_cu == 0 && (F / n_cu) % 8 == 0 && F / n_cu > 96 &&
-      F / n_cu <= 112) {
-    return packed ? launch_even7<true>(MT, n_cu, st, X, W, act, M, F, K, F / n_cu)
-                  : launch_even7<false>(MT, n_cu, st, X, W, act, M, F, K, F / n_cu);
-  }
-  // Other widths from 49 rows on: 64 gate + 64 up columns per workgroup (four column groups, 128-k chunks) where that
+  // From 49 rows on: 64 gate + 64 up columns per workgroup (four column groups, 128-k chunks) where that
   // still gives every CU a workgroup, so that the staged panel is at most as large as the weights it meets
   // (70B shape: gate/up 193.6 -> 179.3 us at 64 rows, 252 -> 212 us at 128 rows); else 32 + 32 columns.  With
   // d_ff = 14336 the wider workgroups number 224 and run level with the 448 narrow ones (53.2 against 53.9 us).
@@ -582,7 +462,7 @@ hipError_t sp_launch_gemm_argmax_bf16(const bf16_t* X, const bf16_t* W, bool pac
   if (eight) {
 #define SP_GOA(MTV, PK)                                                                                        \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, 128, SP_GEMM_PF, PK, true, 8>), grid, dim3(512), 0, st, X, W, \
-                     pairs, nullptr, M, V, K, K / 128, 1, 0)
+                     pairs, nullptr, M, V, K, K / 128, 1)
     if (packed) { if (MT == 2) SP_GOA(2, true); else if (MT == 3) SP_GOA(3, true); else SP_GOA(4, true); }
     else { if (MT == 2) SP_GOA(2, false); else if (MT == 3) SP_GOA(3, false); else SP_GOA(4, false); }
 #undef SP_GOA
@@ -603,8 +483,8 @@ hipError_t sp_launch_gemm_logits_bf16(const bf16_t* X, const bf16_t* W, bool pac
   *tile_cols = TILE;
   const dim3 grid(V / TILE);
 #define SP_GOL(MTV, NCGV, PK)                                                                                          \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, NCGV, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, NCGV, false, true, true>), \
-                     grid, dim3(64 * NCGV), 0, st, X, W, logits, nullptr, M, V, K, K / SP_GEMM_KC_PLAIN, 1, 0, 0, nullptr, 0.f, stats, inv_T)
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, NCGV, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, NCGV, true, true>), \
+                     grid, dim3(64 * NCGV), 0, st, X, W, logits, nullptr, M, V, K, K / SP_GEMM_KC_PLAIN, 1, 0, nullptr, 0.f, stats, inv_T)
 #define SP_GOT(NCGV, PK) \
   if (MT == 1) SP_GOL(1, NCGV, PK); else if (MT == 2) SP_GOL(2, NCGV, PK); else if (MT == 3) SP_GOL(3, NCGV, PK); else SP_GOL(4, NCGV, PK)
   if (eight) { if (packed) { SP_GOT(8, true); } else { SP_GOT(8, false); } }

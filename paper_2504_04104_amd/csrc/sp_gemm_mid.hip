@@ -1,15 +1,23 @@
-// bf16 projections for 49-160 rows: still a weight stream (one pass over the weights, the activation panel staged
-// through LDS once per workgroup), but with this many rows the fragments read back from LDS, not HBM, set the pace if a
-// fragment feeds a single MFMA: eight waves with one strip of 16 weight rows each ask LDS for 8 * MT KB per 32 k, at 128
-// rows twice the time of the MFMAs they feed.  Here a wave holds two strips and half of the k steps of a chunk, so that
-// a fragment feeds two MFMAs, and the two waves that share their strips are folded through LDS at the end (four strips
-// per wave measured the same at 128 rows, and at 160 rows the registers do not suffice).  The loop runs without guards
-// around its loads up to the last chunks, so that a period of six chunks is one basic block and its waits count exactly.
+// bf16 products of up to 160 rows (gate/up 192): a weight stream, one pass over the weights, with the activation panel
+// staged through LDS once per workgroup.  Two things bound it beside HBM.  The fragments read back from LDS, if each feeds a
+// single MFMA: eight waves with one strip of 16 weight rows each ask LDS for 8 * MT KB per 32 k, at 128 rows twice the time of
+// the MFMAs they feed, so a wave holds two strips and half of the k steps of a chunk and the two waves that share their strips
+// are folded through LDS at the end.  And the panel's way from L2 into the CU, which moves 1 KB of consecutive addresses at
+// 120 B/ns per CU, 128-byte pieces at 78 and 64-byte pieces at 38: X comes in fragment order.
 //
-// A workgroup is eight waves over eight strips (plain: 128 columns; gate/up: the CU's even share of the columns as four
-// gate strips and the four up strips behind them, the last one short) or six waves over 96 columns, one workgroup per
-// CU.  Measured on one 8B layer (forward of the whole layer, before / now): 65 rows 151 -> 134 us, 96 rows 156 -> 141 us,
-// 128 rows 171 -> 162 us, 145 rows 190 -> 169 us; 70B layer at 128 rows 399 -> 388 us.
+// Panels come in by direct-to-LDS loads of waves of their own.  A wave's loads return in order, so one that waits for its
+// piece of the panel would wait for all its older weight loads too; the loading waves need no registers for either.
+// Row-major weights take the same way: a wave loads whole 128-byte lines of its rows to LDS (the 16-byte units swizzled over
+// the banks) and reads fragments back, 6.3-6.5 TB/s against some 5 for 64-byte pieces in operand layout; so do weights
+// in fragment order where the registers are needed for the sums (PlainPipe, GateupPipe).  A period of the ring is one basic
+// block without guards around its loads (a load past the end goes through an empty buffer descriptor), so that its waits
+// count exactly.
+//
+// A workgroup covers eight strips (plain: 128 columns; gate/up: the CU's even share of the columns as gate strips and the up
+// strips behind them, the last one short), twelve (96 columns: six waves) or, gate/up of 97-112 columns per CU, fourteen, one
+// workgroup per CU.  Two layers, the kernels before / here, us: 8B row-major 16 rows 262 / 212, 64 rows 287 / 238, 160 rows
+// 376 / 320; 70B row-major 17 rows 371 / 301, 64 rows 412 / 320, 128 rows 476 / 372, 160 rows 666 / 405; 70B in fragment order
+// 160 rows 562 / 392; 12288 wide in fragment order 112 rows 594 / 555.
 //
 //   out[y][m][n] = sum_{k in slice y} X[m][k] * W[n][k]        (f32 partial sums)
 //   gate/up:      act[m][f] = silu(X Wg^T) * (X Wu^T)
@@ -342,26 +350,19 @@ static MidCut mid_cut(int M, int N, int K, int n_cu) {
   return {six ? 96 : 128, n_cu / (N / (six ? 96 : 128))};
 }
 
-// Where this kernel is the faster one (us per launch, k_gemm_bf16 or k_gemm_wide against this one, 8B and 70B shapes):
-// gate/up 64 rows 45.5 / 43.7, 128 rows 60.4 / 54.6, 145 rows 70.2 / 59.3, at 48 rows 43.5 / 49.8; down, 14336 or 28672
-// deep, 64 rows 28.1 / 26.8 and 83 / 77, 145 rows 42.1 / 35.9; QKV and O of both shapes lose up to 8 % at 64 rows (their
-// k slices are four to eight chunks long) and gain from 65 on (145 rows 25.5 / 24.4 and 22.2 / 18.6).  From 161 rows on
-// the register-blocked kernel is level, and with twelve row tiles slower here.
-// Over other widths (one layer, us, k_gemm_bf16 against this one): up to 64 rows it loses in tiles of 96 columns (6144
-// wide, 64 rows 199 / 205) and where the columns leave two slices or one (12288 wide, row-major 534 / 550).  With seven
-// and eight row tiles a launch costs 0.8 us more here, the fold of the waves that share their strips, which slices of one
-// chunk do not earn back (97 rows: 768 wide 60.5 / 62.9, 1024 wide 69.5 / 71.8; with two chunks in QKV alone, 2048 wide,
-// 94.5 / 92.5), nor do two slices of a wide matrix (12288 wide 451 / 470, row-major 605 / 638).  65-96 and 129-160 rows:
-// level (768 wide) to 8 % faster throughout.
+// Which plain products: all over row-major weights (1 to 160 rows, above).  In fragment order all of 65-160 rows, and of
+// 17-64 rows those whose slices are at least 1024 deep: shorter ones (8B and 70B QKV and O, four to eight chunks) lose up to
+// 8 % at 64 rows, down gains (14336 and 28672 deep, 64 rows 28.1 / 26.8 and 83 / 77 us), and so do 12288-wide matrices (two
+// layers at 64 rows 504 / 473).  At 17 rows two 8B layers lose 1.5 % (217 / 221 us), at 33 they are level.  Up to 16 rows the
+// kernels of one row tile stream weights in fragment order as fast without the loading waves.
 bool sp_gemm_mid_takes(int M, int N, int K, bool packed, int n_cu) {
   if (M < 1 || M > 160 || N % 128 || K % MID_KC) return false;
   const MidCut cut = mid_cut(M, N, K, n_cu);
-  if (!packed) return cut.S >= 1;
-  if (M <= 64) return M > 16 && K >= 1024 * cut.S && cut.S >= 1;
-  return true;
+  return !packed || M > 64 || (M > 16 && cut.S >= 1 && K >= 1024 * cut.S);
 }
-// columns of a CU's share of the gate/up product: 48 < cpw <= 64 (four groups, two waves each) or, from two row tiles on,
-// 96 < cpw <= 112 (seven groups, one wave each)
+// Which gate/up products: a CU's even share of 49-64 columns (four groups, two waves each; row-major from one row on,
+// fragment order from two row tiles to 192 rows: 192 rows 57.7 us, in blocks of 128 rows 63.5) or of 97-112 from two row tiles
+// to 160 rows (seven groups, one wave each: 70B shape at 128 rows 177.6 -> 149.4 us).
 bool sp_gemm_mid_takes_gateup(int M, int F, int K, bool packed, int n_cu) {
   if (M < (packed ? 17 : 1) || M > 192 || K % 128 || n_cu < 1 || F % n_cu || (F / n_cu) % 8) return false;
   const int cpw = F / n_cu;

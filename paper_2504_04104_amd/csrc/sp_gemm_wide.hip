@@ -1,7 +1,9 @@
 // bf16 projections for many rows (plain products from 161 rows on, gate/up from 129 or, where sp_gemm_mid.hip takes it,
-// 161: a cold ragged batch forwards several hundred tree nodes at once, Sec. 4 "Implementation" / Sec. 4.4).  Here the matrix cores, not the weight
-// stream, set the pace, so each wave keeps SPW strips of 16 weight rows in registers and every
-// activation fragment it reads from LDS feeds SPW MFMAs.  A workgroup covers up to 16*MT rows x
+// 161 or 193: a cold ragged batch forwards several hundred tree nodes at once, Sec. 4 "Implementation" / Sec. 4.4).  Here the
+// matrix cores, not the weight stream, set the pace, so each wave keeps SPW strips of 16 weight rows in registers and every
+// activation fragment it reads from LDS feeds SPW MFMAs.  Two kernels: k_gemm_wide here, over row-major weights in blocks of
+// 128 rows and, from 385 on, 256, and over weights in fragment order in blocks of 128 up to 384 rows (gate/up 256);
+// k_gemm_wide32 further down beyond those.  A workgroup covers up to 16*MT rows x
 // 64*SPW output columns.  Full row blocks come first in launch order, and those of one column
 // tile get consecutive ids modulo 8: they run at the same time on the same XCD and share the
 // tile's weights through its L2.  The last, partial row block of every tile comes after all
@@ -445,7 +447,7 @@ static inline int wide_rows(int M) { return SP_WIDE_ROWS(M); }
 hipError_t sp_launch_gemm_wide(const bf16_t* X, bool frag, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int n_cu, size_t part_capacity_floats, int* S_out, hipStream_t st) {
   constexpr int SPW = 4;
-  if (M < 1 || N % (64 * SPW) || K % WKC || (packed && !frag)) return hipErrorInvalidValue;
+  if (M < 1 || N % (64 * SPW) || K % WKC || packed != frag) return hipErrorInvalidValue;
   if (wide32_takes(M, packed, false)) {
     int max_s = K / 32 < 8 ? K / 32 : 8;
     while (max_s > 1 && (size_t)max_s * M * N > part_capacity_floats) --max_s;
@@ -466,29 +468,24 @@ hipError_t sp_launch_gemm_wide(const bf16_t* X, bool frag, const bf16_t* W, bool
   *S_out = S;
   const int tiles8 = (n_tiles + 7) / 8 * 8;
   const dim3 grid(tiles8 * m_blocks, S);
-#define SP_GO(MT, PK, XF) return launch_wide<SPW, MT, false, PK, XF>(grid, st, X, W, out, nullptr, M, N, K, n_tiles, S)
-#define SP_BY_ORDER(MT) { if (packed) SP_GO(MT, true, true); else if (frag) SP_GO(MT, false, true); else SP_GO(MT, false, false); }
-  if (WROWS == 256) SP_BY_ORDER(16)
-  SP_BY_ORDER(8)
-#undef SP_BY_ORDER
-#undef SP_GO
+  if (packed) return launch_wide<SPW, 8, false, true, true>(grid, st, X, W, out, nullptr, M, N, K, n_tiles, S);
+  if (WROWS == 256) return launch_wide<SPW, 16, false, false, false>(grid, st, X, W, out, nullptr, M, N, K, n_tiles, S);
+  return launch_wide<SPW, 8, false, false, false>(grid, st, X, W, out, nullptr, M, N, K, n_tiles, S);
 }
 
 hipError_t sp_launch_gemm_wide_gateup(const bf16_t* X, bool frag, const bf16_t* W, bool packed, bf16_t* act, int M, int F, int K,
                                       int n_cu, hipStream_t st) {
   constexpr int SPW = 4;                            // two gate strips and two up strips per wave
   constexpr int TW = 64 * (SPW / 2);                // activation columns per workgroup
-  if (M < 1 || F % TW || K % WKC || (packed && !frag)) return hipErrorInvalidValue;
+  if (M < 1 || F % TW || K % WKC || (packed ? !frag : frag && M > 256)) return hipErrorInvalidValue;
   if (wide32_takes(M, packed, true))
     return launch_wide32<true>(wide_plan(M, F / TW, K, 0, n_cu, 1), st, X, W, nullptr, act, M, F, K, F / TW);
   const int WROWS = wide_rows(M);
   const int n_tiles = F / TW, m_blocks = (M + WROWS - 1) / WROWS;
   const int tiles8 = (n_tiles + 7) / 8 * 8;
   const dim3 grid(tiles8 * m_blocks, 1);
-#define SP_GO(MT, PK, XF) return launch_wide<SPW, MT, true, PK, XF>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1)
-#define SP_BY_ORDER(MT) { if (packed) SP_GO(MT, true, true); else if (frag) SP_GO(MT, false, true); else SP_GO(MT, false, false); }
-  if (WROWS == 256) SP_BY_ORDER(16)
-  SP_BY_ORDER(8)
-#undef SP_BY_ORDER
-#undef SP_GO
+  if (packed) return launch_wide<SPW, 8, true, true, true>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1);
+  if (frag) return launch_wide<SPW, 8, true, false, true>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1);
+  if (WROWS == 256) return launch_wide<SPW, 16, true, false, false>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1);
+  return launch_wide<SPW, 8, true, false, false>(grid, st, X, W, nullptr, act, M, F, K, n_tiles, 1);
 }

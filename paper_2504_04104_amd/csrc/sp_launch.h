@@ -126,8 +126,9 @@ hipError_t sp_launch_residual_f32(const float* X, const float* W, float* h, cons
                                   int K, hipStream_t st);
 hipError_t sp_launch_attn_f32(const float* q, const RowInfo* rows, const ReqTables* tables, KvGeom g, int layer, float* out,
                               int M, int n_q, int n_kv, int d_head, hipStream_t st);
-// bf16 MFMA kernels: the rows X and the gate/up products are in fragment order (frag_at).  Returns the split count used in *S_out (partials [S][M][N]).  packed: the
-// weights are in MFMA fragment order (sp_launch_pack_weights); frag false (at most eight rows): X is row-major.
+// bf16 MFMA kernels: the rows X and the gate/up products are in fragment order (frag_at).  Up to 64 rows.  Returns the split
+// count used in *S_out (partials [S][M][N]).  packed: the weights are in MFMA fragment order (sp_launch_pack_weights); frag
+// false (at most eight rows, packed only): X is row-major.
 hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st,
                                bool resident = false, bool frag = true);
@@ -155,8 +156,8 @@ hipError_t sp_launch_few_residual(const bf16_t* X, bool frag, const bf16_t* W, b
 // rows of the plan's x_out = bf16(h + X W^T)
 hipError_t sp_launch_few_out(const bf16_t* X, bool frag, const bf16_t* W, bool packed, const float* h, const AttnPlan* plan_dev, int M,
                              int N, int K, int n_cu, hipStream_t st);
-// 49-160 rows (sp_gemm_mid.hip): one workgroup per CU, two strips of weight rows per wave; `takes` says for which
-// sizes these are to be called (gate/up: where every CU gets the same 56 or 64 columns)
+// Up to 160 rows, gate/up 192 (sp_gemm_mid.hip): one workgroup per CU, two strips of weight rows per wave, X in fragment
+// order; `takes` says for which sizes these are to be called (gate/up: where every CU gets the same 49-64 or 97-112 columns)
 bool sp_gemm_mid_takes(int M, int N, int K, bool packed, int n_cu);
 bool sp_gemm_mid_takes_gateup(int M, int F, int K, bool packed, int n_cu);
 hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,
