@@ -27,7 +27,8 @@ struct F32Args {
 };
 
 // RMSNorm as a prologue: rows come as h[m][k] * gain[k], their squares are summed on the way (every workgroup reads whole
-// rows, each of its waves and lanes another part), and rsqrt(mean + eps) multiplies the finished sums.
+// rows, each of its waves and lanes another part), and 1 / sqrt(mean + eps) multiplies the finished sums.  Scale and residual
+// are applied to the sums in 64 bits, so that a product is rounded as often as behind a norm of its own.
 // F_QKV: the 16 columns of a workgroup are eight rotation pairs, t0 .. t0 + 7 and the same d_head / 2 further on, so a
 // lane's partner value is its neighbour's in lane ^ 32.
 // A workgroup covers 16 columns and 16 * MT rows.  A lane's 16-byte piece holds four consecutive k of its row; MFMA i of
@@ -137,7 +138,7 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
   __syncthreads();
   if (wave >= MT) return;
   // wave mt finishes row tile mt: row r, columns n0 + 4 * kg .. + 3
-  f32x4_t y[NS];
+  double y[NS][4];
 #pragma unroll
   for (int a = 0; a < NS; ++a) {
     f32x4_t p[F_WAVES];
@@ -148,19 +149,23 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
       double d = 0.0;
 #pragma unroll
       for (int v = 0; v < F_WAVES; ++v) d += (double)p[v][i];
-      y[a][i] = (float)d;
+      y[a][i] = d;
     }
   }
   if constexpr (NORM) {
     double t = 0.0;
 #pragma unroll
     for (int v = 0; v < F_WAVES; ++v) t += s_ss[v][wave][r];
-    const float scale = rsqrtf((float)t / (float)K + fa.eps);
+    const double scale = 1.0 / sqrt(t / (double)K + (double)fa.eps);
 #pragma unroll
-    for (int a = 0; a < NS; ++a) y[a] *= scale;
+    for (int a = 0; a < NS; ++a)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) y[a][i] *= scale;
   }
   const int m = m0 + wave * 16 + r, n = n0 + 4 * kg;
-  f32x4_t o = y[0];
+  f32x4_t o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = (float)y[0][i];
   if constexpr (MODE == F_QKV) {
     f32x4_t b;
 #pragma unroll
@@ -186,17 +191,21 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
   if (m >= M) return;
   if (GATEUP) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = y[0][i] / (1.f + __expf(-y[0][i])) * y[NS - 1][i];
+    for (int i = 0; i < 4; ++i) o[i] = o[i] / (1.f + __expf(-o[i])) * (float)y[NS - 1][i];
   }
   const float* h = out + (size_t)m * N + n;
   float* dst = (MODE == F_OUT ? reinterpret_cast<float*>(fa.plan->x_out) : out) + (size_t)m * N + n;
   constexpr bool ADD = MODE == F_RESIDUAL || MODE == F_OUT;
   if (n + 4 <= N && (N & 3) == 0) {
-    if (ADD) o = *reinterpret_cast<const f32x4_t*>(h) + o;
+    if (ADD) {
+      const f32x4_t hv = *reinterpret_cast<const f32x4_t*>(h);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = (float)((double)hv[i] + y[0][i]);
+    }
     *reinterpret_cast<f32x4_t*>(dst) = o;
   } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) if (n + i < N) dst[i] = ADD ? h[i] + o[i] : o[i];
+    for (int i = 0; i < 4; ++i) if (n + i < N) dst[i] = ADD ? (float)((double)h[i] + y[0][i]) : o[i];
   }
 }
 

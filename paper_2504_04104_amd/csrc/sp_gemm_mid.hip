@@ -351,9 +351,10 @@ static MidCut mid_cut(int M, int N, int K, int n_cu) {
 }
 
 // Which plain products: all over row-major weights (1 to 160 rows, above).  In fragment order all of 65-160 rows, and of
-// 17-64 rows those whose slices are at least 1024 deep: shorter ones (8B and 70B QKV and O, four to eight chunks) lose up to
-// 8 % at 64 rows, down gains (14336 and 28672 deep, 64 rows 28.1 / 26.8 and 83 / 77 us), and so do 12288-wide matrices (two
-// layers at 64 rows 504 / 473).  At 17 rows two 8B layers lose 1.5 % (217 / 221 us), at 33 they are level.  Up to 16 rows the
+// 17-64 rows those whose slices are at least 1024 deep: shorter ones (the 8B shape's O, four chunks) lose up to 8 % at 64
+// rows, down gains (14336 and 28672 deep, 64 rows 28.1 / 26.8 and 83 / 77 us), and so do 12288-wide matrices (two
+// layers at 64 rows 504 / 473).  Four 8B layers lose 1 % at
+// 17 rows (438 / 442 us), are level at 24 and gain from 28 on (48 rows 477 / 468).  Up to 16 rows the
 // kernels of one row tile stream weights in fragment order as fast without the loading waves.
 bool sp_gemm_mid_takes(int M, int N, int K, bool packed, int n_cu) {
   if (M < 1 || M > 160 || N % 128 || K % MID_KC) return false;
