@@ -30,12 +30,21 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16, published
 
 
 def gateup_kernel(n, d_ff, n_cu):
-    """Name of the kernel that runs a packed stage's gate/up projection of n rows on n_cu compute units (the rules of
-    sp_stage_forward, sp_gemm_mid_takes_gateup and sp_launch_gemm_gateup_bf16)."""
+    """Name of the kernel of a packed stage's gate/up projection of n rows on n_cu compute units, as far as launched_kernel
+    has no other for them."""
     cols = d_ff // n_cu if d_ff % n_cu == 0 else 0          # columns per compute unit
     if 49 <= n <= 160 and cols % 8 == 0 and 48 < cols <= 64:
         return "k_gemm_mid"
     return "k_gemm_wide" if n > 128 else "k_gemm_bf16"
+
+
+def launched_kernel(n, d_ff, n_cu):
+    """Name of the kernel that the library launches for it (the rules of sp_stage_forward, sp_gemm_mid_takes_gateup,
+    sp_launch_gemm_wide_gateup and sp_launch_gemm_gateup_bf16)."""
+    cols = d_ff // n_cu if d_ff % n_cu == 0 else 0
+    if cols % 8 == 0 and (17 <= n <= 192 and 48 < cols <= 64 or 17 <= n <= 160 and 96 < cols <= 112):
+        return "k_gemm_mid"
+    return "k_gemm_wide32" if n > 256 else gateup_kernel(n, d_ff, n_cu)
 
 
 def profiled_traffic(kernel=None, path=os.path.join(ROOT, "profiles", "pmc_hbm_traffic_stage_step_c2.txt")):
@@ -191,7 +200,7 @@ def main() -> int:
     # HBM bytes per launch from rocprofv3 PMC runs of this same command (FETCH_SIZE x 2.00 + WRITE_SIZE x 1.00,
     # factors from a 1 GiB copy), read from the committed summary of those runs; it holds the profiled shape
     # only (C2 at 64 rows) and the kernel that ran then, and otherwise the field stays null.
-    gu_kernel = gateup_kernel(n, sh.d_ff, torch.cuda.get_device_properties(0).multi_processor_count)
+    gu_kernel = launched_kernel(n, sh.d_ff, torch.cuda.get_device_properties(0).multi_processor_count)
     traffic = profiled_traffic(gu_kernel) if (args.workload == "C2" and n == 64 and not args.unpacked) else None
     roofline = {"bound": "hbm", "kernel": "gemm_gateup (%s GATEUP)" % gu_kernel, "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),

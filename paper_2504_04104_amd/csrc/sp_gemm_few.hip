@@ -19,7 +19,8 @@
 // steps are all within 2 % of this.
 //
 // Every workgroup reads all of X from L2, as much as it reads of the weights when all 16 rows are there, and that is
-// what more rows cost (8192 x 28672: 71.5 us with one row, 95.4 with 16).  Where N has 32 columns for each of the CUs a
+// what more rows cost (row-major rows, read in 64-byte pieces, 8192 x 28672: 71.5 us with one row, 95.4 with 16; beyond four
+// rows they come in fragment order now, four 8B layers at 16 rows 426 -> 400 us a step).  Where N has 32 columns for each of the CUs a
 // workgroup takes two strips of 16 and so half of that: 8192 x 28672 at 8 / 16 rows 75.6 -> 71.8 / 95.4 -> 80.8 us,
 // 8192 x 8192 29.6 -> 27.2 / 35.4 -> 28.1, level up to 4 rows.  The two strips of all workgroups start 16 KB or a
 // multiple apart in X, so these walk k from staggered starts (8192 x 8192: 31.1 -> 28.1 us; with one strip no gain).
