@@ -15,7 +15,7 @@
 //
 // A workgroup covers eight strips (plain: 128 columns; gate/up: the CU's even share of the columns as gate strips and the up
 // strips behind them, the last one short), twelve (96 columns: six waves) or, gate/up of 97-112 columns per CU, fourteen, one
-// workgroup per CU.  Two layers, the kernels before / here, us: 8B row-major 16 rows 262 / 212, 64 rows 287 / 238, 160 rows
+// workgroup per CU.  Two 8B or one 70B layer, the kernels before / here, us: 8B row-major 16 rows 262 / 212, 64 rows 287 / 238, 160 rows
 // 376 / 320; 70B row-major 17 rows 371 / 301, 64 rows 412 / 320, 128 rows 476 / 372, 160 rows 666 / 405; 70B in fragment order
 // 160 rows 562 / 392; 12288 wide in fragment order 112 rows 594 / 555.
 //
@@ -89,9 +89,10 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   // one row tile of gate/up: the rows may come without their RMSNorm, whose scale is then a factor of the products
   constexpr bool SCALED = GATEUP && MT == 1;
   __shared__ float s_tot[SCALED ? 16 : 1];
-  RowSquares<64 * (SCALED ? NMM : 1)> sq;
-  static_assert(!SCALED || 16 % NMM == 0, "the multiplying waves share the rows evenly");
-  if (SCALED && mm && ssq) sq.load(ssq, K / 16, M);
+  constexpr int SQW = !SCALED ? 1 : 16 % NMM == 0 ? NMM : 4;      // multiplying waves that share the 16 rows evenly
+  static_assert(SQW <= NMM, "the row sums belong to multiplying waves");
+  RowSquares<64 * SQW> sq;
+  if (SCALED && wave < SQW && ssq) sq.load(ssq, K / 16, M);
 
   // One barrier per chunk.  Behind that of chunk C, panel C is complete and nobody reads panel C - 1 any more, whose
   // place panel C + D takes.  Loads past the last chunk go to an empty buffer: they cost an issue slot and keep every
@@ -200,7 +201,8 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   }
 #undef SP_PC
 
-  if (SCALED && mm && ssq) sq.post(ssq, K / 16, M, s_tot);
+  if (SCALED && wave < SQW && ssq) sq.post(ssq, K / 16, M, s_tot);
+  if (SCALED && KQ == 1) __syncthreads();       // (with two waves per strip the fold has its barriers)
   if (KQ > 1) {
     // Fold the two waves that share their strips: strip by strip, a wave leaves the row tiles that are not its own (tile
     // mt belongs to wave mt % 2) and adds the other's products of its own tiles, in order.
@@ -228,7 +230,6 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   // lane holds, for row m = mt*16 + l%16 of its own tiles, columns (strip base) + 4*(l/16) + 0..3
   if (GATEUP) {
     if (!mm) return;
-    static_assert(!SCALED || KQ > 1, "the fold's barrier stands between the row sums and their use");
     float row_scale = 1.f;
     if (SCALED && ssq) row_scale = rsqrtf(s_tot[min(r, M - 1)] / (float)K + eps);
 #pragma unroll
@@ -325,7 +326,7 @@ static hipError_t launch_gateup(int n_cu, hipStream_t st, const bf16_t* X, const
                                 const float* ssq, float eps) {
   constexpr int NPR = KQ == 2 ? MID_NPR : 1;
 #define SP_GO(MTV)                                                                                                        \
-  if constexpr ((MTV > 1 || KQ > 1) && (MTV <= 10 || (KQ == 2 && PACKED))) {                                              \
+  if constexpr ((MTV > 1 || KQ > 1 || !PACKED) && (MTV <= 10 || (KQ == 2 && PACKED))) {                                              \
     typedef GateupPipe<MTV, KQ, PACKED> P;                                                                                \
     hipLaunchKernelGGL((k_gemm_mid<MTV, CW, KQ, true, PACKED, true, P::KC, P::D, P::PF, NPR, P::WL>), dim3(n_cu),         \
                        dim3(64 * (CW * KQ + NPR)), 0, st, X, W, nullptr, act, M, F, K, 1, F / n_cu, ssq, eps);            \
@@ -362,12 +363,13 @@ bool sp_gemm_mid_takes(int M, int N, int K, bool packed, int n_cu) {
   return !packed || M > 64 || (M > 16 && cut.S >= 1 && K >= 1024 * cut.S);
 }
 // Which gate/up products: a CU's even share of 49-64 columns (four groups, two waves each; row-major from one row on,
-// fragment order from two row tiles to 192 rows: 192 rows 57.7 us, in blocks of 128 rows 63.5) or of 97-112 from two row tiles
-// to 160 rows (seven groups, one wave each: 70B shape at 128 rows 177.6 -> 149.4 us).
+// fragment order from two row tiles to 192 rows: 192 rows 57.7 us, in blocks of 128 rows 63.5) or of 97-112 to 160
+// rows (seven groups, one wave each; row-major from one row on, a 70B layer at 1 / 16 rows 371 / 390 -> 293 / 298 us; fragment
+// order from two row tiles on, gate/up of the 70B shape at 128 rows 177.6 -> 149.4 us).
 bool sp_gemm_mid_takes_gateup(int M, int F, int K, bool packed, int n_cu) {
   if (M < (packed ? 17 : 1) || M > 192 || K % 128 || n_cu < 1 || F % n_cu || (F / n_cu) % 8) return false;
   const int cpw = F / n_cu;
-  return cpw > 48 && cpw <= 64 ? M <= 160 || packed : M > 16 && M <= 160 && cpw > 96 && cpw <= 112;
+  return cpw > 48 && cpw <= 64 ? M <= 160 || packed : M <= 160 && cpw > 96 && cpw <= 112;
 }
 
 hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,

@@ -19,7 +19,7 @@ def test_few_row_tiles(n, packed):
     check(wl.ModelShape(n_layers=2, d_model=512, n_q_heads=32, n_kv_heads=8, d_head=128, d_ff=14336), n, packed)
 
 
-@pytest.mark.parametrize("n,packed", [(17, True), (48, True), (65, True), (128, True), (160, True), (16, False), (17, False),
+@pytest.mark.parametrize("n,packed", [(17, True), (48, True), (65, True), (128, True), (160, True), (1, False), (4, False), (5, False), (16, False), (17, False),
                                       (64, False), (96, False), (129, False), (160, False)])
 def test_seven_column_groups(n, packed):
     check(wl.ModelShape(n_layers=1, d_model=512, n_q_heads=8, n_kv_heads=2, d_head=128, d_ff=28672), n, packed)
