@@ -281,12 +281,15 @@ k_gemm_wide32(const bf16_t* X, const bf16_t* W, float* out, bf16_t* act, int M, 
   const int wl = (r >> 4) * (K * 32) + hf * 256 + (r & 15) * 16;
   const int ll = (r >> 4) * 1024 + hf * 256 + (r & 15) * 16;
   const int t0 = mblk * RT * 2, t_last = (M - 1) >> 4;
+  // The descriptor starts at the workgroup's row block: the activations of a call may be longer than its 2 GB (16384 rows of
+  // d_ff above 65536), a block's offsets stay below 512 * K bytes.
+  const bf16_t* xblk = X + (size_t)t0 * (K / 32) * 512;
   int xo[NX], xl[NX];                               // (row tiles and blocks past the last one repeat it)
 #pragma unroll
   for (int j = 0; j < NX; ++j) {
     const int b = min(wave * NX + j, BLOCKS - 1);
     xl[j] = b * 1024;
-    xo[j] = min(t0 + b, t_last) * (K * 32);
+    xo[j] = min(b, t_last - t0) * (K * 32);
   }
   const int lane16 = lane * 16;
   u32x4_t wb[NB][2][2];
@@ -302,7 +305,7 @@ k_gemm_wide32(const bf16_t* X, const bf16_t* W, float* out, bf16_t* act, int M, 
 #define SP_LOADS(I, C)                                                                                  \
   {                                                                                                     \
     const bool on_ = (C) < c_end;                                                                       \
-    const auto xb_ = buffer_at(X, on_);                                                                 \
+    const auto xb_ = buffer_at(xblk, on_);                                                                 \
     _Pragma("unroll") for (int j = 0; j < NX; ++j) load_to_lds(xb_, SP_PAN(I) + xl[j], lane16, (C) * 1024 + xo[j]); \
     __builtin_amdgcn_sched_barrier(0);                                                                  \
     _Pragma("unroll") for (int a = 0; a < 2; ++a) {                                                     \

@@ -7,7 +7,7 @@ import pytest
 
 import workloads as wl
 import paper_2504_04104_amd as sp
-from gpu_harness import Pair, elementwise_figure, rel_err
+from gpu_harness import Pair, elementwise_figure, rel_err, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -27,6 +27,24 @@ def test_row_blocks(rows, packed):
 def test_k_slices_of_the_plain_products(rows):
     """K = 4096 in O and 3072 in the down projection with 512 to 768 columns: up to eight slices."""
     check(wl.ModelShape(n_layers=1, d_model=768, n_q_heads=32, n_kv_heads=4, d_head=128, d_ff=3072), rows, True)
+
+
+def test_activations_longer_than_2_gb():
+    """The most rows a call can carry (64 requests of 256 nodes) over d_ff = 66048: the products' rows take 2.16 GB, the
+    last request's the part beyond 2^31 bytes.  Increment of its rows as above."""
+    shape = wl.ModelShape(n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=1, d_head=128, d_ff=66048)
+    n_req, n = sp.SP_MAX_BATCH_REQ, sp.SP_MAX_TREE_NODES
+    assert (n_req - 1) * n * shape.d_ff * 2 < 2 ** 31 < (n_req * n - 16) * shape.d_ff * 2
+    pair = Pair(shape, 29, {r: 1 for r in range(n_req)}, max_batch_nodes=n_req * n, flags=sp.SP_FLAG_PACKED_WEIGHTS, oracle_reqs=[n_req - 1])
+    trees = [wl.tree_uniform_parents(29, n, 9, name=("long", r)) for r in range(n_req)]
+    pair.insert_batch(list(range(n_req)), trees)
+    x = wl.hidden_rows(shape, 29, ("long",), n_req * n) * np.float32(2.0 ** -6)
+    y = to_np(pair.gpu.stage_forward(list(range(n_req)), [0] * n_req, [n] * n_req, to_dev(x, pair.gpu)))[-n:]
+    x = x[-n:]
+    ref = pair.ora.stage_forward(n_req - 1, 0, x)
+    assert rel_err(y - x, ref - x) <= 2e-2
+    assert elementwise_figure(y.astype(np.float64) - x, ref - x, 2e-2, 5e-2) <= 1.0
+    pair.close()
 
 
 def check(shape, rows, packed):
