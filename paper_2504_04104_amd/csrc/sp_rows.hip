@@ -61,9 +61,10 @@ __device__ __forceinline__ f32x4_t fold4(const float* p, int S, size_t stride) {
 // first two passes stay in registers.
 #define ENTER_ROWS 4       // rows a workgroup of descriptors and rotary tables takes (few: double precision is slow)
 // Workgroups of the rows: one each.  Fragment order puts eight rows into a 128-byte line: they go to the same XCD, whose L2
-// puts the line together, in whole groups of 64 rows (145 rows 7.1 -> 6.8 us).  Up to 64 rows that would leave XCDs, and
+// puts the line together, in whole groups of 64 rows (145 rows 7.1 -> 6.8 us, 128 rows of 8192 8.1 -> 7.3).  Up to 64 rows that would leave XCDs, and
 // their share of the bandwidth for the partial sums, idle (24 rows 9.1 us against 7.2): consecutive workgroups there.
-__host__ __device__ inline int norm_blocks(int M, bool frag) { return frag && M > 64 ? (M + 63) / 64 * 64 : M; }
+__host__ __device__ inline bool norm_grouped(int M, bool frag) { return frag && M > 64; }
+__host__ __device__ inline int norm_blocks(int M, bool frag) { return norm_grouped(M, frag) ? (M + 63) / 64 * 64 : M; }
 struct NoPlan { int unused; };
 template <bool FIRST> struct PlanArg { typedef NoPlan type; };
 template <> struct PlanArg<true> { typedef AttnPlan type; };
@@ -76,7 +77,7 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
                                                     float* cs, int d_head, float theta, bool frag) {
   __shared__ float s_red[16];
   const int row_blocks = norm_blocks(M, frag);
-  const int row = row_blocks != M ? (((blockIdx.x >> 6) * 8 + (blockIdx.x & 7)) * 8 + ((blockIdx.x >> 3) & 7)) : blockIdx.x;
+  const int row = norm_grouped(M, frag) ? (((blockIdx.x >> 6) * 8 + (blockIdx.x & 7)) * 8 + ((blockIdx.x >> 3) & 7)) : blockIdx.x;
   if constexpr (FIRST) {
     const int half = d_head >> 1;
     if ((int)blockIdx.x >= row_blocks) {
