@@ -404,19 +404,26 @@ k_gemm_wide32(const bf16_t* X, const bf16_t* W, float* out, bf16_t* act, int M, 
 #undef SP_PAN
 }
 
-// Height of the row blocks and number of k slices.  us[RT][n]: what n workgroups of a height take on a CU over 4096 k (8B
-// gate/up, measured with 224 workgroups and more); two of up to 160 rows share a CU.  A slice costs its partial sums, M * N
-// floats written here and read by the kernel that folds them, at 3.5 TB/s for the two.
+// Height of the row blocks and number of k slices.  A column tile's workgroups run on one XCD (ids equal modulo 8), so what
+// counts is the XCD with the most tiles: 20 tiles put three on four of them and two on the others (5120 columns, 768 rows: O
+// 79.7 us planned over all CUs, 53.3 here).  one, two: us that one workgroup alone on a CU, or two of up to 160 rows side by
+// side, take over 4096 k, the least-squares fit of 2090 launches (all heights and slices, 257 to 1024 rows, 2048 to 8192
+// columns; residual 4 %; the plan costs 0.4 % of the best choice on average).  A slice costs its partial sums, M * N floats
+// written here at 4.6 TB/s and read by the kernel that folds them at 3.4.  gate/up (row_bytes 0): a further round of one
+// workgroup a CU costs some 20 us beside its products (700 and 768 rows, heights 6 or 8 / 4: 8B shape 169 / 161, 70B shape 628
+// / 602; 70B shape, 512 rows, two rounds of height 8 / 4: 420 / 440).
 struct WidePlan { int RT, S; };
 static WidePlan wide_plan(int M, int n_tiles, int K, size_t row_bytes, int n_cu, int max_s) {
-  static const float one[9] = {0, 0, 0, 0, 81, 87, 95, 100, 104}, two[6] = {0, 0, 0, 0, 112, 130};
+  static const float one[9] = {0, 0, 0, 0, 60, 68, 77, 87, 96}, two[6] = {0, 0, 0, 0, 103, 117};
+  const int xcd_tiles = (n_tiles + 7) / 8, xcd_cus = (n_cu + 7) / 8;
   WidePlan best = {8, 1};
   float best_us = 0.f;
   for (int RT = 4; RT <= 8; ++RT)
     for (int S = 1; S <= max_s; ++S) {
-      const int wgs = n_tiles * ((M + RT * 32 - 1) / (RT * 32)) * S, n = (wgs + n_cu - 1) / n_cu;
+      const int wgs = xcd_tiles * ((M + RT * 32 - 1) / (RT * 32)) * S, n = (wgs + xcd_cus - 1) / xcd_cus;
       const float loop = RT <= 5 ? (n / 2) * two[RT] + (n % 2) * one[RT] : n * one[RT];
-      const float us = loop * (float)K / (4096.f * (float)S) + (float)S * (float)M * (float)row_bytes * 2.f / 3.5e6f;
+      const float more = row_bytes == 0 && RT > 5 ? 22.f * (float)(n - 1) : 0.f;
+      const float us = loop * (float)K / (4096.f * (float)S) + more + (float)S * (float)M * (float)row_bytes / 1.95e6f;
       if (best_us == 0.f || us < best_us) { best_us = us; best = {RT, S}; }
     }
   return best;

@@ -1,7 +1,11 @@
-"""Many rows over weights in fragment order: the 32 x 32 kernel at the row counts that select each of its heights (the
-8B stage's column counts over a short k range: d_ff = 14336 makes 112 column tiles, so that the rounds of workgroups decide
-as they do at full depth), one and two workgroups per CU, ragged last tiles, several k slices of the plain products; and
-161-192 rows of gate/up in the kernel of the fewer rows.  Row-major weights stay in blocks of 128 and 256 rows."""
+"""Many rows over weights in fragment order: the 32 x 32 kernel at the row counts that select each of its heights, in gate/up
+(the 8B stage's column counts over a short k range: d_ff = 14336 makes 112 column tiles, so that the rounds of workgroups
+decide as they do at full depth) and in the plain products, whose write-out is another; one and two workgroups per CU, ragged
+last tiles, several k slices; 161-192 rows of gate/up in the kernel of the fewer rows.  Row-major
+weights stay in blocks of 128 and 256 rows."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -47,10 +51,38 @@ def test_activations_longer_than_2_gb():
     pair.close()
 
 
-def check(shape, rows, packed):
+def wide_plan(rows, tiles, K, columns, cus=256, max_s=8):
+    """The library's choice of (height in tiles of 32 rows, k slices) for a plain product, on the constants of its source."""
+    src = open(os.path.join(os.path.dirname(sp.__file__), "csrc", "sp_gemm_wide.hip")).read()
+    one, two = ([float(v) for v in re.search(name + r"\[\d\] = \{([^}]*)\}", src).group(1).split(",")] for name in ("one", "two"))
+    best = None
+    for rt in range(4, 9):
+        for s in range(1, max_s + 1):
+            n = -(-(-(-tiles // 8) * -(-rows // (rt * 32)) * s) // (cus // 8))
+            loop = n // 2 * two[rt] + n % 2 * one[rt] if rt <= 5 else n * one[rt]
+            us = loop * K / (4096 * s) + s * rows * columns * 4 / 1.95e6
+            if best is None or us < best[0]:
+                best = us, rt, s
+    return best[1:]
+
+
+# rows: height and slices of QKV (10240 columns, whose slices fill the scratch) and of O (8192 deep, 512 columns)
+PLAIN = {513: ((4, 1), (5, 8)), 641: ((4, 1), (6, 8)), 767: ((4, 1), (6, 8)), 769: ((5, 1), (5, 6)), 850: ((5, 1), (7, 8)),
+         895: ((5, 1), (7, 8)), 1000: ((6, 1), (8, 8)), 1023: ((6, 1), (8, 8))}
+
+
+@pytest.mark.parametrize("rows", PLAIN)
+def test_heights_of_the_plain_products(rows):
+    """Heights of five to eight tiles with their write-out, last tiles of one row to one row short."""
+    shape = wl.ModelShape(n_layers=1, d_model=512, n_q_heads=64, n_kv_heads=8, d_head=128, d_ff=512)
+    assert (wide_plan(rows, 40, 512, 10240, max_s=1024 * 10240 // (rows * 10240)), wide_plan(rows, 2, 8192, 512)) == PLAIN[rows]
+    check(shape, rows, True, max_rows=1024)
+
+
+def check(shape, rows, packed, max_rows=704):
     n_req = (rows + 249) // 250
     counts = [rows // n_req + (r < rows % n_req) for r in range(n_req)]
-    pair = Pair(shape, 29, {r: 19 + r for r in range(n_req)}, max_batch_nodes=704, flags=sp.SP_FLAG_PACKED_WEIGHTS if packed else 0)
+    pair = Pair(shape, 29, {r: 19 + r for r in range(n_req)}, max_batch_nodes=max_rows, flags=sp.SP_FLAG_PACKED_WEIGHTS if packed else 0)
     for r, n in enumerate(counts):
         pair.insert(r, wl.tree_uniform_parents(29, n, 9, name=("many", rows, r)))
     x = wl.hidden_rows(shape, 29, ("many", rows), rows) * np.float32(2.0 ** -6)
