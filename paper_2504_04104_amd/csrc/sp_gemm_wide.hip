@@ -444,9 +444,14 @@ static hipError_t launch_wide32(const WidePlan& p, hipStream_t st, const bf16_t*
 #undef SP_GO
   return hipGetLastError();
 }
-// From how many rows: gate/up 256 rows 72.0 above / 81.2 us here, 288 rows 105.9 / 86.8; plain products in blocks of 128 rows are
-// level or better up to 384 rows (320 rows: QKV 30.0 / 30.0, O 21.4 / 24.7, down 50.2 / 50.9).
-static bool wide32_takes(int M, bool packed, bool gateup) { return packed && M > (gateup ? 256 : 384); }
+// From how many rows: gate/up 256 rows 72.0 above / 81.2 us here, 288 rows 105.9 / 86.8; but up to 320 rows where either
+// kernel makes one round of workgroups (no XCD has more tiles in three row blocks than CUs), as the one above runs its third
+// block at half height (8192 columns, 257 / 320 rows, four layers 3072 wide 696 / 764 above, 713 / 769 us here).  Plain products
+// in blocks of 128 rows are level or better up to 384 rows (320 rows: QKV 30.0 / 30.0, O 21.4 / 24.7, down 50.2 / 50.9).
+static bool wide32_takes(int M, bool packed, bool gateup, int n_tiles, int n_cu) {
+  if (!packed || M <= (gateup ? 256 : 384)) return false;
+  return !gateup || M > 320 || (n_tiles + 7) / 8 * 3 > n_cu / 8;
+}
 
 // rows per workgroup: 256 once there are enough rows to fill them, else 128
 #ifndef SP_WIDE_ROWS
@@ -458,7 +463,7 @@ hipError_t sp_launch_gemm_wide(const bf16_t* X, bool frag, const bf16_t* W, bool
                                int n_cu, size_t part_capacity_floats, int* S_out, hipStream_t st) {
   constexpr int SPW = 4;
   if (M < 1 || N % (64 * SPW) || K % WKC || packed != frag) return hipErrorInvalidValue;
-  if (wide32_takes(M, packed, false)) {
+  if (wide32_takes(M, packed, false, N / 256, n_cu)) {
     int max_s = K / 32 < 8 ? K / 32 : 8;
     while (max_s > 1 && (size_t)max_s * M * N > part_capacity_floats) --max_s;
     if ((size_t)max_s * M * N > part_capacity_floats) return hipErrorInvalidValue;
@@ -488,7 +493,7 @@ hipError_t sp_launch_gemm_wide_gateup(const bf16_t* X, bool frag, const bf16_t* 
   constexpr int SPW = 4;                            // two gate strips and two up strips per wave
   constexpr int TW = 64 * (SPW / 2);                // activation columns per workgroup
   if (M < 1 || F % TW || K % WKC || (packed ? !frag : frag && M > 256)) return hipErrorInvalidValue;
-  if (wide32_takes(M, packed, true))
+  if (wide32_takes(M, packed, true, F / TW, n_cu))
     return launch_wide32<true>(wide_plan(M, F / TW, K, 0, n_cu, 1), st, X, W, nullptr, act, M, F, K, F / TW);
   const int WROWS = wide_rows(M);
   const int n_tiles = F / TW, m_blocks = (M + WROWS - 1) / WROWS;

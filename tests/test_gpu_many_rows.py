@@ -1,8 +1,8 @@
 """Many rows over weights in fragment order: the 32 x 32 kernel at the row counts that select each of its heights, in gate/up
 (the 8B stage's column counts over a short k range: d_ff = 14336 makes 112 column tiles, so that the rounds of workgroups
 decide as they do at full depth) and in the plain products, whose write-out is another; one and two workgroups per CU, ragged
-last tiles, several k slices; 161-192 rows of gate/up in the kernel of the fewer rows.  Row-major
-weights stay in blocks of 128 and 256 rows."""
+last tiles, several k slices; 161-192 rows of gate/up in the kernel of the fewer rows, 257-320 of a narrow one in blocks of
+128.  Row-major weights stay in blocks of 128 and 256 rows."""
 import os
 import re
 
@@ -77,6 +77,12 @@ def test_heights_of_the_plain_products(rows):
     shape = wl.ModelShape(n_layers=1, d_model=512, n_q_heads=64, n_kv_heads=8, d_head=128, d_ff=512)
     assert (wide_plan(rows, 40, 512, 10240, max_s=1024 * 10240 // (rows * 10240)), wide_plan(rows, 2, 8192, 512)) == PLAIN[rows]
     check(shape, rows, True, max_rows=1024)
+
+
+@pytest.mark.parametrize("rows", [257, 320, 321])
+def test_gateup_in_one_round(rows):
+    """64 column tiles, three row blocks: blocks of 128 rows up to 320."""
+    check(wl.ModelShape(n_layers=1, d_model=512, n_q_heads=4, n_kv_heads=1, d_head=128, d_ff=8192), rows, True)
 
 
 def check(shape, rows, packed, max_rows=704):
