@@ -181,6 +181,8 @@ inline hipError_t other_gemm(const sp_stage* s, const void* X, const void* W, fl
 
 // vocabulary products on the bf16 matrix-core kernels
 inline bool head_on_mfma(const sp_stage* s, int V) { return s->fast && V % 64 == 0 && s->cfg.d_model % 128 == 0; }
+// ... which take their rows in fragment order beside packed weights
+inline bool head_rows_frag(const sp_stage* s, int V) { return head_on_mfma(s, V) && s->packed; }
 
 // Brackets a launch with events when its kind is being profiled.
 struct ProfScope {
@@ -1102,7 +1104,7 @@ static int verify_head_on(sp_stage* s, const HeadScratch& w, const sp_head_weigh
     rows_of.seg_first[i] = b.first[i];
   }
   e = sp_launch_enter_norm(c.dtype, x, rows_of, nullptr, s->d_meta, s->d_tables, w.rows, w.cs, c.d_head, c.rope_theta,
-                           w.h, head->norm, w.xn, head_on_mfma(s, V), M, d, c.rms_eps, st);
+                           w.h, head->norm, w.xn, head_rows_frag(s, V), M, d, c.rms_eps, st);
   if (e != hipSuccess) return hip_fail(s, e);
   ProfScope p(s, SP_K_VERIFY_HEAD, st);
   if (head_on_mfma(s, V)) {
@@ -1173,13 +1175,13 @@ int sp_stage_verify_lossy(sp_stage* s, const sp_head_weights* head, int32_t n, c
   const size_t logit_floats = (size_t)n * V;
   if (logit_floats + sp_lossy_scratch_floats(n, V) > w.part_floats) return SP_E_CAPACITY;
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, head_on_mfma(s, V), n, d, c.rms_eps, st);
+  hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, head_rows_frag(s, V), n, d, c.rms_eps, st);
   if (e != hipSuccess) return hip_fail(s, e);
   ProfScope p(s, SP_K_VERIFY_HEAD, st);
   if (head_on_mfma(s, V)) {
     int S = 1;
     e = sp_launch_gemm_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, n, V, d, 1,
-                            logit_floats, &S, st);
+                            logit_floats, &S, st, false, s->packed);
   } else {
     e = other_gemm(s, w.xn, head->wvocab, w.part, n, V, d, st);
   }
@@ -1215,7 +1217,7 @@ int sp_stage_verify_sample(sp_stage* s, const sp_head_weights* head, int32_t n, 
   const size_t logit_floats = (size_t)n * V;
   if (logit_floats > w.part_floats) return SP_E_CAPACITY;
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, head_on_mfma(s, V), n, d, c.rms_eps, st);
+  hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, head_rows_frag(s, V), n, d, c.rms_eps, st);
   if (e != hipSuccess) return hip_fail(s, e);
   ProfScope p(s, SP_K_VERIFY_HEAD, st);
   // statistics of the logits' tiles behind them, where the workspace has room; the deciding kernel can do without
@@ -1229,7 +1231,7 @@ int sp_stage_verify_sample(sp_stage* s, const sp_head_weights* head, int32_t n, 
     } else {
       int S = 1;
       e = sp_launch_gemm_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, n, V, d, 1,
-                              logit_floats, &S, st);
+                              logit_floats, &S, st, false, s->packed);
     }
   } else {
     e = other_gemm(s, w.xn, head->wvocab, w.part, n, V, d, st);

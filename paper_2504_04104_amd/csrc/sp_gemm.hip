@@ -79,11 +79,13 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   constexpr int ROWS = MT * 16;
   constexpr int UPT = KC * 2;             // 16-byte units of a row tile's chunk (KC / 32 fragment blocks, consecutive in X)
   constexpr int UNITS = MT * UPT;
+  constexpr int XS = KC * 2 + 16, UPR = KC / 8;    // row-major X: padded LDS row in bytes, units per row
   constexpr int PASSES = (UNITS + NTH - 1) / NTH;  // the last staging pass may cover fewer units
   constexpr bool RAGGED_PASS = UNITS % NTH != 0;
   constexpr int NB = PF + 1;              // weight register buffers
-  // two panels in fragment order, as X: the fragment reads are conflict-free without padding
-  __shared__ __attribute__((aligned(16))) char lds[2 * UNITS * 16];
+  // two panels laid as X: in fragment order the fragment reads are conflict-free without padding
+  constexpr int PANEL = FRAG ? UNITS * 16 : ROWS * XS;
+  __shared__ __attribute__((aligned(16))) char lds[2 * PANEL];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int cg = wave % NCG, kh = wave / NCG;
@@ -110,12 +112,10 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 #pragma unroll
   for (int p = 0; p < PASSES; ++p) {
     const int u = p * NTH + tid;
-    xo[p] = (unsigned)min(blockIdx.z * MT + u / UPT, (M - 1) >> 4) * (unsigned)(K * 16) + (u % UPT) * 8;
-    // few rows may come row-major
-    if (!FRAG) xo[p] = (unsigned)(min(u & 15, M - 1) * K + ((u % UPT) >> 4) * 8);
+    xo[p] = FRAG ? (unsigned)min(blockIdx.z * MT + u / UPT, (M - 1) >> 4) * (unsigned)(K * 16) + (u % UPT) * 8
+                 : (unsigned)min(m_base + u / UPR, M - 1) * (unsigned)K + (u % UPR) * 8;
   }
   constexpr int XCHUNK = FRAG ? KC * 16 : KC;
-  static_assert(FRAG || MT == 1, "row-major rows: one tile only");
 
   u32x4_t wb[NB][NW][KSTEPS];
   u32x4_t xnxt[PASSES];
@@ -132,7 +132,7 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 #define SP_STORE_X(BUF)                                                                                 \
   _Pragma("unroll") for (int p = 0; p < PASSES; ++p)                                                    \
       if (!RAGGED_PASS || p * NTH + tid < UNITS)                                                        \
-        *reinterpret_cast<u32x4_t*>(&lds[((BUF) * UNITS + p * NTH + tid) * 16]) = xnxt[p];
+        *reinterpret_cast<u32x4_t*>(&lds[(BUF) * PANEL + (FRAG ? (p * NTH + tid) * 16 : (p * NTH + tid) / UPR * XS + tid % UPR * 16)]) = xnxt[p];
   // Every weight is read once per launch: the loads carry the non-temporal hint (WNT), so the stream does not
   // push the activation panel (which every workgroup re-reads) out of L2 nor fill the Infinity Cache
   // (gate/up at 8 rows: 43.4 -> 38.8 us, at 64 rows: 50.7 -> 49.5 us).  The exception is a matrix the caller
@@ -161,7 +161,8 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
     _Pragma("unroll") for (int s = 0; s < KSTEPS; ++s) {                                                \
       _Pragma("unroll") for (int mt = 0; mt < MT; ++mt) {                                               \
         const bf16x8_t b = *reinterpret_cast<const bf16x8_t*>(                                          \
-            &lds[(buf * UNITS + (mt * (KC / 32) + kh * KSTEPS + s) * 64 + lane) * 16]);                 \
+            &lds[buf * PANEL + (FRAG ? ((mt * (KC / 32) + kh * KSTEPS + s) * 64 + lane) * 16            \
+                                     : (mt * 16 + r) * XS + ((kh * KSTEPS + s) * 32 + kg * 8) * 2)]);   \
         _Pragma("unroll") for (int a = 0; a < NW; ++a) acc[a][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16( \
             *reinterpret_cast<const bf16x8_t*>(&wb[B][a][s]), b, acc[a][mt], 0, 0, 0);                  \
       }                                                                                                 \
@@ -310,6 +311,10 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 }
 
 // ---- launchers -------------------------------------------------------------------
+// Rows beside row-major weights (the output head and the logits; gate/up takes them as the call's other products do) lie
+// row-major, whatever their number: as many 64-byte pieces of the weights are on their way as L2 takes, and the panel of
+// sixteen rows in fragment order came on top (128256 x 4096, 1 / 8 / 48 rows: 212 / 218 / 250 us, in fragment order 222 / 224 /
+// 257).
 // Up to 64 rows run as one block of MT = ceil(M/16) tiles; more rows (gate/up of other widths, the output head) run in
 // blocks of 128 (MT = 8, always with the 128-wide chunk so that the two LDS panels fit), each block streaming the weights
 // once.
@@ -320,7 +325,7 @@ template <int NCG, bool GATEUP, int KCV, bool PACKED, bool ARGMAX = false>
 static hipError_t launch_mt(int MT, dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out,
                             bf16_t* act, int M, int N, int K, int S, const float* ssq = nullptr, float eps = 0.f, bool frag = true) {
 #define SP_GO(MTV, KCX)                                                                                        \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, NCG, GATEUP, KCX, SP_GEMM_PF, PACKED, ARGMAX>), grid, dim3(256), 0, st, X, \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, NCG, GATEUP, KCX, SP_GEMM_PF, PACKED, ARGMAX, 4, true, false, GATEUP || PACKED>), grid, dim3(256), 0, st, X, \
                      W, out, act, M, N, K, K / KCX, S, (!GATEUP && !ARGMAX) ? rot_for(S, K) : 0, ssq, eps)
   if constexpr (!ARGMAX && (GATEUP ? NCG != 4 : PACKED))
     if (!frag) {
@@ -368,7 +373,7 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   const bool six = SP_GEMM_PLAIN6 && eight && N % 96 == 0 && (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 128) != 0 &&
                    (SP_GEMM_TARGET_WGS_ROWS / 2) % (N / 96) == 0;
   const int TILE = six ? 96 : eight ? 128 : 16 * SP_GEMM_NCG_PLAIN;
-  if (M < 1 || M > 64 || (!frag && M > 8) || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
+  if (M < 1 || M > 64 || (packed ? !frag && M > 8 : frag) || N % TILE || K % SP_GEMM_KC_PLAIN || K % 128) return hipErrorInvalidValue;
   const int chunks = K / SP_GEMM_KC_PLAIN;
   const int tiles = N / TILE;
   // Enough workgroups to keep every CU streaming, within the partial-sum buffer.  Every slice costs M*N*4 bytes
@@ -391,7 +396,7 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   const dim3 grid(tiles, S);
   if (six) {
 #define SP_GO6(MTV, PK)                                                                                          \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 6, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, 6>), grid, dim3(384), 0, \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, 6, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, 6, true, false, PK>), grid, dim3(384), 0, \
                      st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, rot_for(S, K))
     if (packed) { if (MT == 2) SP_GO6(2, true); else if (MT == 3) SP_GO6(3, true); else SP_GO6(4, true); }
     else { if (MT == 2) SP_GO6(2, false); else if (MT == 3) SP_GO6(3, false); else SP_GO6(4, false); }
@@ -404,7 +409,7 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
     hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, true, false, 8, false>),  \
                        grid, dim3(512), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, rot_for(S, K)); \
   else                                                                                                           \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, PK, false, 8>), grid, dim3(512), 0, \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF_EIGHT, PK, false, 8, true, false, PK>), grid, dim3(512), 0, \
                      st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, rot_for(S, K))
     if (packed) { if (MT == 2) SP_GO8(2, true); else if (MT == 3) SP_GO8(3, true); else SP_GO8(4, true); }
     else { if (MT == 2) SP_GO8(2, false); else if (MT == 3) SP_GO8(3, false); else SP_GO8(4, false); }
@@ -461,7 +466,7 @@ hipError_t sp_launch_gemm_argmax_bf16(const bf16_t* X, const bf16_t* W, bool pac
   const dim3 grid(tiles, 1, mblocks);
   if (eight) {
 #define SP_GOA(MTV, PK)                                                                                        \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, 128, SP_GEMM_PF, PK, true, 8>), grid, dim3(512), 0, st, X, W, \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, 8, false, 128, SP_GEMM_PF, PK, true, 8, true, false, PK>), grid, dim3(512), 0, st, X, W, \
                      pairs, nullptr, M, V, K, K / 128, 1)
     if (packed) { if (MT == 2) SP_GOA(2, true); else if (MT == 3) SP_GOA(3, true); else SP_GOA(4, true); }
     else { if (MT == 2) SP_GOA(2, false); else if (MT == 3) SP_GOA(3, false); else SP_GOA(4, false); }
@@ -483,7 +488,7 @@ hipError_t sp_launch_gemm_logits_bf16(const bf16_t* X, const bf16_t* W, bool pac
   *tile_cols = TILE;
   const dim3 grid(V / TILE);
 #define SP_GOL(MTV, NCGV, PK)                                                                                          \
-  hipLaunchKernelGGL((k_gemm_bf16<MTV, NCGV, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, NCGV, true, true>), \
+  hipLaunchKernelGGL((k_gemm_bf16<MTV, NCGV, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, NCGV, true, true, PK>), \
                      grid, dim3(64 * NCGV), 0, st, X, W, logits, nullptr, M, V, K, K / SP_GEMM_KC_PLAIN, 1, 0, nullptr, 0.f, stats, inv_T)
 #define SP_GOT(NCGV, PK) \
   if (MT == 1) SP_GOL(1, NCGV, PK); else if (MT == 2) SP_GOL(2, NCGV, PK); else if (MT == 3) SP_GOL(3, NCGV, PK); else SP_GOL(4, NCGV, PK)

@@ -127,11 +127,12 @@ hipError_t sp_launch_residual_f32(const float* X, const float* W, float* h, cons
 hipError_t sp_launch_attn_f32(const float* q, const RowInfo* rows, const ReqTables* tables, KvGeom g, int layer, float* out,
                               int M, int n_q, int n_kv, int d_head, hipStream_t st);
 // bf16 MFMA kernels: the rows X and the gate/up products are in fragment order (frag_at).  Up to 64 rows.  Returns the split
-// count used in *S_out (partials [S][M][N]).  packed: the weights are in MFMA fragment order (sp_launch_pack_weights); frag
-// false (at most eight rows, packed only): X is row-major.
+// count used in *S_out (partials [S][M][N]).  packed: the weights are in MFMA fragment order (sp_launch_pack_weights).  frag
+// false: X is row-major, as it has to be beside row-major weights, and may be up to eight rows beside packed ones.
 hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st,
-                               bool resident = false, bool frag = true);
+                               bool resident, bool frag);
+// Logits and output head: X in fragment order beside packed weights, row-major beside row-major ones.
 hipError_t sp_launch_gemm_logits_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* logits, float* stats, float inv_T,
                                       int M, int V, int K, int* tile_cols, hipStream_t st);
 // act[m][f] = silu(X Wg^T) * (X Wu^T), W = [gate rows ; up rows]

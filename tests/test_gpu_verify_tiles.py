@@ -134,3 +134,26 @@ def test_sampling_never_draws_a_token_without_probability():
             wrong.append((case, k, float(logits[tok])))
     pair.close()
     assert not wrong, wrong
+
+
+@pytest.mark.parametrize("packed", [True, False], ids=["packed", "rowmajor"])
+@pytest.mark.parametrize("n,V", [(1, 704), (3, 640), (4, 704), (5, 640), (8, 704), (9, 640), (16, 640), (17, 704), (17, 640), (33, 640), (48, 704),
+                                 (48, 640), (64, 640), (70, 704)])
+def test_vocabulary_products_of_distinct_rows(n, V, packed):
+    """Output head, relaxed and top-p verification of rows that all differ, tiles of 64 and of 128 columns, one to eight row
+    tiles and the ends of their blocks: tokens and winning logits within 2e-2 of the largest logit (rows and weights are
+    stored in bf16), as everywhere."""
+    reqs = list(range(min(n, 64)))
+    pair = Pair(SHAPE, 37, {r: 5 + r % 7 for r in reqs}, max_batch_nodes=80, vocab=V, flags=sp.SP_FLAG_PACKED_WEIGHTS if packed else 0)
+    counts = [n - len(reqs) + 1] + [1] * (len(reqs) - 1)
+    for r, c in zip(reqs, counts):
+        pair.insert(r, [-1] * c, [(r * 31 + 7 * k) % V for k in range(c)], [0.5] * c)
+    x = torch.from_numpy(wl.hidden_rows(SHAPE, 37, ("head", n), n)).to("cuda:0", torch.bfloat16)
+    pair.gpu.stage_forward(reqs, [0] * len(reqs), counts, x)
+    for r, c in zip(reqs, counts):
+        pair.ora.stage_forward(r, 0, np.zeros((c, SHAPE.d_model)))
+    pair.verify_head(reqs, [0] * len(reqs), counts, x, 2e-2)
+    rows = x[:len(reqs)].contiguous()
+    for mode in ("relaxed", "top_p"):
+        pair.verify_lossy(reqs, rows, mode, 0.9, 2e-2)
+    pair.close()
