@@ -184,16 +184,18 @@ __global__ void __launch_bounds__(64 * FEW_WAVES) k_gemm_few(FewArgs a) {
 // an uneven last round (8192 deep, 1 / 16 rows: 31.0 -> 38.2 / 44.0 -> 46.7 us).
 static bool two_strips(int N, int K, int n_cu) { return N % 32 == 0 && N >= 32 * n_cu && K % (256 * FEW_WAVES) == 0; }
 
-// Where complete projections are faster than split products and the small kernels behind them.  Measured with both over
-// the widths 1024 to 8192, one layer, us complete / split:
-// - Workgroups of O and down in whole rounds over the CUs (up to 4096 columns in strips of 16, 8192 in two strips):
-//   packed 1024 16 rows 40 / 46, 3072 16 rows 72 / 77, 4096 16 rows 106.7 / 107.1, 8192 12 rows 302 / 305, 13 rows 306 /
-//   305.  An uneven last round leaves most of the chip idle and more X to read: 4608 (288 workgroups) 1 / 4 / 16 rows 143 /
-//   146 / 177 against 142 / 143 / 147, 5120 (320) 116 / 122 / 151 against 123 / 127 / 128, 6144 (384) 156 / 163 / 178
-//   against 160 / 164 / 162, 7168 (448) 217 / 212 / 250 against 221 / 216 / 222: up to four rows there.
-// - Row-major weights (16 half lines a request, as X's own): 3072 10 / 14 rows 83 / 87 against 86 / 87, 4096 8 / 12 rows
-//   127 / 133 against 129 / 133, 3584 8 rows 146 / 145; from 4608 on slower or level with any number of rows (4608 one row
-//   195 / 177, 8192 four rows 378 / 372).
+// Where complete projections are taken: where they are faster than split products and the small kernels behind them, within
+// some 3 %.  Measured with both over the widths 1024 to 16384, us a layer, complete / split:
+// - Weights in fragment order, workgroups of O and down in whole rounds over the CUs (up to 4096 columns in strips of 16,
+//   8192 in two strips): 1024 1 / 16 rows 33 / 38 and 38 / 44, 2048 45 / 53 and 54 / 61, 3072 56 / 66 and 66 / 74, 4096 90 / 99
+//   and 100 / 106, 8192 1 / 12 / 16 rows 282 / 291, 293.8 / 296.0 and 295.1 / 297.1, 16384 967 / 981 and 16 rows 999 / 984.  An
+//   uneven last round leaves most of the chip idle and more X to read: 4608 (288 workgroups) 1 / 4 / 16 rows 131 / 137 / 152
+//   against 132 / 136 / 140, 5120 (320) d_ff = 13824 110 / 116 / 134 against 117 / 121 / 125, 27648 184 / 192 / 220 against 187
+//   / 190 / 195, 7168 (448) 204 / 210 / 223 against 208 / 213 / 216: up to four rows there.
+// - Row-major weights come in half lines here and in whole ones in the split products' kernel; what the complete ones save
+//   behind the products makes up for that on narrow models: 1024 1 / 16 rows 37 / 44 and 44 / 48, 2048 54 / 61 and 64 / 67,
+//   3072 1 / 8 / 10 rows 69 / 74, 76 / 78 and 79.8 / 78.7, 3584 1 / 4 / 8 rows 132 / 135, 140 / 138 and 142 / 138, 4096 1 / 8 / 16
+//   rows 103.1 / 100.8, 106.8 / 105.2 and 112.6 / 106.0, 8192 one row 322 / 291.
 // - One load in flight per wave does not stream: d_ff = 8960 and 11008 (35 and 43 k steps a wave) 54.5 / 51.1 and 106.6 /
 //   106.0 with one row, 61.3 / 58.6 and 113.4 / 109.9 with 16.  Up to 1792 deep a wave has seven steps and it does not matter.
 bool sp_few_takes(int M, int d, int dq, int F, bool packed, int n_cu) {
