@@ -124,8 +124,8 @@ __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u 
 // workgroup of a projection reads all of its input rows out of L2, and a load instruction that covers 1 KB of consecutive
 // addresses gets 120 GB/s per CU from there (31 TB/s over the chip), one that covers 128 bytes of each of eight rows of
 // 8 KB 78, and one that covers 64 bytes of each of sixteen rows 38 (256 workgroups of eight waves that read 0.5 to 18 MB
-// in step).  Up to four rows of a one-tile call with packed weights stay row-major (frag false): a k step of a single row
-// is then half a line instead of a piece of each of four.  Element index of (row m, column k) in rows of K columns:
+// in step).  Up to four or eight rows of a one-tile call with packed weights stay row-major (frag false): a k step of a
+// single row is then half a line instead of a piece of each of four.  Element index of (row m, column k) in rows of K columns:
 __device__ __forceinline__ size_t frag_at(int m, int k, int K) {
   return ((size_t)(m >> 4) * (K >> 5) + (k >> 5)) * 512 + (((k >> 3) & 3) * 16 + (m & 15)) * 8 + (k & 7);
 }
