@@ -107,12 +107,14 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   const int c_n = c_end - c_begin;
   const int c_rot = rot && c_n > 1 ? (int)((blockIdx.x >> 3) % (unsigned)c_n) : 0;
 #define SP_PC(C) ((C) + c_rot < c_end ? (C) + c_rot : (C) + c_rot - c_n)
-  // row tiles past the last one repeat it; what they and the last tile's rows past M multiply is never stored
+  // row tiles past the last one repeat it, rows past M the last one (half of a nearly empty tile's lines are then not asked
+  // for); what these multiply is never stored
   unsigned xo[PASSES];
 #pragma unroll
   for (int p = 0; p < PASSES; ++p) {
     const int u = p * NTH + tid;
-    xo[p] = FRAG ? (unsigned)min(blockIdx.z * MT + u / UPT, (M - 1) >> 4) * (unsigned)(K * 16) + (u % UPT) * 8
+    const int tile = min((int)blockIdx.z * MT + u / UPT, (M - 1) >> 4);
+    xo[p] = FRAG ? (unsigned)tile * (unsigned)(K * 16) + ((u % UPT & ~15) | min(u & 15, M - 1 - tile * 16)) * 8
                  : (unsigned)min(m_base + u / UPR, M - 1) * (unsigned)K + (u % UPR) * 8;
   }
   constexpr int XCHUNK = FRAG ? KC * 16 : KC;
