@@ -66,12 +66,18 @@
 // index (the lowest one among equal maxima) as a (float, int) pair at out[(m * tiles + tile) * 2].
 // STATS (logits of a stochastic verification): beside the products, a workgroup leaves per row the maximum mx of its
 // 16*NCG columns and the sum of exp((l - mx) * inv_T) over them as a float pair at stats[(m * tiles + tile) * 2].
+// EVEN (gate/up of two row tiles over weights in fragment order): one workgroup per CU covers cpw = d_ff / CUs columns, a
+// multiple of 8 in 49-64, in four groups of 16 and a last one of cpw - 48, by four groups times two k-halves of waves (the
+// upper lanes of a short last group re-read its last row and their results are dropped).  With so few rows the loading waves
+// of sp_gemm_mid.hip's kernel only take issue slots: gate/up of 17 / 32 rows 41.3 / 41.4 us here, 42.0 / 42.0 there, two 8B
+// layers 216.6 / 222.1 and 219.4 / 223.4; from 33 rows on it is the other way round (43.0 / 42.2).
 template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, int NWAVES = 4, bool WNT = true,
-          bool STATS = false, bool FRAG = true>
+          bool STATS = false, bool FRAG = true, bool EVEN = false>
 __global__ void __launch_bounds__(64 * NWAVES)
 k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
             bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int rot = 0,
-            const float* ssq = nullptr, float eps = 0.f, float* stats = nullptr, float inv_T = 0.f) {
+            const float* ssq = nullptr, float eps = 0.f, float* stats = nullptr, float inv_T = 0.f, int cpw = 0) {
+  static_assert(!EVEN || (GATEUP && PACKED), "even share: gate/up over weights in fragment order");
   constexpr int NTH = 64 * NWAVES;
   constexpr int NKH = NWAVES / NCG;       // waves sharing a column group split each chunk's k-steps
   constexpr int KSTEPS = (KC / 32) / NKH;
@@ -90,14 +96,19 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int cg = wave % NCG, kh = wave / NCG;
   const int r = lane & 15, kg = lane >> 4;
-  const int n0 = blockIdx.x * (16 * NCG) + cg * 16;
+  const int n0 = EVEN ? blockIdx.x * cpw + cg * 16 : blockIdx.x * (16 * NCG) + cg * 16;
+  const int vr = EVEN ? min(16, cpw - cg * 16) : 16;     // valid columns of this wave's group (8 or 16)
   const int m_base = blockIdx.z * ROWS;
   const int c_begin = (int)(((long long)blockIdx.y * chunks_total) / S);
   const int c_end = (int)(((long long)(blockIdx.y + 1) * chunks_total) / S);
 
-  const bf16_t* w0 = PACKED ? W + ((size_t)(n0 / 16) * (K / 32) + kh * KSTEPS) * 512 + lane * 8
+  // EVEN: a group starts at a multiple of 8, so its 16 rows may lie in two fragment blocks: per-lane row addresses
+  const int wr = n0 + min(r, vr - 1);
+  const bf16_t* w0 = EVEN ? W + ((size_t)(wr >> 4) * (K / 32) + kh * KSTEPS) * 512 + (kg * 16 + (wr & 15)) * 8
+                   : PACKED ? W + ((size_t)(n0 / 16) * (K / 32) + kh * KSTEPS) * 512 + lane * 8
                             : W + (size_t)(n0 + r) * K + kg * 8 + kh * (KSTEPS * 32);
-  const bf16_t* w1 = PACKED ? W + ((size_t)((N + n0) / 16) * (K / 32) + kh * KSTEPS) * 512 + lane * 8     // the up rows
+  const bf16_t* w1 = EVEN ? W + ((size_t)((N + wr) >> 4) * (K / 32) + kh * KSTEPS) * 512 + (kg * 16 + (wr & 15)) * 8
+                   : PACKED ? W + ((size_t)((N + n0) / 16) * (K / 32) + kh * KSTEPS) * 512 + lane * 8     // the up rows
                             : W + (size_t)(N + n0 + r) * K + kg * 8 + kh * (KSTEPS * 32);
 #define SP_WOFF(C, s) (PACKED ? ((size_t)(C) * (KC / 32) + (s)) * 512 : (size_t)(C)*KC + (s) * 32)
   // rot: workgroups start at different chunks of their k slice and wrap around, so that the workgroups of one
@@ -107,14 +118,14 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   const int c_n = c_end - c_begin;
   const int c_rot = rot && c_n > 1 ? (int)((blockIdx.x >> 3) % (unsigned)c_n) : 0;
 #define SP_PC(C) ((C) + c_rot < c_end ? (C) + c_rot : (C) + c_rot - c_n)
-  // row tiles past the last one repeat it, rows past M the last one (half of a nearly empty tile's lines are then not asked
-  // for); what these multiply is never stored
+  // row tiles past the last one repeat it, and of up to four tiles rows past M the last one (half of a nearly empty tile's
+  // lines are then not asked for); what these multiply is never stored
   unsigned xo[PASSES];
 #pragma unroll
   for (int p = 0; p < PASSES; ++p) {
     const int u = p * NTH + tid;
     const int tile = min((int)blockIdx.z * MT + u / UPT, (M - 1) >> 4);
-    xo[p] = FRAG ? (unsigned)tile * (unsigned)(K * 16) + ((u % UPT & ~15) | min(u & 15, M - 1 - tile * 16)) * 8
+    xo[p] = FRAG ? (unsigned)tile * (unsigned)(K * 16) + ((u % UPT & ~15) | (MT <= 4 ? min(u & 15, M - 1 - tile * 16) : u & 15)) * 8
                  : (unsigned)min(m_base + u / UPR, M - 1) * (unsigned)K + (u % UPR) * 8;
   }
   constexpr int XCHUNK = FRAG ? KC * 16 : KC;
@@ -222,6 +233,7 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
 
   // lane holds, for activation row m = mt*16 + l%16, output columns n0 + 4*(l/16) + 0..3
   const int ncol = n0 + 4 * kg;
+  if (EVEN && 4 * kg >= vr) return;       // columns past a short last group
   if (ARGMAX) {
     static_assert(!ARGMAX || (NKH == 1 && !GATEUP), "one wave per column group");
     float* s_val = reinterpret_cast<float*>(lds);          // [NCG][ROWS]; the panels are no longer read
@@ -436,6 +448,12 @@ hipError_t sp_launch_gemm_gateup_bf16(const bf16_t* X, bool frag, const bf16_t* 
   row_blocks(M, &MT, &mblocks);
   if ((ssq || !frag) && MT != 1) return hipErrorInvalidValue;
   if (M < 1 || F % 64 || K % SP_GEMM_KC_GATEUP || K % 128) return hipErrorInvalidValue;
+  // two row tiles and a CU's even share of 49-64 columns: one workgroup of eight waves per CU (see EVEN)
+  if (packed && MT == 2 && n_cu > 0 && F % n_cu == 0 && (F / n_cu) % 8 == 0 && F / n_cu > 48 && F / n_cu <= 64) {
+    hipLaunchKernelGGL((k_gemm_bf16<2, 4, true, SP_GEMM_KC_GATEUP, SP_GEMM_PF, true, false, 8, true, false, true, true>), dim3(n_cu), dim3(512), 0, st,
+                       X, W, nullptr, act, M, F, K, K / SP_GEMM_KC_GATEUP, 1, 0, nullptr, 0.f, nullptr, 0.f, F / n_cu);
+    return hipGetLastError();
+  }
   // From 49 rows on: 64 gate + 64 up columns per workgroup (four column groups, 128-k chunks) where that
   // still gives every CU a workgroup, so that the staged panel is at most as large as the weights it meets
   // (70B shape: gate/up 193.6 -> 179.3 us at 64 rows, 252 -> 212 us at 128 rows); else 32 + 32 columns.  With

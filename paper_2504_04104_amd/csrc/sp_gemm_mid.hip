@@ -99,15 +99,16 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   // chunk's wait the same.
   if (!mm) {
     const int pr = wave - NMM;
-    // Row tiles past the last one repeat it, rows past M the last one, so that half of a nearly empty tile's lines are not asked
-    // for (17 and 33 rows, two 8B layers 221.5 -> 220.7 and 228.8 -> 227.8 us); they multiply into rows that are never stored.
+    // Row tiles past the last one repeat it, and of up to four tiles rows past M the last one, so that half of a nearly empty
+    // tile's lines are not asked for (33 rows, two 8B layers 228.8 -> 227.8 us; of eight tiles whole blocks are faster, 108
+    // rows 286.0 against 289.3); they multiply into rows that are never stored.
     int xo[NX], xl[NX];
 #pragma unroll
     for (int j = 0; j < NX; ++j) {
       const int b = pr * NX + j;
       const int tile = min(b / CS, (M - 1) >> 4);
       xo[j] = tile * (K * 32) + (b % CS) * 1024;
-      xl[j] = (kg * 16 + min(r, M - 1 - tile * 16)) * 16;
+      xl[j] = (kg * 16 + (MT <= 4 ? min(r, M - 1 - tile * 16) : r)) * 16;
     }
     int pan = pr * NX * 1024;
     auto load_x = [&](int c) {
@@ -366,13 +367,13 @@ bool sp_gemm_mid_takes(int M, int N, int K, bool packed, int n_cu) {
   return !packed || M > 64 || (M > 16 && cut.S >= 1 && K >= 1024 * cut.S);
 }
 // Which gate/up products: a CU's even share of 49-64 columns (four groups, two waves each; row-major from one row on,
-// fragment order from two row tiles to 192 rows: 192 rows 57.7 us, in blocks of 128 rows 63.5) or of 97-112 to 160
-// rows (seven groups, one wave each; row-major from one row on, a 70B layer at 1 / 16 rows 371 / 390 -> 293 / 298 us; fragment
-// order from two row tiles on, gate/up of the 70B shape at 128 rows 177.6 -> 149.4 us).
+// fragment order from three row tiles to 192 rows: 192 rows 57.7 us, in blocks of 128 rows 63.5; two row tiles sp_gemm.hip)
+// or of 97-112 to 160 rows (seven groups, one wave each; row-major from one row on, a 70B layer at 1 / 16 rows 371 / 390 -> 293
+// / 298 us; fragment order from two row tiles on, gate/up of the 70B shape at 128 rows 177.6 -> 149.4 us).
 bool sp_gemm_mid_takes_gateup(int M, int F, int K, bool packed, int n_cu) {
   if (M < (packed ? 17 : 1) || M > 192 || K % 128 || n_cu < 1 || F % n_cu || (F / n_cu) % 8) return false;
   const int cpw = F / n_cu;
-  return cpw > 48 && cpw <= 64 ? M <= 160 || packed : M <= 160 && cpw > 96 && cpw <= 112;
+  return cpw > 48 && cpw <= 64 ? (packed ? M > 32 : M <= 160) : M <= 160 && cpw > 96 && cpw <= 112;
 }
 
 hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K, int n_cu,
