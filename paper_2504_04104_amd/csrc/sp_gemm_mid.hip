@@ -384,7 +384,9 @@ hipError_t sp_launch_gemm_mid(const bf16_t* X, const bf16_t* W, bool packed, flo
   const int tiles = N / cut.cols, chunks = K / MID_KC;
   int S = cut.S;
   if (S > max_split) S = max_split;
-  if (S > chunks) S = chunks;
+  // Two chunks a slice at least: one makes no use of the ring and costs twice the partial sums (2048 wide, four layers, 104 rows
+  // 381 -> 367 us, row-major 64 rows 335 -> 320).
+  if (S > chunks / 2) S = chunks > 1 ? chunks / 2 : 1;
   while (S > 1 && (size_t)S * M * N > part_capacity_floats) --S;
   if (S < 1) S = 1;
   if ((size_t)S * M * N > part_capacity_floats) return hipErrorInvalidValue;
