@@ -715,13 +715,25 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     return hipSuccess;
   };
   // float32: five launches a layer (the same products between norms, rotation, append, residual and write-out as launches
-  // of their own were eight, 2 layers of d = 256 at 16 nodes 70.1 -> 60.7 us a call)
+  // of their own were eight, 2 layers of d = 256 at 16 nodes 70.1 -> 60.7 us a call), seven where QKV has many workgroups
+  const bool qkv_joined = s->f32 && sp_qkv_f32_joined(M, nqkv, s->n_cu);
   auto run_layers_f32 = [&]() -> hipError_t {
     for (int l = 0; l < c.n_layers; ++l) {
       const sp_layer_weights& L = s->W[l];
-      { ProfScope p(s, SP_K_GEMM_QKV, st);
+      if (qkv_joined) {
+        ProfScope p(s, SP_K_GEMM_QKV, st);
         SP_STEP(sp_launch_qkv_f32(w.h, (const float*)L.norm1, c.rms_eps, (const float*)L.wqkv, w.rows, w.cs, (float*)w.qbuf,
-                                  s->geom, l, M, d, nq, nkv, dh, st)); }
+                                  s->geom, l, M, d, nq, nkv, dh, st));
+      } else {
+        if (l > 0) {                                // (the kernel that opens the call has formed the first layer's)
+          ProfScope p(s, SP_K_NORM, st);
+          SP_STEP(sp_launch_add_norm(dt, w.h, w.part, 0, 0, L.norm1, w.xn, false, M, d, c.rms_eps, st));
+        }
+        { ProfScope p(s, SP_K_GEMM_QKV, st);
+          SP_STEP(sp_launch_gemm_f32((const float*)w.xn, (const float*)L.wqkv, w.part, M, nqkv, d, st)); }
+        { ProfScope p(s, SP_K_ROPE_KV, st);
+          SP_STEP(sp_launch_rope_kv(dt, w.part, 1, strideQ, w.rows, w.cs, w.qbuf, s->geom, l, M, nq, nkv, dh, st)); }
+      }
       { ProfScope p(s, SP_K_ATTENTION, st);
         SP_STEP(sp_launch_attn_f32((const float*)w.qbuf, w.rows, s->d_tables, s->geom, l, (float*)w.attn, M, nq, nkv, dh, st)); }
       { ProfScope p(s, SP_K_GEMM_O, st);
@@ -789,15 +801,18 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
 
   // A shape that comes back replays its graph; one seen for the second time is captured.  Not while a
   // kernel kind is being timed (the events sit between the launches) and not inside a caller's capture.
-  const bool fused = few || s->f32;                 // rotation, norms and write-out are no launches of their own
+  // launches among the layers' of their own: norms, rotation
+  const int n_norm = few || qkv_joined ? 0 : s->f32 ? c.n_layers - 1 : 2 * c.n_layers - 1;
+  const int n_rope = few || qkv_joined ? 0 : c.n_layers;
   sp_stage::FwdGraph* fg = nullptr;
   bool timed = false;                               // an event bracket falls inside this call's layers
   int n_kind = 0;                                   // launches of the timed kind among them
   if (s->prof_kind != 0) {
     const int k = s->prof_kind;
     if (k == SP_K_GEMM_QKV || k == SP_K_GEMM_O || k == SP_K_GEMM_GATEUP || k == SP_K_GEMM_DOWN ||
-        k == SP_K_ATTENTION || (k == SP_K_ROPE_KV && !fused)) n_kind = c.n_layers;
-    else if (k == SP_K_NORM && !fused) n_kind = 2 * c.n_layers - 1;
+        k == SP_K_ATTENTION) n_kind = c.n_layers;
+    else if (k == SP_K_ROPE_KV) n_kind = n_rope;
+    else if (k == SP_K_NORM) n_kind = n_norm;
     if (n_kind > 0) {
       // whole calls are sampled: align the count to this call's group of launches
       s->prof_group = n_kind;

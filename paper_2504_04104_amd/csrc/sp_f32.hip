@@ -60,6 +60,19 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
   }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) x[mt] = X + (size_t)min(m0 + mt * 16 + r, M - 1) * K;
+  // What the finishing waves need is asked for first: the largest workgroups are alone on their CUs, and nothing would cover
+  // the wait (d = 256, 1536 columns, 64 / 1024 rows 11.7 / 49.6 -> 11.4 / 46.7 us).
+  RowInfo ri;
+  f32x4_t co, si;
+  if constexpr (MODE == F_QKV) {
+    if (wave < MT) {
+      const int rc = min(m0 + wave * 16 + r, M - 1);
+      ri = fa.rows[rc];
+      const float* c = fa.cs + (size_t)rc * fa.d_head + t0 + 4 * (kg & 1);
+      co = *reinterpret_cast<const f32x4_t*>(c);
+      si = *reinterpret_cast<const f32x4_t*>(c + half);
+    }
+  }
   // Several short chains of additions per result instead of one long one, and their sums taken in 64 bits: the error
   // against 64-bit arithmetic stays below that of the plain kernel (64 lanes with a few terms each, added pairwise),
   // which float32 sums of the chains miss by 2 % (the matrix unit rounds inside its four-term step).
@@ -172,18 +185,12 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
     for (int i = 0; i < 4; ++i) b[i] = __shfl_xor(o[i], 32, 64);
     if (m >= M) return;
     const int t = t0 + 4 * (kg & 1), col = t + (kg >> 1) * half;
-    const RowInfo ri = fa.rows[m];
-    const size_t slot = sp_phys_slot(fa.g, ri.req, ri.base, ri.P + ri.node);
-    if (head < fa.n_q + fa.n_kv) {
-      const float* c = fa.cs + (size_t)m * fa.d_head;
-      const f32x4_t co = *reinterpret_cast<const f32x4_t*>(c + t), si = *reinterpret_cast<const f32x4_t*>(c + half + t);
-      o = kg < 2 ? o * co - b * si : o * co + b * si;
-    }
+    if (head < fa.n_q + fa.n_kv) o = kg < 2 ? o * co - b * si : o * co + b * si;
     float* dst = out + ((size_t)m * fa.n_q + head) * fa.d_head;
     if (head >= fa.n_q) {
       const int value = head >= fa.n_q + fa.n_kv, kvh = head - fa.n_q - value * fa.n_kv;
       dst = reinterpret_cast<float*>(fa.g.kv + ((size_t)(fa.layer * 2 + value) * fa.n_kv + kvh) * fa.g.plane_bytes +
-                                     slot * fa.g.row_bytes);
+                                     (size_t)sp_phys_slot(fa.g, ri.req, ri.base, ri.P + ri.node) * fa.g.row_bytes);
     }
     *reinterpret_cast<f32x4_t*>(dst + col) = o;
     return;
@@ -329,6 +336,10 @@ static hipError_t launch_gemm_f32(const float* X, const float* W, float* out, in
 hipError_t sp_launch_gemm_f32(const float* X, const float* W, float* out, int M, int N, int K, hipStream_t st) {
   return launch_gemm_f32<F_PLAIN>(X, W, out, M, N, K, F32Args{}, st);
 }
+// RMSNorm and rotation cost every workgroup of QKV some 2.2 us (each column tile forms the norm of its rows again), a norm and a
+// rotation of their own about 10 us together: joined up to four rounds of workgroups over the CUs (d = 512, 3072 columns:
+// QKV 512 rows 57.2 / 43.7 us, 1024 rows 109 / 82; two layers at 384 rows 309 / 304).
+bool sp_qkv_f32_joined(int M, int N, int n_cu) { return (long long)((M + 63) / 64) * ((N + 15) / 16) <= 4ll * n_cu; }
 hipError_t sp_launch_qkv_f32(const float* h, const float* gain, float eps, const float* W, const RowInfo* rows, const float* cs,
                              float* qbuf, KvGeom g, int layer, int M, int d, int n_q, int n_kv, int d_head, hipStream_t st) {
   if (d_head < 16 || d_head % 16) return hipErrorInvalidValue;      // eight pairs to a workgroup

@@ -118,6 +118,7 @@ hipError_t sp_launch_gemm_f32(const float* X, const float* W, float* out, int M,
 // the float32 layer's products with what stands before and after them (h: the residual stream [M][d], float32):
 // qkv of rmsnorm(h), rotated, to qbuf and the cache; silu(gate) * up of rmsnorm(h); h += X W^T, or with plan_out the plan's
 // x_out = h + X W^T
+bool sp_qkv_f32_joined(int M, int N, int n_cu);       // else: a norm, sp_launch_gemm_f32 and a rotation of their own
 hipError_t sp_launch_qkv_f32(const float* h, const float* gain, float eps, const float* W, const RowInfo* rows, const float* cs,
                              float* qbuf, KvGeom g, int layer, int M, int d, int n_q, int n_kv, int d_head, hipStream_t st);
 hipError_t sp_launch_gateup_f32(const float* h, const float* gain, float eps, const float* W, float* act, int M, int F, int K,

@@ -74,3 +74,25 @@ def test_f32_infinite_value_row(shape, page_slots):
     want_inf[:, :shape.n_q_heads // shape.n_kv_heads, col] = True
     assert int((~torch.isposinf(rows[want_inf])).sum()) == 0
     assert int((~torch.isfinite(rows[~want_inf])).sum()) == 0
+
+
+@pytest.mark.parametrize("page_slots", [0, 32], ids=["contiguous", "pages32"])
+@pytest.mark.parametrize("n", [128, 129, 250])
+def test_f32_many_qkv_workgroups(n, page_slots):
+    """6144 QKV columns: up to 128 rows norm and rotation join the product, from 129 on they are launches of their own
+    (bound as in test_f32_tiles)."""
+    shape = wl.ModelShape(n_layers=2, d_model=72, n_q_heads=16, n_kv_heads=16, d_head=128, d_ff=40, rms_eps=1e-6, dtype="f32")
+    pair = Pair(shape, 29, {0: 61}, max_batch_nodes=256, page_slots=page_slots)
+    pair.insert(0, wl.tree_deep(29, n, 20))
+    pair.gpu.profile_begin(11, 16)               # SP_K_ROPE_KV
+    for k in range(3):
+        x = wl.hidden_rows(shape, 29, ("f32 many", n, k), n)
+        y, ref = pair.forward([0], [0], [n], x)
+        assert rel_err(y - x, ref - x) <= 2e-5
+    assert (pair.gpu.profile_end()[0] > 0) == (n > 128)
+    x = wl.hidden_rows(shape, 29, ("f32 many", n), n)
+    for k in range(3):                            # replayed
+        y, ref = pair.forward([0], [0], [n], x)
+        assert rel_err(y - x, ref - x) <= 2e-5
+    pair.check_kv(0, 2e-5)
+    pair.close()
