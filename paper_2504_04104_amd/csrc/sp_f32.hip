@@ -38,7 +38,9 @@ __global__ void __launch_bounds__(64 * F_WAVES) k_gemm_f32(const float* __restri
                                                            float* __restrict__ out, int M, int N, int K, F32Args fa) {
   constexpr bool GATEUP = MODE == F_GATEUP, NORM = MODE == F_QKV || MODE == F_GATEUP;
   constexpr int NS = GATEUP ? 2 : 1;
-  constexpr int F_D = MT * NS == 8 ? 2 : 4;     // 16-byte pieces of every operand in flight per lane (four of the largest spill)
+  // 16-byte pieces of every operand in flight per lane: four; two in the largest gate/up, which spills with four, and in that of
+  // one row tile, where two leave 128 registers and so two workgroups to a CU (4096 x 28672, one row, 113 -> 103 us)
+  constexpr int F_D = GATEUP && MT != 2 ? 2 : 4;
   __shared__ __attribute__((aligned(16))) f32x4_t s_acc[F_WAVES][NS * MT][64];
   __shared__ double s_ss[F_WAVES][NORM ? MT : 1][16];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
