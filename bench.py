@@ -30,8 +30,8 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16, published
 
 
 def gateup_kernel(n, d_ff, n_cu):
-    """Name of the kernel of a packed stage's gate/up projection of n rows on n_cu compute units, as far as launched_kernel
-    has no other for them."""
+    """Name of the kernel of a packed stage's gate/up projection of n rows on n_cu compute units where rows are counted in
+    the ranges 1-48, 49-160 and beyond; launched_kernel has the library's own rules."""
     cols = d_ff // n_cu if d_ff % n_cu == 0 else 0          # columns per compute unit
     if 49 <= n <= 160 and cols % 8 == 0 and 48 < cols <= 64:
         return "k_gemm_mid"
@@ -40,11 +40,14 @@ def gateup_kernel(n, d_ff, n_cu):
 
 def launched_kernel(n, d_ff, n_cu):
     """Name of the kernel that the library launches for it (the rules of sp_stage_forward, sp_gemm_mid_takes_gateup,
-    sp_launch_gemm_wide_gateup and sp_launch_gemm_gateup_bf16)."""
+    sp_launch_gemm_wide_gateup with its wide32_takes, and sp_launch_gemm_gateup_bf16)."""
     cols = d_ff // n_cu if d_ff % n_cu == 0 else 0
-    if cols % 8 == 0 and (17 <= n <= 192 and 48 < cols <= 64 or 17 <= n <= 160 and 96 < cols <= 112):
+    if cols % 8 == 0 and (33 <= n <= 192 and 48 < cols <= 64 or 17 <= n <= 160 and 96 < cols <= 112):
         return "k_gemm_mid"
-    return "k_gemm_wide32" if n > 256 else gateup_kernel(n, d_ff, n_cu)
+    if n <= 128:
+        return "k_gemm_bf16"
+    one_round = -(-d_ff // 128 // 8) * 3 <= n_cu // 8         # three row blocks on the XCD with the most column tiles
+    return "k_gemm_wide32" if n > (320 if one_round else 256) else "k_gemm_wide"
 
 
 def profiled_traffic(kernel=None, path=os.path.join(ROOT, "profiles", "pmc_hbm_traffic_stage_step_c2.txt")):

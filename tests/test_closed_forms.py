@@ -74,3 +74,17 @@ def test_bench_traffic_is_that_of_the_kernel_that_runs(tmp_path):
     assert bench.profiled_traffic("k_gemm_mid", str(tmp_path / "none")) is None
     # the committed summary is of the kernel that runs the profiled shape
     assert bench.profiled_traffic(bench.gateup_kernel(64, c2.d_ff, 256)) is not None
+
+
+def test_bench_names_the_kernel_that_is_launched():
+    """bench.launched_kernel against the kernels that traces of the library show, at the ends of their row ranges: 56 and 112
+    gate/up columns per compute unit, and widths that are no even share."""
+    import bench
+    c2, c3 = wl.CONFIGS["C2"].shape.d_ff, wl.CONFIGS["C3"].shape.d_ff
+    few, mid, wide, wide32 = "k_gemm_bf16", "k_gemm_mid", "k_gemm_wide", "k_gemm_wide32"
+    assert [bench.launched_kernel(n, c2, 256) for n in (1, 32, 33, 64, 192, 193, 256, 257)] == [few, few, mid, mid, mid, wide, wide, wide32]
+    assert [bench.launched_kernel(n, c3, 256) for n in (16, 17, 128, 160, 161, 256, 257)] == [few, mid, mid, mid, wide, wide, wide32]
+    assert [bench.launched_kernel(n, 8192, 256) for n in (64, 128, 129, 257, 320, 321)] == [few, few, wide, wide, wide, wide32]
+    assert [bench.launched_kernel(n, 11008, 256) for n in (64, 129, 256, 257)] == [few, wide, wide, wide32]
+    # the committed counter summary is of the kernel that runs the profiled shape
+    assert bench.profiled_traffic(bench.launched_kernel(64, c2, 256)) is not None

@@ -1,5 +1,5 @@
-"""49-160 rows: the kernels with two strips of weight rows per wave, at the edges of their row tiles and of their k
-loops, and what runs beside them, against the CPU oracle.  The first shape has the 8B stage's column counts (QKV 6144 columns: 96-column tiles; d_ff = 14336 and 16384: 56
+"""49-160 rows: the kernel with two strips of weight rows per wave and loading waves, at the edges of its row tiles and of
+its k loops, and what runs beside it, against the CPU oracle.  The first shape has the 8B stage's column counts (QKV 6144 columns: 96-column tiles; d_ff = 14336 and 16384: 56
 and 64 gate/up columns per CU, with a short and a full last column group) over a short k range."""
 import numpy as np
 import pytest
@@ -21,8 +21,8 @@ def test_row_tiles(n, d_ff, packed):
     check_increment(shape, [n], packed)
 
 
-# Products and gate/up whose workgroups walk eight to sixteen chunks of 128 k: the unguarded six-chunk loop once and
-# twice, and every length of what follows it, at each number of row tiles; row-major gate/up from staggered starts.
+# Products and gate/up whose workgroups walk eight to sixteen chunks of 128 k, the ring of panels and weight sets several
+# times round and left at each of its places, at each number of row tiles; row-major gate/up from staggered starts.
 @pytest.mark.parametrize("n,d_model,d_ff,packed", [(64, 1024, 14336, True), (64, 1280, 16384, False), (96, 1536, 14336, False),
                                                    (96, 1280, 14336, True), (128, 2048, 16384, False), (128, 1792, 14336, True),
                                                    (145, 1024, 14336, False), (160, 2048, 14336, True)])
@@ -37,8 +37,8 @@ def test_96_column_tiles_of_resident_weights(packed):
 
 
 def test_two_strips_per_wave_of_a_wide_matrix():
-    """97-128 rows of a matrix that leaves its workgroups two k slices (11264 columns, 6144 deep): workgroups of four
-    waves with two strips each.  The element-wise allowance is 7.5e-2 of the rms here: the plain kernels, whose float32
+    """97-128 rows of a matrix that leaves its workgroups two k slices (11264 columns, 6144 deep: 88 tiles of 128
+    columns on 256 CUs).  The element-wise allowance is 7.5e-2 of the rms here: the plain kernels, whose float32
     sums run in another order, need 6.0e-2 on the same inputs (1.2 million numbers a call)."""
     shape = wl.ModelShape(n_layers=1, d_model=11264, n_q_heads=16, n_kv_heads=2, d_head=128, d_ff=6144)
     weights = wl.layer_weights(shape, 83, 0)

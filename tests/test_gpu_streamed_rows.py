@@ -1,5 +1,6 @@
 """The one-workgroup-per-CU kernel outside 49-160 rows of four column groups: row-major weights from one row on (whole lines
-to LDS), 17-48 rows over weights in fragment order, seven column groups (97-112 gate/up columns per CU), and a matrix
+to LDS), 17-48 rows over weights in fragment order (two row tiles of gate/up: the eight-wave kernel without loading waves),
+seven column groups (97-112 gate/up columns per CU), and a matrix
 with more column tiles than CUs; against the CPU oracle."""
 import numpy as np
 import pytest
