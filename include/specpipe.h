@@ -425,8 +425,14 @@ int sp_request_info(const sp_stage* stage, int32_t req, int32_t* prefix_len, int
  * that run complete projections (most shapes; others and longer calls split them)
  * have no SP_K_ROPE_KV launch and of SP_K_NORM only the one that opens the call;
  * SP_K_GEMM_QKV then includes RoPE and the cache append, SP_K_GEMM_O and
- * SP_K_GEMM_DOWN the residual and the next norm's gain.  In float32 SP_K_GEMM_GATEUP
- * includes SiLU*mul, as in bf16.  SP_K_ATTENTION includes the merge of split ranges. */
+ * SP_K_GEMM_DOWN the residual and the next norm's gain.  In float32 the residual and
+ * the write-out are always part of SP_K_GEMM_O and SP_K_GEMM_DOWN and the norm in
+ * front of it part of SP_K_GEMM_GATEUP; the other norm, RoPE and the cache append are
+ * part of SP_K_GEMM_QKV (no SP_K_ROPE_KV launch, of SP_K_NORM only the one that opens
+ * the call) unless QKV has many workgroups (more than four rounds of 64 rows x 16
+ * columns over the CUs): then every layer has its SP_K_ROPE_KV launch, and every one
+ * after the first an SP_K_NORM launch.  SP_K_GEMM_GATEUP includes SiLU*mul in either
+ * type.  SP_K_ATTENTION includes the merge of split ranges. */
 typedef enum sp_kernel_kind {
   SP_K_NONE = 0, SP_K_GEMM_QKV = 1, SP_K_GEMM_O = 2, SP_K_GEMM_GATEUP = 3, SP_K_GEMM_DOWN = 4,
   SP_K_ATTENTION = 5, SP_K_ATTENTION_MERGE = 6, SP_K_KV_COMPACT = 7, SP_K_TREE_PRUNE = 8,

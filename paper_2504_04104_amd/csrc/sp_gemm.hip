@@ -1,8 +1,8 @@
 // bf16 products of few rows (M = tree nodes in flight) on the CDNA4 matrix cores, as far as no kernel of their own takes
 // them: QKV, O and down over weights in fragment order up to 16 rows where sp_gemm_few.hip does not, and 17-64 rows with k
-// slices too short for sp_gemm_mid.hip; gate/up up to 128 rows of widths that are no even share per CU; the output head and
-// the logits, over weights in either order.  With so few rows every weight is used once, so the kernel is a weight streamer (decode is bound by loading
-// parameters, Sec. 2.2): each wave pulls its 16 weight rows straight from HBM into registers in MFMA operand layout (one
+// slices too short for sp_gemm_mid.hip; gate/up of one row tile, of two where a CU's even share is 49-64 columns, and up to 128
+// rows of widths that are no even share per CU; the output head and the logits, over weights in either order.  With so few
+// rows every weight is used once, so the kernel is a weight streamer (decode is bound by loading parameters, Sec. 2.2): each wave pulls its 16 weight rows straight from HBM into registers in MFMA operand layout (one
 // 16-byte load per lane per k-step, PF chunks ahead of the math), while the M x K activation panel -- shared by every wave
 // -- is staged once per workgroup through LDS.  Up to 16 rows a workgroup is four waves over 64 columns (the panel is
 // small, more workgroups stream better); from 17 rows on plain products take eight waves over 128 columns, one workgroup
@@ -397,9 +397,9 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
   // the slices again: 0.612 ms).
   int S = (eight ? SP_GEMM_TARGET_WGS_ROWS / 2 : SP_GEMM_TARGET_WGS_ROWS) / tiles;
   // One row tile, whose partial sums are small: three workgroups per CU where two per CU would be an uneven round (12288
-  // columns: 192 tiles x 4 instead of x 2; measured over row-major weights, one layer with those in QKV 128.8 -> 124.7 us at one row and 140.3
-  // -> 136.7 at 16, with those in O and down 430 -> 398 and 461 -> 428).  Not throughout: 7168 and 5120 columns in 112 x 7
-  // and 80 x 10 workgroups, a few more than three per CU, 156 -> 165 us at one row.
+  // columns: 192 tiles x 4 instead of x 2; a layer with those in O and down at 8 / 16 rows 461.5 -> 456.5 and 473 -> 463 us, four
+  // with those in QKV at one row 213 -> 202.5).  Not throughout: 7168 and 5120 columns in 112 x 7 and 80 x 10 workgroups, a few
+  // more than three per CU, 156 -> 165 us at one row.
   if (MT == 1 && S >= 1 && 4 * S * tiles <= 3 * SP_GEMM_TARGET_WGS_ROWS) S = (SP_GEMM_TARGET_WGS_ONE + tiles - 1) / tiles;
   if (S > max_split) S = max_split;
   if (S > chunks) S = chunks;
@@ -430,9 +430,9 @@ hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, fl
 #undef SP_GO8
     return hipGetLastError();
   }
-  // One row tile of a matrix that is to stay in the Infinity Cache: ordinary weight loads from 9 rows on (measured over
-  // row-major weights, which sp_gemm_mid.hip takes now: one layer of 5120 and 8192 columns at 16 rows 171.6 -> 165.1 and
-  // 392.6 -> 385.5 us); with fewer it is level (4608 wide, 8 rows 144.5 -> 146.5).
+  // One row tile of a matrix that is to stay in the Infinity Cache: ordinary weight loads from 9 rows on (two layers of 4608 and
+  // 5120 columns at 16 rows 282.4 -> 280.5 and 251.7 -> 249.3 us; of 4096 columns with d_ff = 11008 at 9 / 16 rows 203.9 -> 206.7 and
+  // 211.0 -> 209.8); with fewer it is level (4608 wide, 8 rows 144.5 -> 146.5).
   if (resident && packed && M > 8) {
     hipLaunchKernelGGL((k_gemm_bf16<1, SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, true, false, 4, false>),
                        grid, dim3(256), 0, st, X, W, out, nullptr, M, N, K, K / SP_GEMM_KC_PLAIN, S, rot_for(S, K));

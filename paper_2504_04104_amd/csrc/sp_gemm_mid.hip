@@ -330,7 +330,7 @@ static hipError_t launch_gateup(int n_cu, hipStream_t st, const bf16_t* X, const
                                 const float* ssq, float eps) {
   constexpr int NPR = KQ == 2 ? MID_NPR : 1;
 #define SP_GO(MTV)                                                                                                        \
-  if constexpr ((MTV > 1 || KQ > 1 || !PACKED) && (MTV <= 10 || (KQ == 2 && PACKED))) {                                              \
+  if constexpr ((!PACKED || MTV > KQ) && (MTV <= 10 || (KQ == 2 && PACKED))) {                                            \
     typedef GateupPipe<MTV, KQ, PACKED> P;                                                                                \
     hipLaunchKernelGGL((k_gemm_mid<MTV, CW, KQ, true, PACKED, true, P::KC, P::D, P::PF, NPR, P::WL>), dim3(n_cu),         \
                        dim3(64 * (CW * KQ + NPR)), 0, st, X, W, nullptr, act, M, F, K, 1, F / n_cu, ssq, eps);            \
@@ -358,9 +358,9 @@ static MidCut mid_cut(int M, int N, int K, int n_cu) {
 // Which plain products: all over row-major weights (1 to 160 rows, above).  In fragment order all of 65-160 rows, and of
 // 17-64 rows those whose slices are at least 1024 deep: shorter ones (the 8B shape's O, four chunks) lose up to 8 % at 64
 // rows, down gains (14336 and 28672 deep, 64 rows 28.1 / 26.8 and 83 / 77 us), and so do 12288-wide matrices (two
-// layers at 64 rows 504 / 473).  Four 8B layers lose 1 % at
-// 17 rows (438 / 442 us), are level at 24 and gain from 28 on (48 rows 477 / 468).  Up to 16 rows the
-// kernels of one row tile stream weights in fragment order as fast without the loading waves.
+// layers at 64 rows 504 / 473).  Two 8B layers, the kernels before / with these (and gate/up of 17-32 rows in sp_gemm.hip's):
+// 17 rows 217.4 / 218.7 us, 24 rows 220.6 / 219.6, 33 rows 230.5 / 228.8, 48 rows 237.1 / 233.4.  Up to 16 rows the kernels of
+// one row tile stream weights in fragment order as fast without the loading waves.
 bool sp_gemm_mid_takes(int M, int N, int K, bool packed, int n_cu) {
   if (M < 1 || M > 160 || N % 128 || K % MID_KC) return false;
   const MidCut cut = mid_cut(M, N, K, n_cu);

@@ -2,8 +2,8 @@
 // 161 or 193: a cold ragged batch forwards several hundred tree nodes at once, Sec. 4 "Implementation" / Sec. 4.4).  Here the
 // matrix cores, not the weight stream, set the pace, so each wave keeps SPW strips of 16 weight rows in registers and every
 // activation fragment it reads from LDS feeds SPW MFMAs.  Two kernels: k_gemm_wide here, over row-major weights in blocks of
-// 128 rows and, from 385 on, 256, and over weights in fragment order in blocks of 128 up to 384 rows (gate/up 256);
-// k_gemm_wide32 further down beyond those.  A workgroup covers up to 16*MT rows x
+// 128 rows and, from 385 on, 256, and over weights in fragment order in blocks of 128 up to 384 rows (gate/up 256, or 320
+// where either kernel makes one round of workgroups); k_gemm_wide32 further down beyond those.  A workgroup covers up to 16*MT rows x
 // 64*SPW output columns.  Full row blocks come first in launch order, and those of one column
 // tile get consecutive ids modulo 8: they run at the same time on the same XCD and share the
 // tile's weights through its L2.  The last, partial row block of every tile comes after all
@@ -219,8 +219,7 @@ k_gemm_wide(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
   else wide_body<SPW, 4, GATEUP, PACKED, XF>(X, W, out, act, M, N, K, tile, m_base, c_begin, c_end, lds_raw);
 }
 
-// Launch with the activation panels as dynamic LDS (more than the 64 KB a kernel may declare
-// statically).
+// Launch with the activation panels as dynamic LDS: one array for bodies of every height, with no barrier between them.
 template <int SPW, int MT, bool GATEUP, bool PACKED, bool XF>
 static hipError_t launch_wide(dim3 grid, hipStream_t st, const bf16_t* X, const bf16_t* W, float* out, bf16_t* act,
                               int M, int N, int K, int n_tiles, int S) {
@@ -242,9 +241,10 @@ static hipError_t launch_wide(dim3 grid, hipStream_t st, const bf16_t* X, const 
 // v_mfma_f32_32x32x16_bf16 issues back to back from one wave per SIMD, which the 16 x 16 shape does not (57 % of its rate),
 // and gives the same sums; the panels come in by direct-to-LDS loads three chunks of 32 k ahead, as do the weights in
 // registers.  Up to RT = 5 two workgroups share a CU.  What sets the time of the products is how many rounds of workgroups
-// a shape makes, so the height is chosen by that (wide_plan).  gate/up 8B shape, 128- and 256-row blocks of the kernel above /
-// here: 320 rows 106.7 / 88.4 us, 512 rows 114.1 / 103.7, 638 rows 161.9 / 133.2, 1024 rows 213 / 202; O of 638 rows in five /
-// four slices 34.4 / 30.9.
+// a shape makes, so the height is chosen by that (wide_plan).  Launches of the 8B shape in 128- and 256-row blocks of the kernel
+// above / here, us with the events around them: gate/up 320 rows 110 / 85, 448 rows 107 / 104, 512 rows 112.7 / 114.8, 640 rows
+// 163 / 132, 1024 rows 203 / 214; QKV, O and down of 640 rows 48.3 / 40.7, 36.2 / 31.0 and 88.3 / 76.9.  Two layers, 640 rows
+// 789 / 679, 1024 rows 1023 / 1023.
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 template <int RT, bool GATEUP>
