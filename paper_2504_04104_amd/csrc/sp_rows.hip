@@ -61,8 +61,9 @@ __device__ __forceinline__ f32x4_t fold4(const float* p, int S, size_t stride) {
 // first two passes stay in registers.
 #define ENTER_ROWS 4       // rows a workgroup of descriptors and rotary tables takes (few: double precision is slow)
 // Workgroups of the rows: one each.  Fragment order puts eight rows into a 128-byte line: they go to the same XCD, whose L2
-// puts the line together, in whole groups of 64 rows (145 rows 7.1 -> 6.8 us, 128 rows of 8192 8.1 -> 7.3).  Up to 64 rows that would leave XCDs, and
-// their share of the bandwidth for the partial sums, idle (24 rows 9.1 us against 7.2): consecutive workgroups there.
+// puts the line together, in whole groups of 64 rows (145 rows 7.1 -> 6.8 us, 128 rows of 8192 8.1 -> 7.3).  Up to 64 rows that
+// would leave XCDs, and their share of the bandwidth for the partial sums, idle (24 rows 9.1 us against 7.2): consecutive
+// workgroups there.
 __host__ __device__ inline bool norm_grouped(int M, bool frag) { return frag && M > 64; }
 __host__ __device__ inline int norm_blocks(int M, bool frag) { return norm_grouped(M, frag) ? (M + 63) / 64 * 64 : M; }
 struct NoPlan { int unused; };
