@@ -663,10 +663,14 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   const size_t strideD = (size_t)M * d, strideQ = (size_t)M * nqkv;
   const bool few = s->fast && sp_few_takes(M, d, dq, F, s->packed, s->n_cu);
   // Activations between the products in fragment order, but few rows row-major where no product takes them by
-  // direct-to-LDS loads: up to four rows of complete projections (8B shape, one node: 105.7 -> 104.0 us; eight rows gain from
-  // the fragments, 101.5 -> 99.8 us a layer), up to eight of split products (5120 and 4096 wide, two layers, 6 rows 247.4 /
-  // 203.4 us in fragment order, 246.1 / 199.9 row-major); and in the many-row kernel beside row-major weights.
-  const bool frag = s->fast && !(M <= (few ? 4 : 8) && (s->packed || (few && !sp_gemm_mid_takes_gateup(M, F, d, false, s->n_cu)))) &&
+  // direct-to-LDS loads; and in the many-row kernel beside row-major weights.  Complete projections: a k step is M pieces of
+  // 64 bytes row-major and 512 bytes for every eight rows in fragment order, which moves 1.75 times as fast per byte: row-major
+  // up to four rows and at nine (8B shape, one node 105.7 -> 104.0 us, nine 120.9 -> 118.8; eight rows gain from the fragments,
+  // 101.5 -> 99.8 us a layer; beside row-major weights nine do too, 2048 and 3072 wide 249.3 -> 247.2 and 165.5 -> 163.4).
+  // Split products up to eight rows (5120 and 4096 wide, two layers, 6 rows 247.4 / 203.4 us in fragment order, 246.1 / 199.9
+  // row-major).
+  const bool few_lines = !few ? M <= 8 : s->packed ? 7 * M < 32 * ((M + 7) / 8) : M <= 4;
+  const bool frag = s->fast && !(few_lines && (s->packed || (few && !sp_gemm_mid_takes_gateup(M, F, d, false, s->n_cu)))) &&
                     (s->packed || M <= 160);
   // projections: few rows stream the weights (HBM-bound); many rows use the register-blocked kernel
   const bool wide = s->fast && M > 128 && nqkv % 256 == 0 && d % 256 == 0 && F % 128 == 0 && dq % 128 == 0;

@@ -80,3 +80,18 @@ def test_which_rows_take_complete_projections(name, dims, packed, calls):
         assert rel_err(y - x, ref - x) <= 2e-2, n
         pair.check_kv(r, 2e-2)
     pair.close()
+
+
+@pytest.mark.parametrize("n", [4, 5, 8, 9, 10])
+@pytest.mark.parametrize("packed", [True, False], ids=["packed", "rowmajor"])
+@pytest.mark.parametrize("name", ["k2048", "k768"])
+def test_layouts_of_few_rows(name, packed, n):
+    """Row counts on either side of where complete projections hold their rows row-major (up to four, nine) or in fragment
+    order."""
+    pair = Pair(SHAPES[name], 73, {0: 45}, flags=sp.SP_FLAG_PACKED_WEIGHTS if packed else 0)
+    pair.insert(0, wl.tree_deep(73, n, 9))
+    x = wl.hidden_rows(SHAPES[name], 73, ("layout", n), n)
+    y, ref = pair.forward([0], [0], [n], x)
+    assert rel_err(y - x, ref - x) <= 2e-2
+    pair.check_kv(0, 2e-2)
+    pair.close()
