@@ -609,11 +609,21 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   std::memset(&plan, 0, sizeof(plan));
   plan.n_seg = b.n_req;
   plan.x_out = x_out;
-  for (int i = 0; i < b.n_req; ++i) {              // which request and node each row belongs to
+  // Which request and node each row belongs to.  Longest cache ranges first (equal ones in the call's order): the attention's
+  // workgroups start in this order, and those of short ranges fill the CUs that the long ones leave over.
+  short order[SP_BATCH];
+  for (int i = 0; i < b.n_req; ++i) {
     const HostReq& r = s->reqs[b.req[i]];
-    plan.seg_row0[i] = b.row0[i]; plan.seg_rows[i] = b.n[i]; plan.seg_req[i] = b.req[i];
-    plan.seg_first[i] = b.first[i]; plan.seg_P[i] = r.P; plan.seg_T[i] = r.T; plan.seg_base[i] = r.base;
-    plan.seg_chunks[i] = 1;
+    int k = i;
+    for (; k > 0 && s->reqs[b.req[order[k - 1]]].P + s->reqs[b.req[order[k - 1]]].T < r.P + r.T; --k) order[k] = order[k - 1];
+    order[k] = (short)i;
+  }
+  for (int k = 0; k < b.n_req; ++k) {
+    const int i = order[k];
+    const HostReq& r = s->reqs[b.req[i]];
+    plan.seg_row0[k] = b.row0[i]; plan.seg_rows[k] = b.n[i]; plan.seg_req[k] = b.req[i];
+    plan.seg_first[k] = b.first[i]; plan.seg_P[k] = r.P; plan.seg_T[k] = r.T; plan.seg_base[k] = r.base;
+    plan.seg_chunks[k] = 1;
   }
   if (s->fast) {
     // Split every request's cache range into chunks so that the grid fills the chip
@@ -622,6 +632,12 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     int maxq = 0;
     for (int i = 0; i < b.n_req; ++i) if (b.n[i] * g > maxq) maxq = b.n[i] * g;
     plan.qt = maxq <= 16 ? 1 : 2;
+    // Blocks of 64 query rows where those alone give every CU a workgroup: half of the tiles' way out of L2 (638 rows of 32
+    // requests behind 512-4096 slots, two layers: 829 us with blocks of 32, 815 with 64; starting the longest ranges first
+    // is the rest of 858 -> 815).  With fewer, the ranges would have to be cut instead, and merging costs more (70B shape, 128 rows).
+    int blocks64 = 0;
+    for (int i = 0; i < b.n_req; ++i) blocks64 += (b.n[i] * g + 63) / 64;
+    if (maxq > 32 && blocks64 * nkv >= s->n_cu) plan.qt = 4;
     const int qrows_per_block = 16 * plan.qt;
     // One workgroup per CU is the target.  If the query blocks alone give that many, every
     // request keeps its whole cache range in one chunk (no partial results, no merge kernel);
@@ -630,21 +646,19 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     auto fill = [&](int want, size_t* units_out) {
       size_t units = 0; int items = 0, split = 0;
       for (int i = 0; i < b.n_req; ++i) {
-        const HostReq& r = s->reqs[b.req[i]];
-        const int span = r.P + r.T;
+        const int span = plan.seg_P[i] + plan.seg_T[i];
         int chunks = want;
         const int max_chunks = (span + 255) / 256;
         if (chunks > max_chunks) chunks = max_chunks;
         if (chunks < 1) chunks = 1;
         const int clen = ((span + chunks - 1) / chunks + 31) / 32 * 32;
         chunks = (span + clen - 1) / clen;
-        const int qblocks = (b.n[i] * g + qrows_per_block - 1) / qrows_per_block;
+        const int qblocks = (plan.seg_rows[i] * g + qrows_per_block - 1) / qrows_per_block;
         plan.seg_item0[i] = items; plan.seg_chunks[i] = chunks; plan.seg_clen[i] = clen; plan.seg_qblocks[i] = qblocks;
         plan.seg_unit0[i] = (int)units;
         items += chunks * qblocks;
-        if (chunks > 1) { units += (size_t)chunks * b.n[i] * nq; split = 1; }
+        if (chunks > 1) { units += (size_t)chunks * plan.seg_rows[i] * nq; split = 1; }
       }
-      plan.seg_item0[b.n_req] = items;
       plan.total_items = items;
       plan.units_total = (int)units;
       plan.any_split = split;

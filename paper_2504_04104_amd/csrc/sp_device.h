@@ -54,7 +54,7 @@ struct RowInfo {
   int pos;          // sequence position = P + depth
   int P;
   int T;
-  int seg;          // index of the request inside the call
+  int seg;          // the segment of the plan that the row belongs to
 };
 
 // A forward call's requests, passed to kernels by value.

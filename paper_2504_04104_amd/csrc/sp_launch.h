@@ -66,11 +66,11 @@ hipError_t sp_launch_kv_compact(const ReqMeta* meta, const ReqTables* tables, co
 // A forward call's requests (segments) and the split of its attention work, made on the host.
 struct AttnPlan {          // host-made split of a forward call's attention work
   int n_seg;
-  int qt;                  // 16-row query tiles per wave: 1 or 2
+  int qt;                  // 16-row query tiles per workgroup: 1, 2, or 4 (two groups of waves with two tiles each)
   int units_total;         // partial-result units: sum over split segments of chunks * rows * n_q
   int total_items;         // sum over segments of q_blocks * chunks
   int any_split;           // some segment has more than one chunk: the merge kernel must run
-  int seg_item0[SP_BATCH + 1];   // first work item of each segment
+  int seg_item0[SP_BATCH]; // first work item of each segment
   int seg_chunks[SP_BATCH];
   int seg_clen[SP_BATCH];  // slots per chunk of the segment (multiple of 32)
   int seg_qblocks[SP_BATCH];

@@ -84,8 +84,8 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
     if ((int)blockIdx.x >= row_blocks) {
       const int r = ((int)blockIdx.x - row_blocks) * ENTER_ROWS + (int)threadIdx.x / half, tt = (int)threadIdx.x % half;
       if (r < M && (int)threadIdx.x < ENTER_ROWS * half) {
-        int seg = 0;
-        while (seg + 1 < b.n_seg && r >= b.seg_row0[seg + 1]) ++seg;
+        int seg = 0;                                 // (in no order of their rows)
+        while (seg + 1 < b.n_seg && (r < b.seg_row0[seg] || r >= b.seg_row0[seg] + b.seg_rows[seg])) ++seg;
         const int req = b.seg_req[seg];
         const int node = b.seg_first[seg] + (r - b.seg_row0[seg]);
         const ReqMeta m = meta[req];

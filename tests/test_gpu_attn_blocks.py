@@ -1,0 +1,39 @@
+"""Attention of many requests at once: blocks of 64 query rows whose tiles two waves share, blocks of 32, and ranges streamed through
+registers, at context lengths around the edges of tiles and runs, against the CPU oracle.  The requests' contexts are in no
+order, so that the longest-first order of the work differs from the call's."""
+import numpy as np
+import pytest
+
+import workloads as wl
+import paper_2504_04104_amd as sp
+from gpu_harness import Pair, elementwise_figure, rel_err
+
+pytestmark = pytest.mark.gpu
+
+SHAPE = wl.ModelShape(n_layers=1, d_model=512, n_q_heads=32, n_kv_heads=8, d_head=128, d_ff=512)
+CONTEXTS = [33, 1, 257, 31, 128, 513, 32, 127, 300, 64, 5, 129, 255, 63, 96, 256, 224, 2, 192, 65, 160, 97, 385, 17]
+
+
+@pytest.mark.parametrize("page_slots", [0, 32], ids=["contiguous", "pages32"])
+@pytest.mark.parametrize("rows", [
+    # one to three blocks of 64 query rows (four per node), 43 in all: 344 workgroups
+    pytest.param([33, 16, 17, 1, 32, 31, 48, 8, 33, 16, 17, 4, 32, 31, 2, 9, 33, 16, 17, 1, 32, 31, 40, 8], id="blocks_of_64"),
+    # 31 blocks of 64: blocks of 32
+    pytest.param([17] * 7 + [16] * 17, id="blocks_of_32"),
+    # a single block each: 24 streamed ranges, one and two query tiles
+    pytest.param([8, 1, 3, 5, 8, 2] * 4, id="streamed"),
+    pytest.param([4, 1, 3, 2, 4, 2] * 4, id="streamed_one_tile")])
+def test_ragged_contexts(rows, page_slots):
+    """Increment y - x of small inputs element by element (2e-2 of the value plus 5e-2 of the rms: about six tensors on the way
+    are stored in bf16), twice (the second call replays the first one's shape), then the cache rows."""
+    n = len(rows)
+    pair = Pair(SHAPE, 91, dict(enumerate(CONTEXTS)), max_batch_nodes=640, page_slots=page_slots, norm1_gain=4.0)
+    pair.insert_batch(list(range(n)), [wl.tree_deep(91 + q, r, 9) for q, r in enumerate(rows)])
+    for k in range(2):
+        x = wl.hidden_rows(SHAPE, 91, ("blocks", k), sum(rows)) * np.float32(2.0 ** -6)
+        y, ref = pair.forward(list(range(n)), [0] * n, rows, x)
+        assert rel_err(y - x, ref - x) <= 2e-2, k
+        assert elementwise_figure(y.astype(np.float64) - x, ref - x, 2e-2, 5e-2) <= 1.0, k
+    for q in range(n):
+        pair.check_kv(q, 2e-2)
+    pair.close()
