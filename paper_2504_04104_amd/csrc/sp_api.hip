@@ -135,7 +135,7 @@ struct sp_stage {
   int n_pages = 0;
   int* d_page_table = nullptr;
   std::vector<int> free_pages;
-  // Forward calls of a shape seen before replay a HIP graph of their launches (all but the first
+  // Forward calls of many launches and a shape seen before replay a HIP graph of their launches (all but the first
   // kernel, which carries the caller's input pointer and the call's plan with the pointer of the result).
   struct FwdGraph {
     int M, qt, items, any_split, units;
@@ -817,8 +817,14 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     SP_TRY(sp_launch_enter_norm(dt, x_in, plan, w.plan, s->d_meta, s->d_tables, w.rows, w.cs, dh,
                                 c.rope_theta, w.h, s->W[0].norm1, w.xn, frag, M, d, c.rms_eps, st)); }
 
-  // A shape that comes back replays its graph; one seen for the second time is captured.  Not while a
+  // A shape of many launches that comes back replays its graph; one seen for the second time is captured.  Not while a
   // kernel kind is being timed (the events sit between the launches) and not inside a caller's capture.
+  // Few launches are made one by one: what follows a graph on its stream starts 8 us late, and its launch takes the host as
+  // long as some ten others (us a call, replayed / one by one: one row of one 8B layer 104.7 / 97.6, 37 rows 129.9 / 124.1, two
+  // float32 layers of 256 67.8 / 64.0, a step of a few rows in four layers 455 / 450).  A launch takes the host 2-6 us and the
+  // device 4.5 at least: long calls leave the host no lead that way (24 layers of 1024: 966 / 962, the host 126 / 850).
+  constexpr int EAGER_LAUNCHES = 24;
+  const int launches = c.n_layers * ((few || qkv_joined ? 5 : s->f32 ? 7 : 8) + (plan.any_split ? 1 : 0));
   // launches among the layers' of their own: norms, rotation
   const int n_norm = few || qkv_joined ? 0 : s->f32 ? c.n_layers - 1 : 2 * c.n_layers - 1;
   const int n_rope = few || qkv_joined ? 0 : c.n_layers;
@@ -838,7 +844,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
       timed = s->prof_n < s->prof_max && ((s->prof_seen / n_kind) % s->prof_every) == 0;
     }
   }
-  if (s->use_graphs && (s->fast || s->f32) && !timed) {
+  if (s->use_graphs && (s->fast || s->f32) && !timed && launches > EAGER_LAUNCHES) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
       for (auto& g : s->graphs)
