@@ -1218,15 +1218,14 @@ int sp_stage_verify_lossy(sp_stage* s, const sp_head_weights* head, int32_t n, c
   hipError_t e = sp_launch_row_norm(c.dtype, x_root, head->norm, w.xn, head_rows_frag(s, V), n, d, c.rms_eps, st);
   if (e != hipSuccess) return hip_fail(s, e);
   ProfScope p(s, SP_K_VERIFY_HEAD, st);
-  if (head_on_mfma(s, V)) {
-    int S = 1;
-    e = sp_launch_gemm_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, n, V, d, 1,
-                            logit_floats, &S, st, false, s->packed);
-  } else {
+  int tile_cols = 0;
+  if (head_on_mfma(s, V))
+    e = sp_launch_gemm_logits_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, nullptr, 0.f, n, V, d,
+                                   &tile_cols, st);
+  else
     e = other_gemm(s, w.xn, head->wvocab, w.part, n, V, d, st);
-  }
   if (e == hipSuccess)
-    e = sp_launch_verify_lossy(s->d_meta, s->d_tables, w.part, n, req_ids, V, mode, top_p, w.part + logit_floats,
+    e = sp_launch_verify_lossy(s->d_meta, s->d_tables, w.part, tile_cols, n, req_ids, V, mode, top_p, w.part + logit_floats,
                                w.part_floats - logit_floats, result_dev, st);
   if (e == hipSuccess && result_host)
     e = hipMemcpyAsync(result_host, result_dev, sizeof(int32_t) * 2 * n, hipMemcpyDeviceToHost, st);
@@ -1264,15 +1263,9 @@ int sp_stage_verify_sample(sp_stage* s, const sp_head_weights* head, int32_t n, 
   float* stats = nullptr;
   int tile_cols = 0;
   if (head_on_mfma(s, V)) {
-    if (logit_floats + (size_t)n * (V / 64) * 2 <= w.part_floats) {
-      stats = w.part + logit_floats;
-      e = sp_launch_gemm_logits_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, stats,
-                                     1.f / temperature, n, V, d, &tile_cols, st);
-    } else {
-      int S = 1;
-      e = sp_launch_gemm_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, n, V, d, 1,
-                              logit_floats, &S, st, false, s->packed);
-    }
+    if (logit_floats + (size_t)n * (V / 64) * 2 <= w.part_floats) stats = w.part + logit_floats;
+    e = sp_launch_gemm_logits_bf16((const bf16_t*)w.xn, (const bf16_t*)head->wvocab, s->packed, w.part, stats,
+                                   1.f / temperature, n, V, d, &tile_cols, st);
   } else {
     e = other_gemm(s, w.xn, head->wvocab, w.part, n, V, d, st);
   }

@@ -64,15 +64,19 @@
 // ARGMAX (output head of the last stage, Algorithm 1 "verify new token"): instead of the
 // products, a workgroup leaves per row the largest of its 16*NCG columns and that column's
 // index (the lowest one among equal maxima) as a (float, int) pair at out[(m * tiles + tile) * 2].
-// STATS (logits of a stochastic verification): beside the products, a workgroup leaves per row the maximum mx of its
-// 16*NCG columns and the sum of exp((l - mx) * inv_T) over them as a float pair at stats[(m * tiles + tile) * 2].
+// LOGITS (lossy and stochastic verification): from two row tiles on the products of a workgroup's 128 columns lie together,
+// [tile][m][column], stored non-temporally: written row by row the logits of 32 rows are pieces of 512 bytes half a megabyte
+// apart and cost as much as 100 MB of weights (128256 x 4096, 32 rows: 187.2 us, in tiles 185.0, in tiles and non-temporal
+// 178.7, without any stores 171.3).  Up to 16 rows what reads them gains more from finding them in L2 (3 to 14 rows, whole
+// calls 0.4-1 % slower in tiles): row by row.  For a stochastic verification (stats given) a workgroup also leaves per row the
+// maximum mx of its columns and the sum of exp((l - mx) * inv_T) over them as a float pair at stats[(m * tiles + tile) * 2].
 // EVEN (gate/up of two row tiles over weights in fragment order): one workgroup per CU covers cpw = d_ff / CUs columns, a
 // multiple of 8 in 49-64, in four groups of 16 and a last one of cpw - 48, by four groups times two k-halves of waves (the
 // upper lanes of a short last group re-read its last row and their results are dropped).  With so few rows the loading waves
 // of sp_gemm_mid.hip's kernel only take issue slots: gate/up of 17 / 32 rows 41.3 / 41.4 us here, 42.0 / 42.0 there, two 8B
 // layers 216.6 / 222.1 and 219.4 / 223.4; from 33 rows on it is the other way round (43.0 / 42.2).
 template <int MT, int NCG, bool GATEUP, int KC, int PF, bool PACKED, bool ARGMAX = false, int NWAVES = 4, bool WNT = true,
-          bool STATS = false, bool FRAG = true, bool EVEN = false>
+          bool LOGITS = false, bool FRAG = true, bool EVEN = false>
 __global__ void __launch_bounds__(64 * NWAVES)
 k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __restrict__ out,
             bf16_t* __restrict__ act, int M, int N, int K, int chunks_total, int S, int rot = 0,
@@ -267,8 +271,8 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
     }
     return;
   }
-  if (STATS) {
-    static_assert(!STATS || (NKH == 1 && !GATEUP && !ARGMAX), "one wave per column group");
+  if (LOGITS && stats) {
+    static_assert(!LOGITS || (NKH == 1 && !GATEUP && !ARGMAX), "one wave per column group");
     float* s_mx = reinterpret_cast<float*>(lds);           // [NCG][ROWS]; the panels are no longer read
     float* s_z = s_mx + NCG * ROWS;
 #pragma unroll
@@ -317,6 +321,8 @@ k_gemm_bf16(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* _
       pk.x = pack_bf16x2(o[0], o[1]);
       pk.y = pack_bf16x2(o[2], o[3]);
       *reinterpret_cast<uint2*>(act + row_at(FRAG, m, ncol, N)) = pk;
+    } else if (LOGITS && NCG == 8) {
+      __builtin_nontemporal_store(acc[0][mt], reinterpret_cast<f32x4_t*>(out + ((size_t)blockIdx.x * M + m) * (16 * NCG) + cg * 16 + 4 * kg));
     } else {
       float* o = out + ((size_t)blockIdx.y * M + m) * N + ncol;
       *reinterpret_cast<f32x4_t*>(o) = acc[0][mt];
@@ -497,8 +503,8 @@ hipError_t sp_launch_gemm_argmax_bf16(const bf16_t* X, const bf16_t* W, bool pac
   return launch_mt<SP_GEMM_NCG_PLAIN, false, SP_GEMM_KC_PLAIN, false, true>(MT, grid, st, X, W, pairs, nullptr, M, V, K, 1);
 }
 
-// Logits [M][V] (M <= 64, no split) with the statistics of every tile of *tile_cols columns: stats[(m * V / *tile_cols +
-// tile) * 2] = (maximum, sum of exp((l - maximum) * inv_T)).
+// Logits (M <= 64, no split), [M][V] or as logits_lie says, and, where stats is given, the statistics of every tile of
+// *tile_cols columns: stats[(m * V / *tile_cols + tile) * 2] = (maximum, sum of exp((l - maximum) * inv_T)).
 hipError_t sp_launch_gemm_logits_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* logits, float* stats, float inv_T,
                                       int M, int V, int K, int* tile_cols, hipStream_t st) {
   const int MT = (M + 15) / 16;

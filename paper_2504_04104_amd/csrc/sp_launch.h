@@ -50,8 +50,11 @@ hipError_t sp_launch_row_norm(int dtype, const void* x, const void* gain, void* 
                               hipStream_t st);
 // floats of scratch sp_launch_verify_lossy needs at least for n rows of V logits (it uses more if there is more)
 size_t sp_lossy_scratch_floats(int n, int V);
-// mode 1 relaxed, 2 top-p; logits [n][V]; out[2i] = verified node of reqs[i] or -1, out[2i+1] = top-1 token
-hipError_t sp_launch_verify_lossy(ReqMeta* meta, const ReqTables* tables, const float* logits, int n, const int* reqs,
+// Logits of n rows whose products were formed in tiles of tile_cols columns (0: none) lie as [n][V] or, tiles of this many
+// columns, as [V / columns][n][columns].
+static inline int logits_lie(int tile_cols) { return tile_cols == 128 ? 128 : 0; }
+// mode 1 relaxed, 2 top-p; out[2i] = verified node of reqs[i] or -1, out[2i+1] = top-1 token
+hipError_t sp_launch_verify_lossy(ReqMeta* meta, const ReqTables* tables, const float* logits, int tile_cols, int n, const int* reqs,
                                   int V, int mode, float top_p, float* scratch, size_t scratch_floats, int* out,
                                   hipStream_t st);
 // stochastic verification: out[2i] = verified node of reqs[i] or -1, out[2i+1] = the token drawn at u[i]
@@ -133,7 +136,7 @@ hipError_t sp_launch_attn_f32(const float* q, const RowInfo* rows, const ReqTabl
 hipError_t sp_launch_gemm_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* out, int M, int N, int K,
                                int max_split, size_t part_capacity_floats, int* S_out, hipStream_t st,
                                bool resident, bool frag);
-// Logits and output head: X in fragment order beside packed weights, row-major beside row-major ones.
+// Logits (in tiles; stats nullable) and output head: X in fragment order beside packed weights, row-major beside row-major ones.
 hipError_t sp_launch_gemm_logits_bf16(const bf16_t* X, const bf16_t* W, bool packed, float* logits, float* stats, float inv_T,
                                       int M, int V, int K, int* tile_cols, hipStream_t st);
 // act[m][f] = silu(X Wg^T) * (X Wu^T), W = [gate rows ; up rows]

@@ -55,8 +55,24 @@ __device__ __forceinline__ int root_children(const ReqTables& t, int T, int* s_n
   return nc;
 }
 
+// A request's logits in memory: its row of [n][V], or of tiles of 1 << shift columns, [tile][n][column].
+struct LogitRow {
+  const float* row;
+  int shift;
+  size_t step;               // from one of its tiles to the next
+  __device__ __forceinline__ LogitRow(const float* logits, int item, int n, int V, int tile_cols) {
+    shift = tile_cols ? 31 - __clz(tile_cols) : 30;
+    row = logits + (size_t)item * (tile_cols ? tile_cols : V);
+    step = (size_t)n * (unsigned)tile_cols;
+  }
+  // (columns of a tile follow each other)
+  __device__ __forceinline__ const float* at(int v) const { return row + (size_t)(v >> shift) * step + (v & ((1 << shift) - 1)); }
+  __device__ __forceinline__ float operator[](int v) const { return *at(v); }
+};
+
 struct LossyBatch {
   int n, mode, V, slice, n_slices;
+  int lie;                   // columns of the tiles that the logits lie in, or 0
   float top_p;
   int req[SP_BATCH];
 };
@@ -74,7 +90,7 @@ __global__ void __launch_bounds__(256) k_lossy_slices(const ReqMeta* meta, const
   const int item = blockIdx.y, slice = blockIdx.x;
   const int req = b.req[item];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const float* L = logits + (size_t)item * b.V;
+  const LogitRow L(logits, item, b.n, b.V, b.lie);
   const int v0 = slice * b.slice, len = min(b.slice, b.V - v0);
   const int nc = root_children(tables[req], meta[req].T, s_node, s_tok, s_wcount);
 
@@ -171,7 +187,7 @@ __global__ void __launch_bounds__(1024) k_lossy_decide(ReqMeta* meta, const ReqT
   __shared__ int s_redi[16];
   const int item = blockIdx.x, req = b.req[item], tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const ReqTables& t = tables[req];
-  const float* L = logits + (size_t)item * b.V;
+  const LogitRow L(logits, item, b.n, b.V, b.lie);
   const float* st = stats + (size_t)item * b.n_slices * 4;
   // the slices' maxima are asked for before the walk over the tables
   float m = -INFINITY;
@@ -286,6 +302,7 @@ __global__ void __launch_bounds__(1024) k_lossy_decide(ReqMeta* meta, const ReqT
 // ones equal to it, a sort by counting, and the running sums by one wave.
 struct SampleBatch {
   int n, V, top_k;
+  int lie;                   // columns of the tiles that the logits lie in, or 0
   int tile_cols;             // STATS: columns per statistics entry
   const float* stats;        // STATS: [n][V / tile_cols] pairs (maximum, sum of exp((l - maximum) / T))
   float inv_T, top_p;
@@ -309,12 +326,12 @@ __device__ __forceinline__ unsigned long long sample_key(float l, int idx) {
 // with a load per iteration a pass would be a chain of V / 1024 memory latencies.  W = 4 needs V % 4 == 0
 // (then an index below V is followed by three more).  Index of element (u, c): base + (u * 1024 + tid) * W + c.
 template <int W>
-__device__ __forceinline__ void sample_load(const float* __restrict__ L, int V, int base, int tid, float (&v)[8][W]) {
+__device__ __forceinline__ void sample_load(const LogitRow& L, int V, int base, int tid, float (&v)[8][W]) {
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
     const int i = base + (u * 1024 + tid) * W;
     if constexpr (W == 4) {
-      const float4 t = i < V ? *reinterpret_cast<const float4*>(L + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+      const float4 t = i < V ? *reinterpret_cast<const float4*>(L.at(i)) : make_float4(0.f, 0.f, 0.f, 0.f);
       v[u][0] = t.x; v[u][1] = t.y; v[u][2] = t.z; v[u][3] = t.w;
     } else {
       v[u][0] = i < V ? L[i] : 0.f;
@@ -350,7 +367,7 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
   __shared__ int s_tok, s_best;
   const int item = blockIdx.x, req = b.req[item];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const float* L = logits + (size_t)item * b.V;
+  const LogitRow L(logits, item, b.n, b.V, b.lie);
   const int V = b.V, K = min(b.top_k, V);
 
   // first pass: thread maxima, from them the row maximum and the bound t0
@@ -417,7 +434,7 @@ __global__ void __launch_bounds__(1024) k_sample_decide(ReqMeta* meta, const Req
           const int k = k0 + u * 16;
           base[u] = k < n_pick ? s_tile[k] * cols : -1;
           v[u] = make_float2(-INFINITY, -INFINITY);
-          if (base[u] >= 0 && 2 * lane < cols) v[u] = *reinterpret_cast<const float2*>(L + base[u] + 2 * lane);
+          if (base[u] >= 0 && 2 * lane < cols) v[u] = *reinterpret_cast<const float2*>(L.at(base[u]) + 2 * lane);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -657,7 +674,7 @@ hipError_t sp_launch_verify_sample(ReqMeta* meta, const ReqTables* tables, const
                                    int V, float temperature, float top_p, int top_k, const float* u,
                                    const float* stats, int tile_cols, int* out, hipStream_t st) {
   SampleBatch b;
-  b.n = n; b.V = V; b.top_k = top_k; b.tile_cols = tile_cols; b.stats = stats; b.inv_T = 1.f / temperature; b.top_p = top_p;
+  b.n = n; b.V = V; b.top_k = top_k; b.lie = logits_lie(tile_cols); b.tile_cols = tile_cols; b.stats = stats; b.inv_T = 1.f / temperature; b.top_p = top_p;
   for (int i = 0; i < n; ++i) { b.req[i] = reqs[i]; b.u[i] = u[i]; }
   // the bound needs ceil(top_k / 16) tiles for each of the 16 waves
   const bool tiles = stats && V / tile_cols >= 16 * ((top_k + 15) / 16);
@@ -694,10 +711,10 @@ size_t sp_lossy_scratch_floats(int n, int V) {
   return (size_t)n * slices * (4 + SP_T);
 }
 
-hipError_t sp_launch_verify_lossy(ReqMeta* meta, const ReqTables* tables, const float* logits, int n, const int* reqs,
+hipError_t sp_launch_verify_lossy(ReqMeta* meta, const ReqTables* tables, const float* logits, int tile_cols, int n, const int* reqs,
                                   int V, int mode, float top_p, float* scratch, size_t scratch_floats, int* out, hipStream_t st) {
   LossyBatch b;
-  b.n = n; b.mode = mode; b.V = V; b.slice = lossy_slice(n, V, scratch_floats);
+  b.n = n; b.mode = mode; b.V = V; b.lie = logits_lie(tile_cols); b.slice = lossy_slice(n, V, scratch_floats);
   b.n_slices = (V + b.slice - 1) / b.slice; b.top_p = top_p;
   for (int i = 0; i < n; ++i) b.req[i] = reqs[i];
   float* stats = scratch;

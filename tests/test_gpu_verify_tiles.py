@@ -58,6 +58,13 @@ def test_sampling_from_exact_logits(n, V, packed, kind):
     pair.close()
 
 
+@pytest.mark.parametrize("V", [64 * 255, 128 * 127])
+def test_sampling_without_room_for_statistics(V):
+    """64 rows of logits in tiles of 64 and of 128 columns that fill the workspace so far that the tiles' statistics do not
+    fit behind them: the row is walked tile by tile."""
+    test_sampling_from_exact_logits(64, V, True, "spread")
+
+
 @pytest.mark.parametrize("n_child", [1, 63, 64, 65, 129, 200])
 @pytest.mark.parametrize("n,V", [(1, 5003), (2, 64 * 140), (40, 64 * 70)])
 def test_lossy_from_exact_logits(n, V, n_child):
