@@ -206,14 +206,24 @@ size_t tables_meta_bytes(const sp_config& c) { return align_up((size_t)c.max_req
 // takes pages from the free list and sends their ids to the device table; shrinking returns
 // pages (their table entries stay behind, unused).  Everything runs in stream order, so a page
 // can be handed to another request as soon as the host has let go of it.
+hipError_t pages_set(sp_stage* s, int req, int have, hipStream_t st) {
+  const HostReq& r = s->reqs[req];
+  return sp_launch_pages_set(s->d_page_table, s->n_pages, req, have, (int)r.pages.size() - have, r.pages.data() + have, st);
+}
+// The pages of a request that grows, on the host only: how many it has come to hold more.
+int pages_take(sp_stage* s, int req, int slots) {
+  HostReq& r = s->reqs[req];
+  const int want = (slots + s->cfg.page_slots - 1) / s->cfg.page_slots, have = (int)r.pages.size();
+  for (int i = have; i < want; ++i) { r.pages.push_back(s->free_pages.back()); s->free_pages.pop_back(); }
+  return want > have ? want - have : 0;
+}
 hipError_t pages_resize(sp_stage* s, int req, int slots, hipStream_t st) {
   HostReq& r = s->reqs[req];
-  const int pg = s->cfg.page_slots;
-  const int want = (slots + pg - 1) / pg;
+  const int want = (slots + s->cfg.page_slots - 1) / s->cfg.page_slots;
   const int have = (int)r.pages.size();
   if (want > have) {
-    for (int i = have; i < want; ++i) { r.pages.push_back(s->free_pages.back()); s->free_pages.pop_back(); }
-    return sp_launch_pages_set(s->d_page_table, s->n_pages, req, have, want - have, r.pages.data() + have, st);
+    pages_take(s, req, slots);
+    return pages_set(s, req, have, st);
   }
   for (int i = have - 1; i >= want; --i) s->free_pages.push_back(r.pages[i]);
   r.pages.resize(want);
@@ -505,7 +515,8 @@ int sp_tree_insert_batch(sp_stage* s, int32_t n_req, const int32_t* req_ids, con
     total += n_new[i];
   }
   hipStream_t st = (hipStream_t)stream;
-  if (is_paged(s->cfg)) {
+  const bool paged = is_paged(s->cfg);
+  if (paged) {
     // pages for the new cache rows, all or nothing
     int need = 0;
     for (int i = 0; i < n_req; ++i) {
@@ -513,24 +524,17 @@ int sp_tree_insert_batch(sp_stage* s, int32_t n_req, const int32_t* req_ids, con
       need += pages_for(s, r.P + r.T + n_new[i]) - (int)r.pages.size();
     }
     if (need > (int)s->free_pages.size()) return SP_E_CAPACITY;
-    for (int i = 0; i < n_req; ++i) {
-      const HostReq& r = s->reqs[req_ids[i]];
-      if (pages_for(s, r.P + r.T + n_new[i]) > (int)r.pages.size()) {
-        hipError_t e = pages_resize(s, req_ids[i], r.P + r.T + n_new[i], st);
-        if (e != hipSuccess) return hip_fail(s, e);
-      }
-    }
   }
   // launches of at most SP_T new nodes each (one launch in every case the configs produce)
   InsertArgs a;
-  a.n_req = 0;
+  a.n_req = a.n_pages = 0;
   a.row0[0] = 0;
   int row = 0;
   auto flush = [&]() -> hipError_t {
     if (a.n_req == 0) return hipSuccess;
     ProfScope scope(s, SP_K_TREE_INSERT, st);
     hipError_t e = sp_launch_tree_insert(s->d_meta, s->d_tables, a, s->geom, st);
-    a.n_req = 0;
+    a.n_req = a.n_pages = 0;
     a.row0[0] = 0;
     return e;
   };
@@ -544,6 +548,20 @@ int sp_tree_insert_batch(sp_stage* s, int32_t n_req, const int32_t* req_ids, con
         if (e != hipSuccess) return hip_fail(s, e);
       }
       const int r0 = a.row0[a.n_req];
+      a.pg_first[a.n_req] = 0;
+      a.pg_n[a.n_req] = a.pg_at[a.n_req] = 0;
+      if (paged) {
+        const int have = (int)r.pages.size(), more = pages_take(s, req_ids[i], r.P + r.T + n);
+        if (more > 0 && a.n_pages + more <= SP_INSERT_PAGES && have < 32768) {
+          a.pg_first[a.n_req] = (short)have;
+          a.pg_n[a.n_req] = (unsigned char)more;
+          a.pg_at[a.n_req] = (unsigned char)a.n_pages;
+          for (int k = 0; k < more; ++k) a.page[a.n_pages++] = r.pages[have + k];
+        } else if (more > 0) {
+          hipError_t e = pages_set(s, req_ids[i], have, st);
+          if (e != hipSuccess) return hip_fail(s, e);
+        }
+      }
       a.req[a.n_req] = (short)req_ids[i];
       a.t0[a.n_req] = (short)r.T;
       a.first_slot[a.n_req] = r.base + r.P + r.T;

@@ -12,7 +12,7 @@ struct KvGeom {
   // Paged storage (SpecPipe-DB keeps its cache in pages, Sec. 4 "Implementation"): request r's
   // logical slot s lives in physical slot page_table[r * pt_stride + (s >> pg_shift)] << pg_shift
   // | (s & mask).  Null: a request owns the contiguous range that starts at its base slot.
-  const int* page_table;
+  int* page_table;
   int pt_stride;
   int pg_shift;
 };

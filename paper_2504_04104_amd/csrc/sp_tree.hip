@@ -58,7 +58,11 @@ __global__ void __launch_bounds__(SP_T) k_tree_insert(ReqMeta* meta, ReqTables* 
     const int n16 = n_new * u16;
     for (int i = threadIdx.x; i < n16; i += blockDim.x) {
       const int row = i / u16, u = i - row * u16;
-      const size_t slot = sp_phys_slot(g, req, 0, (int)a.first_slot[item] + row);   // first_slot includes the base
+      const int lslot = (int)a.first_slot[item] + row;        // (includes the base of a contiguous request)
+      const int fresh = (lslot >> g.pg_shift) - a.pg_first[item];
+      const size_t slot = fresh >= 0 && fresh < a.pg_n[item]  // a page that this launch is about to enter into the table
+                              ? ((size_t)a.page[a.pg_at[item] + fresh] << g.pg_shift) | (size_t)(lslot & ((1 << g.pg_shift) - 1))
+                              : sp_phys_slot(g, req, 0, lslot);
       reinterpret_cast<uint4*>(plane + slot * g.row_bytes)[u] = make_uint4(0u, 0u, 0u, 0u);
     }
     return;
@@ -66,6 +70,7 @@ __global__ void __launch_bounds__(SP_T) k_tree_insert(ReqMeta* meta, ReqTables* 
   ReqTables& t = tables[req];
   const int T0 = a.t0[item];
   const int k = threadIdx.x;
+  if (k < a.pg_n[item]) g.page_table[(size_t)req * g.pt_stride + a.pg_first[item] + k] = a.page[a.pg_at[item] + k];
   if (k < n_new) {
     unsigned long long bits[SP_W] = {0ull, 0ull, 0ull, 0ull};
     const int self = T0 + k;
@@ -300,6 +305,7 @@ hipError_t sp_launch_request_init(ReqMeta* meta, ReqTables* tables, int req, lon
   hipLaunchKernelGGL(k_request_init, dim3(1), dim3(64), 0, st, meta, tables, req, base, cap, P);
   return hipGetLastError();
 }
+static_assert(2 * sizeof(void*) + sizeof(InsertArgs) + sizeof(KvGeom) <= 4096, "kernel arguments");
 hipError_t sp_launch_tree_insert(ReqMeta* meta, ReqTables* tables, const InsertArgs& a, KvGeom g, hipStream_t st) {
   hipLaunchKernelGGL(k_tree_insert, dim3(1 + g.n_layers * 2 * g.n_kv_heads, a.n_req), dim3(SP_T), 0, st, meta, tables,
                      a, g);

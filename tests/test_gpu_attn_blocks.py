@@ -37,3 +37,22 @@ def test_ragged_contexts(rows, page_slots):
     for q in range(n):
         pair.check_kv(q, 2e-2)
     pair.close()
+
+
+@pytest.mark.parametrize("n", [33, 3])
+def test_requests_that_take_pages_at_once(n):
+    """More requests than an insert launch carries pages for (and a few) whose rows reach a new page, one of them three, twice: the
+    cache rows land there and the attention finds them."""
+    pair = Pair(SHAPE, 93, {q: 31 + q % 2 for q in range(n)}, max_batch_nodes=640, page_slots=32)
+    for k in range(2):
+        rows = [70 if q == 1 and k == 0 else 5 for q in range(n)]
+        first = pair.insert_batch(list(range(n)), [wl.tree_deep(93 + q, r, 9) for q, r in enumerate(rows)])
+        x = wl.hidden_rows(SHAPE, 93, ("pages", k), sum(rows))
+        y, ref = pair.forward(list(range(n)), first, rows, x)
+        assert rel_err(y - x, ref - x) <= 2e-2, k
+        for q in range(n):
+            pair.check_kv(q, 2e-2)
+        if k == 0:
+            for q in range(n):
+                pair.prune(q, sp.SP_CLEAR, 0)
+    pair.close()
