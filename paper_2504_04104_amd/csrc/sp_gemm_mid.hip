@@ -68,14 +68,15 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   const int c_begin = (int)(((long long)blockIdx.y * chunks) / S);
   const int c_end = (int)(((long long)(blockIdx.y + 1) * chunks) / S);
   const int c_n = c_end - c_begin;
-  // Staggered starting chunks where the rows that the workgroups stream lie a multiple of 8 KB apart and would be at the
-  // same offset of it at the same moment: gate/up over row-major weights (8B shape 64 rows 58.8 -> 54.3 us, 145 rows 75.6
-  // -> 69.0; nothing gained in fragment order, whose strips are contiguous) and plain products 8192 deep (8192 x 8192, 65
-  // rows: 36.3 -> 33.2 us, row-major 40.7 -> 35.5; with K = 4096 slices are four to eight chunks long and lose 1 %, with
-  // 14336 and more nothing changes).
-  const bool stagger = GATEUP ? !PACKED : K > 4096 && K <= 8192;
+  // Staggered starting chunks where the rows or strips that the workgroups stream lie a multiple of 8 KB apart and would be
+  // at the same offset of it at the same moment: gate/up over row-major weights (8B shape 64 rows 58.8 -> 54.3 us, 145 rows
+  // 75.6 -> 69.0) and, up to 96 rows, over weights in fragment order (four 8B layers, five machines: 33-48 rows 0.4-1 %
+  // faster, 56-64 level to 1 %, 72-96 0.6-1.5 %; alone, 64 rows 40.8 -> 39.8 us; with more rows level), and plain products 8192
+  // deep (8192 x 8192, 65 rows: 36.3 -> 33.2 us, row-major 40.7 -> 35.5; with K = 4096 slices are four to eight chunks long
+  // and lose 1 %, with 14336 and more nothing changes).
+  const bool stagger = GATEUP ? !PACKED || MT <= 6 : K > 4096 && K <= 8192;
   const int rot = stagger && c_n > 1 ? (int)((blockIdx.x >> 3) % (unsigned)c_n) : 0;
-#define SP_PC(C) ((GATEUP && PACKED) || (C) + rot < c_end ? (C) + rot : (C) + rot - c_n)
+#define SP_PC(C) ((GATEUP && PACKED && MT > 6) || (C) + rot < c_end ? (C) + rot : (C) + rot - c_n)
 
   // strip a of a wave: plain, strip cw * NS + a; gate/up, a gate strip and the up strip of the same columns
   constexpr int GS = GATEUP ? NS / 2 : NS;
@@ -307,7 +308,7 @@ template <int MT, bool PACKED, bool SHORT> struct PlainPipe
                                             std::conditional_t<(MT <= 6), MidPipe<128, 2, 1, true>, MidPipe<128, 2, 2, false>>>> {};
 template <int MT, int KQ, bool PACKED> struct GateupPipe
     : std::conditional_t<KQ == 1, std::conditional_t<(MT <= 8 || !PACKED), MidPipe<64, MT <= 8 ? 3 : 2, MT <= 8 && PACKED ? 2 : 1, true>, MidPipe<128, 2, 1, false>>,
-                         std::conditional_t<(MT <= 6), MidPipe<128, 2, (MT <= 4 && !PACKED) ? 2 : 1, true>,
+                         std::conditional_t<(MT <= 6), MidPipe<128, 2, MT <= 4 ? 2 : 1, true>,
                                             std::conditional_t<(MT > 10), MidPipe<64, 3, 3, false>,
                                                                std::conditional_t<PACKED, MidPipe<128, 2, 2, false>, MidPipe<128, 1, 1, true>>>>> {};
 
