@@ -686,6 +686,19 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     int base_blocks = 0;
     for (int i = 0; i < b.n_req; ++i) base_blocks += (b.n[i] * g + qrows_per_block - 1) / qrows_per_block;
     int want = s->n_cu / (base_blocks * nkv);
+    // One chunk after all where the tiles that a wave saves by the split are not worth the merge: a launch of 4.7 us and the
+    // partial rows, against 1-1.2 us a tile (rounds: 32-slot tiles of the longest range per wave).  Us a layer, split / whole,
+    // 8B shape: 64 rows (64 workgroups) behind 450, 1450 and 2700 slots 127.2 / 123.6, 129.5 / 127.2 and 131.2 / 132.9, 37 rows
+    // (40) 700, 1700, 2200 120.7 / 117.6, 121.7 / 121.5, 123.1 / 123.7, 128 rows (128) 2700 163.7 / 162.6.  With few workgroups
+    // a tile is a memory latency: one to eight rows 450, 513, 700, 960 96 / 94, 99.2 / 97.1, 96.3 / 96.0, 96.1 / 97.9, 70B shape 450,
+    // 700, 960 292.3 / 292.9, 292.5 / 295.6 and 292.3 / 297.0.
+    const int wgs = base_blocks * nkv;
+    if (want > 1) {
+      int longest = 0;
+      for (int i = 0; i < b.n_req; ++i) longest = plan.seg_P[i] + plan.seg_T[i] > longest ? plan.seg_P[i] + plan.seg_T[i] : longest;
+      const int rounds = (longest + 255) / 256, saved = rounds - (rounds + want - 1) / want;
+      if (wgs > s->n_cu / 8 ? saved <= 5 : longest <= 576) want = 1;
+    }
     size_t units = 0;
     fill(want, &units);
     while (units > w.attn_units && want > 1) { want = (want + 1) / 2; fill(want, &units); }

@@ -56,3 +56,18 @@ def test_requests_that_take_pages_at_once(n):
             for q in range(n):
                 pair.prune(q, sp.SP_CLEAR, 0)
     pair.close()
+
+
+@pytest.mark.parametrize("n,prefixes", [(5, [571, 572, 768]), (20, [1531, 1532, 1790])], ids=["few_workgroups", "many_workgroups"])
+def test_one_chunk_or_several(n, prefixes):
+    """One request whose cache range (with its n nodes) lies on either side of where it is cut into chunks: 576 slots where the blocks
+    of query rows make few workgroups; six rounds of tiles where they make more than an eighth of the CUs (40 here)."""
+    shape = wl.ModelShape(n_layers=1, d_model=512, n_q_heads=64, n_kv_heads=8, d_head=128, d_ff=512)
+    for P in prefixes:
+        pair = Pair(shape, 95, {0: P}, norm1_gain=4.0)
+        pair.insert(0, wl.tree_deep(95, n, 7))
+        x = wl.hidden_rows(shape, 95, ("chunks", P), n) * np.float32(2.0 ** -6)
+        y, ref = pair.forward([0], [0], [n], x)
+        assert rel_err(y - x, ref - x) <= 2e-2, P
+        assert elementwise_figure(y.astype(np.float64) - x, ref - x, 2e-2, 5e-2) <= 1.0, P
+        pair.close()
