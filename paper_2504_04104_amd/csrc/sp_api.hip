@@ -643,67 +643,7 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     plan.seg_first[k] = b.first[i]; plan.seg_P[k] = r.P; plan.seg_T[k] = r.T; plan.seg_base[k] = r.base;
     plan.seg_chunks[k] = 1;
   }
-  if (s->fast) {
-    // Split every request's cache range into chunks so that the grid fills the chip
-    // and the partial results fit the workspace.
-    const int g = nq / nkv;
-    int maxq = 0;
-    for (int i = 0; i < b.n_req; ++i) if (b.n[i] * g > maxq) maxq = b.n[i] * g;
-    plan.qt = maxq <= 16 ? 1 : 2;
-    // Blocks of 64 query rows where those alone give every CU a workgroup: half of the tiles' way out of L2 (638 rows of 32
-    // requests behind 512-4096 slots, two layers: 829 us with blocks of 32, 815 with 64; starting the longest ranges first
-    // is the rest of 858 -> 815).  With fewer, the ranges would have to be cut instead, and merging costs more (70B shape, 128 rows).
-    int blocks64 = 0;
-    for (int i = 0; i < b.n_req; ++i) blocks64 += (b.n[i] * g + 63) / 64;
-    if (maxq > 32 && blocks64 * nkv >= s->n_cu) plan.qt = 4;
-    const int qrows_per_block = 16 * plan.qt;
-    // One workgroup per CU is the target.  If the query blocks alone give that many, every
-    // request keeps its whole cache range in one chunk (no partial results, no merge kernel);
-    // otherwise each range is cut into `want` chunks, but never below one 32-slot tile per
-    // wave, and fewer if the partial results would not fit the workspace.
-    auto fill = [&](int want, size_t* units_out) {
-      size_t units = 0; int items = 0, split = 0;
-      for (int i = 0; i < b.n_req; ++i) {
-        const int span = plan.seg_P[i] + plan.seg_T[i];
-        int chunks = want;
-        const int max_chunks = (span + 255) / 256;
-        if (chunks > max_chunks) chunks = max_chunks;
-        if (chunks < 1) chunks = 1;
-        const int clen = ((span + chunks - 1) / chunks + 31) / 32 * 32;
-        chunks = (span + clen - 1) / clen;
-        const int qblocks = (plan.seg_rows[i] * g + qrows_per_block - 1) / qrows_per_block;
-        plan.seg_item0[i] = items; plan.seg_chunks[i] = chunks; plan.seg_clen[i] = clen; plan.seg_qblocks[i] = qblocks;
-        plan.seg_unit0[i] = (int)units;
-        items += chunks * qblocks;
-        if (chunks > 1) { units += (size_t)chunks * plan.seg_rows[i] * nq; split = 1; }
-      }
-      plan.total_items = items;
-      plan.units_total = (int)units;
-      plan.any_split = split;
-      *units_out = units;
-      return items;
-    };
-    int base_blocks = 0;
-    for (int i = 0; i < b.n_req; ++i) base_blocks += (b.n[i] * g + qrows_per_block - 1) / qrows_per_block;
-    int want = s->n_cu / (base_blocks * nkv);
-    // One chunk after all where the tiles that a wave saves by the split are not worth the merge: a launch of 4.7 us and the
-    // partial rows, against 1-1.2 us a tile (rounds: 32-slot tiles of the longest range per wave).  Us a layer, split / whole,
-    // 8B shape: 64 rows (64 workgroups) behind 450, 1450 and 2700 slots 127.2 / 123.6, 129.5 / 127.2 and 131.2 / 132.9, 37 rows
-    // (40) 700, 1700, 2200 120.7 / 117.6, 121.7 / 121.5, 123.1 / 123.7, 128 rows (128) 2700 163.7 / 162.6.  With few workgroups
-    // a tile is a memory latency: one to eight rows 450, 513, 700, 960 96 / 94, 99.2 / 97.1, 96.3 / 96.0, 96.1 / 97.9, 70B shape 450,
-    // 700, 960 292.3 / 292.9, 292.5 / 295.6 and 292.3 / 297.0.
-    const int wgs = base_blocks * nkv;
-    if (want > 1) {
-      int longest = 0;
-      for (int i = 0; i < b.n_req; ++i) longest = plan.seg_P[i] + plan.seg_T[i] > longest ? plan.seg_P[i] + plan.seg_T[i] : longest;
-      const int rounds = (longest + 255) / 256, saved = rounds - (rounds + want - 1) / want;
-      if (wgs > s->n_cu / 8 ? saved <= 5 : longest <= 576) want = 1;
-    }
-    size_t units = 0;
-    fill(want, &units);
-    while (units > w.attn_units && want > 1) { want = (want + 1) / 2; fill(want, &units); }
-    if (units > w.attn_units) return SP_E_CAPACITY;
-  }
+  if (s->fast && !attn_split(plan, nq, nkv, s->n_cu, w.attn_units)) return SP_E_CAPACITY;
 
   const size_t strideD = (size_t)M * d, strideQ = (size_t)M * nqkv;
   const bool few = s->fast && sp_few_takes(M, d, dq, F, s->packed, s->n_cu);

@@ -3,9 +3,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "sp_plan.h"
+
 #define SP_T 256          // tree capacity per request (== SP_MAX_TREE_NODES)
 #define SP_W 4            // 64-bit words per ancestor-bitmask row
-#define SP_BATCH 64       // requests per batched call (== SP_MAX_BATCH_REQ)
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits
 

@@ -66,28 +66,6 @@ hipError_t sp_launch_kv_compact(const ReqMeta* meta, const ReqTables* tables, co
                                 void* rows /*nullable: hidden rows of the one request, same launch*/,
                                 size_t row_stride_bytes, int row_bytes, const RowList* l, hipStream_t st);
 
-// A forward call's requests (segments) and the split of its attention work, made on the host.
-struct AttnPlan {          // host-made split of a forward call's attention work
-  int n_seg;
-  int qt;                  // 16-row query tiles per workgroup: 1, 2, or 4 (two groups of waves with two tiles each)
-  int units_total;         // partial-result units: sum over split segments of chunks * rows * n_q
-  int total_items;         // sum over segments of q_blocks * chunks
-  int any_split;           // some segment has more than one chunk: the merge kernel must run
-  int seg_item0[SP_BATCH]; // first work item of each segment
-  int seg_chunks[SP_BATCH];
-  int seg_clen[SP_BATCH];  // slots per chunk of the segment (multiple of 32)
-  int seg_qblocks[SP_BATCH];
-  int seg_unit0[SP_BATCH];
-  int seg_row0[SP_BATCH];  // first row of the call that belongs to the segment
-  int seg_rows[SP_BATCH];
-  int seg_req[SP_BATCH];
-  int seg_first[SP_BATCH]; // first node of the segment
-  int seg_P[SP_BATCH];     // host mirror of prefix length and live nodes
-  int seg_T[SP_BATCH];
-  long long seg_base[SP_BATCH];
-  void* x_out;             // where the call's result rows go
-};
-
 // ---- elementwise / row kernels --------------------------------------------------
 // Rows enter the stage: row descriptors and rotary tables (cs: [rows][d_head], cos then sin),
 // h = x, xn = rmsnorm(h) * gain (frag, bf16 only: in fragment order, as every bf16 matrix-core product reads its rows).

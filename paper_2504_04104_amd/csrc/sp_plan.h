@@ -1,0 +1,91 @@
+// The plan of a forward call: its requests (segments) and the split of its attention work, made on the host.  Plain C++.
+#pragma once
+#include <stddef.h>
+
+#define SP_BATCH 64       // requests per batched call (== SP_MAX_BATCH_REQ)
+
+struct AttnPlan {          // host-made split of a forward call's attention work
+  int n_seg;
+  int qt;                  // 16-row query tiles per workgroup: 1, 2, or 4 (two groups of waves with two tiles each)
+  int units_total;         // partial-result units: sum over split segments of chunks * rows * n_q
+  int total_items;         // sum over segments of q_blocks * chunks
+  int any_split;           // some segment has more than one chunk: the merge kernel must run
+  int seg_item0[SP_BATCH]; // first work item of each segment
+  int seg_chunks[SP_BATCH];
+  int seg_clen[SP_BATCH];  // slots per chunk of the segment (multiple of 32)
+  int seg_qblocks[SP_BATCH];
+  int seg_unit0[SP_BATCH];
+  int seg_row0[SP_BATCH];  // first row of the call that belongs to the segment
+  int seg_rows[SP_BATCH];
+  int seg_req[SP_BATCH];
+  int seg_first[SP_BATCH]; // first node of the segment
+  int seg_P[SP_BATCH];     // host mirror of prefix length and live nodes
+  int seg_T[SP_BATCH];
+  long long seg_base[SP_BATCH];
+  void* x_out;             // where the call's result rows go
+};
+
+// Blocks of `per` query rows that the segments make (g query heads of a KV head times the rows).
+inline int attn_blocks(const AttnPlan& plan, int g, int per) {
+  int n = 0;
+  for (int i = 0; i < plan.n_seg; ++i) n += (plan.seg_rows[i] * g + per - 1) / per;
+  return n;
+}
+
+// Splits every request's cache range into at most `want` chunks; returns the partial-result units that this takes.
+inline size_t attn_cut(AttnPlan& plan, int g, int n_q, int want) {
+  const int per = 16 * plan.qt;
+  size_t units = 0; int items = 0, split = 0;
+  for (int i = 0; i < plan.n_seg; ++i) {
+    const int span = plan.seg_P[i] + plan.seg_T[i];
+    int chunks = want;
+    const int max_chunks = (span + 255) / 256;
+    if (chunks > max_chunks) chunks = max_chunks;
+    if (chunks < 1) chunks = 1;
+    const int clen = ((span + chunks - 1) / chunks + 31) / 32 * 32;
+    chunks = (span + clen - 1) / clen;
+    const int qblocks = (plan.seg_rows[i] * g + per - 1) / per;
+    plan.seg_item0[i] = items; plan.seg_chunks[i] = chunks; plan.seg_clen[i] = clen; plan.seg_qblocks[i] = qblocks;
+    plan.seg_unit0[i] = (int)units;
+    items += chunks * qblocks;
+    if (chunks > 1) { units += (size_t)chunks * plan.seg_rows[i] * n_q; split = 1; }
+  }
+  plan.total_items = items;
+  plan.units_total = (int)units;
+  plan.any_split = split;
+  return units;
+}
+
+// The attention work of a plan whose segments are entered, longest cache ranges first: so that the grid fills the chip and the
+// partial results fit `room` units.  False: they do not fit.
+inline bool attn_split(AttnPlan& plan, int n_q, int n_kv, int n_cu, size_t room) {
+  const int g = n_q / n_kv;
+  int maxq = 0;
+  for (int i = 0; i < plan.n_seg; ++i) if (plan.seg_rows[i] * g > maxq) maxq = plan.seg_rows[i] * g;
+  plan.qt = maxq <= 16 ? 1 : 2;
+  // Blocks of 64 query rows where those alone give every CU a workgroup: half of the tiles' way out of L2 (638 rows of 32
+  // requests behind 512-4096 slots, two layers: 829 us with blocks of 32, 815 with 64; starting the longest ranges first
+  // is the rest of 858 -> 815).  With fewer, the ranges would have to be cut instead, and merging costs more (70B shape, 128 rows).
+  if (maxq > 32 && attn_blocks(plan, g, 64) * n_kv >= n_cu) plan.qt = 4;
+  // One workgroup per CU is the target.  If the query blocks alone give that many, every
+  // request keeps its whole cache range in one chunk (no partial results, no merge kernel);
+  // otherwise each range is cut into `want` chunks, but never below one 32-slot tile per
+  // wave, and fewer if the partial results would not fit the workspace.
+  const int wgs = attn_blocks(plan, g, 16 * plan.qt) * n_kv;
+  int want = n_cu / wgs;
+  // One chunk after all where the tiles that a wave saves by the split are not worth the merge: a launch of 4.7 us and the
+  // partial rows, against 1-1.2 us a tile (rounds: 32-slot tiles of the longest range per wave).  Us a layer, split / whole,
+  // 8B shape: 64 rows (64 workgroups) behind 450, 1450 and 2700 slots 127.2 / 123.6, 129.5 / 127.2 and 131.2 / 132.9, 37 rows
+  // (40) 700, 1700, 2200 120.7 / 117.6, 121.7 / 121.5, 123.1 / 123.7, 128 rows (128) 2700 163.7 / 162.6.  With few workgroups
+  // a tile is a memory latency: one to eight rows 450, 513, 700, 960 96 / 94, 99.2 / 97.1, 96.3 / 96.0, 96.1 / 97.9, 70B shape 450,
+  // 700, 960 292.3 / 292.9, 292.5 / 295.6 and 292.3 / 297.0.
+  if (want > 1) {
+    int longest = 0;
+    for (int i = 0; i < plan.n_seg; ++i) longest = plan.seg_P[i] + plan.seg_T[i] > longest ? plan.seg_P[i] + plan.seg_T[i] : longest;
+    const int rounds = (longest + 255) / 256, saved = rounds - (rounds + want - 1) / want;
+    if (wgs > n_cu / 8 ? saved <= 5 : longest <= 576) want = 1;
+  }
+  size_t units = attn_cut(plan, g, n_q, want);
+  while (units > room && want > 1) { want = (want + 1) / 2; units = attn_cut(plan, g, n_q, want); }
+  return units <= room;
+}

@@ -1,0 +1,73 @@
+"""The split of a forward call's attention work (csrc/sp_plan.h, plain C++) on the CPU."""
+import ctypes as C
+import os
+import random
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2504_04104_amd", "csrc")
+DRIVER = """
+#include <string.h>
+#include "sp_plan.h"
+extern "C" int split(int n, const int* rows, const int* spans, int n_q, int n_kv, int n_cu, long room, int* head, int* segs) {
+  AttnPlan p;
+  memset(&p, 0, sizeof(p));
+  p.n_seg = n;
+  for (int i = 0; i < n; ++i) { p.seg_rows[i] = rows[i]; p.seg_P[i] = spans[i] - rows[i]; p.seg_T[i] = rows[i]; }
+  if (!attn_split(p, n_q, n_kv, n_cu, (size_t)room)) return 0;
+  const int h[] = {p.qt, p.total_items, p.any_split, p.units_total};
+  memcpy(head, h, sizeof(h));
+  for (int i = 0; i < n; ++i) {
+    const int s[] = {p.seg_item0[i], p.seg_chunks[i], p.seg_clen[i], p.seg_qblocks[i], p.seg_unit0[i]};
+    memcpy(segs + i * 5, s, sizeof(s));
+  }
+  return 1;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def split(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "driver.cpp").write_text(DRIVER)
+    so = str(d / "driver.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(d / "driver.cpp"), "-o", so], check=True)
+    lib = C.CDLL(so)
+
+    def call(rows, spans, n_q=32, n_kv=8, n_cu=256, room=1 << 20):
+        """Segments longest first, as the forward call enters them.  None where the partial results do not fit."""
+        order = sorted(range(len(rows)), key=lambda i: -spans[i])
+        r, s = ((C.c_int * len(rows))(*[v[i] for i in order]) for v in (rows, spans))
+        head, segs = (C.c_int * 4)(), (C.c_int * (5 * len(rows)))()
+        if not lib.split(len(rows), r, s, n_q, n_kv, n_cu, C.c_long(room), head, segs):
+            return None
+        out = dict(zip(("qt", "items", "any_split", "units"), head))
+        out["segs"] = np.array(segs).reshape(-1, 5)
+        out["rows"], out["spans"] = list(r), list(s)
+        return out
+    return call
+
+
+def test_every_plan_covers_its_ranges(split):
+    """Chunks are whole tiles, none is empty, they cover the range; items and units of the segments follow each other; the
+    partial results fit the room, and no call is refused (one chunk each needs none)."""
+    r = random.Random(1)
+    for _ in range(3000):
+        n_kv = r.choice([1, 2, 4, 8])
+        n_q = n_kv * r.choice([1, 2, 4, 8])
+        rows = [r.choice([1, 2, 5, 9, 17, 64, 200]) for _ in range(r.choice([1, 1, 2, 5, 31, 64]))]
+        spans = [v + int(2 ** r.uniform(0, 15)) for v in rows]
+        room = r.choice([0, 2000, 1 << 20])
+        p = split(rows, spans, n_q, n_kv, room=room)
+        item, unit, any_split = 0, 0, 0
+        for (item0, chunks, clen, qblocks, unit0), m, span in zip(p["segs"].tolist(), p["rows"], p["spans"]):
+            assert clen % 32 == 0 and (chunks - 1) * clen < span <= chunks * clen
+            assert qblocks == -(-m * (n_q // n_kv) // (16 * p["qt"]))
+            assert (item0, unit0) == (item, unit)
+            item += chunks * qblocks
+            unit += chunks * m * n_q if chunks > 1 else 0
+            any_split |= chunks > 1
+        assert (item, unit, any_split) == (p["items"], p["units"], p["any_split"])
+        assert unit <= room
