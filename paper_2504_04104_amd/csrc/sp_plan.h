@@ -63,10 +63,16 @@ inline bool attn_split(AttnPlan& plan, int n_q, int n_kv, int n_cu, size_t room)
   int maxq = 0;
   for (int i = 0; i < plan.n_seg; ++i) if (plan.seg_rows[i] * g > maxq) maxq = plan.seg_rows[i] * g;
   plan.qt = maxq <= 16 ? 1 : 2;
-  // Blocks of 64 query rows where those alone give every CU a workgroup: half of the tiles' way out of L2 (638 rows of 32
-  // requests behind 512-4096 slots, two layers: 829 us with blocks of 32, 815 with 64; starting the longest ranges first
-  // is the rest of 858 -> 815).  With fewer, the ranges would have to be cut instead, and merging costs more (70B shape, 128 rows).
-  if (maxq > 32 && attn_blocks(plan, g, 64) * n_kv >= n_cu) plan.qt = 4;
+  // Blocks of 64 query rows: half of the tiles' way out of L2, but four runs of slots instead of eight, so that a workgroup takes
+  // twice as long, and ranges that a block of 32 would stream by itself are not streamed any more.  They are taken where they
+  // are at most two thirds as many as blocks of 32, and not in one round of workgroups of different lengths, whose longest would
+  // set the time.  Us a layer of the 8B shape behind 512-4096 slots, blocks of 32 / 64: 31 requests of four nodes and one of nine
+  // (33 blocks of 32, 32 of 64; 256 workgroups) 211.4 / 220.3, every second of nine instead of one (48, 32) 212.9 / 225.2, 28
+  // requests of 4 and 64 nodes (56, 40) 282.1 / 288.5, 32 of nine (64, 32) 284.4 / 286.9, 32 of 9-16 (64, 32) 315.3 / 322.2; 16 of
+  // 24-48 (76, 41; 328 workgroups) 365.1 / 353.8, 64 of 4-12 (99, 64) 444.7 / 438.2, 32 of 8-32 (91, 51) 415.6 / 410.5, two layers of
+  // 638 rows (93, 53) 785.0 / 777.1.  One request's ranges are of one length: 70B shape, 256 rows (64, 32; 256) 602.6 / 595.2.
+  const int b64 = attn_blocks(plan, g, 64), b32 = attn_blocks(plan, g, 32);
+  if (maxq > 32 && 3 * b64 <= 2 * b32 && b64 * n_kv >= (plan.n_seg == 1 ? n_cu : n_cu + n_cu / 4)) plan.qt = 4;
   // One workgroup per CU is the target.  If the query blocks alone give that many, every
   // request keeps its whole cache range in one chunk (no partial results, no merge kernel);
   // otherwise each range is cut into `want` chunks, but never below one 32-slot tile per

@@ -71,3 +71,21 @@ def test_every_plan_covers_its_ranges(split):
             any_split |= chunks > 1
         assert (item, unit, any_split) == (p["items"], p["units"], p["any_split"])
         assert unit <= room
+
+
+# 32 query heads over 8 KV heads: a node is four query rows of a KV head
+@pytest.mark.parametrize("rows,spans,n_q,qt", [
+    # one request of more than 32 query rows, or half of them, among short ones: nearly as many blocks of 64 as of 32
+    ([4] * 31 + [9], None, 32, 2), ([2] * 31 + [16], None, 32, 2), ([1, 9] * 16, None, 32, 2), ([4, 12] * 16, None, 32, 2),
+    ([128] + [2] * 30, None, 32, 2), ([64] * 4 + [4] * 24, None, 32, 2), ([16] * 16 + [5] * 48, None, 32, 2),
+    # half as many, but ranges of different lengths in one round of workgroups
+    ([9] * 32, None, 32, 2), ([16] * 32, None, 32, 2), ([16] * 16, None, 64, 2),
+    # ... in more than one
+    ([16] * 40, None, 32, 4), ([25, 32] * 12, None, 32, 4), ([9, 12, 16, 8] * 12, None, 32, 4), ([32] * 16, None, 64, 4),
+    # ranges of one length
+    ([256], [2304], 64, 4), ([256], [2304], 32, 2),
+    # small ones only
+    ([8] * 64, None, 32, 2), ([4] * 64, None, 32, 1)])
+def test_blocks_of_64_query_rows(split, rows, spans, n_q, qt):
+    """... are taken where they are at most two thirds as many as blocks of 32, and a quarter more than the CUs or all of one request."""
+    assert split(rows, spans or [700 + 97 * i % 3300 for i in range(len(rows))], n_q)["qt"] == qt
