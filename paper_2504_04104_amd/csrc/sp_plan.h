@@ -79,17 +79,26 @@ inline bool attn_split(AttnPlan& plan, int n_q, int n_kv, int n_cu, size_t room)
   // wave, and fewer if the partial results would not fit the workspace.
   const int wgs = attn_blocks(plan, g, 16 * plan.qt) * n_kv;
   int want = n_cu / wgs;
-  // One chunk after all where the tiles that a wave saves by the split are not worth the merge: a launch of 4.7 us and the
-  // partial rows, against 1-1.2 us a tile (rounds: 32-slot tiles of the longest range per wave).  Us a layer, split / whole,
-  // 8B shape: 64 rows (64 workgroups) behind 450, 1450 and 2700 slots 127.2 / 123.6, 129.5 / 127.2 and 131.2 / 132.9, 37 rows
-  // (40) 700, 1700, 2200 120.7 / 117.6, 121.7 / 121.5, 123.1 / 123.7, 128 rows (128) 2700 163.7 / 162.6.  With few workgroups
-  // a tile is a memory latency: one to eight rows 450, 513, 700, 960 96 / 94, 99.2 / 97.1, 96.3 / 96.0, 96.1 / 97.9, 70B shape 450,
-  // 700, 960 292.3 / 292.9, 292.5 / 295.6 and 292.3 / 297.0.
+  // One chunk after all where what the split saves (rounds: 32-slot tiles of the longest range per wave) is not worth the merge,
+  // a launch of 4.7 us and the partial rows.  Where no request has a second block, every workgroup streams a range of its own
+  // and a tile is a memory latency, 2-2.4 us: two rounds saved are not worth it, three are, or four where half of the CUs
+  // stream even uncut.  Blocks that share ranges find them in L2, a tile takes 1-1.2 us, and the more blocks, the more partial
+  // rows there are.  Us a layer of the 8B shape, split / whole (workgroups, rounds saved): one row behind 620 and 900 slots (8; 2
+  // and 3) 87.6 / 87.6 and 87.3 / 88.8, five requests of one row behind 500, 800 and 1500 (40; 2, 3 and 5) 91.8 / 90.2, 91.2 / 93.2
+  // and 94.3 / 98.9, 12 of three behind 1500 (96; 3) 119.7 / 121.7, 16 of one behind 1500 and 2200 (128; 3 and 4) 109.9 / 109.3 and
+  // 116.6 / 116.8; 16 rows of one request behind 900 and 1150 (16; 3 and 4) 97.8 / 97.5 and 98.2 / 98.9, 37 behind 700, 1000 and 1450
+  // (40; 2, 4 and 5) 120.7 / 117.6, 111.8 / 112.3 and 112.4 / 113.8, 64 behind 1450 and 2000 (64; 4 and 6) 121.4 / 120.1 and 121.6 /
+  // 123.3, 128 behind 2200, 2700 and 3400 (128; 5, 6 and 7) 152.9 / 152.0, 154.3 / 153.9 and 155.1 / 156.0, four requests of 24 behind
+  // 1700 and 3000 (96; 3 and 6) 135.3 / 133.0 and 138.7 / 139.6.
   if (want > 1) {
     int longest = 0;
-    for (int i = 0; i < plan.n_seg; ++i) longest = plan.seg_P[i] + plan.seg_T[i] > longest ? plan.seg_P[i] + plan.seg_T[i] : longest;
+    bool shared = false;
+    for (int i = 0; i < plan.n_seg; ++i) {
+      longest = plan.seg_P[i] + plan.seg_T[i] > longest ? plan.seg_P[i] + plan.seg_T[i] : longest;
+      shared = shared || plan.seg_rows[i] * g > 16 * plan.qt;
+    }
     const int rounds = (longest + 255) / 256, saved = rounds - (rounds + want - 1) / want;
-    if (wgs > n_cu / 8 ? saved <= 5 : longest <= 576) want = 1;
+    if (shared ? 2 * saved <= 5 + 16 * wgs / n_cu : saved <= (2 * wgs < n_cu ? 2 : 3)) want = 1;
   }
   size_t units = attn_cut(plan, g, n_q, want);
   while (units > room && want > 1) { want = (want + 1) / 2; units = attn_cut(plan, g, n_q, want); }

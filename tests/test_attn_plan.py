@@ -89,3 +89,17 @@ def test_every_plan_covers_its_ranges(split):
 def test_blocks_of_64_query_rows(split, rows, spans, n_q, qt):
     """... are taken where they are at most two thirds as many as blocks of 32, and a quarter more than the CUs or all of one request."""
     assert split(rows, spans or [700 + 97 * i % 3300 for i in range(len(rows))], n_q)["qt"] == qt
+
+
+@pytest.mark.parametrize("rows,prefixes,cut", [
+    # each request a block of its own: three rounds of tiles to save, four where the ranges occupy half of the CUs uncut
+    ([1], [760], False), ([1], [780], True), ([1] * 5, [700] * 5, False), ([1] * 5, [1500] * 5, True), ([1] * 5, [1100] * 5, True),
+    ([8] * 8, [1500] * 8, True), ([3] * 12, [1500] * 12, True), ([1] * 16, [1500] * 16, False), ([1] * 16, [2200] * 16, True),
+    ([2] * 5, [700] * 4 + [1400], True),
+    # blocks that share ranges: the more, the more rounds
+    ([16], [900], False), ([16], [1200], True), ([37], [777], False), ([37], [1450], True), ([48], [1150], False), ([48], [1700], True),
+    ([64], [1450], False), ([64], [2048], True), ([128], [2200], False), ([128], [2700], False), ([128], [3400], True),
+    ([24] * 4, [1700] * 4, False), ([24] * 4, [3000] * 4, True)])
+def test_ranges_whole_or_cut(split, rows, prefixes, cut):
+    """Ranges of the 8B shape are cut into chunks only where the tiles that a wave saves are worth the merge."""
+    assert bool(split(rows, [p + n for p, n in zip(prefixes, rows)])["any_split"]) == cut

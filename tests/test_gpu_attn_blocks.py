@@ -58,10 +58,11 @@ def test_requests_that_take_pages_at_once(n):
     pair.close()
 
 
-@pytest.mark.parametrize("n,prefixes", [(5, [571, 572, 768]), (20, [1531, 1532, 1790])], ids=["few_workgroups", "many_workgroups"])
+@pytest.mark.parametrize("n,prefixes", [(2, [571, 766, 767]), (5, [571, 1019, 1020]), (20, [1004, 1005, 1532, 1790])],
+                         ids=["one_block", "two_blocks", "five_blocks"])
 def test_one_chunk_or_several(n, prefixes):
-    """One request whose cache range (with its n nodes) lies on either side of where it is cut into chunks: 576 slots where the blocks
-    of query rows make few workgroups; six rounds of tiles where they make more than an eighth of the CUs (40 here)."""
+    """One request whose cache range (with its n nodes) lies on either side of where it is cut into chunks: four rounds of 256 slots
+    where it is a single block of query rows, five where it is a few that share it."""
     shape = wl.ModelShape(n_layers=1, d_model=512, n_q_heads=64, n_kv_heads=8, d_head=128, d_ff=512)
     for P in prefixes:
         pair = Pair(shape, 95, {0: P}, norm1_gain=4.0)
