@@ -138,7 +138,8 @@ struct sp_stage {
   // Forward calls of many launches and a shape seen before replay a HIP graph of their launches (all but the first
   // kernel, which carries the caller's input pointer and the call's plan with the pointer of the result).
   struct FwdGraph {
-    int M, qt, items, any_split, units;
+    int M;
+    AttnShape shape;
     int seen;
     bool failed;
     hipGraphExec_t exec;
@@ -819,10 +820,9 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
       for (auto& g : s->graphs)
-        if (g.M == M && g.qt == plan.qt && g.items == plan.total_items && g.any_split == plan.any_split &&
-            g.units == plan.units_total) { fg = &g; break; }
+        if (g.M == M && g.shape == AttnShape(plan)) { fg = &g; break; }
       if (!fg && s->graphs.size() < 256) {
-        s->graphs.push_back({M, plan.qt, plan.total_items, plan.any_split, plan.units_total, 0, false, nullptr});
+        s->graphs.push_back({M, AttnShape(plan), 0, false, nullptr});
         fg = &s->graphs.back();
       }
     }

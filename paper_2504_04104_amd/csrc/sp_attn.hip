@@ -532,16 +532,9 @@ hipError_t sp_launch_attn_bf16(const bf16_t* q, const ReqTables* tables, KvGeom 
   a.frag = frag;
   a.plan = plan_dev;
   dim3 grid(plan.total_items * n_kv);
-  bool stream = true;                     // one block of query rows per request: K/V rows are read once
-  for (int i = 0; i < plan.n_seg; ++i) stream = stream && plan.seg_qblocks[i] <= 1;
-  // Through registers where one workgroup per request streams ranges of different lengths: the longest ones set the time, alone
-  // on their CUs, and a tile that waits in registers keeps their loads in flight all the time (32 requests of 512-4096 slots
-  // 58.8 us, direct to LDS 65.4).  One request, or ranges cut into chunks: every CU streams, and direct-to-LDS loads are level
-  // or faster (above; two to sixteen requests of a few rows, whole steps 0.5-2 %).
-  const bool regs = stream && plan.n_seg > 1 && !plan.any_split;
 #define SP_ATTN_GO(RQV, QTV, PG, NTV, REGSV) hipLaunchKernelGGL((k_attn_bf16<RQV, QTV, PG, NTV, REGSV>), grid, dim3(64 * AW), 0, st, a)
 #define SP_ATTN_PG(RQV, QTV, PG) \
-  { if (RQV > 1 || !stream) SP_ATTN_GO(RQV, QTV, PG, false, false); else if (regs) SP_ATTN_GO(1, QTV, PG, true, true); else SP_ATTN_GO(1, QTV, PG, true, false); }
+  { if (RQV > 1 || plan.loads == ATTN_SHARED) SP_ATTN_GO(RQV, QTV, PG, false, false); else if (plan.loads == ATTN_STREAM_REGS) SP_ATTN_GO(1, QTV, PG, true, true); else SP_ATTN_GO(1, QTV, PG, true, false); }
 #define SP_ATTN_QT(RQV, QTV) { if (g.page_table) SP_ATTN_PG(RQV, QTV, true) else SP_ATTN_PG(RQV, QTV, false) }
   switch (plan.qt) {
     case 1: SP_ATTN_QT(1, 1) break;

@@ -4,12 +4,19 @@
 
 #define SP_BATCH 64       // requests per batched call (== SP_MAX_BATCH_REQ)
 
+enum AttnLoads {
+  ATTN_SHARED,             // direct to LDS, staying in the caches
+  ATTN_STREAM,             // direct to LDS, non-temporal
+  ATTN_STREAM_REGS         // through registers, non-temporal
+};
+
 struct AttnPlan {          // host-made split of a forward call's attention work
   int n_seg;
   int qt;                  // 16-row query tiles per workgroup: 1, 2, or 4 (two groups of waves with two tiles each)
   int units_total;         // partial-result units: sum over split segments of chunks * rows * n_q
   int total_items;         // sum over segments of q_blocks * chunks
   int any_split;           // some segment has more than one chunk: the merge kernel must run
+  int loads;               // how K/V rows come in (AttnLoads)
   int seg_item0[SP_BATCH]; // first work item of each segment
   int seg_chunks[SP_BATCH];
   int seg_clen[SP_BATCH];  // slots per chunk of the segment (multiple of 32)
@@ -23,6 +30,15 @@ struct AttnPlan {          // host-made split of a forward call's attention work
   int seg_T[SP_BATCH];
   long long seg_base[SP_BATCH];
   void* x_out;             // where the call's result rows go
+};
+
+// What the launches of a call depend on beside its number of rows: a captured graph serves the calls for which all of it is equal.
+struct AttnShape {
+  int qt, items, units, any_split, loads;
+  explicit AttnShape(const AttnPlan& p) : qt(p.qt), items(p.total_items), units(p.units_total), any_split(p.any_split), loads(p.loads) {}
+  bool operator==(const AttnShape& o) const {
+    return qt == o.qt && items == o.items && units == o.units && any_split == o.any_split && loads == o.loads;
+  }
 };
 
 // Blocks of `per` query rows that the segments make (g query heads of a KV head times the rows).
@@ -102,5 +118,13 @@ inline bool attn_split(AttnPlan& plan, int n_q, int n_kv, int n_cu, size_t room)
   }
   size_t units = attn_cut(plan, g, n_q, want);
   while (units > room && want > 1) { want = (want + 1) / 2; units = attn_cut(plan, g, n_q, want); }
-  return units <= room;
+  if (units > room) return false;
+  // K/V rows are read once where every request is one block.  Through registers where one workgroup per request streams ranges of
+  // different lengths: the longest ones set the time, alone on their CUs, and a tile that waits in registers keeps their loads in
+  // flight all the time (32 requests of 512-4096 slots 58.8 us, direct to LDS 65.4).  One request, or ranges cut into chunks:
+  // every CU streams, and direct-to-LDS loads are level or faster (two to sixteen requests of a few rows, whole steps 0.5-2 %).
+  plan.loads = ATTN_STREAM;
+  for (int i = 0; i < plan.n_seg; ++i) if (plan.seg_qblocks[i] > 1) plan.loads = ATTN_SHARED;
+  if (plan.loads == ATTN_STREAM && plan.n_seg > 1 && !plan.any_split) plan.loads = ATTN_STREAM_REGS;
+  return true;
 }

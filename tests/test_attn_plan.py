@@ -11,21 +11,25 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 DRIVER = """
 #include <string.h>
 #include "sp_plan.h"
-extern "C" int split(int n, const int* rows, const int* spans, int n_q, int n_kv, int n_cu, long room, int* head, int* segs) {
+extern "C" int split(int n, const int* rows, const int* spans, int n_q, int n_kv, int n_cu, long room, int* head, int* segs, AttnShape* shape) {
   AttnPlan p;
   memset(&p, 0, sizeof(p));
   p.n_seg = n;
   for (int i = 0; i < n; ++i) { p.seg_rows[i] = rows[i]; p.seg_P[i] = spans[i] - rows[i]; p.seg_T[i] = rows[i]; }
   if (!attn_split(p, n_q, n_kv, n_cu, (size_t)room)) return 0;
-  const int h[] = {p.qt, p.total_items, p.any_split, p.units_total};
+  const int h[] = {p.qt, p.total_items, p.any_split, p.units_total, p.loads};
   memcpy(head, h, sizeof(h));
+  *shape = AttnShape(p);
   for (int i = 0; i < n; ++i) {
     const int s[] = {p.seg_item0[i], p.seg_chunks[i], p.seg_clen[i], p.seg_qblocks[i], p.seg_unit0[i]};
     memcpy(segs + i * 5, s, sizeof(s));
   }
   return 1;
 }
+extern "C" int shape_bytes() { return (int)sizeof(AttnShape); }
+extern "C" int same_shape(const AttnShape* a, const AttnShape* b) { return *a == *b; }
 """
+SHARED, STREAM, STREAM_REGS = 0, 1, 2
 
 
 @pytest.fixture(scope="module")
@@ -40,10 +44,12 @@ def split(tmp_path_factory):
         """Segments longest first, as the forward call enters them.  None where the partial results do not fit."""
         order = sorted(range(len(rows)), key=lambda i: -spans[i])
         r, s = ((C.c_int * len(rows))(*[v[i] for i in order]) for v in (rows, spans))
-        head, segs = (C.c_int * 4)(), (C.c_int * (5 * len(rows)))()
-        if not lib.split(len(rows), r, s, n_q, n_kv, n_cu, C.c_long(room), head, segs):
+        head, segs, shape = (C.c_int * 5)(), (C.c_int * (5 * len(rows)))(), C.create_string_buffer(lib.shape_bytes())
+        if not lib.split(len(rows), r, s, n_q, n_kv, n_cu, C.c_long(room), head, segs, shape):
             return None
-        out = dict(zip(("qt", "items", "any_split", "units"), head))
+        out = dict(zip(("qt", "items", "any_split", "units", "loads"), head))
+        out["replays"] = lambda other: bool(lib.same_shape(shape, other["shape"]))
+        out["shape"] = shape
         out["segs"] = np.array(segs).reshape(-1, 5)
         out["rows"], out["spans"] = list(r), list(s)
         return out
@@ -103,3 +109,21 @@ def test_blocks_of_64_query_rows(split, rows, spans, n_q, qt):
 def test_ranges_whole_or_cut(split, rows, prefixes, cut):
     """Ranges of the 8B shape are cut into chunks only where the tiles that a wave saves are worth the merge."""
     assert bool(split(rows, [p + n for p, n in zip(prefixes, rows)])["any_split"]) == cut
+
+
+def test_graphs_keep_to_their_kind_of_loads(split):
+    """A graph holds the attention kernel that was launched when it was captured.  Calls of as many rows, blocks and chunks whose
+    K/V rows come in another way have a graph of their own; other contexts, or the same requests in another order, do not."""
+    two_blocks, one_each = split([8, 8, 8, 16], [700] * 4), split([8] * 5, [700] * 5)
+    for name in ("qt", "items", "any_split", "units"):
+        assert two_blocks[name] == one_each[name]
+    assert (two_blocks["loads"], one_each["loads"]) == (SHARED, STREAM_REGS)
+    assert not two_blocks["replays"](one_each)
+    assert two_blocks["replays"](split([16, 8, 8, 8], [500, 600, 300, 64]))
+    two_blocks, one_each = split([8, 8, 8, 16], [2000] * 4), split([8] * 5, [2000] * 5)
+    assert two_blocks["units"] == one_each["units"] > 0
+    assert (two_blocks["loads"], one_each["loads"]) == (SHARED, STREAM)
+    assert not two_blocks["replays"](one_each)
+    assert one_each["replays"](split([8] * 5, [1990, 1930, 1960, 2010, 1980]))
+    assert split([8], [700])["loads"] == split([8], [5000])["loads"] == STREAM
+    assert split([64], [5000])["loads"] == SHARED
