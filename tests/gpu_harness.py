@@ -15,9 +15,9 @@ _OWN_STREAM = None
 
 
 def use_own_stream():
-    """The GPU tests run on a stream of their own, as bench.py does: the forward call captures and replays
-    HIP graphs of its launches only on a stream that can be captured, and the parity tests should see that
-    path whenever a shape comes back (streaming steps, repeated forwards)."""
+    """The GPU tests run on a stream of their own, as bench.py does: a forward call of many launches captures and
+    replays a HIP graph of them only on a stream that can be captured, and the tests with enough layers (more than
+    24 launches a call) should see that path whenever a shape comes back."""
     global _OWN_STREAM
     if _OWN_STREAM is None and torch.cuda.is_available():
         _OWN_STREAM = torch.cuda.Stream(device="cuda:0")

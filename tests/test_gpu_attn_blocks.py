@@ -25,7 +25,7 @@ CONTEXTS = [33, 1, 257, 31, 128, 513, 32, 127, 300, 64, 5, 129, 255, 63, 96, 256
     pytest.param([4, 1, 3, 2, 4, 2] * 4, id="streamed_one_tile")])
 def test_ragged_contexts(rows, page_slots):
     """Increment y - x of small inputs element by element (2e-2 of the value plus 5e-2 of the rms: about six tensors on the way
-    are stored in bf16), twice (the second call replays the first one's shape), then the cache rows."""
+    are stored in bf16), twice with other rows, then the cache rows."""
     n = len(rows)
     pair = Pair(SHAPE, 91, dict(enumerate(CONTEXTS)), max_batch_nodes=640, page_slots=page_slots, norm1_gain=4.0)
     pair.insert_batch(list(range(n)), [wl.tree_deep(91 + q, r, 9) for q, r in enumerate(rows)])

@@ -14,10 +14,10 @@ SP_K_ROPE_KV = 11          # sp_kernel_kind
 
 # k steps per wave: 8 / 8 / 16 (eight fragments in flight), 2 / 4 / 6 (two), 3 / 4 / 5 (one and two)
 SHAPES = {"k2048": wl.ModelShape(n_layers=2, d_model=2048, n_q_heads=16, n_kv_heads=4, d_head=128, d_ff=4096),
-          "k512": wl.ModelShape(n_layers=2, d_model=512, n_q_heads=8, n_kv_heads=8, d_head=128, d_ff=1536),
+          "k512": wl.ModelShape(n_layers=5, d_model=512, n_q_heads=8, n_kv_heads=8, d_head=128, d_ff=1536),
           # 8192 columns in O and down: two strips per workgroup; 16 rows, and all of row-major: split products
           "n8192": wl.ModelShape(n_layers=2, d_model=8192, n_q_heads=16, n_kv_heads=2, d_head=128, d_ff=2048),
-          "k768": wl.ModelShape(n_layers=2, d_model=768, n_q_heads=8, n_kv_heads=1, d_head=128, d_ff=1280)}
+          "k768": wl.ModelShape(n_layers=5, d_model=768, n_q_heads=8, n_kv_heads=1, d_head=128, d_ff=1280)}
 
 
 @pytest.mark.parametrize("page_slots", [0, 32], ids=["contiguous", "pages32"])
@@ -26,8 +26,8 @@ SHAPES = {"k2048": wl.ModelShape(n_layers=2, d_model=2048, n_q_heads=16, n_kv_he
 @pytest.mark.parametrize("shape", SHAPES.values(), ids=SHAPES.keys())
 def test_one_row_tile(shape, n, packed, page_slots):
     """Increment and cache rows against the oracle (bf16 bar: 2e-2 of the largest value), then the same call again with
-    other inputs into other tensors, in place at last: a replayed call has to write where that call says and nowhere
-    else."""
+    other inputs into other tensors, in place at last: every call has to write where it says and nowhere else, also where it
+    replays a graph (five layers: at least 25 launches; two are made one by one)."""
     pair = Pair(shape, 71, {0: 45}, flags=sp.SP_FLAG_PACKED_WEIGHTS if packed else 0, page_slots=page_slots)
     pair.insert(0, wl.tree_deep(71, n, 9))
     outs = []

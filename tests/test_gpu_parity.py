@@ -5,6 +5,8 @@ compaction; hidden states and freshly written K/V rows within max|gpu - oracle| 
 <= 2e-2 for bf16 storage (the oracle computes in float64 from the same bf16-rounded weights,
 inputs and context) and <= 2e-4 for float32 storage (float32 accumulation over up to
 14336 terms against float64)."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 import torch
@@ -236,10 +238,10 @@ def test_forward_replays_from_a_hip_graph():
 
 
 def test_forward_graph_of_its_own_matches_eager_calls():
-    """On a stream that can be captured the forward call replays a graph of its own launches from the
-    second time a shape is seen.  The same steps on a stage that may not (SP_FLAG_NO_GRAPHS) must give
+    """On a stream that can be captured a forward call of more than 24 launches (30 and 48 here) replays a graph of its own
+    launches from the second time a shape is seen.  The same steps on a stage that may not (SP_FLAG_NO_GRAPHS) must give
     the same bits, call after call, with other shapes and a prune in between."""
-    shape = MINI_GQA4
+    shape = replace(MINI_GQA4, n_layers=6)
     a = Pair(shape, 27, {0: 70}, flags=sp.SP_FLAG_PACKED_WEIGHTS, oracle=False)
     b = Pair(shape, 27, {0: 70}, flags=sp.SP_FLAG_PACKED_WEIGHTS | sp.SP_FLAG_NO_GRAPHS, oracle=False)
     assert torch.cuda.current_stream() != torch.cuda.default_stream()
