@@ -65,7 +65,7 @@ def test_sampling_without_room_for_statistics(V):
     test_sampling_from_exact_logits(64, V, True, "spread")
 
 
-@pytest.mark.parametrize("n_child", [1, 63, 64, 65, 129, 200])
+@pytest.mark.parametrize("n_child", [1, 2, 15, 16, 17, 27, 32, 33, 63, 64, 65, 128, 129, 200])
 @pytest.mark.parametrize("n,V", [(1, 5003), (2, 64 * 140), (40, 64 * 70)])
 def test_lossy_from_exact_logits(n, V, n_child):
     """Relaxed: the child whose token has the highest logit, the first among equals.  Top-p: of the children whose token
@@ -99,6 +99,50 @@ def test_lossy_from_exact_logits(n, V, n_child):
         ok = [i for i in ok if before[tok[i]] < 0.9]
         want = max(ok, key=lambda i: (draft[i], -i)) if ok else -1
         assert top_p[q] == (want, int(order[0])), q
+    pair.close()
+
+
+@pytest.mark.parametrize("n_child", [3, 16, 17, 32, 33, 64, 100, 200])
+@pytest.mark.parametrize("tie", [0.0, 1.5])
+@pytest.mark.parametrize("n,V", [(1, 5003), (2, 64 * 140), (40, 64 * 70)])
+def test_lossy_among_equal_tokens(n, V, tie, n_child):
+    """Most tokens have the same logit (zero: the next float below is a denormal), in runs that fill slices; some stand above, some
+    have no mass.  A child's mass is counted in tied tokens; the children, tokens all over the row, have draft probabilities that
+    grow with it, and top_p lies half a token behind or in front of one child's: a single tied token miscounted changes the
+    verdict (float32 sums of 9000 terms are off by less than a hundredth of one)."""
+    r = np.random.RandomState(V + n_child)
+    logits = np.full(V, tie)
+    for value, count in ((tie + 2.0, 12), (-120.0, V // 12), (-np.inf, V // 12)):
+        logits[r.choice(V, count, replace=False)] = value
+    at = int(r.randint(V // 2))
+    logits[at:at + 2100] = tie
+    pair = Pair(SHAPE, 5, {q: 9 for q in range(n)}, max_batch_nodes=64, oracle=False)
+    x = torch.ones(n, SHAPE.d_model, dtype=torch.bfloat16, device="cuda:0")
+    head = exact_head(logits, False)
+    mass = np.exp(logits - tie)
+    order = np.lexsort((np.arange(V), -logits))
+    before = np.empty(V)
+    before[order] = np.concatenate(([0.0], np.cumsum(mass[order])))[:-1]
+    tied = np.flatnonzero(logits == tie)
+    kids = []
+    for q in range(n):
+        tok = np.sort(r.choice(tied[1:], n_child - 1, replace=False))
+        tok = [int(tied[0])] + [int(t) for t in tok]        # ascending: each has more in front of it
+        draft = [float(np.float32((k + 1) / (n_child + 1))) for k in range(n_child)]
+        mix = r.permutation(n_child)
+        kids.append([tok[k] for k in mix])
+        pair.gpu.tree_insert(q, [-1] * n_child, kids[q], [draft[k] for k in mix])
+    for j in sorted({0, 1, n_child // 2, n_child - 1} | set(r.randint(0, n_child, 4))):
+        for half in (0.5, -0.5):
+            q0 = int(r.randint(n))
+            bound = before[sorted(kids[q0])[j]] + half
+            got = pair.gpu.verify_lossy(head, list(range(n)), x, sp.SP_VERIFY_TOP_P, float(bound / mass.sum()))
+            for q in range(n):
+                if q != q0 and min(abs(before[t] - bound) for t in kids[q]) < 0.25:
+                    continue
+                ok = [t for t in kids[q] if before[t] < bound]
+                want = kids[q].index(max(ok)) if ok else -1
+                assert got[q] == (want, int(order[0])), (q, j, half)
     pair.close()
 
 
