@@ -528,14 +528,14 @@ int sp_tree_insert_batch(sp_stage* s, int32_t n_req, const int32_t* req_ids, con
   }
   // launches of at most SP_T new nodes each (one launch in every case the configs produce)
   InsertArgs a;
-  a.n_req = a.n_pages = 0;
+  a.n_req = 0;
   a.row0[0] = 0;
-  int row = 0;
+  int row = 0, n_pages = 0;                        // (n_pages: of the launch being put together)
   auto flush = [&]() -> hipError_t {
     if (a.n_req == 0) return hipSuccess;
     ProfScope scope(s, SP_K_TREE_INSERT, st);
     hipError_t e = sp_launch_tree_insert(s->d_meta, s->d_tables, a, s->geom, st);
-    a.n_req = a.n_pages = 0;
+    a.n_req = n_pages = 0;
     a.row0[0] = 0;
     return e;
   };
@@ -553,11 +553,11 @@ int sp_tree_insert_batch(sp_stage* s, int32_t n_req, const int32_t* req_ids, con
       a.pg_n[a.n_req] = a.pg_at[a.n_req] = 0;
       if (paged) {
         const int have = (int)r.pages.size(), more = pages_take(s, req_ids[i], r.P + r.T + n);
-        if (more > 0 && a.n_pages + more <= SP_INSERT_PAGES && have < 32768) {
+        if (more > 0 && n_pages + more <= SP_INSERT_PAGES && have < 32768) {
           a.pg_first[a.n_req] = (short)have;
           a.pg_n[a.n_req] = (unsigned char)more;
-          a.pg_at[a.n_req] = (unsigned char)a.n_pages;
-          for (int k = 0; k < more; ++k) a.page[a.n_pages++] = r.pages[have + k];
+          a.pg_at[a.n_req] = (unsigned char)n_pages;
+          for (int k = 0; k < more; ++k) a.page[n_pages++] = r.pages[have + k];
         } else if (more > 0) {
           hipError_t e = pages_set(s, req_ids[i], have, st);
           if (e != hipSuccess) return hip_fail(s, e);

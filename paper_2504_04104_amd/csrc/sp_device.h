@@ -55,7 +55,6 @@ struct RowInfo {
   int pos;          // sequence position = P + depth
   int P;
   int T;
-  int seg;          // the segment of the plan that the row belongs to
 };
 
 // A forward call's requests, passed to kernels by value.
@@ -76,7 +75,6 @@ struct FwdBatch {
 #define SP_INSERT_PAGES 32
 struct InsertArgs {
   int n_req;
-  int n_pages;
   short pg_first[SP_BATCH];
   unsigned char pg_n[SP_BATCH], pg_at[SP_BATCH];
   int page[SP_INSERT_PAGES];

@@ -516,9 +516,9 @@ hipError_t sp_launch_gemm_logits_bf16(const bf16_t* X, const bf16_t* W, bool pac
 #define SP_GOL(MTV, NCGV, PK)                                                                                          \
   hipLaunchKernelGGL((k_gemm_bf16<MTV, NCGV, false, SP_GEMM_KC_PLAIN, SP_GEMM_PF, PK, false, NCGV, true, true, PK>), \
                      grid, dim3(64 * NCGV), 0, st, X, W, logits, nullptr, M, V, K, K / SP_GEMM_KC_PLAIN, 1, 0, nullptr, 0.f, stats, inv_T)
-#define SP_GOT(NCGV, PK) \
-  if (MT == 1) SP_GOL(1, NCGV, PK); else if (MT == 2) SP_GOL(2, NCGV, PK); else if (MT == 3) SP_GOL(3, NCGV, PK); else SP_GOL(4, NCGV, PK)
+#define SP_GOT(NCGV, PK) if (MT == 2) SP_GOL(2, NCGV, PK); else if (MT == 3) SP_GOL(3, NCGV, PK); else SP_GOL(4, NCGV, PK)
   if (eight) { if (packed) { SP_GOT(8, true); } else { SP_GOT(8, false); } }
+  else if (MT == 1) { if (packed) SP_GOL(1, 4, true); else SP_GOL(1, 4, false); }
   else { if (packed) { SP_GOT(4, true); } else { SP_GOT(4, false); } }
 #undef SP_GOT
 #undef SP_GOL

@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(1024) k_add_norm(float* h, const float* part, 
         const int pos = m.P + tables[req].depth[node];
         if (tt == 0) {
           RowInfo ri;
-          ri.base = m.base; ri.req = req; ri.node = node; ri.pos = pos; ri.P = m.P; ri.T = m.T; ri.seg = seg;
+          ri.base = m.base; ri.req = req; ri.node = node; ri.pos = pos; ri.P = m.P; ri.T = m.T;
           rows[r] = ri;
         }
         const double inv_freq = exp2(-(2.0 * (double)tt / (double)d_head) * log2((double)theta));
