@@ -239,7 +239,7 @@ int sp_tree_insert_batch(sp_stage* stage, int32_t n_req, const int32_t* req_ids 
  * The nodes' K and V rows are written to the slab.  A node's parent must have been
  * forwarded before or be part of this call (SP_E_ORDER).  A request may appear once.
  * Launch overhead: when a call of more than 24 launches has the same shape (rows, attention
- * work items) as an earlier one, its launches except the first are replayed from a HIP graph
+ * work) as an earlier one, its launches except the first are replayed from a HIP graph
  * captured the second time that shape was seen; results are identical.  The call stays
  * eager on a stream that cannot be captured (the default stream: pass a stream of your
  * own), while the stream is being captured by the caller, while sp_profile_begin

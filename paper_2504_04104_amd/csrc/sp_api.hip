@@ -791,10 +791,12 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
 
   // A shape of many launches that comes back replays its graph; one seen for the second time is captured.  Not while a
   // kernel kind is being timed (the events sit between the launches) and not inside a caller's capture.
-  // Few launches are made one by one: what follows a graph on its stream starts 8 us late, and its launch takes the host as
-  // long as some ten others (us a call, replayed / one by one: one row of one 8B layer 104.7 / 97.6, 37 rows 129.9 / 124.1, two
-  // float32 layers of 256 67.8 / 64.0, a step of a few rows in four layers 455 / 450).  A launch takes the host 2-6 us and the
-  // device 4.5 at least: long calls leave the host no lead that way (24 layers of 1024: 966 / 962, the host 126 / 850).
+  // Few launches are made one by one: what follows a graph on its stream starts up to 8 us late (us a call, replayed / one by
+  // one: one row of one 8B layer 104.7 / 97.6, 37 rows 129.9 / 124.1, one to three float32 layers of 256 32.7 / 27.3, 55.7 / 51.3
+  // and 78.3 / 75.1).  24 is a bound on what that costs the host, not where the two cross on the device: 25 to 60 launches are
+  // level to 6 us faster one by one too (12 float32 layers 303.4 / 298.0, 64 rows of four 8B layers 485.6 / 482.3; 48 launches of small
+  // products 194.7 / 203.2), but take the host 72 to 196 us a call (20 launches 64, a replay 35 to 49): long calls leave the
+  // host no lead (24 layers of 1024: 966 / 962, the host 126 / 850).
   constexpr int EAGER_LAUNCHES = 24;
   const int launches = c.n_layers * ((few || qkv_joined ? 5 : s->f32 ? 7 : 8) + (plan.any_split ? 1 : 0));
   // launches among the layers' of their own: norms, rotation

@@ -70,10 +70,11 @@ k_gemm_mid(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, float* __
   const int c_n = c_end - c_begin;
   // Staggered starting chunks where the rows or strips that the workgroups stream lie a multiple of 8 KB apart and would be
   // at the same offset of it at the same moment: gate/up over row-major weights (8B shape 64 rows 58.8 -> 54.3 us, 145 rows
-  // 75.6 -> 69.0) and, up to 96 rows, over weights in fragment order (four 8B layers, five machines: 33-48 rows 0.4-1 %
-  // faster, 56-64 level to 1 %, 72-96 0.6-1.5 %; alone, 64 rows 40.8 -> 39.8 us; with more rows level), and plain products 8192
-  // deep (8192 x 8192, 65 rows: 36.3 -> 33.2 us, row-major 40.7 -> 35.5; with K = 4096 slices are four to eight chunks long
-  // and lose 1 %, with 14336 and more nothing changes).
+  // 75.6 -> 69.0) and, up to 96 rows, over weights in fragment order (8B layers, on several machines with buffers at many places:
+  // 33-48 rows level to 1 % faster, 56-64 from 0.8 % slower to 1.4 % faster, mostly faster, 72-96 0.4-1.5 % faster; 70B shape 33-40
+  // rows level to 1 % slower, 48-96 0.3-0.5 % faster; with more rows level), and plain products 8192 deep (8192 x 8192, 65 rows:
+  // 36.3 -> 33.2 us, row-major 40.7 -> 35.5; with K = 4096 slices are four to eight chunks long and lose 1 %, with 14336 and
+  // more nothing changes).
   const bool stagger = GATEUP ? !PACKED || MT <= 6 : K > 4096 && K <= 8192;
   const int rot = stagger && c_n > 1 ? (int)((blockIdx.x >> 3) % (unsigned)c_n) : 0;
 #define SP_PC(C) ((GATEUP && PACKED && MT > 6) || (C) + rot < c_end ? (C) + rot : (C) + rot - c_n)
