@@ -629,7 +629,9 @@ int sp_stage_forward(sp_stage* s, int32_t n_req, const int32_t* req_ids, const i
   plan.n_seg = b.n_req;
   plan.x_out = x_out;
   // Which request and node each row belongs to.  Longest cache ranges first (equal ones in the call's order): the attention's
-  // workgroups start in this order, and those of short ranges fill the CUs that the long ones leave over.
+  // workgroups start in this order, and those of short ranges fill the CUs that the long ones leave over (us a layer of the 8B shape
+  // behind 512-4096 slots, the call's order / longest first: 32 requests of 8-32 nodes 429.9 / 397.3, 64 of 1-4 256.8 / 244.5, two
+  // layers of 638 rows 823 / 780; one round of workgroups, or ranges cut into chunks, level).
   short order[SP_BATCH];
   for (int i = 0; i < b.n_req; ++i) {
     const HostReq& r = s->reqs[b.req[i]];
